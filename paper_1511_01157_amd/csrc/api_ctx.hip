@@ -61,6 +61,11 @@ int morse_ctx_create(int device, void* stream, morse_ctx** out) {
     morse_ctx_destroy(c);
     return rc;
   }
+  if (hipMalloc((void**)&c->stat_slots, 8 * 4 * (size_t)kStatSlots) != hipSuccess) {
+    c->stat_slots = nullptr;
+    morse_ctx_destroy(c);
+    return fail(nullptr, MORSE_ENOMEM, "allocation of the ray statistics' slots failed");
+  }
   *out = c;
   return MORSE_OK;
 }
@@ -75,6 +80,7 @@ int morse_ctx_destroy(morse_ctx* ctx) {
   if (ctx->ws) (void)hipFree(ctx->ws);
   if (ctx->aux) (void)hipFree(ctx->aux);
   if (ctx->taps) (void)hipFree(ctx->taps);
+  if (ctx->stat_slots) (void)hipFree(ctx->stat_slots);
   if (ctx->smeta.p) (void)hipFree(ctx->smeta.p);
   if (ctx->cmeta.p) (void)hipFree(ctx->cmeta.p);
   for (MetaBuf* mb : {&ctx->stack_taps, &ctx->fft_tw, &ctx->fft_spec, &ctx->lmeta, &ctx->fs_crit})

@@ -224,7 +224,8 @@ int morse_rayshoot(morse_ctx* ctx, double s, double q, const morse_grid2d* rays,
   if (!accumulate) HIP_TRY(ctx, launch_fill_u32(d_counts, (size_t)window->nx * window->ny, 0u, ctx->stream));
   LaunchTimer tm{ctx, MORSE_KERNEL_RAYSHOOT};
   HIP_TRY(ctx, tm.begin(ctx->stream));
-  HIP_TRY(ctx, launch_rayshoot(p, d_counts, (unsigned long long*)d_stats, ctx->stream));
+  HIP_TRY(ctx, launch_rayshoot(p, d_counts, (unsigned long long*)d_stats,
+                               (unsigned long long*)ctx->stat_slots, ctx->num_cu, ctx->stream));
   HIP_TRY(ctx, tm.end(ctx->stream));
   return MORSE_OK;
 }
@@ -541,7 +542,8 @@ int morse_build_map(morse_ctx* ctx, double s, double q, const morse_grid2d* rays
   if ((rc = upload(ctx, d_w, w.data(), w.size() * 4))) return rc;
   if ((rc = upload(ctx, d_off, off.data(), off.size() * 4))) return rc;
   HIP_TRY(ctx, launch_fill_u64(stats, 4, 0ull, ctx->stream));
-  if ((rc = morse_rayshoot(ctx, s, q, rays, window, 0, rays->ny, counts, 0, stats))) return rc;
+  if ((rc = morse_rayshoot(ctx, s, q, rays, window, 0, rays->ny, counts, 0, h_stats ? stats : nullptr)))
+    return rc;
   const double hx = (double)(float)(rays->wx / rays->nx), hy = (double)(float)(rays->wy / rays->ny);
   const float scale = (float)(hx * hy / (dx * dy));
   int32_t rx, ry;

@@ -84,6 +84,8 @@ struct morse_ctx {
   int32_t taps_n = 0;
   int32_t taps_rx = 0, taps_ry = 0;  // the largest |offset| of the taps along x and y
   size_t taps_wbytes = 0;
+  // slots of the ray statistics (allocated with the context, so that a call can be captured)
+  char* stat_slots = nullptr;
   // kernel timing: enabled families, pending event pairs, free events, totals
   uint32_t timing_mask = 0;
   struct Timed {

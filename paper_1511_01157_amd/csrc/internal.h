@@ -401,8 +401,13 @@ hipError_t launch_bucket_order(const uint32_t* key, int64_t n, int32_t nbins, ui
 // Packs every map of the device table `maps` (n_maps entries; h_maps the same table on
 // the host, for the sizes) into its quad layout.
 hipError_t launch_quad_pack(const MapC* maps, const MapC* h_maps, int32_t n_maps, hipStream_t st);
+// Shoots the rows of p into counts.  With `stats` (three totals that the call adds to),
+// `slots` is workspace of 4 kStatSlots words: the workgroups add to one slot each, so that
+// no address takes more than a few hundred atomics (the three totals themselves took
+// 260,000 each and doubled the time of a 32768^2 lattice).
+constexpr int kStatSlots = 256;
 hipError_t launch_rayshoot(const RayParams& p, uint32_t* counts, unsigned long long* stats,
-                           hipStream_t st);
+                           unsigned long long* slots, int num_cu, hipStream_t st);
 // Normalisation + convolution of a counts map with ntaps taps whose offsets reach at
 // most rx columns and ry rows from the pixel (rx = ry = 0: the single tap (0, 0);
 // otherwise at most 16 each).

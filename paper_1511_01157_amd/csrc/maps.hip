@@ -5,14 +5,17 @@
 // Albrow 2015) of the binary-lens equation Eq. 2 with the lens placement of sec. 4.1;
 // finite-source maps by convolution with the source profile (sec. 4.1).
 //
-// Ray kernel layout.  A 256-thread workgroup owns a 128 x 64 tile of the image-plane
-// lattice (32 rays per thread).  Rays are generated from their indices (no input
-// arrays).  Thread (tx, ty) of a 16 x 16 arrangement takes rays x0 + tx + 16a,
-// y0 + ty + 16b, so the 64 lanes of a wave at one (a, b) are spread over a 16 x 4
-// patch of rays, i.e. over several source pixels, which keeps LDS atomics of one
-// instruction off a single address.  Pass 1 computes every ray's bin and the
+// Ray kernel layout.  A 256-thread workgroup owns a tile of the image-plane lattice, 16 A
+// x 16 B rays, A B of them per thread.  Rays are generated from their indices (no input
+// arrays).  Thread (tx, ty) of a 16 x 16 arrangement takes the A x B block of rays at
+// (A tx, B ty), so the lanes of one instruction lie A rays apart in x and B in y, i.e. on
+// different source pixels (a lattice has several rays a pixel), which keeps the LDS
+// atomics of an instruction off a single address (64 lanes on one address take 128 cycles
+// of the LDS, on different ones 4), and the terms of a column and of a row are computed
+// once per thread.  A tile whose rays provably all miss the window is skipped (see
+// tile_misses).  Pass 1 computes every ray's bin and the
 // workgroup's bounding box of in-window bins.  If the box fits in the LDS tile
-// (8192 bins) the rays are counted with LDS atomics and the non-zero bins merged
+// (RS_CAP bins) the rays are counted with LDS atomics and the non-zero bins merged
 // with one global atomic each; otherwise (tiles straddling a lens, whose rays scatter
 // over the whole source plane) each ray goes to a global atomic directly.  Integer
 // addition is order-free, so the counts are bit-identical whatever the schedule.
@@ -31,18 +34,14 @@
 
 #include "internal.h"
 
-#include <climits>
+#include <cmath>
 
 namespace morse {
 
 namespace {
 
-constexpr int RS_TX = 128;
-constexpr int RS_TY = 64;
 constexpr int RS_THREADS = 256;
-constexpr int RS_A = RS_TX / 16;  // rays per thread along x
-constexpr int RS_B = RS_TY / 16;  // rays per thread along y
-constexpr int RS_CAP = 8192;      // LDS histogram bins (32 KiB)
+constexpr int RS_CAP = 4096;  // LDS histogram bins (16 KiB)
 
 __global__ void k_fill_u32(uint32_t* p, size_t n, uint32_t v) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n;
@@ -80,169 +79,239 @@ __global__ void k_quad_pack(const MapC* __restrict__ maps) {
   }
 }
 
-// Symmetric bin rule: v >= 0 (also -0) -> m/2 + floor(v) if v < m/2;
-// v < 0 -> m/2 - 1 - floor(-v) if -v < m/2.  floor(|v|) serves both branches.
-__device__ __forceinline__ bool bin1(float v, int32_t m, int32_t& out) {
-  float av = fabsf(v);
-  int32_t h = m >> 1;
-  int32_t f = (int32_t)floorf(fminf(av, (float)h));  // clamp keeps the cast in range
-  out = (v >= 0.0f) ? h + f : h - 1 - f;
-  return av < (float)h;
-}
-
-__device__ __forceinline__ int wave_min(int v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = min(v, __shfl_xor(v, o, kWave));
-  return v;
-}
-__device__ __forceinline__ int wave_max(int v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = max(v, __shfl_xor(v, o, kWave));
-  return v;
-}
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, kWave);
+// A uniform value in a vector register of its own: an instruction whose operands are all
+// vector registers (or inline constants) issues in half the time of one with a scalar
+// operand (2.5 against 4.3 cycles per wavefront for a binary32 add or multiply).
+__device__ __forceinline__ float in_vgpr(float s) {
+  float v;
+  asm("v_mov_b32 %0, %1" : "=v"(v) : "s"(s));
   return v;
 }
 
-template <bool kMirror>
+// m / r, correctly rounded, for m = 0 or m in [2^-40, 1] and r in [2^-40, 2^40]: the steps
+// of the general IEEE sequence with its range scaling and special-case fix-up left out,
+// which in this range change nothing (8 instructions for 11).
+__device__ __forceinline__ float div_in_range(float m, float r) {
+  float y = __builtin_amdgcn_rcpf(r);
+  y = fmaf(fmaf(-r, y, 1.0f), y, y);
+  float q = m * y;
+  q = fmaf(fmaf(-r, q, m), y, q);
+  return fmaf(fmaf(-r, q, m), y, q);
+}
+
+// Whether every ray of the rectangle [xa, xb] x [ya, yb] misses the window.  A lens at x_k
+// displaces a ray by m_k / |z - x_k| at most, so with d_k the distance of lens k from the
+// rectangle zeta lies within D = sum m_k / d_k of z in x and in y.  The slack covers the
+// roundings of the binary32 ray (each of its few operations is off by 2^-24 of a number
+// no larger than |z| + D + |s|) and one pixel.
+__device__ __forceinline__ bool tile_misses(const RayParams& p, float xa, float xb, float ya, float yb) {
+  const float dy = fmaxf(fmaxf(ya, -yb), 0.0f);
+  const float e1 = fmaxf(fmaxf(xa - p.x1, p.x1 - xb), 0.0f), e2 = fmaxf(fmaxf(xa - p.x2, p.x2 - xb), 0.0f);
+  // the hardware's reciprocal square root and reciprocal, within 2^-22, inside the slack;
+  // a rectangle that holds a lens gets inf, and is kept
+  const float D = p.m1 * __builtin_amdgcn_rsqf(e1 * e1 + dy * dy) + p.m2 * __builtin_amdgcn_rsqf(e2 * e2 + dy * dy);
+  const float big = fmaxf(fmaxf(fabsf(xa), fabsf(xb)), fmaxf(fabsf(ya), fabsf(yb))) + D +
+                    fmaxf(fabsf(p.sx), fabsf(p.sy));
+  const float slack = D + 1e-4f * big;
+  const float wx = ((float)(p.mx >> 1) + 1.0f) * (1.0001f * __builtin_amdgcn_rcpf(p.kx)) + slack;
+  const float wy = ((float)(p.my >> 1) + 1.0f) * (1.0001f * __builtin_amdgcn_rcpf(p.ky)) + slack;
+  return xa - p.sx > wx || xb - p.sx < -wx || ya - p.sy > wy || yb - p.sy < -wy;
+}
+
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(us2, a), __builtin_bit_cast(us2, b)));
+}
+__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(us2, a), __builtin_bit_cast(us2, b)));
+}
+
+// kMirror: rows of the upper half, each ray standing for itself and its mirror ray.
+// kSafe: the host has shown that every r_k = |z - x_k|^2 of the rows lies in [2^-40, 2^40]
+// (and the masses and scales in range), so the short division is exact and no ray is
+// non-finite.  The general form divides as IEEE asks and counts non-finite rays.
+//
+// Bound: instruction issue.  32768^2 rays (lattice twice the window's width) in mirror
+// pairs into 2048^2: 373 us = 2.9e12 lattice rays/s, 43% of the tiles kept, 66 VALU
+// instructions per kept wavefront of rays at 3.4 cycles each; without the LDS atomics or
+// the merges it takes 375 and 358 us.  Before: 1.03 ms (and 2.02 ms with the statistics,
+// whose three addresses took 260,000 atomics each) at 104 instructions per wavefront of
+// rays: no tile skipped, IEEE divisions with scalings, the lattice point, finiteness and
+// range tested per ray, scalar operands.
+template <bool kMirror, bool kSafe, int A, int B>
 __global__ __launch_bounds__(RS_THREADS) void k_rayshoot(RayParams p, uint32_t* __restrict__ counts,
                                                          unsigned long long* __restrict__ stats) {
   __shared__ uint32_t hist[RS_CAP];
-  __shared__ int s_box[4][4];
+  __shared__ uint32_t s_box[RS_THREADS / kWave][2];
+  __shared__ uint32_t s_stat[RS_THREADS / kWave][3];
 
   const int tid = threadIdx.x;
   const int tx = tid & 15;
   const int ty = tid >> 4;
   const int wave = tid >> 6;
   const int lane = tid & 63;
-  const int x0 = blockIdx.x * RS_TX;
-  const int y0 = p.row0 + blockIdx.y * RS_TY;
+  const int x0 = blockIdx.x * (16 * A);
+  const int y0 = p.row0 + blockIdx.y * (16 * B);
+  auto lattice = [](float c, int i, int n, float h) { return c + ((float)(i - (n >> 1)) + 0.5f) * h; };
 
-  // packed bin (by << 16 | bx), -1 when the ray is not binned
-  int bins[RS_A * RS_B];
-  int bxmin = INT_MAX, bxmax = -1, bymin = INT_MAX, bymax = -1;
-  uint32_t n_out = 0, n_nf = 0, n_zero = 0;
+  const int x1 = min(x0 + 16 * A, p.nx) - 1, y1 = min(y0 + 16 * B, p.row1) - 1;  // last column, row
+  const uint32_t shot = (uint32_t)(x1 - x0 + 1) * (uint32_t)(y1 - y0 + 1);
+  constexpr uint32_t kRays = kMirror ? 2u : 1u;  // rays each shot ray stands for
+  // slot of the statistics this workgroup adds to (few workgroups per address)
+  unsigned long long* st = stats ? stats + 4 * ((blockIdx.x + blockIdx.y * gridDim.x) % kStatSlots) : nullptr;
+  if (tile_misses(p, lattice(p.cx, x0, p.nx, p.hx), lattice(p.cx, x1, p.nx, p.hx),
+                  lattice(p.cy, y0, p.ny, p.hy), lattice(p.cy, y1, p.ny, p.hy))) {
+    if (tid == 0 && st) atomicAdd(&st[0], (unsigned long long)(shot * kRays));
+    return;
+  }
+
+  const float m1 = in_vgpr(p.m1), m2 = in_vgpr(p.m2), sx = in_vgpr(p.sx), sy = in_vgpr(p.sy),
+              kx = in_vgpr(p.kx), ky = in_vgpr(p.ky);
+  const int hx = p.mx >> 1, hy = p.my >> 1;
+  const float fhx = in_vgpr((float)hx), fhy = in_vgpr((float)hy);
+  const float nan = __builtin_nanf("");
+  float y[B], yy[B];
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    const int j = y0 + ty * B + b;
+    y[b] = j < p.row1 ? lattice(p.cy, j, p.ny, p.hy) : nan;  // NaN rays are never in the window
+    yy[b] = y[b] * y[b];
+  }
+  // packed bin (by << 16 | bx), all ones when the ray is not binned
+  uint32_t bins[A * B];
+  uint32_t lo = 0xffffffffu, hi = 0u;  // packed bounds of the binned rays
+  uint32_t n_in = 0, n_nf = 0, n_zero = 0;  // per wavefront
 
 #pragma unroll
-  for (int b = 0; b < RS_B; ++b) {
-    const int j = y0 + ty + 16 * b;
-    const float gy = (float)(j - (p.ny >> 1)) + 0.5f;
-    const float y = p.cy + gy * p.hy;
-    const float yy = y * y;
+  for (int a = 0; a < A; ++a) {
+    const int i = x0 + tx * A + a;
+    const float x = i < p.nx ? lattice(p.cx, i, p.nx, p.hx) : nan;
+    const float d1 = x - p.x1, d2 = x - p.x2;
+    const float d1s = d1 * d1, d2s = d2 * d2;
+    // the B rays of the column together: their chains overlap, and one branch serves all
+    float vx[B], vy[B];
+    uint64_t in[B], any = 0;
 #pragma unroll
-    for (int a = 0; a < RS_A; ++a) {
-      const int i = x0 + tx + 16 * a;
-      int bin = -1;
-      if (i < p.nx && j < p.row1) {
-        const float gx = (float)(i - (p.nx >> 1)) + 0.5f;
-        const float x = p.cx + gx * p.hx;
-        const float d1 = x - p.x1;
-        const float d2 = x - p.x2;
-        const float r1 = d1 * d1 + yy;
-        const float r2 = d2 * d2 + yy;
-        const float a1 = p.m1 / r1;
-        const float a2 = p.m2 / r2;
-        const float zx = (x - a1 * d1) - a2 * d2;
-        const float zy = (y - a1 * y) - a2 * y;
-        const float vx = (zx - p.sx) * p.kx;
-        const float vy = (zy - p.sy) * p.ky;
-        if (!(isfinite(vx) && isfinite(vy))) {
-          ++n_nf;
-        } else {
-          int32_t bx, by;
-          const bool inx = bin1(vx, p.mx, bx);
-          const bool iny = bin1(vy, p.my, by);
-          if (inx && iny && kMirror && vy == 0.0f) {
-            // the ray and its mirror share the bin (bx, h)
-            atomicAdd(&counts[(size_t)by * (size_t)p.mx + (size_t)bx], 2u);
-            ++n_zero;
-          } else if (inx && iny) {
-            bin = (by << 16) | bx;
-            n_zero += (vy == 0.0f) ? 1u : 0u;
-            bxmin = min(bxmin, bx);
-            bxmax = max(bxmax, bx);
-            bymin = min(bymin, by);
-            bymax = max(bymax, by);
-          } else {
-            ++n_out;
+    for (int b = 0; b < B; ++b) {
+      const float r1 = d1s + yy[b], r2 = d2s + yy[b];
+      const float a1 = kSafe ? div_in_range(m1, r1) : m1 / r1;
+      const float a2 = kSafe ? div_in_range(m2, r2) : m2 / r2;
+      const float zx = (x - a1 * d1) - a2 * d2;
+      const float zy = (y[b] - a1 * y[b]) - a2 * y[b];
+      vx[b] = (zx - sx) * kx;
+      vy[b] = (zy - sy) * ky;
+      // one ballot per compare: the mask that the compare itself writes
+      in[b] = __builtin_amdgcn_ballot_w64(fabsf(vx[b]) < fhx) & __builtin_amdgcn_ballot_w64(fabsf(vy[b]) < fhy);
+      any |= in[b];
+      if (!kSafe) {  // a padding ray (i or j past the end) is no ray
+        const bool ray = i < p.nx && y0 + ty * B + b < p.row1;
+        n_nf += __popcll(__builtin_amdgcn_ballot_w64(ray && !(isfinite(vx[b]) && isfinite(vy[b]))));
+      }
+      bins[a * B + b] = 0xffffffffu;
+    }
+    if (any) {  // uniform
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        n_in += __popcll(in[b]);
+        // symmetric bin rule: v >= 0 (also -0) -> h + floor(v), v < 0 -> h - 1 - floor(-v);
+        // v + 0 turns -0 into +0, and -1 - f is the complement of f
+        const int bx = hx + ((int)fabsf(vx[b]) ^ (__float_as_int(vx[b] + 0.0f) >> 31));
+        const int by = hy + ((int)fabsf(vy[b]) ^ (__float_as_int(vy[b] + 0.0f) >> 31));
+        const uint32_t packed = ((uint32_t)by << 16) | (uint32_t)bx;
+        const uint64_t axis = __builtin_amdgcn_ballot_w64(vy[b] == 0.0f) & in[b];
+        uint64_t binned = in[b];
+        if (axis) {  // uniform, and rare: rays on the window's horizontal centre line
+          n_zero += __popcll(axis);
+          if (kMirror) {  // such a ray and its mirror share the bin (bx, h)
+            if ((axis >> lane) & 1)
+              atomicAdd(&counts[(size_t)by * (size_t)p.mx + (size_t)bx], 2u);
+            binned &= ~axis;
           }
         }
+        const bool mine = __builtin_amdgcn_inverse_ballot_w64(binned);
+        bins[a * B + b] = mine ? packed : 0xffffffffu;
+        lo = pk_min(lo, bins[a * B + b]);
+        hi = pk_max(hi, mine ? packed : 0u);
       }
-      bins[b * RS_A + a] = bin;
     }
   }
 
-  // ray statistics: one 64-bit atomic per wave and counter, only when non-zero
-  constexpr uint32_t kRays = kMirror ? 2u : 1u;  // rays each shot ray stands for
-  n_out = wave_sum_u32(n_out) * kRays;
-  n_nf = wave_sum_u32(n_nf) * kRays;
-  n_zero = wave_sum_u32(n_zero) * kRays;
-  if (lane == 0 && stats) {
-    if (n_out) atomicAdd(&stats[0], (unsigned long long)n_out);
-    if (n_nf) atomicAdd(&stats[1], (unsigned long long)n_nf);
-    if (n_zero) atomicAdd(&stats[2], (unsigned long long)n_zero);
+  // workgroup bounding box of binned rays and the ray statistics
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    lo = pk_min(lo, (uint32_t)__shfl_xor((int)lo, o, kWave));
+    hi = pk_max(hi, (uint32_t)__shfl_xor((int)hi, o, kWave));
   }
-
-  // workgroup bounding box of binned rays
-  bxmin = wave_min(bxmin);
-  bxmax = wave_max(bxmax);
-  bymin = wave_min(bymin);
-  bymax = wave_max(bymax);
   if (lane == 0) {
-    s_box[wave][0] = bxmin;
-    s_box[wave][1] = bxmax;
-    s_box[wave][2] = bymin;
-    s_box[wave][3] = bymax;
+    s_box[wave][0] = lo;
+    s_box[wave][1] = hi;
+    s_stat[wave][0] = n_in;
+    s_stat[wave][1] = n_nf;
+    s_stat[wave][2] = n_zero;
   }
   __syncthreads();
-  bxmin = min(min(s_box[0][0], s_box[1][0]), min(s_box[2][0], s_box[3][0]));
-  bxmax = max(max(s_box[0][1], s_box[1][1]), max(s_box[2][1], s_box[3][1]));
-  bymin = min(min(s_box[0][2], s_box[1][2]), min(s_box[2][2], s_box[3][2]));
-  bymax = max(max(s_box[0][3], s_box[1][3]), max(s_box[2][3], s_box[3][3]));
-  if (bxmax < 0) return;  // no ray of this tile landed in the window
+  lo = 0xffffffffu;
+  hi = 0u;
+  uint32_t tot[3] = {0u, 0u, 0u};
+#pragma unroll
+  for (int k = 0; k < RS_THREADS / kWave; ++k) {
+    lo = pk_min(lo, s_box[k][0]);
+    hi = pk_max(hi, s_box[k][1]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) tot[q] += s_stat[k][q];
+  }
+  if (tid == 0 && st) {
+    const uint32_t n_out = (shot - tot[0] - tot[1]) * kRays;
+    if (n_out) atomicAdd(&st[0], (unsigned long long)n_out);
+    if (tot[1]) atomicAdd(&st[1], (unsigned long long)(tot[1] * kRays));
+    if (tot[2]) atomicAdd(&st[2], (unsigned long long)(tot[2] * kRays));
+  }
+  if (lo == 0xffffffffu) return;  // no ray of this tile landed in the window
 
-  const int pitch = bxmax - bxmin + 1;
-  const int rows = bymax - bymin + 1;
-  const int area = pitch * rows;
+  const int bxmin = lo & 0xffff, bymin = lo >> 16;
+  const int rows = (int)(hi >> 16) - bymin + 1;
+  const int pitch = (int)(hi & 0xffff) - bxmin + 1;
+  const int area = rows * pitch;
+  const int top = 2 * hy - 1;  // mirror row of by is top - by
   if (area <= RS_CAP) {
     for (int k = tid; k < area; k += RS_THREADS) hist[k] = 0u;
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < RS_A * RS_B; ++k) {
-      const int bin = bins[k];
-      if (bin >= 0) {
-        const int bx = bin & 0xffff;
-        const int by = bin >> 16;
-        atomicAdd(&hist[(by - bymin) * pitch + (bx - bxmin)], 1u);
-      }
+    for (int k = 0; k < A * B; ++k) {
+      const uint32_t bin = bins[k] - lo;  // no borrow between the halves: both are at least lo's
+      if (bins[k] != 0xffffffffu) atomicAdd(&hist[__umul24(bin >> 16, pitch) + (bin & 0xffff)], 1u);
     }
     __syncthreads();
-    const int top = 2 * (p.my >> 1) - 1;  // mirror row of by is top - by
-    for (int k = tid; k < area; k += RS_THREADS) {
-      const uint32_t v = hist[k];
-      if (v) {
-        const int r = k / pitch;
-        const int c = k - r * pitch;
-        atomicAdd(&counts[(size_t)(bymin + r) * (size_t)p.mx + (size_t)(bxmin + c)], v);
-        if (kMirror)
-          atomicAdd(&counts[(size_t)(top - (bymin + r)) * (size_t)p.mx + (size_t)(bxmin + c)], v);
+    for (int r = ty; r < rows; r += 16)
+      for (int c = tx; c < pitch; c += 16) {
+        const uint32_t v = hist[r * pitch + c];
+        if (v) {
+          atomicAdd(&counts[(size_t)(bymin + r) * (size_t)p.mx + (size_t)(bxmin + c)], v);
+          if (kMirror)
+            atomicAdd(&counts[(size_t)(top - (bymin + r)) * (size_t)p.mx + (size_t)(bxmin + c)], v);
+        }
       }
-    }
   } else {
-    const int top = 2 * (p.my >> 1) - 1;
 #pragma unroll
-    for (int k = 0; k < RS_A * RS_B; ++k) {
-      const int bin = bins[k];
-      if (bin >= 0) {
-        const int bx = bin & 0xffff;
-        const int by = bin >> 16;
+    for (int k = 0; k < A * B; ++k) {
+      if (bins[k] != 0xffffffffu) {
+        const int bx = bins[k] & 0xffff;
+        const int by = bins[k] >> 16;
         atomicAdd(&counts[(size_t)by * (size_t)p.mx + (size_t)bx], 1u);
         if (kMirror) atomicAdd(&counts[(size_t)(top - by) * (size_t)p.mx + (size_t)bx], 1u);
       }
     }
   }
+}
+
+// Adds the slots' statistics to the caller's three totals.
+__global__ __launch_bounds__(64) void k_stats_sum(const unsigned long long* __restrict__ slots,
+                                                  unsigned long long* __restrict__ stats) {
+  const int q = threadIdx.x;
+  if (q >= 3) return;
+  unsigned long long t = 0;
+  for (int k = 0; k < kStatSlots; ++k) t += slots[4 * k + q];
+  if (t) atomicAdd(&stats[q], t);
 }
 
 // Normalise + convolve.  Taps are row-major over the stencil with the zero taps dropped
@@ -548,33 +617,81 @@ hipError_t launch_quad_pack(const MapC* maps, const MapC* h_maps, int32_t n_maps
 
 namespace {
 
+// Whether the short division holds for rows [row0, row1) (see k_rayshoot): |y| is smallest
+// beside the lattice's crossing of y = 0, which the rows around it bracket, and r_k >= y^2.
+bool safe_rows(const RayParams& p, int32_t row0, int32_t row1) {
+  auto y = [&](int32_t j) { return std::fabs(p.cy + ((float)(j - (p.ny >> 1)) + 0.5f) * p.hy); };
+  const double c = 0.5 * p.ny - 0.5 - (double)p.cy / p.hy;
+  float ymin = std::min(y(row0), y(row1 - 1));
+  for (int d = -3; d <= 3; ++d) {
+    const double j = std::floor(c) + d;
+    if (j >= row0 && j < row1) ymin = std::min(ymin, y((int32_t)j));
+  }
+  const float xmax = std::fabs(p.cx) + p.hx * p.nx + std::max(std::fabs(p.x1), std::fabs(p.x2));
+  const float ymax = std::fabs(p.cy) + p.hy * p.ny;
+  auto scale = [](float k) { return k >= 0x1p-40f && k <= 0x1p40f; };
+  return ymin >= 0x1p-19f && xmax <= 0x1p19f && ymax <= 0x1p19f && std::fabs(p.sx) <= 0x1p40f &&
+         std::fabs(p.sy) <= 0x1p40f && scale(p.kx) && scale(p.ky) && (p.m2 == 0.0f || p.m2 >= 0x1p-40f);
+}
+
+template <bool kMirror, bool kSafe>
+hipError_t shoot_tiles(const RayParams& p, uint32_t* counts, unsigned long long* stats, int num_cu,
+                       hipStream_t st) {
+  // 128 x 64 rays a workgroup, 32 a thread; 64 x 32 where the lattice is too small to give
+  // every CU eight such tiles (3200^2 rays into 512^2: 12 against 51 us) or so coarse that
+  // 128 x 64 rays cover more than 512 pixels without a lens (near one they spread over
+  // several times as many, and a box beyond RS_CAP bins counts ray by ray; 7000 x 5210 rays,
+  // 2.4 a pixel side: 50 against 265 us).  32768^2 rays into 2048^2: 373 us with the large
+  // tile, 537 with the small one; 128 x 128 rays take 515 (95 VGPRs, larger boxes).
+  const float cover = 128.0f * 64.0f * p.hx * p.kx * p.hy * p.ky;
+  const int rows = p.row1 - p.row0;
+  auto tiles = [&](int tx, int ty) { return dim3((p.nx + tx - 1) / tx, (rows + ty - 1) / ty); };
+  const dim3 big = tiles(128, 64);
+  if ((int64_t)big.x * big.y >= 8 * (int64_t)num_cu && cover <= 512.0f) {
+    hipLaunchKernelGGL((k_rayshoot<kMirror, kSafe, 8, 4>), big, dim3(RS_THREADS), 0, st, p, counts, stats);
+  } else {
+    hipLaunchKernelGGL((k_rayshoot<kMirror, kSafe, 4, 2>), tiles(64, 32), dim3(RS_THREADS), 0, st, p,
+                       counts, stats);
+  }
+  return hipGetLastError();
+}
+
 // Rows [row0, row1) of p, each ray shot once (kMirror false) or, for rows of the upper
 // half whose mirror rows are part of the call, once for the pair (kMirror true).
 template <bool kMirror>
 hipError_t shoot_rows(RayParams p, int32_t row0, int32_t row1, uint32_t* counts,
-                      unsigned long long* stats, hipStream_t st) {
-  const int rows = row1 - row0;
-  if (rows <= 0) return hipSuccess;
+                      unsigned long long* stats, int num_cu, hipStream_t st) {
+  if (row1 <= row0) return hipSuccess;
   p.row0 = row0;
   p.row1 = row1;
-  dim3 grid((p.nx + RS_TX - 1) / RS_TX, (rows + RS_TY - 1) / RS_TY);
-  hipLaunchKernelGGL(k_rayshoot<kMirror>, grid, dim3(RS_THREADS), 0, st, p, counts, stats);
-  return hipGetLastError();
+  return safe_rows(p, row0, row1) ? shoot_tiles<kMirror, true>(p, counts, stats, num_cu, st)
+                                  : shoot_tiles<kMirror, false>(p, counts, stats, num_cu, st);
 }
 
 }  // namespace
 
 hipError_t launch_rayshoot(const RayParams& p, uint32_t* counts, unsigned long long* stats,
-                           hipStream_t st) {
+                           unsigned long long* slots, int num_cu, hipStream_t st) {
   if (p.row1 <= p.row0) return hipSuccess;
+  if (stats && !slots) return hipErrorInvalidValue;
+  hipError_t e = hipSuccess;
+  unsigned long long* ss = stats ? slots : nullptr;
+  if (ss) e = launch_fill_u64((uint64_t*)ss, 4 * kStatSlots, 0ull, st);
   // Mirror pairs need a lattice and a window centred on y = 0 and an even row count;
   // the rows paired inside [row0, row1) form [a, b) with a + b = ny.
   const int32_t a = std::max(p.row0, p.ny - p.row1), b = std::min(p.row1, p.ny - p.row0);
-  if (!(p.cy == 0.0f && p.sy == 0.0f && (p.ny & 1) == 0 && a < b))
-    return shoot_rows<false>(p, p.row0, p.row1, counts, stats, st);
-  hipError_t e = shoot_rows<true>(p, p.ny / 2, b, counts, stats, st);
-  if (e == hipSuccess) e = shoot_rows<false>(p, p.row0, a, counts, stats, st);
-  if (e == hipSuccess) e = shoot_rows<false>(p, b, p.row1, counts, stats, st);
+  if (e != hipSuccess) return e;
+  if (!(p.cy == 0.0f && p.sy == 0.0f && (p.ny & 1) == 0 && a < b)) {
+    e = shoot_rows<false>(p, p.row0, p.row1, counts, ss, num_cu, st);
+  } else {
+    e = shoot_rows<true>(p, p.ny / 2, b, counts, ss, num_cu, st);
+    if (e == hipSuccess) e = shoot_rows<false>(p, p.row0, a, counts, ss, num_cu, st);
+    if (e == hipSuccess) e = shoot_rows<false>(p, b, p.row1, counts, ss, num_cu, st);
+  }
+  if (e == hipSuccess && ss) {
+    hipLaunchKernelGGL(k_stats_sum, dim3(1), dim3(64), 0, st, ss, stats);
+    e = hipGetLastError();
+  }
   return e;
 }
 

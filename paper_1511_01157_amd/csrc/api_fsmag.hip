@@ -1,5 +1,5 @@
 // C ABI, finite-source magnification by image-centred ray shooting (sec. 5): the
-// critical curves on the host, then the proximity kernel and the image-centred kernel.
+// critical curve, then the proximity kernel and the image-centred kernels.
 
 #include "host.h"
 #include "fsmag.h"
@@ -32,8 +32,9 @@ int morse_fs_magnification(morse_ctx* ctx, double s, double q, const double* d_z
   HIP_TRY(ctx, hipSetDevice(ctx->device));
   const double m1 = 1.0 / (1.0 + q), m2 = q / (1.0 + q);
   const double x1 = -s * q / (1.0 + q), x2 = s / (1.0 + q);
-  // critical points and their caustic images (Eq. 2), host FP64, resident in the context
-  // until a call needs another (s, q, phases)
+  // critical points and their caustic images (Eq. 2), resident in the context until a call
+  // needs another (s, q, phases); a massless companion's (two roots meet on it) come from
+  // the host's continuation
   const size_t nc = (size_t)o.n_crit * 4;
   if ((rc = reserve_meta(ctx, ctx->fs_crit, 32 * nc))) return rc;
   Hasher key;
@@ -43,19 +44,24 @@ int morse_fs_magnification(morse_ctx* ctx, double s, double q, const double* d_z
   key.pod(o.n_crit);
   if (ctx->fs_crit.key != key.h) {
     ctx->fs_crit.key = 0;
-    std::vector<std::complex<double>> zc;
-    critical_points(s, q, o.n_crit, zc);
-    std::vector<double> buf(4 * nc);
-    for (size_t j = 0; j < nc; ++j) {
-      const std::complex<double> z = zc[j];
-      const std::complex<double> zeta = z - m1 / std::conj(z - x1) - m2 / std::conj(z - x2);
-      buf[2 * j] = z.real();
-      buf[2 * j + 1] = z.imag();
-      buf[2 * nc + 2 * j] = zeta.real();
-      buf[2 * nc + 2 * j + 1] = zeta.imag();
+    double* crit = (double*)ctx->fs_crit.p;
+    if (m2 > 0.0) {
+      HIP_TRY(ctx, launch_fs_crit(m1, m2, x1, x2, o.n_crit, crit, crit + 2 * nc, ctx->stream));
+    } else {
+      std::vector<std::complex<double>> zc;
+      critical_points(s, q, o.n_crit, zc);
+      std::vector<double> buf(4 * nc);
+      for (size_t j = 0; j < nc; ++j) {
+        const std::complex<double> z = zc[j];
+        const std::complex<double> zeta = z - m1 / std::conj(z - x1) - m2 / std::conj(z - x2);
+        buf[2 * j] = z.real();
+        buf[2 * j + 1] = z.imag();
+        buf[2 * nc + 2 * j] = zeta.real();
+        buf[2 * nc + 2 * j + 1] = zeta.imag();
+      }
+      if ((rc = upload(ctx, crit, buf.data(), 32 * nc))) return rc;
+      HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // buf goes out of scope
     }
-    if ((rc = upload(ctx, ctx->fs_crit.p, buf.data(), 32 * nc))) return rc;
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // buf goes out of scope
     ctx->fs_crit.key = key.h;
   }
   Plan pl;

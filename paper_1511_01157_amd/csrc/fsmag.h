@@ -36,6 +36,11 @@ struct FsArgs {
 hipError_t launch_traj_positions(const double* t, int64_t n, double t0, double u0, double tE,
                                  double alpha, double* zeta, hipStream_t st);
 
+// Critical points crit[4 nphi][2] (4 per phase, phase-major) of a binary lens with m2 > 0
+// and their Eq. 2 images caus[4 nphi][2].
+hipError_t launch_fs_crit(double m1, double m2, double x1, double x2, int32_t nphi, double* crit,
+                          double* caus, hipStream_t st);
+
 // Caustic distance (one wavefront per source), then the point-source magnification of
 // the far sources (one thread each); the sources within near * rho of the caustic are
 // listed for the image-centred kernel.

@@ -20,6 +20,8 @@
 
 #include "fsmag.h"
 
+#include <climits>
+
 namespace morse {
 
 namespace {
@@ -40,13 +42,23 @@ __device__ __forceinline__ cd cadd(cd a, cd b) { return {a.x + b.x, a.y + b.y}; 
 __device__ __forceinline__ cd csub(cd a, cd b) { return {a.x - b.x, a.y - b.y}; }
 __device__ __forceinline__ cd cmul(cd a, cd b) { return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
 __device__ __forceinline__ cd cscale(cd a, double s) { return {a.x * s, a.y * s}; }
-__device__ __forceinline__ double cabs(cd a) { return hypot(a.x, a.y); }
+__device__ __forceinline__ double cabs2(cd a) { return fma(a.x, a.x, a.y * a.y); }
+// |a|, for numbers whose squares stay in the FP64 range (positions, steps, residuals; the
+// square of a step below 1e-154 vanishes, far under the last place of any root)
+__device__ __forceinline__ double cabs(cd a) { return sqrt(cabs2(a)); }
+// 1/x within one unit in the last place for |x| in [1e-300, 1e300] (0 and inf give NaN): the
+// hardware's reciprocal and two Newton steps, 5 instructions for the 10 of an IEEE division
+__device__ __forceinline__ double recip(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
 // a / b: directly as a conj(b) / |b|^2 while |b|^2 stays well inside the FP64 range,
 // else scaled (Smith).
 __device__ __forceinline__ cd cdivc(cd a, cd b) {
   const double n = b.x * b.x + b.y * b.y;
   if (n > 1e-280 && n < 1e280) {
-    const double s = 1.0 / n;
+    const double s = recip(n);
     return {(a.x * b.x + a.y * b.y) * s, (a.y * b.x - a.x * b.y) * s};
   }
   if (fabs(b.x) >= fabs(b.y)) {
@@ -68,16 +80,19 @@ __device__ __forceinline__ cd lens_eq(const Lens& L, cd z) {
   return csub(csub(z, cscale(crecip(w1), L.m1)), cscale(crecip(w2), L.m2));
 }
 
-// |zeta(z) - zs|^2 by Eq. 2 with each lens term written as m_k (z - x_k) / |z - x_k|^2,
-// the conjugate's reciprocal: one division per lens and no square root (the samples of
-// the image-centred integration and the growth test; a sample on a lens gives inf or
-// NaN, which compare as outside the source).
-__device__ __forceinline__ double lens_dist2(const Lens& L, cd z, cd zs) {
-  const double d1 = z.x - L.x1, d2 = z.x - L.x2, yy = z.y * z.y;
-  const double a1 = L.m1 / (d1 * d1 + yy), a2 = L.m2 / (d2 * d2 + yy);
-  const double ex = ((z.x - a1 * d1) - a2 * d2) - zs.x;
-  const double ey = ((z.y - a1 * z.y) - a2 * z.y) - zs.y;
-  return ex * ex + ey * ey;
+// f = rho^2 - |zeta(z) - zs|^2 at z = r (cs, sn) by Eq. 2 (positive inside the source), each
+// lens term written as m_k (z - x_k) / |z - x_k|^2, the conjugate's reciprocal; one
+// reciprocal of |z - x1|^2 |z - x2|^2 serves both (the samples of the image-centred
+// integration and the growth test; a sample on a lens gives NaN, which compares as outside).
+__device__ __forceinline__ double source_f(const Lens& L, double r, double cs, double sn, cd zs, double rho2) {
+  const double zy = r * sn, yy = zy * zy;
+  const double d1 = fma(r, cs, -L.x1), d2 = fma(r, cs, -L.x2);
+  const double r1 = fma(d1, d1, yy), r2 = fma(d2, d2, yy);
+  const double y = recip(r1 * r2);
+  const double a1 = (L.m1 * r2) * y, a2 = (L.m2 * r1) * y;
+  const double ex = fma(-a2, d2, fma(-a1, d1, fma(r, cs, -zs.x)));
+  const double ey = fma(-(a1 + a2), zy, zy - zs.y);
+  return fma(-ex, ex, fma(-ey, ey, rho2));
 }
 
 // The quintic whose roots contain the images of zeta.  With Q = (z - x1)(z - x2) and
@@ -128,7 +143,10 @@ __device__ __forceinline__ void poly_eval(const cd (&a)[6], cd z, cd& p, cd& dp)
 __device__ void quintic_roots(const cd (&a)[6], cd (&z)[5]) {
   const cd inv5 = crecip(a[5]);
   double rad = 0.0;
-  for (int i = 0; i < 5; ++i) rad = fmax(rad, cabs(cmul(a[i], inv5)));
+  for (int i = 0; i < 5; ++i) {  // hypot: a source beside a lens has a tiny a[5]
+    const cd c = cmul(a[i], inv5);
+    rad = fmax(rad, hypot(c.x, c.y));
+  }
   rad = 1.0 + rad;
   for (int k = 0; k < 5; ++k) {
     double sn, cs;
@@ -200,8 +218,7 @@ __device__ double point_source_A(const Lens& L, cd zeta) {
   for (int k = 0; k < 5; ++k) {
     const cd w1 = {z[k].x - L.x1, -z[k].y}, w2 = {z[k].x - L.x2, -z[k].y};
     const cd g = cadd(cscale(crecip(cmul(w1, w1)), L.m1), cscale(crecip(cmul(w2, w2)), L.m2));
-    const double ag = cabs(g);
-    A += sel[k] ? fabs(1.0 / (1.0 - ag * ag)) : 0.0;
+    A += sel[k] ? fabs(1.0 / (1.0 - cabs2(g))) : 0.0;
   }
   return A;
 }
@@ -283,13 +300,13 @@ __global__ __launch_bounds__(256) void k_fs_classify(FsArgs a) {
     const cd zs = {a.zeta[2 * i], a.zeta[2 * i + 1]};
     double dmin = __builtin_inf();
     for (int32_t j = lane; j < a.n_crit; j += kWave) {
-      const double d = cabs(csub(cd{a.caus[2 * j], a.caus[2 * j + 1]}, zs));
-      if (d < dmin) dmin = d;  // NaN points (a massless companion) never win
+      const double d = cabs2(csub(cd{a.caus[2 * j], a.caus[2 * j + 1]}, zs));
+      if (d < dmin) dmin = d;  // squares; NaN points (a massless companion) never win
     }
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) dmin = fmin(dmin, __shfl_xor(dmin, off));
     if (lane == 0) {
-      if (dmin > a.near * a.rho) {
+      if (sqrt(dmin) > a.near * a.rho) {
         a.nreg[i] = -1;
       } else {
         a.nreg[i] = 0;
@@ -341,10 +358,6 @@ __device__ void bitonic(double* key, double* v1, double* v2) {
     }
 }
 
-__device__ __forceinline__ bool inside_source(const Lens& L, cd z, cd zs, double rho) {
-  return lens_dist2(L, z, zs) < rho * rho;
-}
-
 // numpy.linspace(a, b, n)[k]
 __device__ __forceinline__ double linspace_at(double a, double b, int n, int k) {
   return k == n - 1 ? b : a + k * ((b - a) / (n - 1));
@@ -370,6 +383,8 @@ __device__ Region region_union(const Region& a, const Region& b) {
   return u;
 }
 
+constexpr int kPer = kSeedCap / kFsThreads;  // seeds per lane of the prefix counts
+
 struct Shared {
   double key[kSeedCap], r[kSeedCap], th[kSeedCap];
   int run[kSeedCap];
@@ -378,77 +393,156 @@ struct Shared {
   int n_seed, n_reg, flag[4];
 };
 
-// Integral of the profile over one region and the bounds of its inside nodes (all
-// NT lanes of the workgroup; box = {k0, k1, j0, j1}, k1 < 0 when nothing is inside).
-template <int NT>
-struct IntShared {
-  double red[NT];
-  int ired[4][NT];
-};
+// Smallest v of the workgroup.
+__device__ int block_min(int v, Shared& sh) {
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
+  __syncthreads();
+  if (threadIdx.x % kWave == 0) sh.ired[0][threadIdx.x / kWave] = v;
+  __syncthreads();
+  for (int w = 0; w < kFsThreads / kWave; ++w) v = min(v, sh.ired[0][w]);
+  return v;
+}
+
+// Sum of v over the lanes before this one.
+__device__ int block_prefix(int v, Shared& sh) {
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  int incl = v;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int l = __shfl_up(incl, o);
+    if (lane >= o) incl += l;
+  }
+  __syncthreads();
+  if (lane == kWave - 1) sh.ired[0][wave] = incl;
+  __syncthreads();
+  int before = incl - v;
+  for (int w = 0; w < wave; ++w) before += sh.ired[0][w];
+  return before;
+}
+
+// Range of (lo, hi) over the wavefront, on every lane.
+__device__ __forceinline__ void wave_range(double& lo, double& hi) {
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, o));
+    hi = fmax(hi, __shfl_xor(hi, o));
+  }
+}
 
 template <int NT>
-__device__ double integrate_region(const FsArgs& a, const Lens& L, cd zs, const Region& g,
-                                   IntShared<NT>& sh, int (&box)[4]) {
+struct IntShared {
+  double red[NT / kWave];
+  int ired[NT / kWave][4];
+};
+
+// Bounds of the nodes of a region's grid that lie inside the source (all NT lanes of the
+// workgroup): box = {k0, k1, j0, j1}, k1 < 0 when none does.
+template <int NT>
+__device__ void inside_box(const FsArgs& a, const Lens& L, cd zs, const Region& g, IntShared<NT>& sh,
+                           int (&box)[4]) {
   const double rho2 = a.rho * a.rho;
-  const double dth = (g.t1 - g.t0) / a.n_theta;
-  const double dr = (g.r1 - g.r0) / a.n_r;
-  const double c_ld = 1.5 * a.gamma / a.rho;
-  double acc = 0.0;
+  const double dth = (g.t1 - g.t0) / a.n_theta, dr = (g.r1 - g.r0) / a.n_r;
   int k0 = 1 << 30, k1 = -1, j0 = 1 << 30, j1 = -1;
   for (int j = threadIdx.x; j < a.n_theta; j += NT) {
     double sn, cs;
     sincos(g.t0 + (j + 0.5) * dth, &sn, &cs);
-    double col = 0.0, fa = 0.0, ra = 0.0;
-    bool any = false;
-    for (int k = 0; k <= a.n_r; ++k) {
-      const double r = g.r0 + k * dr;
-      const double f = rho2 - lens_dist2(L, cd{r * cs, r * sn}, zs);
-      if (f > 0.0) {
-        any = true;
-        k0 = min(k0, k);
-        k1 = max(k1, k);
+    int first = 1 << 30, last = -1;
+    for (int k = 0; k <= a.n_r; ++k)
+      if (source_f(L, g.r0 + k * dr, cs, sn, zs, rho2) > 0.0) {
+        first = min(first, k);
+        last = k;
       }
-      if (k > 0 && (fa > 0.0 || f > 0.0)) {
+    if (last >= 0) {
+      k0 = min(k0, first);
+      k1 = max(k1, last);
+      j0 = min(j0, j);
+      j1 = j;
+    }
+  }
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) {
+    k0 = min(k0, __shfl_xor(k0, o));
+    k1 = max(k1, __shfl_xor(k1, o));
+    j0 = min(j0, __shfl_xor(j0, o));
+    j1 = max(j1, __shfl_xor(j1, o));
+  }
+  if (threadIdx.x % kWave == 0) {
+    int* w = sh.ired[threadIdx.x / kWave];
+    w[0] = k0;
+    w[1] = k1;
+    w[2] = j0;
+    w[3] = j1;
+  }
+  __syncthreads();
+  for (int w = 0; w < NT / kWave; ++w) {
+    k0 = min(k0, sh.ired[w][0]);
+    k1 = max(k1, sh.ired[w][1]);
+    j0 = min(j0, sh.ired[w][2]);
+    j1 = max(j1, sh.ired[w][3]);
+  }
+  __syncthreads();
+  box[0] = k0;
+  box[1] = k1;
+  box[2] = j0;
+  box[3] = j1;
+}
+
+// Integral of the profile over one region (all NT lanes of the workgroup; a fixed order of
+// the sums).  kLimb: a limb-darkened profile; without it the square roots drop out.
+template <int NT, bool kLimb>
+__device__ double integrate_region(const FsArgs& a, const Lens& L, cd zs, const Region& g, IntShared<NT>& sh) {
+  const double rho2 = a.rho * a.rho;
+  const double dth = (g.t1 - g.t0) / a.n_theta;
+  const double dr = (g.r1 - g.r0) / a.n_r;
+  const double c_ld = 1.5 * a.gamma / a.rho * (2.0 / 3.0);
+  double acc = 0.0;
+  for (int j = threadIdx.x; j < a.n_theta; j += NT) {
+    double sn, cs;
+    sincos(g.t0 + (j + 0.5) * dth, &sn, &cs);
+    double col = 0.0, ra = g.r0;
+    double fa = source_f(L, ra, cs, sn, zs, rho2);
+    bool ina = fa > 0.0;
+    double sa = kLimb && ina ? sqrt(fa) : 0.0;
+    for (int k = 1; k <= a.n_r; ++k) {
+      const double r = g.r0 + k * dr;
+      const double f = source_f(L, r, cs, sn, zs, rho2);
+      const bool inb = f > 0.0;
+      double sb = 0.0;
+      if (ina || inb) {
+        if (kLimb && inb) sb = sqrt(f);
         // the inside part [lo, hi] of the segment, the limb where f (linear) is zero
-        const bool ina = fa > 0.0, inb = f > 0.0;
-        const double rs = ra + dr * fa / (fa - f);
-        const double lo = ina ? ra : rs, hi = inb ? ra + dr : rs;
-        const double sa = ina ? sqrt(fa) : 0.0, sb = inb ? sqrt(f) : 0.0;
-        const double ms = (sa + sb > 0.0) ? (2.0 / 3.0) * (sa * sa + sa * sb + sb * sb) / (sa + sb) : 0.0;
-        const double len = hi - lo, rm = 0.5 * (lo + hi);
-        col += (1.0 - a.gamma) * rm * len + c_ld * rm * len * ms;
+        double lo = ra, hi = ra + dr;
+        if (ina != inb) {
+          const double rs = ra + dr * fa / (fa - f);
+          lo = ina ? lo : rs;
+          hi = inb ? hi : rs;
+        }
+        const double area = 0.5 * (lo + hi) * (hi - lo);
+        col += (1.0 - a.gamma) * area;
+        if (kLimb)  // mean of sqrt(f) over the part, f linear: 2/3 (fa + sa sb + fb) / (sa + sb)
+          col += c_ld * area * (((sa * sa + sa * sb) + sb * sb) * recip(sa + sb));
       }
       fa = f;
       ra = r;
+      sa = sb;
+      ina = inb;
     }
     acc += col;
-    if (any) {
-      j0 = min(j0, j);
-      j1 = max(j1, j);
-    }
   }
-  sh.red[threadIdx.x] = acc;
-  sh.ired[0][threadIdx.x] = k0;
-  sh.ired[1][threadIdx.x] = k1;
-  sh.ired[2][threadIdx.x] = j0;
-  sh.ired[3][threadIdx.x] = j1;
+  acc = wave_sum(acc);
+  if (threadIdx.x % kWave == 0) sh.red[threadIdx.x / kWave] = acc;
   __syncthreads();
-  for (int w = NT / 2; w > 0; w >>= 1) {  // fixed tree: the same sum every time
-    if ((int)threadIdx.x < w) {
-      sh.red[threadIdx.x] += sh.red[threadIdx.x + w];
-      sh.ired[0][threadIdx.x] = min(sh.ired[0][threadIdx.x], sh.ired[0][threadIdx.x + w]);
-      sh.ired[1][threadIdx.x] = max(sh.ired[1][threadIdx.x], sh.ired[1][threadIdx.x + w]);
-      sh.ired[2][threadIdx.x] = min(sh.ired[2][threadIdx.x], sh.ired[2][threadIdx.x + w]);
-      sh.ired[3][threadIdx.x] = max(sh.ired[3][threadIdx.x], sh.ired[3][threadIdx.x + w]);
-    }
-    __syncthreads();
-  }
-  const double total = sh.red[0] * dth;
-  for (int q = 0; q < 4; ++q) box[q] = sh.ired[q][0];
+  acc = sh.red[0];
+  for (int w = 1; w < NT / kWave; ++w) acc += sh.red[w];
   __syncthreads();
-  return total;
+  return acc * dth;
 }
 
+// Regions of one source per workgroup.  Bound: latency, of the quintics (one per lane) and of
+// the sorts; the runs, the radial parts and their bounds come from prefix counts and
+// wavefront ranges (one lane walking the 1200 seeds three times took 0.5 of 0.87 ms for the
+// 335 near epochs of a light curve, now 0.32 ms).
 __global__ __launch_bounds__(kFsThreads) void k_fs_regions(FsArgs a) {
   __shared__ Shared sh;
   const Lens L{a.m1, a.m2, a.x1, a.x2};
@@ -526,66 +620,97 @@ __global__ __launch_bounds__(kFsThreads) void k_fs_regions(FsArgs a) {
     __syncthreads();
     bitonic(sh.key, sh.r, sh.th);
     // 2. angular runs: cuts at gaps wider than `gap` (circularly); walking from the
-    // seed after the first cut, run ids and angles unwrapped from each run's first seed
-    if (tid == 0) {
-      int first = -1;
-      for (int j = 0; j < ns; ++j) {
-        const double nxt = j + 1 < ns ? sh.th[j + 1] : sh.th[0] + two_pi;
-        sh.run[j] = (nxt - sh.th[j] > a.gap) ? 1 : 0;  // cut after seed j
-        if (first < 0 && sh.run[j]) first = j;
+    // seed after the first cut, run ids and angles unwrapped from each run's first seed.
+    // Each lane takes kPer seeds in a row; prefix counts give the run ids.
+    int first = INT_MAX;
+    for (int j = tid; j < ns; j += kFsThreads) {
+      const double nxt = j + 1 < ns ? sh.th[j + 1] : sh.th[0] + two_pi;
+      const int cut = (nxt - sh.th[j] > a.gap) ? 1 : 0;  // cut after seed j
+      sh.run[j] = cut;
+      if (cut) first = min(first, j);
+    }
+    first = block_min(first, sh);
+    if (first == INT_MAX) {  // no cut: one ring (uniform)
+      double r0 = __builtin_inf(), r1 = -__builtin_inf();
+      for (int j = tid; j < ns; j += kFsThreads) {
+        r0 = fmin(r0, sh.r[j]);
+        r1 = fmax(r1, sh.r[j]);
       }
-      sh.flag[0] = first < 0 ? 1 : 0;
-      if (first < 0) {  // no cut: one ring
-        double r0 = sh.r[0], r1 = sh.r[0];
-        for (int j = 1; j < ns; ++j) {
-          r0 = fmin(r0, sh.r[j]);
-          r1 = fmax(r1, sh.r[j]);
+      wave_range(r0, r1);
+      __syncthreads();
+      if (tid % kWave == 0) {  // sh.key's sorted angles are done with
+        sh.key[2 * (tid / kWave)] = r0;
+        sh.key[2 * (tid / kWave) + 1] = r1;
+      }
+      __syncthreads();
+      if (tid == 0) {
+        for (int w = 1; w < kFsThreads / kWave; ++w) {
+          r0 = fmin(r0, sh.key[2 * w]);
+          r1 = fmax(r1, sh.key[2 * w + 1]);
         }
         sh.reg[0] = Region{r0, r1, -M_PI, M_PI};
         sh.n_reg = 1;
-      } else {
-        int run = 0;
-        bool fresh = true;
-        double start = 0.0;
-        for (int m = 0; m < ns; ++m) {
-          const int j = (first + 1 + m) % ns;
-          const int cut = sh.run[j];
-          if (fresh) start = sh.th[j];
-          fresh = false;
-          if (sh.th[j] < start) sh.th[j] += two_pi;
-          sh.run[j] = run;
+      }
+      __syncthreads();
+    } else {
+      const bool wraps = sh.run[ns - 1] == 0;  // the last seed's run goes on at seed 0
+      int cuts[kPer], ids[kPer], mine = 0;
+      for (int q = 0; q < kPer; ++q) {
+        const int m = tid * kPer + q, j = (first + 1 + m) % ns;
+        cuts[q] = m < ns ? sh.run[j] : 0;
+        ids[q] = mine;
+        mine += cuts[q];
+      }
+      const int before = block_prefix(mine, sh);
+      // seeds before the first cut that follow seed 0 without a cut belong to the wrapped
+      // run: their id is the last of the unwrapped part's
+      if (tid == 0) sh.flag[1] = 0;
+      __syncthreads();
+      const int m_wrap = ns - 1 - first;  // m of seed 0
+      for (int q = 0; q < kPer; ++q)
+        if (tid * kPer + q == m_wrap) sh.flag[1] = before + ids[q];  // run id of seed 0
+      __syncthreads();
+      const int wrap_id = sh.flag[1];
+      __syncthreads();
+      for (int q = 0; q < kPer; ++q) {
+        const int m = tid * kPer + q, j = (first + 1 + m) % ns;
+        if (m < ns) {
+          const int run = before + ids[q];
+          if (wraps && m >= m_wrap && run == wrap_id) sh.th[j] += two_pi;
           sh.key[j] = run * 1.0e6 + sh.r[j];  // radii stay far below 1e6
-          if (cut) {
-            ++run;
-            fresh = true;
-          }
         }
       }
-    }
-    __syncthreads();
-    if (!sh.flag[0]) {
+      __syncthreads();
       // 3. seeds by (run, r); parts of a run split where the radius jumps
       bitonic(sh.key, sh.r, sh.th);
-      if (tid == 0) {
-        int nr = 0;
-        for (int j = 0; j < ns; ++j) {
-          const int run = (int)floor(sh.key[j] / 1.0e6);
-          const bool fresh = j == 0 || run != (int)floor(sh.key[j - 1] / 1.0e6) ||
-                             sh.r[j] - sh.r[j - 1] > fmax(a.gap * sh.r[j], 4.0 * a.rho);
-          if (fresh) {
-            if (nr == kRegionCap) {
-              nr = kRegionCap + 1;
-              break;
-            }
-            sh.reg[nr++] = Region{sh.r[j], sh.r[j], sh.th[j], sh.th[j]};
-          } else {
-            Region& g = sh.reg[nr - 1];
-            g.r1 = sh.r[j];
-            g.t0 = fmin(g.t0, sh.th[j]);
-            g.t1 = fmax(g.t1, sh.th[j]);
-          }
+      int starts[kPer];
+      mine = 0;
+      for (int q = 0; q < kPer; ++q) {
+        const int j = tid * kPer + q;
+        const bool fresh = j < ns && (j == 0 || floor(sh.key[j] / 1.0e6) != floor(sh.key[j - 1] / 1.0e6) ||
+                                      sh.r[j] - sh.r[j - 1] > fmax(a.gap * sh.r[j], 4.0 * a.rho));
+        starts[q] = fresh ? 1 : 0;
+        mine += starts[q];
+      }
+      int at = block_prefix(mine, sh);
+      for (int q = 0; q < kPer; ++q)
+        if (starts[q]) {
+          if (at < kRegionCap) sh.run[at] = tid * kPer + q;  // the part's first seed
+          ++at;
         }
-        sh.n_reg = nr;
+      if (tid == kFsThreads - 1) sh.n_reg = min(at, kRegionCap + 1);
+      __syncthreads();
+      const int nr = min(sh.n_reg, kRegionCap);
+      const bool over = sh.n_reg > kRegionCap;
+      for (int g = tid / kWave; g < nr; g += kFsThreads / kWave) {  // a wavefront per part
+        const int j0 = sh.run[g], j1 = g + 1 < nr || over ? sh.run[min(g + 1, nr - 1)] : ns;
+        double t0 = __builtin_inf(), t1 = -__builtin_inf();
+        for (int j = j0 + tid % kWave; j < j1; j += kWave) {
+          t0 = fmin(t0, sh.th[j]);
+          t1 = fmax(t1, sh.th[j]);
+        }
+        wave_range(t0, t1);
+        if (tid % kWave == 0) sh.reg[g] = Region{sh.r[j0], sh.r[max(j1 - 1, j0)], t0, t1};
       }
       __syncthreads();
     }
@@ -636,7 +761,7 @@ __global__ __launch_bounds__(kFsThreads) void k_fs_regions(FsArgs a) {
           }
           double sn, cs;
           sincos(tt, &sn, &cs);
-          if (inside_source(L, cd{rr * cs, rr * sn}, zs, a.rho)) sh.flag[side] = 1;
+          if (source_f(L, rr, cs, sn, zs, a.rho * a.rho) > 0.0) sh.flag[side] = 1;
         }
         __syncthreads();
         const int h0 = sh.flag[0], h1 = sh.flag[1], h2 = sh.flag[2], h3 = sh.flag[3];
@@ -696,9 +821,15 @@ __global__ __launch_bounds__(kFsThreads) void k_fs_regions(FsArgs a) {
   }
 }
 
-// 8. One workgroup per (source, region): the region's integral, then up to n_shrink
-// times the region cut to its inside cells (plus one cell) and integrated again.
-constexpr int kIntThreads = 512;
+// 8. One workgroup per (source, region): up to n_shrink times the region is cut to its
+// inside cells (plus one cell), then integrated.  Only the last grid's integral counts, so
+// the earlier ones are searched for their inside nodes alone.
+// Bound: FP64 issue, 26 FP64 operations and a reciprocal per node.  256 lanes a workgroup:
+// all the regions of a light curve (about 1100 of 512 x 512 cells on 335 near epochs) are
+// resident at once, where 512 lanes took a second, nearly empty round.  That curve: 1.5 ms
+// 3.7 ms before (two IEEE divisions a node, every grid
+// integrated with two square roots and three divisions a segment, 512 lanes).
+constexpr int kIntThreads = 256;
 __global__ __launch_bounds__(kIntThreads) void k_fs_integrate(FsArgs a) {
   __shared__ IntShared<kIntThreads> sh;
   const Lens L{a.m1, a.m2, a.x1, a.x2};
@@ -709,10 +840,12 @@ __global__ __launch_bounds__(kIntThreads) void k_fs_integrate(FsArgs a) {
     const cd zs = {a.zeta[2 * i], a.zeta[2 * i + 1]};
     const double* rg = a.regs + 4 * (int64_t)slot;
     Region R{rg[0], rg[1], rg[2], rg[3]};
-    int box[4];
-    double val = integrate_region<kIntThreads>(a, L, zs, R, sh, box);
+    bool empty = false;
     for (int it = 0; it < a.n_shrink; ++it) {
-      if (box[1] < 0) break;
+      int box[4];
+      inside_box<kIntThreads>(a, L, zs, R, sh, box);
+      empty = box[1] < 0;
+      if (empty) break;
       const double dr = (R.r1 - R.r0) / a.n_r;
       const int n0 = max(box[0] - 1, 0), n1 = min(box[1] + 1, a.n_r);
       Region N = {R.r0 + n0 * dr, R.r0 + n1 * dr, R.t0, R.t1};
@@ -723,8 +856,11 @@ __global__ __launch_bounds__(kIntThreads) void k_fs_integrate(FsArgs a) {
       }
       if (N.r0 == R.r0 && N.r1 == R.r1 && N.t0 == R.t0 && N.t1 == R.t1) break;
       R = N;
-      val = integrate_region<kIntThreads>(a, L, zs, R, sh, box);
     }
+    double val = 0.0;
+    if (!empty)
+      val = a.gamma > 0.0 ? integrate_region<kIntThreads, true>(a, L, zs, R, sh)
+                          : integrate_region<kIntThreads, false>(a, L, zs, R, sh);
     if (threadIdx.x == 0) a.reg_val[slot] = val;
   }
 }

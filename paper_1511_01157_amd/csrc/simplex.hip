@@ -16,7 +16,10 @@
 // ordered by a stable sort (a new vertex ranks after old ones of equal value; NaN
 // counts as +inf).  The steps form a state machine around a single chi-square call,
 // and all control flow is uniform across the workgroup, since every lane holds the
-// same sums.
+// same sums.  A simplex that a shrink no longer moves (its vertices one unit in the last
+// place apart across a step of the binary32 samples, or all at +inf) would repeat the same
+// iteration up to max_iter: it ends there with the result and the counts of the full run.
+// Two such lines among 1200 took 69 ms of serial evaluations where the others take 1.8.
 
 #include "simplex.h"
 
@@ -32,6 +35,12 @@ constexpr int kStagePoints = 3072;  // light curves up to this length go to LDS 
 struct Vertex {
   double x0, x1, f;
 };
+
+// Bit for bit the same vertex (NaN included).
+__device__ __forceinline__ bool same(const Vertex& a, const Vertex& b) {
+  auto bits = [](double x) { return __double_as_longlong(x); };
+  return bits(a.x0) == bits(b.x0) && bits(a.x1) == bits(b.x1) && bits(a.f) == bits(b.f);
+}
 
 __device__ __forceinline__ void order3(Vertex (&v)[3]) {
   for (int i = 1; i < 3; ++i)
@@ -153,6 +162,7 @@ __global__ __launch_bounds__(kItemThreads) void k_line_simplex(SimplexArgs a) {
     double px0 = s0, px1 = s1, b0 = 0.0, b1 = 0.0, r0 = 0.0, r1 = 0.0, fr = 0.0;
     int state = kInit0;
     int32_t it = 0, evals = 0;
+    bool still = false;  // the last iteration left every vertex as it was
     for (;;) {
       const double f = chi2_at(px0, px1);
       ++evals;
@@ -214,12 +224,14 @@ __global__ __launch_bounds__(kItemThreads) void k_line_simplex(SimplexArgs a) {
           }
           break;
         case kShrink1:
+          still = same(v[1], {px0, px1, f});
           v[1] = {px0, px1, f};
           px0 = v[0].x0 + 0.5 * (v[2].x0 - v[0].x0);
           px1 = v[0].x1 + 0.5 * (v[2].x1 - v[0].x1);
           state = kShrink2;
           break;
         default:  // kShrink2
+          still = still && same(v[2], {px0, px1, f});
           v[2] = {px0, px1, f};
           next = true;
           break;
@@ -232,6 +244,14 @@ __global__ __launch_bounds__(kItemThreads) void k_line_simplex(SimplexArgs a) {
       if (!next) continue;
       order3(v);
       if (it >= a.max_iter || v[2].f - v[0].f <= a.ftol * fabs(v[0].f)) break;
+      if (still) {
+        // A shrink that moved nothing: the vertices are those of the iteration's start, and
+        // every later iteration repeats it (an iteration depends on them alone) to the last
+        // one allowed, four evaluations each.
+        evals += 4 * (a.max_iter - it);
+        it = a.max_iter;
+        break;
+      }
       ++it;
       b0 = (v[0].x0 + v[1].x0) * 0.5;
       b1 = (v[0].x1 + v[1].x1) * 0.5;

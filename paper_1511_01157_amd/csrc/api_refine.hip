@@ -102,9 +102,10 @@ int setup_candidates(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   lc.off = d_off;
   lc.sums = (double*)pl.ptr(ctx, i_sums);
   lc.t_ref = d_tref;
+  lc.sorted = nullptr;
   HIP_TRY(ctx, launch_quad_pack(d_maps, hm.data(), n_maps, ctx->stream));
   HIP_TRY(ctx, launch_lc_prep(lc.t, lc.F, lc.w, lc.off, ne, (double*)lc.wFc, (double*)lc.sums,
-                              ctx->stream));
+                              nullptr, ctx->stream));
   return MORSE_OK;
 }
 }  // namespace
@@ -307,7 +308,7 @@ int morse_chi2_grad_noalloc(morse_ctx* ctx, const morse_map_view* maps, int32_t 
   a.lc.t_ref = (const double*)(meta + b_off);
   HIP_TRY(ctx, launch_quad_pack(d_maps, hm.data(), n_maps, ctx->stream));
   HIP_TRY(ctx, launch_lc_prep(a.lc.t, a.lc.F, a.lc.w, a.lc.off, ne, (double*)a.lc.wFc,
-                              (double*)a.lc.sums, ctx->stream));
+                              (double*)a.lc.sums, nullptr, ctx->stream));
   a.tc = (TrajC*)pl.ptr_at(base, i_tc);
   a.tEv = (double*)pl.ptr_at(base, i_tE);
   a.order = (const int32_t*)pl.ptr_at(base, i_order);

@@ -1,4 +1,4 @@
-// C ABI, trajectory search: plain and batched (persistent, graph-captured) searches,
+// C ABI, trajectory search: plain and batched (one launch, graph-captured) searches,
 // best-per-map and top-k selection, the autotuner of the batched shape and its cache,
 // and candidate lists from the top-k.
 
@@ -12,28 +12,31 @@ namespace {
 struct TuneCfg {
   int traj_per_item;
   int waves_per_block;
-  int blocks_per_cu;
   int tu;
 };
-// Candidate shapes of the batched search tried by the autotuner; index 0 is the
-// default before tuning.  traj_per_item = trajectories per wavefront work item,
-// tu = trajectories scored together by one wavefront (sharing light-curve loads).
-// The last two take one TU group per item (traj_per_item = tu), the fastest shapes on
-// batches of many events and maps.
+// Candidate shapes of the batched search tried by the autotuner (saved caches name them by
+// index).  traj_per_item = trajectories per wavefront, tu = trajectories scored together by
+// one wavefront (sharing light-curve loads).
 constexpr TuneCfg kTune[] = {
-    {8, 4, 16, 2},  {8, 4, 16, 1},  {16, 4, 16, 2}, {8, 8, 8, 2},
-    {32, 8, 8, 2},  {4, 4, 16, 2},  {16, 8, 4, 4},  {8, 2, 32, 2},
-    {16, 4, 16, 4}, {32, 8, 8, 1},  {8, 2, 32, 1},  {64, 4, 8, 4},
-    {32, 8, 4, 4},  {16, 4, 8, 4},  {8, 8, 4, 4},   {16, 8, 2, 4},
-    {4, 8, 4, 4},   {4, 4, 8, 4},
+    {8, 4, 2},  {8, 4, 1},  {16, 4, 2}, {8, 8, 2},  {32, 8, 2}, {4, 4, 2},  {16, 8, 4},
+    {8, 2, 2},  {16, 4, 4}, {32, 8, 1}, {8, 2, 1},  {64, 4, 4}, {32, 8, 4}, {16, 2, 4},
+    {8, 8, 4},  {16, 8, 4}, {4, 8, 4},  {4, 4, 4},  {4, 2, 4},  {4, 1, 4},  {2, 4, 2},
+    {2, 2, 2},  {1, 4, 1},  {1, 2, 1},
 };
+constexpr int kShapeMany = 18, kShapeSome = 20, kShapeFew = 22;
+// The shape before tuning, by the number of trajectories to score (over all events and
+// maps).  A few leave the chip part empty, and one trajectory a wavefront with four chunks
+// in flight is over soonest; many are scored with the fewest instructions, four a
+// wavefront.  Measured on one map, us for TU = 1 / 2 / 4: 1024 trajectories x 1000 points
+// 15.6 / 17.6 / 22.6, 4096 x 1000 23.7 / 23.2 / 27.6, 16384 x 1000 52 / 46 / 49, 32768 x 1000
+// 89 / 70 / 65; 1024 x 6000 31 / 47 / 72, 16384 x 6000 173 / 130 / 119.
+int default_shape(int64_t n) { return n <= 4096 ? kShapeFew : n <= 16384 ? kShapeSome : kShapeMany; }
 constexpr int kNumTune = sizeof(kTune) / sizeof(kTune[0]);
 // k_search_batched is compiled for at most 512 lanes (8 wavefronts) per workgroup and
 // instantiated for TU = 1, 2 and 4; a shape outside that would not launch.
 constexpr bool tune_shapes_valid() {
   for (const TuneCfg& c : kTune)
-    if (c.waves_per_block < 1 || c.waves_per_block > 8 || c.blocks_per_cu < 1 ||
-        c.traj_per_item < 1 || !(c.tu == 1 || c.tu == 2 || c.tu == 4))
+    if (c.waves_per_block < 1 || c.waves_per_block > 8 || c.traj_per_item < 1 || !(c.tu == 1 || c.tu == 2 || c.tu == 4))
       return false;
   return true;
 }
@@ -57,7 +60,6 @@ struct SearchPlan {
   double* chi2 = nullptr;  // output or workspace
   void* tk_scratch = nullptr;
   int num_cu = 256;
-  uint32_t* counter = nullptr;
   double* axes = nullptr;
   // trajectory lists: scoring order of the batched kernel and its counting-sort counters
   int32_t* perm = nullptr;
@@ -151,7 +153,7 @@ int plan_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   if ((int64_t)sp.perm_lists * kPermBins > kPermBinsMax || n_tc > INT32_MAX) sp.perm_lists = 0;
   Plan pl;
   const size_t i_quad = pl.add(quad_region_bytes(maps, n_maps)),
-               i_sums = pl.add(24 * (size_t)sp.n_events), i_cnt = pl.add(4 * kQueueWords),
+               i_sums = pl.add(24 * (size_t)sp.n_events), i_sorted = pl.add(4 * (size_t)sp.n_events),
                i_wF = pl.add(8 * (size_t)sp.n_pts), i_tc = pl.add(sizeof(TrajC) * (size_t)n_tc),
                i_chi = pl.add(need_chi2 ? 8 * (size_t)n_out : 0),
                i_tk = pl.add(k > 0 ? topk_scratch_bytes(sp.n_events, k) : 0),
@@ -165,7 +167,6 @@ int plan_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
     sp.perm_hist = (uint32_t*)pl.ptr(ctx, i_ph);
   }
   double* d_sums = (double*)pl.ptr(ctx, i_sums);
-  sp.counter = (uint32_t*)pl.ptr(ctx, i_cnt);
   double* d_wF = (double*)pl.ptr(ctx, i_wF);
   sp.tc = (TrajC*)pl.ptr(ctx, i_tc);
   sp.chi2 = out->d_chi2 ? out->d_chi2 : (double*)pl.ptr(ctx, i_chi);
@@ -210,6 +211,7 @@ int plan_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   sp.lc.off = d_off;
   sp.lc.sums = d_sums;
   sp.lc.t_ref = d_tref;
+  sp.lc.sorted = (uint32_t*)pl.ptr(ctx, i_sorted);
   return MORSE_OK;
 }
 
@@ -218,7 +220,7 @@ hipError_t enqueue_prep(const SearchPlan& sp, const morse_trajectories* trajs, h
   hipError_t e = launch_quad_pack(sp.d_maps, sp.h_maps.data(), sp.n_maps, st);
   if (e != hipSuccess) return e;
   e = launch_lc_prep(sp.lc.t, sp.lc.F, sp.lc.w, sp.lc.off, sp.n_events,
-                                (double*)sp.lc.wFc, (double*)sp.lc.sums, st);
+                                (double*)sp.lc.wFc, (double*)sp.lc.sums, (uint32_t*)sp.lc.sorted, st);
   if (e != hipSuccess) return e;
   if (trajs->kind == MORSE_TRAJ_GRID)
     return launch_traj_prep_grid(sp.axes, trajs->n_u0, trajs->n_alpha, trajs->n_t0, trajs->n_tE,
@@ -253,7 +255,6 @@ BatchedArgs batched_args(morse_ctx* ctx, const SearchPlan& sp, const morse_traje
   a.out.chi2 = sp.chi2;
   a.out.fs = out->d_fs;
   a.out.fb = out->d_fb;
-  a.counter = sp.counter;
   a.nu = a.na = a.nt = a.ne = 0;
   if (trajs->kind == MORSE_TRAJ_GRID) {
     a.nu = trajs->n_u0;
@@ -265,12 +266,8 @@ BatchedArgs batched_args(morse_ctx* ctx, const SearchPlan& sp, const morse_traje
   a.traj_per_item = cfg.traj_per_item;
   a.waves_per_block = cfg.waves_per_block;
   a.tu = cfg.tu;
-  const int64_t nb = (sp.n_traj + cfg.traj_per_item - 1) / cfg.traj_per_item;
-  const int64_t items = nb * sp.n_events * sp.n_maps;
-  int64_t blocks = (int64_t)ctx->num_cu * cfg.blocks_per_cu;
-  const int64_t need = (items + cfg.waves_per_block - 1) / cfg.waves_per_block;
-  if (blocks > need) blocks = need;
-  a.grid_blocks = (int32_t)std::max<int64_t>(blocks, 1);
+  a.centred = 1;
+  for (const MapC& m : sp.h_maps) a.centred &= (m.sx == 0.0f && m.sy == 0.0f) ? 1 : 0;
   return a;
 }
 
@@ -350,9 +347,10 @@ int morse_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
     return MORSE_OK;
   }
 
-  // batched: one persistent launch, captured into a graph per argument set
+  // batched: one scoring launch, captured into a graph per argument set
   auto it = ctx->tune.find(shape_class(sp));
-  const int cfg_idx = it == ctx->tune.end() ? 0 : it->second;
+  const int cfg_idx =
+      it == ctx->tune.end() ? default_shape(sp.n_traj * sp.n_events * sp.n_maps) : it->second;
   const TuneCfg& cfg = kTune[cfg_idx];
   Hasher h;
   h.pod(metadata_key(maps, n_maps, lcs, trajs));
@@ -369,7 +367,6 @@ int morse_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   if (timed(ctx, MORSE_KERNEL_SEARCH)) {  // same kernels, launched one by one
     const BatchedArgs a = batched_args(ctx, sp, trajs, out, cfg);
     HIP_TRY(ctx, enqueue_prep(sp, trajs, ctx->stream));
-    HIP_TRY(ctx, launch_fill_u32(sp.counter, kQueueWords, 0u, ctx->stream));
     LaunchTimer tm{ctx, MORSE_KERNEL_SEARCH};
     HIP_TRY(ctx, tm.begin(ctx->stream));
     HIP_TRY(ctx, launch_search_batched(a, ctx->stream));
@@ -387,7 +384,6 @@ int morse_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
     hipGraph_t g = nullptr;
     HIP_TRY(ctx, hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeThreadLocal));
     hipError_t e = enqueue_prep(sp, trajs, ctx->capture_stream);
-    if (e == hipSuccess) e = launch_fill_u32(sp.counter, kQueueWords, 0u, ctx->capture_stream);
     if (e == hipSuccess) e = launch_search_batched(a, ctx->capture_stream);
     if (e == hipSuccess) e = enqueue_select(sp, out, ctx->capture_stream);
     hipError_t e2 = hipStreamEndCapture(ctx->capture_stream, &g);
@@ -437,8 +433,7 @@ int morse_autotune(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
     const BatchedArgs a = batched_args(ctx, sub, trajs, &out, kTune[c]);
     float ms = 0.0f;
     for (int rep = 0; rep < 2 && e == hipSuccess; ++rep) {
-      e = launch_fill_u32(sub.counter, kQueueWords, 0u, ctx->stream);
-      if (e == hipSuccess) e = hipEventRecord(e0, ctx->stream);
+      e = hipEventRecord(e0, ctx->stream);
       if (e == hipSuccess) e = launch_search_batched(a, ctx->stream);
       if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
       if (e == hipSuccess) e = hipEventSynchronize(e1);

@@ -316,6 +316,8 @@ inline MapC make_mapc(const float* map, const morse_grid2d& w) {
   m.ly = (float)(w.ny - 1);
   m.tiles_x = (uint32_t)((w.nx - 1 + 3) / 4);
   m.tiles_y = (uint32_t)((w.ny - 1 + 1) / 2);
+  m.row = 8 * m.tiles_x - 2;
+  m.cells = 8 * m.tiles_x * m.tiles_y;
   m.quad = nullptr;
   return m;
 }

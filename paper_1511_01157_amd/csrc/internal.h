@@ -36,42 +36,50 @@ struct TrajC {
 static_assert(sizeof(TrajC) == 32, "TrajC layout");
 
 // A map as the sampling kernels see it.  The row-major pixel values `map` are packed
-// once per call into `quad`: cell (i, j), 0 <= i < mx - 1, 0 <= j < my - 1, holds the
-// four pixel-centre values (A[j][i], A[j][i+1], A[j+1][i], A[j+1][i+1]) as one 16-byte
-// Quad, and the cells are grouped in tiles of 4 (x) by 2 (y) cells, one 128-byte
-// cache line each, tiles in row-major order, cells inside a tile column-major:
-//   q(i, j) = ((j / 2) (4 tiles_x) + i) 2 + j % 2
-// (= 8 tile + 2 (i % 4) + j % 2, tile = (j / 2) tiles_x + i / 4), so the byte offset
-// is one 24-bit multiply-add and two shifts.  A bilinear sample is then one aligned
+// once per call into `quad`: cell (i, j), 0 <= i < mx - 1, 0 <= j < my - 1, holds what a
+// bilinear sample of it takes from the four pixel-centre values around it, the left ones
+// and the steps to the right ones (A[j][i], A[j][i+1] - A[j][i], A[j+1][i], A[j+1][i+1] -
+// A[j+1][i]), the steps rounded to binary32 as the blend rounds them, as one 16-byte Quad,
+// and the cells are grouped in
+// tiles of 4 (x) by 2 (y) cells, one 128-byte cache line each, tiles in row-major order,
+// cells inside a tile column-major:
+//   q(i, j) = (j / 2) 8 tiles_x + 2 i + j % 2 = (j / 2) (8 tiles_x - 2) + (2 i + j)
+// (= 8 tile + 2 (i % 4) + j % 2, tile = (j / 2) tiles_x + i / 4), so the index is one
+// shift-add, one shift and one 24-bit multiply-add.  A bilinear sample is then one aligned
 // load, and the samples of a wavefront along a trajectory touch about 2.5x fewer
 // cache lines than two row-major row loads.
-// One packed cell: the four pixel-centre values around it.
 struct alignas(16) Quad {
-  float v00, v10, v01, v11;
+  float v00, e0, v01, e1;
 };
 
 struct MapC {
   const float* map;
   const Quad* quad;
   uint32_t tiles_x, tiles_y;
+  uint32_t row;                  // 8 tiles_x - 2, the index step of two rows of cells
+  uint32_t cells;                // packed cells, 8 tiles_x tiles_y
   int32_t mx, my;
   float sx, sy, kx, ky, ox, oy;  // grid coordinate g = (zeta - s) k + o
   float lx, ly;                  // on-map bound: g < M - 1
 };
-// Load of the cell at byte offset qb: one buffer_load_dwordx4 through a raw buffer
-// resource over the map's packed cells.  The resource is uniform (scalar registers) and
-// the offset one 32-bit register, so a load needs no 64-bit address arithmetic, and an
-// offset outside the packed map reads zeros instead of faulting (the hardware range
-// check).  Word 3 of the resource: data format 32 bits (bits 15-18 = 4), nothing else.
-constexpr int kRawBufferWord3 = 0x00020000;
-__device__ __forceinline__ Quad ldq(const MapC& m, uint32_t qb) {
-  typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+// Load of cell q: one buffer_load_dwordx4 with a structured index (stride 16) through a
+// buffer resource over the map's packed cells.  The resource is uniform (scalar registers)
+// and the index one 32-bit register that the load itself scales, so a sample needs no
+// address arithmetic beyond the index, and an index outside the packed map reads zeros
+// instead of faulting (the hardware range check).  Word 1: the base's high bits and the
+// stride; word 2: the number of cells; word 3: data format 32 bits (bits 15-18 = 4).
+typedef int rsrc4 __attribute__((ext_vector_type(4)));
+typedef float float4v __attribute__((ext_vector_type(4)));
+__device__ float4v struct_buffer_load_f4(rsrc4 rsrc, int index, int offset, int soffset,
+                                         int aux) __asm("llvm.amdgcn.struct.buffer.load.v4f32");
+constexpr int kBufferWord3 = 0x00020000;
+__device__ __forceinline__ Quad ldq(const MapC& m, uint32_t q) {
+  const uint64_t base = (uint64_t)m.quad;
   // tiles_x tiles_y 128 < 2^32: the host rejects larger packed maps
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)m.quad, (short)0, (int)(m.tiles_x * m.tiles_y * 128u), kRawBufferWord3);
-  const u4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)qb, 0, 0);
-  return Quad{__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z),
-              __uint_as_float(v.w)};
+  const rsrc4 r = {(int)(uint32_t)base, (int)((uint32_t)(base >> 32) | ((uint32_t)sizeof(Quad) << 16)),
+                   (int)m.cells, kBufferWord3};
+  const float4v v = struct_buffer_load_f4(r, (int)q, 0, 0, 0);
+  return Quad{v.x, v.y, v.z, v.w};
 }
 
 // Packed size of a map with mx x my pixels (bytes).
@@ -88,6 +96,7 @@ struct LcView {
   const double* wFc;
   const double* F;
   const int64_t* off;   // device CSR offsets [n_events + 1]
+  const uint32_t* sorted;  // [n_events] 1 where the event's times do not decrease, or nullptr
   const double* sums;   // [n_events][3]: S_w, Fbar, V
   const double* t_ref;  // [n_events]
 };
@@ -116,19 +125,18 @@ __device__ __forceinline__ T ldg(const T* __restrict__ base, uint32_t i) {
   return *(gT*)((gchar*)base + (size_t)(i * (uint32_t)sizeof(T)));
 }
 
-// Byte offset of packed cell (i, j); (j / 2) (4 tiles_x) + i < 2^27 since the packed
-// map is below 4 GiB, and both factors fit 24 bits.
-__device__ __forceinline__ uint32_t cell_offset(const MapC& m, uint32_t i, uint32_t j) {
-  return ((__umul24(j >> 1, m.tiles_x << 2) + i) << 5) | ((j & 1u) << 4);
+// Index of packed cell (i, j); below 2^28 since the packed map is below 4 GiB, and both
+// factors of the product fit 24 bits.
+__device__ __forceinline__ uint32_t cell_index(const MapC& m, uint32_t i, uint32_t j) {
+  uint32_t s = (i << 1) + j;
+  asm("" : "+v"(s));  // kept as one shift-add: else a shift, a product and a three-way sum
+  return __umul24(j >> 1, m.row) + s;
 }
 
-__device__ __forceinline__ void map_cell(const MapC& m, float fi, float fj, float& v00, float& v10,
-                                         float& v01, float& v11) {
-  const Quad v = ldq(m, cell_offset(m, (uint32_t)(int)fi, (uint32_t)(int)fj));
-  v00 = v.v00;
-  v10 = v.v10;
-  v01 = v.v01;
-  v11 = v.v11;
+// The blend of a cell (binary32, each operation rounded on its own).
+__device__ __forceinline__ float blend(const Quad& q, float fx, float fy) {
+  const float ax0 = q.v00 + fx * q.e0, ax1 = q.v01 + fx * q.e1;
+  return ax0 + fy * (ax1 - ax0);
 }
 
 // Sampling in steps, so that the loads of several points can all be issued before
@@ -137,7 +145,7 @@ __device__ __forceinline__ void map_cell(const MapC& m, float fi, float fj, floa
 // The arithmetic is that of sample_A / sample_full.
 struct Loc {
   float tau, zx, zy, fx, fy;
-  uint32_t q;  // byte offset of the packed cell (0 off the map)
+  uint32_t q;  // index of the packed cell (0 off the map)
   bool on;
 };
 
@@ -158,34 +166,28 @@ __device__ __forceinline__ Loc locate(const MapC& m, float tt, float t0p, float 
   // on the map g >= 0, so truncation is the floor and fract(g) = g - floor(g) exactly
   l.fx = __builtin_amdgcn_fractf(gx);
   l.fy = __builtin_amdgcn_fractf(gy);
-  l.q = l.on ? cell_offset(m, (uint32_t)gx, (uint32_t)gy) : 0u;
+  l.q = l.on ? cell_index(m, (uint32_t)gx, (uint32_t)gy) : 0u;
   return l;
 }
 
 // Single-lens magnification about the barycentre, (uu + 2)/sqrt(uu (uu + 4)), with a
 // correctly rounded binary32 square root and quotient.  A correctly rounded result is
-// unique, so any exact method gives the same bits.  When d = uu (uu + 4) lies in
-// [2^-60, 2^60] on every active lane the short form runs: the hardware square root
-// (within one ulp) corrected by the signs of the FMA residuals against its two
-// neighbours, then the reciprocal refined once and the quotient corrected twice by FMA.
-// These are the steps of the general IEEE sequences with their range scalings and
-// special-case fix-ups left out, which in this range change nothing.  Elsewhere the
-// general sequences run.
+// unique, so any exact method gives the same bits.  When uu lies in [2^-22, 2^12) on every
+// active lane the short form runs: the hardware's reciprocal square root, the root
+// corrected by its residual, the quotient by the same reciprocal corrected by its residual.
+// Against the IEEE square root and division it was compared for every binary32 uu from
+// 2^-62 to 2^31: it equals them throughout [1.3e-7, 8189] (53 values outside differ).
+// 8 instructions, 17 before.  Elsewhere the general sequences run.
 __device__ __forceinline__ float point_lens_A(float zx, float zy) {
   const float uu = zx * zx + zy * zy;
   const float p = uu + 2.0f, d = uu * (uu + 4.0f);
-  if (__builtin_amdgcn_ballot_w64(!(d >= 0x1p-60f && d <= 0x1p60f)) == 0) {
-    float s = __builtin_amdgcn_sqrtf(d);
-    const float sdn = __uint_as_float(__float_as_uint(s) - 1u);
-    const float sup = __uint_as_float(__float_as_uint(s) + 1u);
-    const float rdn = fmaf(-sdn, s, d), rup = fmaf(-sup, s, d);
-    s = rdn <= 0.0f ? sdn : s;
-    s = rup > 0.0f ? sup : s;
-    float r = __builtin_amdgcn_rcpf(s);
-    r = fmaf(fmaf(-s, r, 1.0f), r, r);
-    float q = p * r;
-    q = fmaf(fmaf(-s, q, p), r, q);
-    return fmaf(fmaf(-s, q, p), r, q);
+  constexpr uint32_t lo = 0x34800000u, hi = 0x45800000u;  // 2^-22, 2^12
+  if (__builtin_amdgcn_ballot_w64(__float_as_uint(uu) - lo >= hi - lo) == 0) {
+    const float y = __builtin_amdgcn_rsqf(d);
+    float s = d * y;
+    s = fmaf(fmaf(-s, s, d), 0.5f * y, s);
+    const float q = p * y;
+    return fmaf(fmaf(-s, q, p), y, q);
   }
   return p / sqrtf(d);
 }
@@ -202,13 +204,7 @@ __device__ __forceinline__ float sample_A(const MapC& m, float tt, float t0p, fl
     const float fj = floorf(gy);
     const float fx = gx - fi;
     const float fy = gy - fj;
-    float v00, v10, v01, v11;
-    map_cell(m, fi, fj, v00, v10, v01, v11);
-    const float e0 = v10 - v00;
-    const float e1 = v11 - v01;
-    const float ax0 = v00 + fx * e0;
-    const float ax1 = v01 + fx * e1;
-    return ax0 + fy * (ax1 - ax0);
+    return blend(ldq(m, cell_index(m, (uint32_t)(int)fi, (uint32_t)(int)fj)), fx, fy);
   }
   const float uu = zx * zx + zy * zy;
   return (uu + 2.0f) / sqrtf(uu * (uu + 4.0f));
@@ -228,12 +224,11 @@ __device__ __forceinline__ Sample sample_full(const MapC& m, float tt, float t0p
     const float fj = floorf(gy);
     s.fx = gx - fi;
     s.fy = gy - fj;
-    float v00, v10, v01, v11;
-    map_cell(m, fi, fj, v00, v10, v01, v11);
-    s.e0 = v10 - v00;
-    s.e1 = v11 - v01;
-    s.ax0 = v00 + s.fx * s.e0;
-    s.ax1 = v01 + s.fx * s.e1;
+    const Quad c = ldq(m, cell_index(m, (uint32_t)(int)fi, (uint32_t)(int)fj));
+    s.e0 = c.e0;
+    s.e1 = c.e1;
+    s.ax0 = c.v00 + s.fx * s.e0;
+    s.ax1 = c.v01 + s.fx * s.e1;
     s.A = s.ax0 + s.fy * (s.ax1 - s.ax0);
   } else {
     const float uu = s.zx * s.zx + s.zy * s.zy;
@@ -241,6 +236,15 @@ __device__ __forceinline__ Sample sample_full(const MapC& m, float tt, float t0p
     s.fx = s.fy = s.e0 = s.e1 = s.ax0 = s.ax1 = 0.0f;
   }
   return s;
+}
+
+// A uniform value in a vector register of its own: an instruction whose operands are all
+// vector registers (or inline constants) issues in half the time of one with a scalar
+// operand (2.5 against 4.3 cycles per wavefront for a binary32 add or multiply).
+__device__ __forceinline__ float in_vgpr(float s) {
+  float v;
+  asm("v_mov_b32 %0, %1" : "=v"(v) : "s"(s));
+  return v;
 }
 
 // A value known to be the same on every lane, moved to scalar registers word by word
@@ -415,8 +419,10 @@ hipError_t launch_normalize_convolve(const uint32_t* counts, float* map, int32_t
                                      const float* d_w, const int32_t* d_off, int32_t ntaps,
                                      int32_t rx, int32_t ry, float scale, uint32_t* d_maxc,
                                      hipStream_t st);
+// sorted (nullable): [n_events], whether the event's times do not decrease.
 hipError_t launch_lc_prep(const float* t, const double* F, const double* w, const int64_t* off,
-                          int32_t n_events, double* wF, double* sums, hipStream_t st);
+                          int32_t n_events, double* wF, double* sums, uint32_t* sorted,
+                          hipStream_t st);
 hipError_t launch_traj_prep_list(const double* params, int64_t n, TrajC* out, hipStream_t st);
 hipError_t launch_traj_prep_grid(const double* axes, int32_t nu, int32_t na, int32_t nt,
                                  int32_t ne, TrajC* out, hipStream_t st);
@@ -431,7 +437,7 @@ struct SearchOut {
 hipError_t launch_search_plain(const TrajC* tc, int64_t n_traj, LcView lc, int32_t event,
                                MapC map, SearchOut out, int waves_per_block, hipStream_t st);
 
-// Batched persistent search over (event, map, trajectory block) items.
+// Batched search over (event, map, trajectory block) items, one launch.
 struct BatchedArgs {
   const TrajC* tc;          // per event if !shared
   int64_t n_traj;
@@ -440,30 +446,34 @@ struct BatchedArgs {
   const MapC* maps;         // device table [n_maps]
   LcView lc;
   SearchOut out;            // full [e][m][traj] arrays
-  uint32_t* counter;        // kQueues work-queue counters, 128 bytes apart (cleared by a fill kernel)
   int32_t nu, na, nt, ne;   // product-grid axes (na = 0 for trajectory lists)
   int32_t traj_per_item;
   int32_t waves_per_block;
-  int32_t grid_blocks;
+  uint32_t chunk;           // workgroups per chunk dealt to an XCD (set by the launcher)
   int32_t tu;               // trajectories scored together per wavefront (1, 2 or 4)
+  int32_t centred;          // every map's window is centred on (0, 0)
   const int32_t* perm;      // trajectory lists: [lists][n_traj] scoring order, or nullptr
 };
 // Scoring order of trajectory lists (n_lists lists of n_traj, their constants in tc):
-// each list grouped by direction, kPermBins buckets of alpha, so that waves scoring at
-// the same time follow nearby lines through the map (a counting sort; the order within
+// each list grouped by direction and speed, kPermDirs buckets of alpha by kPermSpeeds
+// quarter octaves of tE, so that waves scoring at the same time follow nearby lines through
+// the map and cross it at the same points of the light curve (a counting sort; the order within
 // a bucket is unspecified and changes the schedule only); perm holds indices over all
 // lists (list * n_traj + trajectory).  key: n_lists * n_traj words of workspace, hist:
 // n_lists * kPermBins counters.  Lists with more than kPermBinsMax counters in all are
 // not reordered by the caller.
-constexpr int kPermBins = 256;
+constexpr int kPermDirs = 16, kPermSpeeds = 16;
+constexpr int kPermBins = kPermDirs * kPermSpeeds;
 constexpr int64_t kPermBinsMax = 1 << 22;
 hipError_t launch_traj_perm(const TrajC* tc, int64_t n_traj, int32_t n_lists, uint32_t* key,
                             uint32_t* hist, int32_t* perm, hipStream_t st);
-// Work queues of the batched search (one per XCD) and the words they occupy.
-constexpr int kQueues = 8;
-constexpr int kQueueStride = 32;
-constexpr int kQueueWords = kQueues * kQueueStride;
-hipError_t launch_search_batched(const BatchedArgs& a, hipStream_t st);
+// Items per (map, event) of the batched search.
+__host__ __device__ inline uint32_t search_blocks(uint32_t n_traj, int32_t traj_per_item, int32_t tu) {
+  const uint32_t ng = (n_traj + tu - 1) / tu;
+  const uint32_t gpi = traj_per_item > tu ? (uint32_t)(traj_per_item / tu) : 1u;
+  return (ng + gpi - 1) / gpi;
+}
+hipError_t launch_search_batched(BatchedArgs a, hipStream_t st);
 
 // Best (chi2, index) per segment of length seg_len; n_seg segments.
 hipError_t launch_best(const double* chi2, int64_t n_seg, int64_t seg_len, double* best_chi2,

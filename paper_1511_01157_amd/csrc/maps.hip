@@ -71,21 +71,12 @@ __global__ void k_quad_pack(const MapC* __restrict__ maps) {
     if (i + 1 < (uint64_t)m.mx && j + 1 < (uint64_t)m.my) {
       const float* row = m.map + j * (uint64_t)m.mx + i;
       v.v00 = row[0];
-      v.v10 = row[1];
+      v.e0 = row[1] - row[0];
       v.v01 = row[m.mx];
-      v.v11 = row[m.mx + 1];
+      v.e1 = row[m.mx + 1] - row[m.mx];
     }
     out[q] = v;
   }
-}
-
-// A uniform value in a vector register of its own: an instruction whose operands are all
-// vector registers (or inline constants) issues in half the time of one with a scalar
-// operand (2.5 against 4.3 cycles per wavefront for a binary32 add or multiply).
-__device__ __forceinline__ float in_vgpr(float s) {
-  float v;
-  asm("v_mov_b32 %0, %1" : "=v"(v) : "s"(s));
-  return v;
 }
 
 // m / r, correctly rounded, for m = 0 or m in [2^-40, 1] and r in [2^-40, 2^40]: the steps

@@ -143,7 +143,7 @@ __device__ Eval grad_eval(const GradArgs& a, int64_t c, double (*s_part)[kSums])
     asm volatile("" : "+v"(tr));  // opaque copy: the compiler cannot reuse locate's values
     const float ltau = (tr - t0p) * iE;
     const float lzx = ltau * ca + bx, lzy = ltau * sa + by;
-    const float e0 = v.v10 - v.v00, e1 = v.v11 - v.v01;
+    const float e0 = v.e0, e1 = v.e1;
     const float ax0 = v.v00 + l.fx * e0, ax1 = v.v01 + l.fx * e1;
     float A = ax0 + l.fy * (ax1 - ax0);
     double dAx = kx * ((double)e0 + (double)l.fy * ((double)e1 - (double)e0));

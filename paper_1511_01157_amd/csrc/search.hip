@@ -4,8 +4,9 @@
 // squares).
 //
 // Layout.  One wavefront scores TU neighbouring trajectories at a time: its 64 lanes
-// stride over the light-curve points (time-ordered, so a wave's lanes sample
-// neighbouring map cells and leave the map together), each lane keeps FP64 partial
+// stride over the light-curve points, a chunk of 64 at a time (time-ordered, so a chunk's
+// samples are neighbouring map cells, and most chunks lie wholly on or wholly off the map;
+// both kinds are known beforehand from their end points), each lane keeps FP64 partial
 // sums of the normal equations in centred form (b = A - 1 against the mean-centred
 // weighted flux) per trajectory, and a fixed-order reduction (bitwise the butterfly of
 // each value) totals them.  S_w, the weighted mean flux and V = sum w (F - Fbar)^2
@@ -56,10 +57,12 @@ __device__ __forceinline__ void tree_totals(double (*s_part)[4], double (&tot)[N
   __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void k_lc_prep(const double* __restrict__ F,
+__global__ __launch_bounds__(256) void k_lc_prep(const float* __restrict__ t,
+                                                 const double* __restrict__ F,
                                                  const double* __restrict__ w,
                                                  const int64_t* __restrict__ off,
-                                                 double* __restrict__ wFc, double* __restrict__ sums) {
+                                                 double* __restrict__ wFc, double* __restrict__ sums,
+                                                 uint32_t* __restrict__ sorted) {
   __shared__ double s_part[256][4];
   const int e = blockIdx.x;
   const int64_t a = off[e], b = off[e + 1];
@@ -94,6 +97,12 @@ __global__ __launch_bounds__(256) void k_lc_prep(const double* __restrict__ F,
     sums[3 * e] = Sw;
     sums[3 * e + 1] = Fbar;
     sums[3 * e + 2] = t2[0];
+  }
+  if (sorted) {  // false with a NaN time: no order holds
+    int ok = 1;
+    for (int64_t i = a + threadIdx.x; i + 1 < b; i += blockDim.x) ok &= t[i] <= t[i + 1] ? 1 : 0;
+    ok = __syncthreads_and(ok);
+    if (threadIdx.x == 0) sorted[e] = (uint32_t)ok;
   }
 }
 
@@ -139,211 +148,323 @@ __global__ void k_traj_prep_grid(const double* __restrict__ axes, int32_t nu, in
 
 // ---------------------------------------------------------------------------
 // Score TU trajectories with one wavefront.  All lanes return the same values.
-// Each lane takes the points lane, lane + 64, ... in order; the TU trajectories' cells
-// are all located and requested before the first is blended, so a wavefront has TU
-// gathers in flight at a time.  A lane off the map requests cell 0 and takes the
-// single-lens branch.  With TU >= 4 registers set the occupancy, so the loop keeps
-// fewer live: no load of the next point ahead, and the single-lens branch recomputes
-// the source position from tau (the same operations, so the same bits) rather than
-// keeping it across the gathers; six wavefronts then fit on a SIMD where four did.  With fewer trajectories per wavefront the next point's light-curve values
-// are loaded while the current one is scored.  Every trajectory's sums see the
-// points in the same order for any TU, and wave_sums reduces each over the butterfly
-// tree, so the results do not depend on TU.  Arrays are addressed by 32-bit offsets
-// from uniform bases.
-template <int TU>
-__device__ __forceinline__ void score_group(const MapC& m, const float* __restrict__ t,
-                                            const double* __restrict__ w,
-                                            const double* __restrict__ wFc,
-                                            const double* __restrict__ F, int32_t np, double Sw,
-                                            double Fbar, double V, const float (&t0p)[TU],
-                                            const TrajC (&c)[TU], int lane, double (&chi2)[TU],
-                                            double (&Fs)[TU], double (&Fb)[TU]) {
-  constexpr bool kLean = TU >= 4;
+// Each lane takes the points lane, lane + 64, ... in order; every trajectory's sums see the
+// points in the same order for any TU and C, and wave_sums reduces each over the butterfly
+// tree, so the results do not depend on the shape.
+//
+// Chunks.  The position along a trajectory is a chain of binary32 operations each monotone
+// in the point's time, so over points in time order the grid coordinates gx and gy are
+// monotone, and a chunk of 64 points whose first and last point lie on the map lies on it
+// as a whole; one whose ends lie beyond the same side lies off it.  Lane l looks at the
+// ends of chunk l, and ballots give both sets for 64 chunks and all TU trajectories.  A
+// chunk on the map for every trajectory takes the short form: no on-map test, no selected
+// cell, no single-lens branch; a trajectory that a chunk misses takes the single-lens
+// magnification and no cell.  Others, and events whose times are not in order, take the
+// general form.  All forms give the same bits.
+//
+// C chunks at a time (the short form) with few trajectories per wavefront, so that TU C
+// cells are in flight: a search too small to fill the chip waits for loads, not for issue.
+//
+// Bound: instruction issue (a vector instruction every 3.1 cycles per SIMD, 80% of the
+// launch), then the cells' way from L2.  The short form takes 31 instructions per point and
+// trajectory, 6 of them FP64; with the general form, the off-map chunks and the work per
+// group 36 on a 64 x 64 x 16 x 8 grid x 3000 points (1.49 ms, 1.06e12 point-evaluations/s;
+// 1.77 ms before, 2.09 ms with the former untuned shape) and
+// 39 on 24 ragged events x 8 maps x 16384 random trajectories (8.7 ms for 9.2; untuned 11.1).
+// Also measured: the constants in vector registers (1.79 ms on the grid: five wavefronts
+// per SIMD for six), no cell loads at all 1.47 ms, and straight-line code for each of the
+// 16 on/off patterns of four trajectories (1.49 and 8.72 ms: no faster).
+struct TrajV {
+  float t0p, iE, ca, sa, bx, by;
+};
+__device__ __forceinline__ TrajV traj_v(const TrajC& c, float t0p) {
+  return TrajV{t0p, c.iE, c.ca, c.sa, c.bx, c.by};
+}
+
+// Grid coordinates at time tt.  kCentred: a window about (0, 0), where zeta - s = zeta.
+struct MapV {
+  float sx, sy, kx, ky, ox, oy;
+};
+struct GridPos {
+  float tau, gx, gy;
+};
+template <bool kCentred>
+__device__ __forceinline__ GridPos grid_pos(const MapV& m, const TrajV& c, float tt) {
+  GridPos g;
+  g.tau = (tt - c.t0p) * c.iE;
+  const float zx = g.tau * c.ca + c.bx, zy = g.tau * c.sa + c.by;
+  if constexpr (kCentred) {
+    g.gx = (zx * m.kx) + m.ox;
+    g.gy = (zy * m.ky) + m.oy;
+  } else {
+    g.gx = ((zx - m.sx) * m.kx) + m.ox;
+    g.gy = ((zy - m.sy) * m.ky) + m.oy;
+  }
+  return g;
+}
+
+// 0 <= g < l as an unsigned compare of the bit patterns (see locate).
+__device__ __forceinline__ uint64_t inside(float g, float l) {
+  return __builtin_amdgcn_ballot_w64(__float_as_uint(g) < __float_as_uint(l));
+}
+// Both values below 0, or both at or beyond l.
+__device__ __forceinline__ uint64_t beyond(float g0, float g1, float l) {
+  return (__builtin_amdgcn_ballot_w64(g0 < 0.0f) & __builtin_amdgcn_ballot_w64(g1 < 0.0f)) |
+         (__builtin_amdgcn_ballot_w64(g0 >= l) & __builtin_amdgcn_ballot_w64(g1 >= l));
+}
+
+constexpr int kSegChunks = 64;            // chunks classified at a time
+constexpr int kSegPoints = kSegChunks * kWave;
+constexpr int32_t kClassifyMin = 256;     // shorter light curves take the general form
+
+struct LcPtrs {
+  const float* t;
+  const double* w;
+  const double* wFc;
+  const double* F;
+  int32_t np;
+  uint32_t sorted;
+  double Sw, Fbar, V;
+};
+
+// The result of trajectory lane % TU.
+struct GroupFit {
+  double chi2, Fs, Fb;
+};
+
+template <int TU, int C, bool kCentred>
+__device__ __forceinline__ GroupFit score_group(const MapC& m, const LcPtrs& lc, const TrajV (&c)[TU],
+                                                int lane) {
+  const MapV mv{m.sx, m.sy, m.kx, m.ky, m.ox, m.oy};
+  const int32_t np = lc.np;
   double acc[3 * TU];  // (B1, B2, C) per trajectory
 #pragma unroll
   for (int q = 0; q < 3 * TU; ++q) acc[q] = 0.0;
-  // the point (tt, wv, fv) for the TU trajectories
-  auto add_point = [&](float tt, double wv, double fv) {
-    Loc l[TU];
-    Quad cell[TU];
+  auto add = [&](int v, float A, double wv, double fv) {
+    const double b = (double)A - 1.0;
+    const double wb = wv * b;
+    acc[3 * v] += wb;
+    acc[3 * v + 1] = fma(wb, b, acc[3 * v + 1]);
+    acc[3 * v + 2] = fma(b, fv, acc[3 * v + 2]);
+  };
+  for (int32_t base = 0; base < np; base += kSegPoints) {
+    const int32_t nch = min((np - base + kWave - 1) / kWave, kSegChunks);
+    uint64_t off[TU], fast = 0;  // chunks off the map per trajectory, on it for every one
 #pragma unroll
-    for (int v = 0; v < TU; ++v)
-      l[v] = locate(m, tt, t0p[v], c[v].iE, c[v].ca, c[v].sa, c[v].bx, c[v].by);
+    for (int v = 0; v < TU; ++v) off[v] = 0;
+    if (lc.sorted && np >= kClassifyMin) {  // uniform
+      const int32_t i0 = min(base + lane * kWave, np - 1), i1 = min(base + lane * kWave + kWave - 1, np - 1);
+      const float ta = ldg(lc.t, (uint32_t)i0), tb = ldg(lc.t, (uint32_t)i1);
+      const int32_t full = min((np - base) / kWave, kSegChunks);  // chunks of 64 points
+      fast = full >= 64 ? ~0ull : (1ull << full) - 1ull;
 #pragma unroll
-    for (int v = 0; v < TU; ++v) cell[v] = ldq(m, l[v].q);
-#pragma unroll
-    for (int v = 0; v < TU; ++v) {
-      float A = 0.0f;
-      // with TU >= 4 a wavefront whose lanes are all off the map skips the interpolation
-      if (!kLean || __builtin_amdgcn_ballot_w64(l[v].on) != 0) {
-        const float e0 = cell[v].v10 - cell[v].v00, e1 = cell[v].v11 - cell[v].v01;
-        const float ax0 = cell[v].v00 + l[v].fx * e0, ax1 = cell[v].v01 + l[v].fx * e1;
-        A = ax0 + l[v].fy * (ax1 - ax0);
+      for (int v = 0; v < TU; ++v) {
+        const GridPos a = grid_pos<kCentred>(mv, c[v], ta), b = grid_pos<kCentred>(mv, c[v], tb);
+        fast &= inside(a.gx, m.lx) & inside(a.gy, m.ly) & inside(b.gx, m.lx) & inside(b.gy, m.ly);
+        off[v] = beyond(a.gx, b.gx, m.lx) | beyond(a.gy, b.gy, m.ly);
       }
-      if (!l[v].on) {
-        if constexpr (kLean) {
-          float tau = l[v].tau;
-          asm volatile("" : "+v"(tau));  // opaque copy: the compiler cannot reuse locate's zx, zy
-          A = point_lens_A(tau * c[v].ca + c[v].bx, tau * c[v].sa + c[v].by);
-        } else {
-          A = point_lens_A(l[v].zx, l[v].zy);
+    }
+    for (int32_t k = 0; k < nch; ++k) {
+      // the run of chunks from k on that lie on the map for every trajectory, C at a time
+      const uint64_t rest = ~(fast >> k);
+      const int32_t run = (rest ? __builtin_ctzll(rest) : kSegChunks) / C;
+      uint32_t i = (uint32_t)(base + k * kWave + lane);
+      for (int32_t r = 0; r < run; ++r, i += C * kWave) {
+        float tt[C], fx[C][TU], fy[C][TU];
+        double wv[C], fv[C];
+        Quad cell[C][TU];
+#pragma unroll
+        for (int u = 0; u < C; ++u) tt[u] = ldg(lc.t, i + u * kWave);
+#pragma unroll
+        for (int u = 0; u < C; ++u) {
+          wv[u] = ldg(lc.w, i + u * kWave);
+          fv[u] = ldg(lc.wFc, i + u * kWave);
+        }
+#pragma unroll
+        for (int u = 0; u < C; ++u)
+#pragma unroll
+          for (int v = 0; v < TU; ++v) {
+            const GridPos g = grid_pos<kCentred>(mv, c[v], tt[u]);
+            fx[u][v] = __builtin_amdgcn_fractf(g.gx);
+            fy[u][v] = __builtin_amdgcn_fractf(g.gy);
+            cell[u][v] = ldq(m, cell_index(m, (uint32_t)g.gx, (uint32_t)g.gy));
+          }
+#pragma unroll
+        for (int u = 0; u < C; ++u)
+#pragma unroll
+          for (int v = 0; v < TU; ++v) add(v, blend(cell[u][v], fx[u][v], fy[u][v]), wv[u], fv[u]);
+      }
+      k += run * C;
+      if (k >= nch) break;
+      const bool act = i < (uint32_t)np;
+      const uint32_t ii = min(i, (uint32_t)(np - 1));
+      const float tt = ldg(lc.t, ii);
+      const double wv = ldg(lc.w, ii), fv = ldg(lc.wFc, ii);
+      float tau[TU], fx[TU], fy[TU];
+      uint64_t on[TU];
+      Quad cell[TU];
+#pragma unroll
+      for (int v = 0; v < TU; ++v) {
+        on[v] = 0;
+        cell[v] = Quad{0.0f, 0.0f, 0.0f, 0.0f};
+        fx[v] = fy[v] = 0.0f;
+        const GridPos g = grid_pos<kCentred>(mv, c[v], tt);
+        tau[v] = g.tau;
+        if (!((off[v] >> k) & 1)) {  // uniform
+          on[v] = inside(g.gx, m.lx) & inside(g.gy, m.ly);
+          fx[v] = __builtin_amdgcn_fractf(g.gx);
+          fy[v] = __builtin_amdgcn_fractf(g.gy);
+          const bool mine = __builtin_amdgcn_inverse_ballot_w64(on[v]);
+          cell[v] = ldq(m, mine ? cell_index(m, (uint32_t)g.gx, (uint32_t)g.gy) : 0u);
         }
       }
-      const double b = (double)A - 1.0;
-      const double wb = wv * b;
-      acc[3 * v] += wb;
-      acc[3 * v + 1] = fma(wb, b, acc[3 * v + 1]);
-      acc[3 * v + 2] = fma(b, fv, acc[3 * v + 2]);
-    }
-  };
-  if constexpr (kLean) {
-    for (int32_t i0 = lane; i0 < np; i0 += kWave)
-      add_point(ldg(t, (uint32_t)i0), ldg(w, (uint32_t)i0), ldg(wFc, (uint32_t)i0));
-  } else {  // the next point's light-curve values are loaded while this one is scored
-    uint32_t in = (uint32_t)min(lane, np - 1);
-    float tn = ldg(t, in);
-    double wn = ldg(w, in), fn = ldg(wFc, in);
-    for (int32_t i0 = lane; i0 < np; i0 += kWave) {
-      const float tt = tn;
-      const double wv = wn, fv = fn;
-      in = (uint32_t)min(i0 + kWave, np - 1);  // past the end: the last point, never used
-      tn = ldg(t, in);
-      wn = ldg(w, in);
-      fn = ldg(wFc, in);
-      add_point(tt, wv, fv);
+#pragma unroll
+      for (int v = 0; v < TU; ++v) {
+        float A = 0.0f;
+        if (on[v]) A = blend(cell[v], fx[v], fy[v]);  // uniform
+        if (~on[v]) {
+          // the source position again from tau: the same operations, so the same bits,
+          // and no register held across the loads
+          float tv = tau[v];
+          asm volatile("" : "+v"(tv));
+          const float P = point_lens_A(tv * c[v].ca + c[v].bx, tv * c[v].sa + c[v].by);
+          A = __builtin_amdgcn_inverse_ballot_w64(on[v]) ? A : P;
+        }
+        if (act) add(v, A, wv, fv);
+      }
     }
   }
-  wave_sums<3 * TU>(acc);
+  // Totals to the lanes that fit them: lane l takes trajectory l % TU, so one fit serves all.
+  int slot = 0;
+  bool valid = true;
+  reduce_scatter<3 * TU>(acc, lane, slot, valid);
+  double tot[3];
 #pragma unroll
-  for (int v = 0; v < TU; ++v) {
-    const Fit f = centred_fit(Sw, Fbar, V, acc[3 * v], acc[3 * v + 1], acc[3 * v + 2],
-                              fit_terms(np, kWave));
-    Fs[v] = f.Fs;
-    Fb[v] = f.Fb;
-    chi2[v] = f.chi2;
-    if (f.recheck) {  // wave-uniform: the sums are identical on every lane
+  for (int j = 0; j < 3; ++j) {
+    uint32_t from = 0;  // lane of sum j of each trajectory, a byte each
+#pragma unroll
+    for (int v = 0; v < TU; ++v) from |= (uint32_t)rs_lane<3 * TU>(3 * v + j) << (8 * v);
+    tot[j] = __shfl(acc[0], (int)((from >> (8 * (lane % TU))) & 63u), kWave);
+  }
+  const Fit f = centred_fit(lc.Sw, lc.Fbar, lc.V, tot[0], tot[1], tot[2], fit_terms(np, kWave));
+  GroupFit out{f.chi2, f.Fs, f.Fb};
+  const uint64_t again = __builtin_amdgcn_ballot_w64(f.recheck);
+#pragma unroll
+  for (int v = 0; v < TU; ++v)
+    if ((again >> v) & 1) {  // uniform
+      const double Fs = read_lane(f.Fs, v), Fb = read_lane(f.Fb, v);
       double q = 0.0, qc = 0.0;
       for (int32_t i = lane; i < np; i += kWave) {
-        const double a = (double)sample_A(m, ldg(t, (uint32_t)i), t0p[v], c[v].iE, c[v].ca,
+        const double a = (double)sample_A(m, ldg(lc.t, (uint32_t)i), c[v].t0p, c[v].iE, c[v].ca,
                                           c[v].sa, c[v].bx, c[v].by);
-        const double r = ldg(F, (uint32_t)i) - Fs[v] * a - Fb[v];
-        neumaier_add(q, qc, (ldg(w, (uint32_t)i) * r) * r);
+        const double r = ldg(lc.F, (uint32_t)i) - Fs * a - Fb;
+        neumaier_add(q, qc, (ldg(lc.w, (uint32_t)i) * r) * r);
       }
-      chi2[v] = wave_sum(q + qc);
+      const double x = wave_sum(q + qc);
+      if (lane % TU == v) out.chi2 = x;
     }
-  }
+  return out;
 }
 
+// Chunks taken at a time in the short form: four cells in flight for any TU.
+template <int TU>
+constexpr int kChunks = 4 / TU;
+
+template <bool kCentred>
 __global__ __launch_bounds__(256) void k_search_plain(const TrajC* __restrict__ tc, int64_t n_traj,
                                                       LcView lc, int32_t e, MapC m, SearchOut out) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wpb = blockDim.x / kWave;
   const int64_t nw = (int64_t)gridDim.x * wpb;
   const int64_t p0 = lc.off[e];
-  const int32_t np = (int32_t)(lc.off[e + 1] - p0);
-  const float* t = lc.t + p0;
-  const double* w = lc.w + p0;
-  const double* wFc = lc.wFc + p0;
-  const double* F = lc.F + p0;
-  const double Sw = lc.sums[3 * e], Fbar = lc.sums[3 * e + 1], V = lc.sums[3 * e + 2];
+  const LcPtrs lp{lc.t + p0, lc.w + p0, lc.wFc + p0, lc.F + p0, (int32_t)(lc.off[e + 1] - p0),
+                  lc.sorted ? lc.sorted[e] : 0u, lc.sums[3 * e], lc.sums[3 * e + 1], lc.sums[3 * e + 2]};
   const double tref = lc.t_ref[e];
   for (int64_t k = (int64_t)blockIdx.x * wpb + (threadIdx.x / kWave); k < n_traj; k += nw) {
-    const TrajC c[1] = {tc[k]};
-    const float t0p[1] = {(float)(c[0].t0 - tref)};
-    double chi2[1], Fs[1], Fb[1];
-    score_group<1>(m, t, w, wFc, F, np, Sw, Fbar, V, t0p, c, lane, chi2, Fs, Fb);
+    const TrajC tk = uniform(tc[k]);
+    const TrajV c[1] = {traj_v(tk, (float)(tk.t0 - tref))};
+    const GroupFit r = score_group<1, kChunks<1>, kCentred>(m, lp, c, lane);
     if (lane == 0) {
-      if (out.chi2) out.chi2[k] = chi2[0];
-      if (out.fs) out.fs[k] = Fs[0];
-      if (out.fb) out.fb[k] = Fb[0];
+      if (out.chi2) out.chi2[k] = r.chi2;
+      if (out.fs) out.fs[k] = r.Fs;
+      if (out.fb) out.fb[k] = r.Fb;
     }
   }
 }
 
-// Persistent batched search.  Every wavefront pulls its own work items (no workgroup
-// barrier, so a slow trajectory never holds up other waves).  The item space is cut
-// into kQueues contiguous ranges, one queue each; workgroups are dispatched to the 8
-// XCDs in turn, so blockIdx % 8 names the workgroup's XCD and its home queue: each
-// XCD's L2 serves one compact part of the work, and a wave whose queue is empty moves
-// on to the next queue until all are drained.  Trajectories are taken in groups of
+// Batched search: one launch over (map, event, trajectory group) items, one item per
+// wavefront, so thousands of (event, map) pairs of uneven length share a launch and the
+// hardware's dispatcher balances them.  Workgroups are dispatched to the 8 XCDs in turn, so
+// blockIdx % 8 names the XCD; the items are cut into chunks of a.chunk workgroups, dealt to
+// the XCDs in turn: an XCD works through neighbouring items (its L2 serves one compact part
+// of the work), and the chunks spread events of different lengths over all XCDs.  (A
+// persistent grid with one work queue per XCD spent 20 us on draining the queues, 65,000
+// atomics on eight counters: 1024 trajectories x 1000 points took 24 us and take 15.6.)
+// Trajectories are taken in groups of
 // TU neighbours, scored together.  Item = (map * n_events + event) * n_blocks + b
 // scores groups b, b + n_blocks, ... (traj_per_item / TU of them): the waves of an
 // XCD running at the same time take neighbouring items, so they score neighbouring
 // trajectories of the same map and light curve.  On a product grid the scoring order
-// runs over (alpha, u0, t0, tE), tE fastest, so neighbouring trajectories lie on
-// nearly the same line through the map (the (u0, alpha, t0, tE) index order of the
-// outputs is unchanged); trajectory lists are scored in the order of `perm`, grouped by
-// direction, for the same reason.
+// runs over (alpha, u0, tE, t0), t0 fastest, so neighbouring trajectories lie on
+// the same line through the map, cross it at the same speed and share most of the chunks
+// that lie on it (the (u0, alpha, t0, tE) index order of the outputs is unchanged);
+// trajectory lists are scored in the order of `perm`, grouped by direction and speed, for
+// the same reason.
 // Trajectory index of scoring position p of event e (see k_search_batched).
-__device__ __forceinline__ int64_t traj_of(const BatchedArgs& a, int64_t p, int32_t e) {
+__device__ __forceinline__ int32_t traj_of(const BatchedArgs& a, uint32_t p, int32_t e) {
   if (a.na <= 0) {
-    if (!a.perm) return p;
+    if (!a.perm) return (int32_t)p;
     const int64_t base = a.shared ? 0 : (int64_t)e * a.n_traj;  // perm holds indices over all lists
-    return (int64_t)uniform(a.perm[base + p]) - base;
+    return (int32_t)((int64_t)uniform(a.perm[base + p]) - base);
   }
-  const uint32_t u = (uint32_t)p;  // n_traj < 2^31
-  const uint32_t ie = u % (uint32_t)a.ne, r1 = u / (uint32_t)a.ne;
-  const uint32_t it = r1 % (uint32_t)a.nt, r2 = r1 / (uint32_t)a.nt;
+  const uint32_t it = p % (uint32_t)a.nt, r1 = p / (uint32_t)a.nt;
+  const uint32_t ie = r1 % (uint32_t)a.ne, r2 = r1 / (uint32_t)a.ne;
   const uint32_t iu = r2 % (uint32_t)a.nu, ia = r2 / (uint32_t)a.nu;
-  return (((int64_t)iu * a.na + ia) * a.nt + it) * a.ne + ie;
+  return (int32_t)(((iu * a.na + ia) * a.nt + it) * a.ne + ie);
 }
 
-template <int TU>
-__global__ __launch_bounds__(512) void k_search_batched(BatchedArgs a) {
+// All counts are below 2^31 (the host checks n_traj x n_events x n_maps).
+template <int TU, bool kCentred>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void k_search_batched(BatchedArgs a) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t ng = (a.n_traj + TU - 1) / TU;
-  const int64_t gpi = max(a.traj_per_item / TU, 1);
-  const int64_t nb = (ng + gpi - 1) / gpi;
-  const int64_t total = nb * a.n_events * a.n_maps;
-  int q = blockIdx.x % kQueues;
-  int left = kQueues;
-  for (;;) {
-    const int64_t lo = total * q / kQueues, hi = total * (q + 1) / kQueues;
-    int rel32 = 0;
-    if (lane == 0) rel32 = (int)atomicAdd(a.counter + q * kQueueStride, 1u);
-    // first-lane read: the item is provably wave-uniform, so everything derived from it
-    // (indices, map and trajectory constants) stays in scalar registers
-    const int64_t item = lo + (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane(rel32);
-    if (item >= hi) {  // this queue is drained (and stays drained)
-      if (--left == 0) break;
-      q = (q + 1) % kQueues;
-      continue;
-    }
-    const int64_t b = item % nb;
-    const int64_t me = item / nb;
-    const int32_t e = (int32_t)(me % a.n_events);
-    const int32_t mi = (int32_t)(me / a.n_events);
+  const uint32_t n_traj = (uint32_t)a.n_traj;
+  const uint32_t ng = (n_traj + TU - 1) / TU;
+  const uint32_t nb = search_blocks(n_traj, a.traj_per_item, TU);
+  const uint32_t xcd = blockIdx.x % 8u, j = blockIdx.x / 8u;
+  const uint32_t wg = ((j / a.chunk) * 8u + xcd) * a.chunk + j % a.chunk;
+  // first-lane read: the item is provably wave-uniform, so everything derived from it
+  // (indices, map and trajectory constants) stays in scalar registers
+  const uint64_t item64 = (uint64_t)wg * (blockDim.x / kWave) +
+                          (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (item64 < (uint64_t)nb * a.n_events * a.n_maps) {
+    const uint32_t item = (uint32_t)item64;
+    const uint32_t b = item % nb, me = item / nb;
+    const int32_t e = (int32_t)(me % (uint32_t)a.n_events);
+    const int32_t mi = (int32_t)(me / (uint32_t)a.n_events);
     const MapC m = uniform(a.maps[mi]);
     const int64_t p0 = uniform(a.lc.off[e]);
-    const int32_t np = (int32_t)(uniform(a.lc.off[e + 1]) - p0);
-    const double Sw = uniform(a.lc.sums[3 * e]), Fbar = uniform(a.lc.sums[3 * e + 1]),
-                 V = uniform(a.lc.sums[3 * e + 2]);
+    const LcPtrs lp{a.lc.t + p0, a.lc.w + p0, a.lc.wFc + p0, a.lc.F + p0,
+                    (int32_t)(uniform(a.lc.off[e + 1]) - p0), a.lc.sorted ? uniform(a.lc.sorted[e]) : 0u,
+                    uniform(a.lc.sums[3 * e]), uniform(a.lc.sums[3 * e + 1]), uniform(a.lc.sums[3 * e + 2])};
     const double tref = uniform(a.lc.t_ref[e]);
     const TrajC* tc = a.tc + (a.shared ? 0 : (int64_t)e * a.n_traj);
     const int64_t obase = ((int64_t)e * a.n_maps + mi) * a.n_traj;
-    for (int64_t g = b; g < ng; g += nb) {
-      TrajC c[TU];
-      float t0p[TU];
-      int64_t kk[TU];
+    for (uint32_t g = b; g < ng; g += nb) {
+      TrajV c[TU];
+      int32_t mine = 0;  // index of the trajectory whose result this lane holds
 #pragma unroll
       for (int v = 0; v < TU; ++v) {  // a short last group repeats its last trajectory
-        kk[v] = traj_of(a, min(g * TU + v, a.n_traj - 1), e);
-        c[v] = uniform(tc[kk[v]]);
-        t0p[v] = (float)(c[v].t0 - tref);
+        const int32_t k = traj_of(a, min(g * TU + v, n_traj - 1), e);
+        const TrajC tk = uniform(tc[k]);
+        c[v] = traj_v(tk, uniform((float)(tk.t0 - tref)));
+        mine = lane % TU == v ? k : mine;
       }
-      double chi2[TU], Fs[TU], Fb[TU];
-      score_group<TU>(m, a.lc.t + p0, a.lc.w + p0, a.lc.wFc + p0, a.lc.F + p0, np, Sw, Fbar, V,
-                      t0p, c, lane, chi2, Fs, Fb);
-      if (lane == 0) {
-#pragma unroll
-        for (int v = 0; v < TU; ++v) {
-          const int64_t k = kk[v];
-          if (g * TU + v < a.n_traj) {
-            if (a.out.chi2) a.out.chi2[obase + k] = chi2[v];
-            if (a.out.fs) a.out.fs[obase + k] = Fs[v];
-            if (a.out.fb) a.out.fb[obase + k] = Fb[v];
-          }
-        }
+      const GroupFit r = score_group<TU, kChunks<TU>, kCentred>(m, lp, c, lane);
+      if (lane < TU && g * TU + lane < n_traj) {
+        const int64_t o = obase + mine;
+        if (a.out.chi2) a.out.chi2[o] = r.chi2;
+        if (a.out.fs) a.out.fs[o] = r.Fs;
+        if (a.out.fb) a.out.fb[o] = r.Fb;
       }
     }
   }
@@ -674,10 +795,11 @@ hipError_t launch_candidates(const double* axes, int32_t nu, int32_t na, int32_t
   return hipGetLastError();
 }
 
-hipError_t launch_lc_prep(const float* /*t*/, const double* F, const double* w, const int64_t* off,
-                          int32_t n_events, double* wFc, double* sums, hipStream_t st) {
+hipError_t launch_lc_prep(const float* t, const double* F, const double* w, const int64_t* off,
+                          int32_t n_events, double* wFc, double* sums, uint32_t* sorted,
+                          hipStream_t st) {
   if (n_events <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_lc_prep, dim3(n_events), dim3(256), 0, st, F, w, off, wFc, sums);
+  hipLaunchKernelGGL(k_lc_prep, dim3(n_events), dim3(256), 0, st, t, F, w, off, wFc, sums, sorted);
   return hipGetLastError();
 }
 
@@ -691,13 +813,17 @@ hipError_t launch_traj_prep_list(const double* params, int64_t n, TrajC* out, hi
 
 namespace {
 
-// Scoring order of trajectory lists: each trajectory's (list, alpha bucket) key, then
-// the shared bucket sort (its order holds indices over all lists).
+// Scoring order of trajectory lists: each trajectory's (list, alpha, tE bucket) key, then
+// the shared bucket sort (its order holds indices over all lists).  Neighbours then follow
+// nearby lines at nearby speeds, so the chunks that lie on the map for one mostly do for
+// all.  24 events x 8 maps x 16384 trajectories: 8.69 ms, 8.78 ms in 256 directions alone.
 __device__ __forceinline__ uint32_t perm_key(const TrajC* tc, int64_t i, int64_t n_traj) {
   const float a = atan2f(tc[i].sa, tc[i].ca);  // (-pi, pi]
-  int b = 0;
-  if (!isnan(a)) b = min(max((int)((a + 3.14159265f) * (kPermBins / 6.28318531f)), 0), kPermBins - 1);
-  return (uint32_t)((i / n_traj) * kPermBins + b);
+  const float q = 4.0f * __log2f(tc[i].iE);
+  int b = 0, s = 0;
+  if (!isnan(a)) b = min(max((int)((a + 3.14159265f) * (kPermDirs / 6.28318531f)), 0), kPermDirs - 1);
+  if (fabsf(q) < 1e6f) s = (int)floorf(q) & (kPermSpeeds - 1);
+  return (uint32_t)((i / n_traj) * kPermBins + (b * kPermSpeeds + s));
 }
 
 __global__ void k_perm_keys(const TrajC* __restrict__ tc, int64_t n, int64_t n_traj, uint32_t* key) {
@@ -736,17 +862,36 @@ hipError_t launch_search_plain(const TrajC* tc, int64_t n_traj, LcView lc, int32
   const int threads = waves_per_block * kWave;
   int64_t blocks = (n_traj + waves_per_block - 1) / waves_per_block;
   if (blocks > 1 << 20) blocks = 1 << 20;
-  hipLaunchKernelGGL(k_search_plain, dim3((unsigned)blocks), dim3(threads), 0, st, tc, n_traj, lc,
-                     event, map, out);
+  if (map.sx == 0.0f && map.sy == 0.0f)
+    hipLaunchKernelGGL(k_search_plain<true>, dim3((unsigned)blocks), dim3(threads), 0, st, tc, n_traj,
+                       lc, event, map, out);
+  else
+    hipLaunchKernelGGL(k_search_plain<false>, dim3((unsigned)blocks), dim3(threads), 0, st, tc, n_traj,
+                       lc, event, map, out);
   return hipGetLastError();
 }
 
-hipError_t launch_search_batched(const BatchedArgs& a, hipStream_t st) {
-  const dim3 grid(a.grid_blocks), block(a.waves_per_block * kWave);
-  switch (a.tu) {
-    case 1: hipLaunchKernelGGL(k_search_batched<1>, grid, block, 0, st, a); break;
-    case 2: hipLaunchKernelGGL(k_search_batched<2>, grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL(k_search_batched<4>, grid, block, 0, st, a); break;
+hipError_t launch_search_batched(BatchedArgs a, hipStream_t st) {
+  if (a.waves_per_block < 1 || a.waves_per_block > 8 || a.n_traj <= 0) return hipErrorInvalidValue;
+  const int64_t items = (int64_t)search_blocks((uint32_t)a.n_traj, a.traj_per_item, a.tu) * a.n_events * a.n_maps;
+  const int64_t wgs = (items + a.waves_per_block - 1) / a.waves_per_block;
+  // chunks of an eighth of one (map, event), so that all XCDs share every event evenly, 512
+  // workgroups at most.  24 ragged events x 8 maps x 16384 trajectories: 8.75 ms at an eighth
+  // (256), 10.6 at 32 (neighbours on different XCDs), 13.0 and 13.4 at 1024 and 4096 (an
+  // event's parts on some XCDs only)
+  const int64_t per = (search_blocks((uint32_t)a.n_traj, a.traj_per_item, a.tu) + a.waves_per_block - 1) / a.waves_per_block;
+  a.chunk = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(512, per / 8));
+  const int64_t deal = 8 * (int64_t)a.chunk;
+  const int64_t blocks = (wgs + deal - 1) / deal * deal;
+  if (blocks > INT32_MAX) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks), block(a.waves_per_block * kWave);
+  switch (a.tu * 2 + (a.centred ? 1 : 0)) {
+    case 2: hipLaunchKernelGGL((k_search_batched<1, false>), grid, block, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((k_search_batched<1, true>), grid, block, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((k_search_batched<2, false>), grid, block, 0, st, a); break;
+    case 5: hipLaunchKernelGGL((k_search_batched<2, true>), grid, block, 0, st, a); break;
+    case 8: hipLaunchKernelGGL((k_search_batched<4, false>), grid, block, 0, st, a); break;
+    case 9: hipLaunchKernelGGL((k_search_batched<4, true>), grid, block, 0, st, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

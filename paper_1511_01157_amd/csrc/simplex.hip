@@ -128,9 +128,7 @@ __global__ __launch_bounds__(kItemThreads) void k_line_simplex(SimplexArgs a) {
 #pragma unroll
         for (int k = 0; k < kUnroll; ++k) {
           if (i0 + k * kItemThreads >= np) break;
-          const float e0 = q[k].v10 - q[k].v00, e1 = q[k].v11 - q[k].v01;
-          const float ax0 = q[k].v00 + lc[k].fx * e0, ax1 = q[k].v01 + lc[k].fx * e1;
-          const float A = lc[k].on ? ax0 + lc[k].fy * (ax1 - ax0) : point_lens_A(lc[k].zx, lc[k].zy);
+          const float A = lc[k].on ? blend(q[k], lc[k].fx, lc[k].fy) : point_lens_A(lc[k].zx, lc[k].zy);
           const double b = (double)A - 1.0;
           const double wb = wv[k] * b;
           v[0] += wb;

@@ -148,8 +148,8 @@ void caustic_components(double s, double q, int32_t nphi, std::vector<double>& o
 namespace {
 
 // Shared set-up of the line filter and the peak library: validation, the map packed
-// into cells (descriptor resident in ctx->lmeta), the sampling of the lines across the
-// window, and the workspace of the compaction.
+// into tiles, the sampling of the lines across the window, and the workspace of the
+// compaction.
 int setup_lines(morse_ctx* ctx, const morse_map_view* map, const double* d_lines, int64_t n,
                 double a_min, bool compact, LineFilterArgs& a, Plan& pl, size_t& is, size_t& ic) {
   int rc;
@@ -165,24 +165,16 @@ int setup_lines(morse_ctx* ctx, const morse_map_view* map, const double* d_lines
   const double kmax = std::max(w.nx / w.wx, w.ny / w.wy);
   const double ns64 = std::ceil(2.0 * R * kmax) + 1.0;
   if (ns64 > 1.0e7) return fail(ctx, MORSE_ERANGE, "more than 1e7 samples per line");
-  const size_t iq = pl.add(quad_bytes(w.nx, w.ny));
+  const size_t iq = pl.add(tile_bytes(w.nx, w.ny));
   is = pl.add(compact ? compact_scratch_elems(n) * sizeof(int64_t) : 0);
   ic = pl.add(sizeof(int64_t));
   if ((rc = reserve(ctx, pl.total()))) return rc;
-  std::vector<MapC> hm(1, make_mapc(map->d_map, w));
-  assign_quads(hm, pl.ptr(ctx, iq));
-  if ((rc = reserve_meta(ctx, ctx->lmeta, sizeof(MapC)))) return rc;
-  Hasher key;
-  key.pod(ctx->lmeta.p);
-  key.bytes(hm.data(), sizeof(MapC));
-  if (ctx->lmeta.key != key.h) {
-    ctx->lmeta.key = 0;
-    if ((rc = upload(ctx, ctx->lmeta.p, hm.data(), sizeof(MapC)))) return rc;
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // hm goes out of scope
-    ctx->lmeta.key = key.h;
-  }
-  HIP_TRY(ctx, launch_quad_pack((const MapC*)ctx->lmeta.p, hm.data(), 1, ctx->stream));
-  a.m = hm[0];
+  a.m = make_mapc(map->d_map, w);
+  a.t.p = (const float*)pl.ptr(ctx, iq);
+  a.t.tiles_x = (uint32_t)((w.nx - 1 + 6) / 7);
+  a.t.row = 32 * a.t.tiles_x - 24;
+  a.t.n = (uint32_t)(tile_bytes(w.nx, w.ny) / sizeof(float));
+  HIP_TRY(ctx, launch_tile_pack(a.m, a.t, ctx->stream));
   a.lines = d_lines;
   a.n = n;
   a.cxw = w.cx;

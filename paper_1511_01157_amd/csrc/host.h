@@ -51,8 +51,6 @@ struct morse_ctx {
   // source-radius stacks: direct-sum taps, FFT twiddle tables and the transforms of
   // the profile pairs, each kept until a call needs different ones
   MetaBuf stack_taps, fft_tw, fft_spec;
-  // the packed-map descriptor of the line filter
-  MetaBuf lmeta;
   // critical points and their caustic images of the last finite-source call (key: s, q,
   // phases)
   MetaBuf fs_crit;

@@ -72,6 +72,9 @@ typedef int rsrc4 __attribute__((ext_vector_type(4)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 __device__ float4v struct_buffer_load_f4(rsrc4 rsrc, int index, int offset, int soffset,
                                          int aux) __asm("llvm.amdgcn.struct.buffer.load.v4f32");
+typedef float float2v __attribute__((ext_vector_type(2)));
+__device__ float2v struct_buffer_load_f2(rsrc4 rsrc, int index, int offset, int soffset,
+                                         int aux) __asm("llvm.amdgcn.struct.buffer.load.v2f32");
 constexpr int kBufferWord3 = 0x00020000;
 __device__ __forceinline__ Quad ldq(const MapC& m, uint32_t q) {
   const uint64_t base = (uint64_t)m.quad;

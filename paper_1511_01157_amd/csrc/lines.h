@@ -6,8 +6,26 @@
 
 namespace morse {
 
+// A map packed for sampling along many lines of all directions: tiles of 8 x 4 pixels, one
+// 128-byte cache line each, whose last column and row repeat the next tile's first, so that
+// the four pixels about each of the 7 x 3 cells lie in one line:
+//   index(i, j) = 32 tile + 8 (j % 3) + i % 7,  tile = (j / 3) tiles_x + i / 7.
+// 6.1 bytes a pixel for the 16 of the search's cells: a sample takes two loads of two
+// pixels and six more instructions, but a line of samples touches 0.30 cache lines per
+// pixel of its path in place of 0.48, of a map 2.6 times smaller, which its L2 misses feel.
+struct TileMap {
+  const float* p;
+  uint32_t row;          // 32 tiles_x - 24: index step of three rows less 24
+  uint32_t n;            // floats, 32 tiles_x tiles_y
+  uint32_t tiles_x;
+};
+inline size_t tile_bytes(int32_t mx, int32_t my) {
+  return (size_t)((mx - 1 + 6) / 7) * (size_t)((my - 1 + 2) / 3) * 128;
+}
+
 struct LineFilterArgs {
-  MapC m;                // the map, packed into cells
+  MapC m;                // the map's geometry and pixels
+  TileMap t;             // the map packed (written by launch_tile_pack)
   const double* lines;   // [n][3] (u0, alpha, shift), FP64
   int64_t n;
   double cxw, cyw;       // window centre
@@ -19,6 +37,7 @@ struct LineFilterArgs {
   uint8_t* keep;         // [n] best >= amin
 };
 
+hipError_t launch_tile_pack(const MapC& m, const TileMap& t, hipStream_t st);
 hipError_t launch_line_filter(const LineFilterArgs& a, hipStream_t st);
 
 // The filter's samples, their largest value and the peak library of each line: peaks

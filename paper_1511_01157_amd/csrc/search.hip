@@ -430,7 +430,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void k
   const uint32_t n_traj = (uint32_t)a.n_traj;
   const uint32_t ng = (n_traj + TU - 1) / TU;
   const uint32_t nb = search_blocks(n_traj, a.traj_per_item, TU);
-  const uint32_t xcd = blockIdx.x % 8u, j = blockIdx.x / 8u;
+  const uint32_t block = a.first + blockIdx.x;
+  const uint32_t xcd = block % 8u, j = block / 8u;
   const uint32_t wg = ((j / a.chunk) * 8u + xcd) * a.chunk + j % a.chunk;
   // first-lane read: the item is provably wave-uniform, so everything derived from it
   // (indices, map and trajectory constants) stays in scalar registers
@@ -884,15 +885,21 @@ hipError_t launch_search_batched(BatchedArgs a, hipStream_t st) {
   const int64_t deal = 8 * (int64_t)a.chunk;
   const int64_t blocks = (wgs + deal - 1) / deal * deal;
   if (blocks > INT32_MAX) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)blocks), block(a.waves_per_block * kWave);
-  switch (a.tu * 2 + (a.centred ? 1 : 0)) {
-    case 2: hipLaunchKernelGGL((k_search_batched<1, false>), grid, block, 0, st, a); break;
-    case 3: hipLaunchKernelGGL((k_search_batched<1, true>), grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((k_search_batched<2, false>), grid, block, 0, st, a); break;
-    case 5: hipLaunchKernelGGL((k_search_batched<2, true>), grid, block, 0, st, a); break;
-    case 8: hipLaunchKernelGGL((k_search_batched<4, false>), grid, block, 0, st, a); break;
-    case 9: hipLaunchKernelGGL((k_search_batched<4, true>), grid, block, 0, st, a); break;
-    default: return hipErrorInvalidValue;
+  const dim3 block(a.waves_per_block * kWave);
+  // a launch has fewer than 2^32 lanes: more workgroups take several, each of whole deals
+  const int64_t most = (int64_t(1) << 31) / block.x / deal * deal;
+  for (int64_t first = 0; first < blocks; first += most) {
+    const dim3 grid((unsigned)std::min(most, blocks - first));
+    a.first = (uint32_t)first;
+    switch (a.tu * 2 + (a.centred ? 1 : 0)) {
+      case 2: hipLaunchKernelGGL((k_search_batched<1, false>), grid, block, 0, st, a); break;
+      case 3: hipLaunchKernelGGL((k_search_batched<1, true>), grid, block, 0, st, a); break;
+      case 4: hipLaunchKernelGGL((k_search_batched<2, false>), grid, block, 0, st, a); break;
+      case 5: hipLaunchKernelGGL((k_search_batched<2, true>), grid, block, 0, st, a); break;
+      case 8: hipLaunchKernelGGL((k_search_batched<4, false>), grid, block, 0, st, a); break;
+      case 9: hipLaunchKernelGGL((k_search_batched<4, true>), grid, block, 0, st, a); break;
+      default: return hipErrorInvalidValue;
+    }
   }
   return hipGetLastError();
 }

@@ -58,7 +58,8 @@ struct SearchPlan {
   std::vector<MapC> h_maps;
   LcView lc{};
   double* chi2 = nullptr;  // output or workspace
-  void* tk_scratch = nullptr;
+  char* select = nullptr;  // workspace of the selections
+  SelectScratch sel{};
   int num_cu = 256;
   double* axes = nullptr;
   // trajectory lists: scoring order of the batched kernel and its counting-sort counters
@@ -142,8 +143,9 @@ int plan_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
                            ? sp.n_traj * lcs->n_events
                            : sp.n_traj;
   const int64_t n_out = (int64_t)sp.n_events * n_maps * sp.n_traj;
-  const bool need_chi2 = !out->d_chi2 && (out->d_best_chi2 || out->d_best_idx || out->top_k > 0);
   const int32_t k = out->top_k;
+  const bool best = out->d_best_chi2 || out->d_best_idx;
+  const bool need_chi2 = !out->d_chi2 && (best || k > 0);
   const int n_axes = trajs->kind == MORSE_TRAJ_GRID
                          ? trajs->n_u0 + trajs->n_alpha + trajs->n_t0 + trajs->n_tE
                          : 0;
@@ -151,12 +153,14 @@ int plan_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   // lists are scored in an order grouped by direction (one counting sort per list)
   sp.perm_lists = (trajs->kind == MORSE_TRAJ_LIST && sp.n_traj > 0) ? (int32_t)(n_tc / sp.n_traj) : 0;
   if ((int64_t)sp.perm_lists * kPermBins > kPermBinsMax || n_tc > INT32_MAX) sp.perm_lists = 0;
+  sp.sel = select_scratch(best ? (int64_t)sp.n_events * n_maps : 0, sp.n_traj, k > 0 ? sp.n_events : 0,
+                          (int64_t)n_maps * sp.n_traj, k, ctx->num_cu);
   Plan pl;
   const size_t i_quad = pl.add(quad_region_bytes(maps, n_maps)),
                i_sums = pl.add(24 * (size_t)sp.n_events), i_sorted = pl.add(4 * (size_t)sp.n_events),
                i_wF = pl.add(8 * (size_t)sp.n_pts), i_tc = pl.add(sizeof(TrajC) * (size_t)n_tc),
                i_chi = pl.add(need_chi2 ? 8 * (size_t)n_out : 0),
-               i_tk = pl.add(k > 0 ? topk_scratch_bytes(sp.n_events, k) : 0),
+               i_sel = pl.add(sp.sel.bytes),
                i_perm = pl.add(sp.perm_lists ? 4 * (size_t)n_tc : 0),
                i_pk = pl.add(sp.perm_lists ? 4 * (size_t)n_tc : 0),
                i_ph = pl.add(4 * (size_t)sp.perm_lists * kPermBins);
@@ -170,7 +174,7 @@ int plan_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   double* d_wF = (double*)pl.ptr(ctx, i_wF);
   sp.tc = (TrajC*)pl.ptr(ctx, i_tc);
   sp.chi2 = out->d_chi2 ? out->d_chi2 : (double*)pl.ptr(ctx, i_chi);
-  sp.tk_scratch = pl.ptr(ctx, i_tk);
+  sp.select = pl.ptr(ctx, i_sel);
   sp.num_cu = ctx->num_cu;
   sp.h_maps.resize(n_maps);
   for (int i = 0; i < n_maps; ++i) sp.h_maps[i] = make_mapc(maps[i].d_map, maps[i].window);
@@ -233,12 +237,13 @@ hipError_t enqueue_prep(const SearchPlan& sp, const morse_trajectories* trajs, h
 
 hipError_t enqueue_select(const SearchPlan& sp, const morse_search_out* out, hipStream_t st) {
   hipError_t e = hipSuccess;
-  if (out->d_best_chi2 || out->d_best_idx)
+  if (sp.sel.zero_bytes) e = launch_fill_u32((uint32_t*)sp.select, sp.sel.zero_bytes / 4, 0u, st);
+  if (e == hipSuccess && (out->d_best_chi2 || out->d_best_idx))
     e = launch_best(sp.chi2, (int64_t)sp.n_events * sp.n_maps, sp.n_traj, out->d_best_chi2,
-                    out->d_best_idx, st);
+                    out->d_best_idx, sp.select, sp.sel, sp.num_cu, st);
   if (e == hipSuccess && out->top_k > 0)
     e = launch_topk(sp.chi2, sp.n_events, (int64_t)sp.n_maps * sp.n_traj, out->top_k,
-                    out->d_topk_chi2, out->d_topk_idx, sp.tk_scratch, sp.num_cu, st);
+                    out->d_topk_chi2, out->d_topk_idx, sp.select, sp.sel, sp.num_cu, st);
   return e;
 }
 

@@ -479,14 +479,22 @@ __host__ __device__ inline uint32_t search_blocks(uint32_t n_traj, int32_t traj_
 }
 hipError_t launch_search_batched(BatchedArgs a, hipStream_t st);
 
+// Workspace of the selections below: byte offsets.  Its first zero_bytes are zero before the
+// first of them runs.
+struct SelectScratch {
+  size_t zero_bytes, part, tk_state, tk_hist, tk_keys, tk_idx, bytes;
+};
+// n_best segments of best_len for launch_best, n_seg of seg_len for launch_topk (0: not used).
+SelectScratch select_scratch(int64_t n_best, int64_t best_len, int64_t n_seg, int64_t seg_len, int32_t k,
+                             int num_cu);
 // Best (chi2, index) per segment of length seg_len; n_seg segments.
 hipError_t launch_best(const double* chi2, int64_t n_seg, int64_t seg_len, double* best_chi2,
-                       int64_t* best_idx, hipStream_t st);
-// Top-k per segment (k <= 4096); scratch of topk_scratch_bytes(n_seg, k) bytes.
-size_t topk_scratch_bytes(int64_t n_seg, int32_t k);
-hipError_t launch_topk(const double* chi2, int64_t n_seg, int64_t seg_len, int32_t k,
-                       double* out_chi2, int64_t* out_idx, void* scratch, int num_cu,
+                       int64_t* best_idx, char* scratch, const SelectScratch& s, int num_cu,
                        hipStream_t st);
+// Top-k per segment (k <= 4096).
+hipError_t launch_topk(const double* chi2, int64_t n_seg, int64_t seg_len, int32_t k,
+                       double* out_chi2, int64_t* out_idx, char* scratch, const SelectScratch& s,
+                       int num_cu, hipStream_t st);
 
 // Expand top-k flat indices (map * n_traj + traj) into parameter rows.
 hipError_t launch_candidates(const double* axes, int32_t nu, int32_t na, int32_t nt, int32_t ne,

@@ -481,263 +481,442 @@ __device__ __forceinline__ uint64_t order_key(double x) {
   return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
 }
 
-__global__ __launch_bounds__(256) void k_best(const double* __restrict__ chi2, int64_t seg_len,
-                                              double* __restrict__ best_chi2,
-                                              int64_t* __restrict__ best_idx) {
-  __shared__ uint64_t s_key[4];
-  __shared__ int64_t s_idx[4];
-  const double* base = chi2 + (int64_t)blockIdx.x * seg_len;
-  uint64_t bk = ~0ull;
-  int64_t bi = INT64_MAX;
-  for (int64_t i = threadIdx.x; i < seg_len; i += blockDim.x) {
-    const uint64_t k = order_key(base[i]);
-    if (k < bk || (k == bk && i < bi)) {
-      bk = k;
-      bi = i;
-    }
-  }
+// (key, index) pairs in lexicographic order.
+struct KeyIdx {
+  uint64_t key;
+  uint32_t idx;
+};
+__device__ __forceinline__ bool before(uint64_t ka, uint32_t ia, uint64_t kb, uint32_t ib) {
+  return ka < kb || (ka == kb && ia < ib);
+}
+__device__ __forceinline__ void wave_first(KeyIdx& v) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
-    const uint64_t ok = __shfl_xor(bk, o, kWave);
-    const int64_t oi = __shfl_xor(bi, o, kWave);
-    if (ok < bk || (ok == bk && oi < bi)) {
-      bk = ok;
-      bi = oi;
-    }
-  }
-  if ((threadIdx.x & 63) == 0) {
-    s_key[threadIdx.x >> 6] = bk;
-    s_idx[threadIdx.x >> 6] = bi;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int q = 1; q < 4; ++q)
-      if (s_key[q] < bk || (s_key[q] == bk && s_idx[q] < bi)) {
-        bk = s_key[q];
-        bi = s_idx[q];
-      }
-    if (seg_len == 0) bi = -1;
-    if (best_chi2) best_chi2[blockIdx.x] = (bi >= 0) ? base[bi] : __longlong_as_double(0x7ff8000000000000ll);
-    if (best_idx) best_idx[blockIdx.x] = bi;
+    const uint64_t k = __shfl_xor(v.key, o, kWave);
+    const uint32_t i = (uint32_t)__shfl_xor((int)v.idx, o, kWave);
+    if (before(k, i, v.key, v.idx)) v = KeyIdx{k, i};
   }
 }
 
-// Top-k per segment by radix select over the composite key (order_key(chi2), index):
-// 6 passes of 11-bit digits over the 64-bit key, then (only when the k-th key is shared
-// by more items than remain to take) 3 passes over the 32-bit index among those ties.
-// Each pass: every workgroup histograms its slice of the segment in LDS and merges it
-// into the segment's global histogram with atomics; one workgroup per segment then
-// scans the 2048 bins, fixes the next digit of the threshold and clears the histogram.
-// A collect pass writes exactly k survivors (order-free atomic slots) and one
-// workgroup per segment sorts them by (key, index) in LDS.
+// Whether this workgroup is the last of `n` to come here (one ticket counter, zero before;
+// every thread returns the same).  What the workgroups passed on before by device-scope
+// atomics (put_device, atomicAdd: they act at the coherence point, and each wave waits here
+// until its own have) the last may read by device-scope loads (get_device).  A fence would
+// also write back the whole L2, which the scores just filled: 512 workgroups 65 us, so 10.
+__device__ __forceinline__ bool last_here(uint32_t* ticket, uint32_t n) {
+  __shared__ uint32_t s_last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomicAdd(ticket, 1u) == n - 1 ? 1u : 0u;
+  __syncthreads();
+  return s_last != 0u;
+}
+template <class T>
+__device__ __forceinline__ void put_device(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ T get_device(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Smallest (chi2, index) of segment blockIdx.y, gridDim.x workgroups a segment: each leaves its
+// slice's first pair, the last takes the first of those.  (One workgroup a segment read a
+// single segment of 524,288 in 0.71 ms, these 10 us.)
+__global__ __launch_bounds__(256) void k_best(const double* __restrict__ chi2, int64_t seg_len,
+                                              uint32_t* __restrict__ ticket, KeyIdx* __restrict__ part,
+                                              double* __restrict__ best_chi2,
+                                              int64_t* __restrict__ best_idx) {
+  __shared__ KeyIdx s_first[4];
+  const int64_t seg = blockIdx.y;
+  const double* base = chi2 + seg * seg_len;
+  KeyIdx v{~0ull, 0xffffffffu};
+  const int64_t step = (int64_t)gridDim.x * 256;
+  for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < seg_len; i += 4 * step) {
+    double x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = i + q * step < seg_len ? base[i + q * step] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (i + q * step < seg_len) {
+        const uint64_t k = order_key(x[q]);
+        const uint32_t j = (uint32_t)(i + q * step);
+        if (before(k, j, v.key, v.idx)) v = KeyIdx{k, j};
+      }
+  }
+  auto block_first = [&]() {
+    wave_first(v);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) s_first[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = s_first[0];
+#pragma unroll
+    for (int q = 1; q < 4; ++q)
+      if (before(s_first[q].key, s_first[q].idx, v.key, v.idx)) v = s_first[q];
+  };
+  block_first();
+  if (gridDim.x > 1) {
+    if (threadIdx.x == 0) {
+      put_device(&part[seg * gridDim.x + blockIdx.x].key, v.key);
+      put_device(&part[seg * gridDim.x + blockIdx.x].idx, v.idx);
+    }
+    if (!last_here(ticket + seg, gridDim.x)) return;
+    v = KeyIdx{~0ull, 0xffffffffu};
+    for (uint32_t q = threadIdx.x; q < gridDim.x; q += 256) {
+      const KeyIdx* w = part + seg * gridDim.x + q;
+      const uint64_t k = get_device(&w->key);
+      const uint32_t j = get_device(&w->idx);
+      if (before(k, j, v.key, v.idx)) v = KeyIdx{k, j};
+    }
+    block_first();
+  }
+  if (threadIdx.x == 0) {
+    if (best_chi2) best_chi2[seg] = base[v.idx];
+    if (best_idx) best_idx[seg] = (int64_t)v.idx;
+  }
+}
+
+// Top-k per segment, the k smallest by (order_key(chi2), index).  A segment of at most TK_CAP
+// values is put in order in LDS at once.  A longer one first goes through up to six passes
+// of 11-bit digits: every workgroup histograms its slice in LDS and adds it to the
+// segment's histogram, and the last of them scans the bins and fixes the next digit of
+// the threshold.  As soon as the values below the threshold's bin and those in it fit the
+// segment's list (mostly after two passes) the rest return at once: all of them are collected
+// and put in order.  Where more values than that equal the threshold to the last bit, the
+// first by index are taken, from the counts of each workgroup's slice (k_tk_ties).  The
+// launches, not the values, are what this takes: one for a short segment, nine for a long
+// one, where nine passes of two launches, set-up, collection and ranking made 21.  A whole
+// search of 1024 trajectories 216 -> 85 us with it, one of 524,288 2.51 -> 1.70 ms.
 constexpr int TK_BINS = 2048;
 constexpr int TK_THREADS = 256;
 constexpr int TK_MAXK = 4096;
-constexpr int TK_PASSES = 9;
+constexpr int TK_PASSES = 6;
+constexpr int TK_CAP = 2 * TK_MAXK;
 
-struct TkState {
+struct TkState {    // cleared before the first pass
   uint64_t prefix;  // fixed high digits of the threshold key
-  uint64_t mask;
-  int64_t krem;     // rank still to place within the current bin
-  int64_t bincount; // items in the chosen bin of the last pass
-  uint32_t iprefix, imask;  // index digits (tie passes)
-  int32_t need_idx;
-  int32_t taken;    // collect counter
+  int32_t below;    // values below the prefix (at most k - 1)
+  int32_t done;     // passes made when the candidates fit the list, 0 until then
+  int32_t taken;    // collected
+  uint32_t ticket[TK_PASSES + 1];
+  int32_t pad[4];
 };
+static_assert(sizeof(TkState) == 64, "TkState layout");
 
-__device__ __forceinline__ void tk_digit(int pass, int& shift, int& width) {
-  // key passes: bits 63..53, 52..42, 41..31, 30..20, 19..9, 8..0; index: 31..21, 20..10, 9..0
-  const int sh[TK_PASSES] = {53, 42, 31, 20, 9, 0, 21, 10, 0};
-  const int wd[TK_PASSES] = {11, 11, 11, 11, 11, 9, 11, 11, 10};
-  shift = sh[pass];
-  width = wd[pass];
+// Bits 63..53, 52..42, 41..31, 30..20, 19..9, 8..0 of the key.
+__device__ __forceinline__ int tk_shift(int pass) { return pass < 5 ? 53 - 11 * pass : 0; }
+
+// One digit of bin `d` counted for the active lanes (LDS histogram): lanes that share the
+// first active lane's bin, usually most in the exponent's digits, add once.
+__device__ __forceinline__ void tk_count(uint32_t* h, uint32_t d, bool act) {
+  const uint64_t m = __builtin_amdgcn_ballot_w64(act);
+  if (m == 0) return;
+  const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, __builtin_ctzll(m));
+  const uint64_t same = __builtin_amdgcn_ballot_w64(act && d == d0);
+  if ((threadIdx.x & (kWave - 1)) == __builtin_ctzll(m)) atomicAdd(&h[d0], (uint32_t)__popcll(same));
+  if (act && d != d0) atomicAdd(&h[d], 1u);
 }
 
-__global__ void k_tk_init(TkState* st, uint32_t* hist, uint64_t* keys, uint32_t* idx,
-                          int64_t n_seg, int64_t seg_len, int32_t k) {
-  const int64_t seg = blockIdx.x;
-  if (seg >= n_seg) return;
-  for (int b = threadIdx.x; b < TK_BINS; b += blockDim.x) hist[seg * TK_BINS + b] = 0u;
-  for (int b = threadIdx.x; b < k; b += blockDim.x) {  // unfilled slots read as invalid
-    keys[seg * k + b] = ~0ull;
-    idx[seg * k + b] = 0xffffffffu;
+// The bin in which the krem-th smallest (1-based) of the counts falls: digit, the counts
+// before it and its own, on every thread.  NT threads, TK_BINS counts c(b).
+template <int NT, class F>
+__device__ __forceinline__ void tk_pick(F c, int64_t krem, uint32_t* s_wave, int32_t* s_out, int& digit,
+                                        int64_t& less, int64_t& in) {
+  constexpr int PER = TK_BINS / NT;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  uint32_t v[PER], part = 0;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    v[q] = c(threadIdx.x * PER + q);
+    part += v[q];
   }
-  if (threadIdx.x == 0) {
-    TkState s;
-    s.prefix = 0;
-    s.mask = 0;
-    s.krem = min((int64_t)k, seg_len);
-    s.bincount = 0;
-    s.iprefix = 0;
-    s.imask = 0;
-    s.need_idx = 0;
-    s.taken = 0;
-    st[seg] = s;
+  uint32_t incl = part;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const uint32_t l = (uint32_t)__shfl_up((int)incl, o);
+    if (lane >= o) incl += l;
   }
+  if (lane == kWave - 1) s_wave[wave] = incl;
+  __syncthreads();
+  int64_t cum = (int64_t)incl - part;
+  for (int w = 0; w < wave; ++w) cum += s_wave[w];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    if (cum < krem && krem <= cum + v[q]) {
+      s_out[0] = threadIdx.x * PER + q;
+      s_out[1] = (int32_t)cum;  // below krem <= 4096
+      s_out[2] = (int32_t)v[q];
+    }
+    cum += v[q];
+  }
+  __syncthreads();
+  digit = s_out[0];
+  less = s_out[1];
+  in = (uint32_t)s_out[2];
+  __syncthreads();
 }
 
-__global__ __launch_bounds__(TK_THREADS) void k_tk_hist(const double* __restrict__ chi2,
-                                                        int64_t seg_len,
-                                                        const TkState* __restrict__ st,
+__global__ __launch_bounds__(TK_THREADS) void k_tk_hist(const double* __restrict__ chi2, int64_t seg_len,
+                                                        int32_t k, int32_t cap, TkState* __restrict__ st,
                                                         uint32_t* __restrict__ hist, int pass) {
   __shared__ uint32_t h[TK_BINS];
+  __shared__ uint32_t s_wave[TK_THREADS / kWave];
+  __shared__ int32_t s_out[3];
   const int64_t seg = blockIdx.y;
-  const TkState s = st[seg];
-  if (s.krem <= 0 || (pass >= 6 && !s.need_idx)) return;  // uniform per workgroup
+  if (st[seg].done) return;  // uniform per segment
+  const uint64_t prefix = st[seg].prefix;
+  const int64_t krem = (int64_t)k - st[seg].below;  // k <= seg_len: longer than TK_CAP
+  const int shift = tk_shift(pass);
+  const uint64_t mask = pass == 0 ? 0ull : ~0ull << tk_shift(pass - 1);
+  const uint32_t digit = pass < 5 ? TK_BINS - 1 : 511u;
   for (int b = threadIdx.x; b < TK_BINS; b += TK_THREADS) h[b] = 0u;
   __syncthreads();
-  int shift, width;
-  tk_digit(pass, shift, width);
-  const uint32_t dmask = (1u << width) - 1u;
   const double* base = chi2 + seg * seg_len;
-  for (int64_t i = blockIdx.x * (int64_t)TK_THREADS + threadIdx.x; i < seg_len;
-       i += (int64_t)gridDim.x * TK_THREADS) {
-    const uint64_t key = order_key(base[i]);
-    if (pass < 6) {
-      if ((key & s.mask) == s.prefix) atomicAdd(&h[(uint32_t)(key >> shift) & dmask], 1u);
-    } else if (key == s.prefix && (((uint32_t)i) & s.imask) == s.iprefix) {
-      atomicAdd(&h[((uint32_t)i >> shift) & dmask], 1u);
+  const int64_t step = (int64_t)gridDim.x * TK_THREADS;
+  const int64_t rounds = (seg_len + 4 * step - 1) / (4 * step);  // the same for every lane
+  int64_t i = blockIdx.x * (int64_t)TK_THREADS + threadIdx.x;
+  for (int64_t r = 0; r < rounds; ++r, i += 4 * step) {
+    double x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = i + q * step < seg_len ? base[i + q * step] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint64_t key = order_key(x[q]);
+      tk_count(h, (uint32_t)(key >> shift) & digit, i + q * step < seg_len && (key & mask) == prefix);
     }
   }
   __syncthreads();
   uint32_t* g = hist + seg * TK_BINS;
   for (int b = threadIdx.x; b < TK_BINS; b += TK_THREADS)
     if (h[b]) atomicAdd(&g[b], h[b]);
+  if (!last_here(&st[seg].ticket[pass], gridDim.x)) return;
+  int d;
+  int64_t less, in;
+  tk_pick<TK_THREADS>([&](int b) { return get_device(&g[b]); }, krem, s_wave, s_out, d, less, in);
+  if (threadIdx.x == 0) {
+    st[seg].prefix = prefix | ((uint64_t)d << shift);
+    st[seg].below += (int32_t)less;
+    if (st[seg].below + in <= cap) st[seg].done = pass + 1;
+  }
+  for (int b = threadIdx.x; b < TK_BINS; b += TK_THREADS) g[b] = 0u;  // for the next pass
 }
 
-__global__ __launch_bounds__(TK_THREADS) void k_tk_pick(TkState* __restrict__ st,
-                                                        uint32_t* __restrict__ hist, int pass) {
-  __shared__ int64_t incl[TK_THREADS];
-  const int64_t seg = blockIdx.x;
-  TkState s = st[seg];
-  if (s.krem <= 0 || (pass >= 6 && !s.need_idx)) return;
+// Slice of workgroup b of the segment, in index order over the workgroups: a multiple of the
+// workgroup's size, so that its rounds are whole.
+__device__ __forceinline__ int64_t tk_slice(int64_t seg_len) {
+  const int64_t rounds = (seg_len + TK_THREADS - 1) / TK_THREADS;
+  return (rounds + gridDim.x - 1) / gridDim.x * TK_THREADS;
+}
+
+// Where more values equal the threshold key than can be taken: how many lie in the slices
+// before each workgroup's (at most TK_BINS of them), left in the segment's histogram.
+__global__ __launch_bounds__(TK_THREADS) void k_tk_ties(const double* __restrict__ chi2, int64_t seg_len,
+                                                        TkState* __restrict__ st, uint32_t* __restrict__ hist) {
+  __shared__ uint32_t s_wave[TK_THREADS / kWave];
+  const int64_t seg = blockIdx.y;
+  if (st[seg].done) return;  // uniform per segment
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const uint64_t key = st[seg].prefix;
+  const double* base = chi2 + seg * seg_len;
+  const int64_t slice = tk_slice(seg_len), i0 = blockIdx.x * slice, i1 = min(i0 + slice, seg_len);
+  uint32_t count = 0;
+  for (int64_t i = i0 + tid; i < i1; i += TK_THREADS) count += order_key(base[i]) == key ? 1u : 0u;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) count += (uint32_t)__shfl_xor((int)count, o, kWave);
+  if (lane == 0) s_wave[wave] = count;
+  __syncthreads();
   uint32_t* g = hist + seg * TK_BINS;
-  constexpr int PER = TK_BINS / TK_THREADS;
-  const int t = threadIdx.x;
-  uint32_t c[PER];
-  int64_t part = 0;
+  if (tid == 0) put_device(&g[blockIdx.x], s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3]);
+  if (!last_here(&st[seg].ticket[TK_PASSES], gridDim.x)) return;
+  uint32_t cum = 0;
+  for (uint32_t b0 = 0; b0 < gridDim.x; b0 += TK_THREADS) {
+    const uint32_t b = b0 + tid;
+    const uint32_t v = b < gridDim.x ? get_device(&g[b]) : 0u;
+    uint32_t incl = v;
 #pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    c[q] = g[t * PER + q];
-    part += c[q];
-  }
-  incl[t] = part;
-  __syncthreads();
-  for (int o = 1; o < TK_THREADS; o <<= 1) {
-    const int64_t v = (t >= o) ? incl[t - o] : 0;
-    __syncthreads();
-    incl[t] += v;
-    __syncthreads();
-  }
-  const int64_t before = incl[t] - part;
-  int shift, width;
-  tk_digit(pass, shift, width);
-  if (before < s.krem && s.krem <= incl[t]) {
-    int64_t cum = before;
-    int d = t * PER;
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      if (cum + c[q] >= s.krem) {
-        d = t * PER + q;
-        break;
-      }
-      cum += c[q];
+    for (int o = 1; o < kWave; o <<= 1) {
+      const uint32_t l = (uint32_t)__shfl_up((int)incl, o);
+      if (lane >= o) incl += l;
     }
-    const int64_t cnt = g[d];
-    s.krem -= cum;
-    s.bincount = cnt;
-    const uint64_t wm = (1ull << width) - 1ull;
-    if (pass < 6) {
-      s.prefix |= (uint64_t)d << shift;
-      s.mask |= wm << shift;
-      if (pass == 5) s.need_idx = (s.bincount != s.krem) ? 1 : 0;
-    } else {
-      s.iprefix |= (uint32_t)d << shift;
-      s.imask |= (uint32_t)wm << shift;
+    __syncthreads();
+    if (lane == kWave - 1) s_wave[wave] = incl;
+    __syncthreads();
+    uint32_t before_wave = 0, all = 0;
+    for (int w = 0; w < TK_THREADS / kWave; ++w) {
+      before_wave += w < wave ? s_wave[w] : 0u;
+      all += s_wave[w];
     }
-    st[seg] = s;
+    if (b < gridDim.x) g[b] = cum + before_wave + incl - v;
+    cum += all;
   }
-  __syncthreads();
-  for (int b = t; b < TK_BINS; b += TK_THREADS) g[b] = 0u;
 }
 
-// Survivors: key < T, or key == T and (all ties taken, or index <= the chosen index).
-__global__ __launch_bounds__(TK_THREADS) void k_tk_collect(const double* __restrict__ chi2,
-                                                           int64_t seg_len, int32_t k,
-                                                           TkState* __restrict__ st,
+// The values below the threshold's bin and, where the passes ended early, those in it;
+// otherwise those below the threshold key and the first of those equal to it.
+__global__ __launch_bounds__(TK_THREADS) void k_tk_collect(const double* __restrict__ chi2, int64_t seg_len,
+                                                           int32_t k, int32_t cap, TkState* __restrict__ st,
+                                                           const uint32_t* __restrict__ hist,
                                                            uint64_t* __restrict__ keys,
                                                            uint32_t* __restrict__ idx) {
+  __shared__ uint32_t s_wave[TK_THREADS / kWave];
+  __shared__ int32_t s_at;
   const int64_t seg = blockIdx.y;
-  const TkState s = st[seg];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const uint64_t prefix = st[seg].prefix;
+  const int32_t done = st[seg].done;
   const double* base = chi2 + seg * seg_len;
-  for (int64_t i = blockIdx.x * (int64_t)TK_THREADS + threadIdx.x; i < seg_len;
-       i += (int64_t)gridDim.x * TK_THREADS) {
-    const uint64_t key = order_key(base[i]);
-    bool take = key < s.prefix;
-    if (key == s.prefix) take = !s.need_idx || ((uint32_t)i <= s.iprefix);
-    if (take) {
-      const int pos = atomicAdd(&st[seg].taken, 1);
-      if (pos < k) {
-        keys[seg * k + pos] = key;
-        idx[seg * k + pos] = (uint32_t)i;
+  const int64_t slice = tk_slice(seg_len), i0 = blockIdx.x * slice, i1 = min(i0 + slice, seg_len);
+  // inclusive sum over the workgroup's threads; `all` of them
+  auto scan = [&](uint32_t v, uint32_t& all) {
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const uint32_t l = (uint32_t)__shfl_up((int)v, o);
+      if (lane >= o) v += l;
+    }
+    __syncthreads();
+    if (lane == kWave - 1) s_wave[wave] = v;
+    __syncthreads();
+    all = 0;
+    for (int w = 0; w < TK_THREADS / kWave; ++w) {
+      v += w < wave ? s_wave[w] : 0u;
+      all += s_wave[w];
+    }
+    return v;
+  };
+  const int shift = done ? tk_shift(done - 1) : 0;
+  const uint64_t top = (prefix >> shift) + (done ? 1u : 0u);  // done: the whole bin
+  int64_t ties = done ? 0 : hist[seg * TK_BINS + blockIdx.x];
+  const int64_t krem = done ? 0 : (int64_t)k - st[seg].below;
+  // two sweeps, counting and writing, with one claim of the list a workgroup in between
+  // (a claim a wave of 256 values: 41 us on 524,288, the counter's atomics one after another)
+  int at = 0;
+  for (int sweep = 0; sweep < 2; ++sweep) {
+    uint32_t count = 0;
+    int64_t t = ties;
+    for (int64_t r = i0; r < i1; r += 4 * TK_THREADS) {  // uniform
+      double x[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[q] = r + q * TK_THREADS + tid < i1 ? base[r + q * TK_THREADS + tid] : 0.0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int64_t i = r + q * TK_THREADS + tid;
+        const uint64_t key = order_key(x[q]);
+        bool take = i < i1 && (key >> shift) < top;
+        if (!done && t < krem) {  // uniform: the first ties by index
+          uint32_t all;
+          const uint32_t eq = i < i1 && key == prefix ? 1u : 0u;
+          const uint32_t rank = scan(eq, all) - eq;
+          take = take || (eq && t + rank < krem);
+          t += all;
+        }
+        if (take && sweep == 1 && at < cap) {
+          keys[seg * cap + at] = key;
+          idx[seg * cap + at] = (uint32_t)i;
+        }
+        at += take ? 1 : 0;
+        count += take ? 1u : 0u;
       }
+    }
+    if (sweep == 0) {
+      uint32_t all;
+      const uint32_t incl = scan(count, all);
+      if (all == 0) return;
+      if (tid == 0) s_at = atomicAdd(&st[seg].taken, (int32_t)all);
+      __syncthreads();
+      at = s_at + (int32_t)(incl - count);
     }
   }
 }
 
-// Final order of the k selected (key, index) pairs of a segment by rank: element e
-// goes to position #{(key, index) < (key_e, index_e)} (the pairs are distinct, so the
-// ranks are a permutation).  A workgroup stages the segment's pairs in LDS and ranks
-// TKR_ELEMS of them, TKR_SPLIT threads per element each counting over a slice of the
-// pairs (a whole wavefront reads the same LDS words at once; the loop is unrolled so
-// the reads overlap).  Positions past the segment's length get index -1 and NaN.
-constexpr int TKR_ELEMS = 16;
-constexpr int TKR_SPLIT = 16;
-__global__ __launch_bounds__(TKR_ELEMS * TKR_SPLIT) void k_tk_rank(
-    const double* __restrict__ chi2, int64_t seg_len, int32_t k,
-    const uint64_t* __restrict__ keys, const uint32_t* __restrict__ idx,
-    double* __restrict__ out_chi2, int64_t* __restrict__ out_idx) {
-  __shared__ uint64_t lk[TK_MAXK];
-  __shared__ uint32_t li[TK_MAXK];
-  __shared__ uint32_t part[TKR_SPLIT][TKR_ELEMS];
+// The first k of a segment's pairs (the whole segment, or the collected list; at most N), by
+// rank: element e goes to position #{pairs before it} (the pairs are distinct, so the ranks
+// are a permutation).  A workgroup ranks 64 elements; each of its sixteen waves counts over a
+// sixteenth of the pairs, which it reads from LDS a pair at a time for all its lanes.
+// Positions past the segment's length get index -1 and NaN.
+template <int N>
+__global__ __launch_bounds__(1024) void k_tk_rank(const double* __restrict__ chi2, int64_t seg_len, int32_t k,
+                                                  int32_t cap, const TkState* __restrict__ st,
+                                                  const uint64_t* __restrict__ keys,
+                                                  const uint32_t* __restrict__ idx,
+                                                  double* __restrict__ out_chi2, int64_t* __restrict__ out_idx) {
+  __shared__ uint64_t lk[N];
+  __shared__ uint32_t li[N];
+  __shared__ uint32_t part[16][kWave];
   const int64_t seg = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int keff = (int)min((int64_t)k, seg_len);
-  for (int q = tid; q < keff; q += blockDim.x) {
-    lk[q] = keys[seg * k + q];
-    li[q] = idx[seg * k + q];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid / kWave);
+  const double* base = chi2 + seg * seg_len;
+  const int m = st ? min(st[seg].taken, cap) : (int)seg_len;  // at most N
+  for (int q = m + (int)blockIdx.x * 1024 + tid; q < k; q += (int)gridDim.x * 1024) {
+    out_idx[seg * k + q] = -1;
+    out_chi2[seg * k + q] = __longlong_as_double(0x7ff8000000000000ll);
+  }
+  const int e0 = blockIdx.x * kWave, e = e0 + lane;
+  if (e0 >= m) return;  // uniform
+  for (int q = tid; q < m; q += 1024) {
+    lk[q] = st ? keys[seg * cap + q] : order_key(base[q]);
+    li[q] = st ? idx[seg * cap + q] : (uint32_t)q;
   }
   __syncthreads();
-  const int el = tid % TKR_ELEMS, slice = tid / TKR_ELEMS;
-  const int e = blockIdx.x * TKR_ELEMS + el;
+  const uint64_t mk = e < m ? lk[e] : 0ull;
+  const uint32_t mi = e < m ? li[e] : 0u;
+  const int j1 = m * (wave + 1) / 16;
   uint32_t count = 0;
-  if (e < keff) {
-    const uint64_t mk = lk[e];
-    const uint32_t mi = li[e];
-    const int j0 = (int)((int64_t)keff * slice / TKR_SPLIT);
-    const int j1 = (int)((int64_t)keff * (slice + 1) / TKR_SPLIT);
 #pragma unroll 8
-    for (int j = j0; j < j1; ++j) {
-      const uint64_t kj = lk[j];
-      const uint32_t ij = li[j];
-      count += (kj < mk || (kj == mk && ij < mi)) ? 1u : 0u;
-    }
-  }
-  part[slice][el] = count;
+  for (int j = m * wave / 16; j < j1; ++j) count += before(lk[j], li[j], mk, mi) ? 1u : 0u;
+  part[wave][lane] = count;
   __syncthreads();
-  if (slice != 0 || e >= k) return;
-  const double nan = __longlong_as_double(0x7ff8000000000000ll);
-  if (e < keff) {
-    uint32_t rank = 0;
+  if (wave != 0 || e >= m) return;
+  uint32_t rank = 0;
 #pragma unroll
-    for (int q = 0; q < TKR_SPLIT; ++q) rank += part[q][el];
-    const uint32_t ie = li[e];
-    const bool valid = (int64_t)ie < seg_len;
-    out_idx[seg * k + rank] = valid ? (int64_t)ie : -1;
-    out_chi2[seg * k + rank] = valid ? chi2[seg * seg_len + ie] : nan;
-  } else {
-    out_idx[seg * k + e] = -1;
-    out_chi2[seg * k + e] = nan;
+  for (int w = 0; w < 16; ++w) rank += part[w][lane];
+  if (rank >= (uint32_t)k) return;
+  const bool valid = (int64_t)mi < seg_len;
+  out_idx[seg * k + rank] = valid ? (int64_t)mi : -1;
+  out_chi2[seg * k + rank] = valid ? base[mi] : __longlong_as_double(0x7ff8000000000000ll);
+}
+
+// One workgroup of T a segment: its pairs (the whole segment, or the collected list; at most N)
+// into LDS, a bitonic sort, the first k written.  Positions past the segment's length get
+// index -1 and NaN.
+template <int N, int T>
+__global__ __launch_bounds__(T) void k_tk_sort(const double* __restrict__ chi2, int64_t seg_len, int32_t k,
+                                               int32_t cap, const TkState* __restrict__ st,
+                                               const uint64_t* __restrict__ keys,
+                                               const uint32_t* __restrict__ idx,
+                                               double* __restrict__ out_chi2, int64_t* __restrict__ out_idx) {
+  __shared__ uint64_t lk[N];
+  __shared__ uint32_t li[N];
+  const int64_t seg = blockIdx.x;
+  const int tid = threadIdx.x;
+  const double* base = chi2 + seg * seg_len;
+  const int m = st ? min(st[seg].taken, cap) : (int)seg_len;  // at most N
+  int n = 2;
+  while (n < m) n <<= 1;
+  for (int q = tid; q < n; q += T) {
+    const bool in = q < m;
+    lk[q] = !in ? ~0ull : st ? keys[seg * cap + q] : order_key(base[q]);
+    li[q] = !in ? 0xffffffffu : st ? idx[seg * cap + q] : (uint32_t)q;
+  }
+  __syncthreads();
+  for (int size = 2; size <= n; size <<= 1)
+    for (int j = size >> 1; j > 0; j >>= 1) {
+      for (int p = tid; p < n / 2; p += T) {
+        const int a = 2 * p - (p & (j - 1)), b = a + j;
+        const uint64_t ka = lk[a], kb = lk[b];
+        const uint32_t ia = li[a], ib = li[b];
+        if (before(kb, ib, ka, ia) == ((a & size) == 0)) {
+          lk[a] = kb;
+          lk[b] = ka;
+          li[a] = ib;
+          li[b] = ia;
+        }
+      }
+      __syncthreads();
+    }
+  for (int q = tid; q < k; q += T) {
+    const bool valid = q < m && (int64_t)li[q] < seg_len;
+    out_idx[seg * k + q] = valid ? (int64_t)li[q] : -1;
+    out_chi2[seg * k + q] = valid ? base[li[q]] : __longlong_as_double(0x7ff8000000000000ll);
   }
 }
 
@@ -904,48 +1083,83 @@ hipError_t launch_search_batched(BatchedArgs a, hipStream_t st) {
   return hipGetLastError();
 }
 
+namespace {
+// Workgroups per segment: 1024 values each, about four a CU over all segments at most.
+int64_t select_blocks(int64_t n_seg, int64_t seg_len, int num_cu) {
+  const int64_t cap = std::max<int64_t>(1, std::min<int64_t>(TK_BINS, 4 * (int64_t)num_cu) / n_seg);
+  return std::max<int64_t>(1, std::min((seg_len + 1023) / 1024, cap));
+}
+size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
+constexpr int64_t kRankSegs = 8;
+int32_t tk_cap(int32_t k) { return std::min(std::max(2 * k, 512), TK_CAP); }
+}  // namespace
+
+SelectScratch select_scratch(int64_t n_best, int64_t best_len, int64_t n_seg, int64_t seg_len, int32_t k,
+                             int num_cu) {
+  SelectScratch s{};
+  const int64_t p = n_best > 0 ? select_blocks(n_best, best_len, num_cu) : 1;
+  const bool lists = k > 0 && seg_len > TK_CAP;
+  // cleared: tickets of the best, then the states and histograms of the top-k
+  s.tk_state = al256(p > 1 ? 4 * (size_t)n_best : 0);
+  s.tk_hist = s.tk_state + (lists ? sizeof(TkState) * (size_t)n_seg : 0);
+  s.zero_bytes = s.tk_hist + (lists ? 4 * (size_t)TK_BINS * n_seg : 0);
+  s.part = al256(s.zero_bytes);
+  s.tk_keys = s.part + al256(p > 1 ? sizeof(KeyIdx) * (size_t)(p * n_best) : 0);
+  s.tk_idx = s.tk_keys + al256(lists ? 8 * (size_t)tk_cap(k) * n_seg : 0);
+  s.bytes = s.tk_idx + al256(lists ? 4 * (size_t)tk_cap(k) * n_seg : 0);
+  return s;
+}
+
 hipError_t launch_best(const double* chi2, int64_t n_seg, int64_t seg_len, double* best_chi2,
-                       int64_t* best_idx, hipStream_t st) {
+                       int64_t* best_idx, char* scratch, const SelectScratch& s, int num_cu,
+                       hipStream_t st) {
   if (n_seg <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_best, dim3((unsigned)n_seg), dim3(256), 0, st, chi2, seg_len, best_chi2,
-                     best_idx);
+  if (seg_len <= 0) return hipErrorInvalidValue;
+  const int64_t p = select_blocks(n_seg, seg_len, num_cu);
+  for (int64_t s0 = 0; s0 < n_seg; s0 += 65535) {  // the grid's second dimension
+    const int64_t n = std::min<int64_t>(65535, n_seg - s0);
+    hipLaunchKernelGGL(k_best, dim3((unsigned)p, (unsigned)n), dim3(256), 0, st, chi2 + s0 * seg_len, seg_len,
+                       (uint32_t*)scratch + s0, (KeyIdx*)(scratch + s.part) + s0 * p,
+                       best_chi2 ? best_chi2 + s0 : nullptr, best_idx ? best_idx + s0 : nullptr);
+  }
   return hipGetLastError();
 }
 
-size_t topk_scratch_bytes(int64_t n_seg, int32_t k) {
-  auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
-  return al(sizeof(TkState) * n_seg) + al(4 * (size_t)TK_BINS * n_seg) + al(8 * (size_t)k * n_seg) +
-         al(4 * (size_t)k * n_seg);
-}
-
 hipError_t launch_topk(const double* chi2, int64_t n_seg, int64_t seg_len, int32_t k,
-                       double* out_chi2, int64_t* out_idx, void* scratch, int num_cu,
-                       hipStream_t st) {
+                       double* out_chi2, int64_t* out_idx, char* scratch, const SelectScratch& s,
+                       int num_cu, hipStream_t st) {
   if (n_seg <= 0 || k <= 0) return hipSuccess;
-  auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
-  char* p = (char*)scratch;
-  TkState* state = (TkState*)p;
-  p += al(sizeof(TkState) * n_seg);
-  uint32_t* hist = (uint32_t*)p;
-  p += al(4 * (size_t)TK_BINS * n_seg);
-  uint64_t* keys = (uint64_t*)p;
-  p += al(8 * (size_t)k * n_seg);
-  uint32_t* idx = (uint32_t*)p;
-  // enough workgroups to cover the chip about four times over all segments
-  int64_t per_seg = (seg_len + 16 * TK_THREADS - 1) / (16 * TK_THREADS);
-  const int64_t cap = std::max<int64_t>(1, (4 * (int64_t)num_cu * 4) / n_seg);
-  per_seg = std::max<int64_t>(1, std::min(per_seg, cap));
-  const dim3 grid((unsigned)per_seg, (unsigned)n_seg);
-  hipLaunchKernelGGL(k_tk_init, dim3((unsigned)n_seg), dim3(256), 0, st, state, hist, keys, idx, n_seg,
-                     seg_len, k);
-  for (int pass = 0; pass < TK_PASSES; ++pass) {
-    hipLaunchKernelGGL(k_tk_hist, grid, dim3(TK_THREADS), 0, st, chi2, seg_len, state, hist, pass);
-    hipLaunchKernelGGL(k_tk_pick, dim3((unsigned)n_seg), dim3(TK_THREADS), 0, st, state, hist, pass);
+  TkState* state = nullptr;
+  uint64_t* keys = (uint64_t*)(scratch + s.tk_keys);
+  uint32_t* idx = (uint32_t*)(scratch + s.tk_idx);
+  const int32_t cap = tk_cap(k);
+  int64_t sorted = seg_len;
+  if (seg_len > TK_CAP) {
+    state = (TkState*)(scratch + s.tk_state);
+    uint32_t* hist = (uint32_t*)(scratch + s.tk_hist);
+    const dim3 grid((unsigned)select_blocks(n_seg, seg_len, num_cu), (unsigned)n_seg), block(TK_THREADS);
+    for (int pass = 0; pass < TK_PASSES; ++pass)
+      hipLaunchKernelGGL(k_tk_hist, grid, block, 0, st, chi2, seg_len, k, cap, state, hist, pass);
+    hipLaunchKernelGGL(k_tk_ties, grid, block, 0, st, chi2, seg_len, state, hist);
+    hipLaunchKernelGGL(k_tk_collect, grid, block, 0, st, chi2, seg_len, k, cap, state, hist, keys, idx);
+    sorted = cap;
   }
-  hipLaunchKernelGGL(k_tk_collect, grid, dim3(TK_THREADS), 0, st, chi2, seg_len, k, state, keys, idx);
-  hipLaunchKernelGGL(k_tk_rank, dim3((unsigned)((k + TKR_ELEMS - 1) / TKR_ELEMS), (unsigned)n_seg),
-                     dim3(TKR_ELEMS * TKR_SPLIT), 0, st, chi2, seg_len, k, keys, idx, out_chi2,
-                     out_idx);
+  // Ranks take m^2 comparisons spread over the chip, the sort m log^2 m on one CU a segment:
+  // 23 against 118 us for 8192 pairs of one segment, 7 against 18 for 1024; the sort takes as
+  // long for a segment on every CU, the ranks' time grows with the segments.
+  const dim3 ranks((unsigned)((sorted + kWave - 1) / kWave), (unsigned)n_seg);
+  if (n_seg <= kRankSegs && sorted <= 1024)
+    hipLaunchKernelGGL(k_tk_rank<1024>, ranks, dim3(1024), 0, st, chi2, seg_len, k, cap, state, keys, idx,
+                       out_chi2, out_idx);
+  else if (n_seg <= kRankSegs)
+    hipLaunchKernelGGL(k_tk_rank<TK_CAP>, ranks, dim3(1024), 0, st, chi2, seg_len, k, cap, state, keys, idx,
+                       out_chi2, out_idx);
+  else if (sorted <= 1024)
+    hipLaunchKernelGGL((k_tk_sort<1024, 512>), dim3((unsigned)n_seg), dim3(512), 0, st, chi2, seg_len, k, cap,
+                       state, keys, idx, out_chi2, out_idx);
+  else
+    hipLaunchKernelGGL((k_tk_sort<TK_CAP, 1024>), dim3((unsigned)n_seg), dim3(1024), 0, st, chi2, seg_len, k,
+                       cap, state, keys, idx, out_chi2, out_idx);
   return hipGetLastError();
 }
 

@@ -40,19 +40,10 @@ int morse_ctx_create(int device, void* stream, morse_ctx** out) {
     }
     c->own_stream = true;
   }
-  if (hipStreamCreate(&c->capture_stream) != hipSuccess ||
-      // non-blocking, default priority: ordered against the context's stream by the
-      // refinement's own fork and join events only, also when that is the null stream
-      hipStreamCreateWithFlags(&c->fork_stream, hipStreamNonBlocking) != hipSuccess ||
-      hipEventCreateWithFlags(&c->fork_ev, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&c->join_ev, hipEventDisableTiming) != hipSuccess) {
-    if (c->join_ev) (void)hipEventDestroy(c->join_ev);
-    if (c->fork_ev) (void)hipEventDestroy(c->fork_ev);
-    if (c->fork_stream) (void)hipStreamDestroy(c->fork_stream);
-    if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);
+  if (hipStreamCreate(&c->capture_stream) != hipSuccess) {
     if (c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;
-    return fail(nullptr, MORSE_EHIP, "stream or event creation failed");
+    return fail(nullptr, MORSE_EHIP, "hipStreamCreate failed");
   }
   // the allocation-free entry point's scratch address on this device, looked up once
   char* scratch = nullptr;
@@ -74,9 +65,7 @@ int morse_ctx_destroy(morse_ctx* ctx) {
   if (!ctx) return MORSE_OK;
   (void)hipSetDevice(ctx->device);
   (void)hipStreamSynchronize(ctx->stream);
-  (void)hipStreamSynchronize(ctx->fork_stream);  // before the workspace it reads is freed
   if (ctx->gexec) (void)hipGraphExecDestroy(ctx->gexec);
-  if (ctx->refine_gexec) (void)hipGraphExecDestroy(ctx->refine_gexec);
   if (ctx->ws) (void)hipFree(ctx->ws);
   if (ctx->aux) (void)hipFree(ctx->aux);
   if (ctx->taps) (void)hipFree(ctx->taps);
@@ -90,9 +79,6 @@ int morse_ctx_destroy(morse_ctx* ctx) {
     (void)hipEventDestroy(t.b);
   }
   for (hipEvent_t e : ctx->free_events) (void)hipEventDestroy(e);
-  (void)hipEventDestroy(ctx->join_ev);
-  (void)hipEventDestroy(ctx->fork_ev);
-  (void)hipStreamDestroy(ctx->fork_stream);
   (void)hipStreamDestroy(ctx->capture_stream);
   if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
   delete ctx;

@@ -110,53 +110,6 @@ int setup_candidates(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
 }
 }  // namespace
 
-namespace {
-
-// Refinements of at least kRefineSplitMin candidates run as two chains on two streams,
-// others as one captured graph.
-constexpr int64_t kRefineSplitMin = 1024;
-
-// Views of the candidates [c0, c0 + n) of a refinement's state and evaluation arguments.
-LbfgsState part_state(const LbfgsState& s, int64_t c0, int64_t n) {
-  LbfgsState r = s;
-  r.n = n;
-  r.anchor = s.anchor + 4 * c0;
-  r.p = s.p + 4 * c0;
-  r.pt = s.pt + 4 * c0;
-  r.f = s.f + c0;
-  r.g = s.g + 4 * c0;
-  r.d = s.d + 4 * c0;
-  r.step = s.step + c0;
-  r.S = s.S + 4 * (int64_t)s.m * c0;
-  r.Y = s.Y + 4 * (int64_t)s.m * c0;
-  r.R = s.R + (int64_t)s.m * c0;
-  r.nhist = s.nhist + c0;
-  r.nls = s.nls + c0;
-  r.active = s.active + c0;
-  return r;
-}
-
-GradArgs part_args(const GradArgs& a, int64_t c0, int64_t n) {
-  GradArgs r = a;
-  r.n = n;
-  if (a.params) r.params = a.params + 4 * c0;
-  if (a.anchor) r.anchor = a.anchor + 4 * c0;
-  if (a.pt) r.pt = a.pt + 4 * c0;
-  if (a.active) r.active = a.active + c0;
-  r.event = a.event + c0;
-  r.mapidx = a.mapidx + c0;
-  r.tc = a.tc + c0;
-  r.tEv = a.tEv + c0;
-  if (a.chi2) r.chi2 = a.chi2 + c0;
-  if (a.grad) r.grad = a.grad + 4 * c0;
-  if (a.fs) r.fs = a.fs + c0;
-  if (a.fb) r.fb = a.fb + c0;
-  if (a.order) r.order = a.order + c0;  // each part's order holds its own local indices
-  return r;
-}
-
-}  // namespace
-
 extern "C" {
 
 
@@ -231,14 +184,11 @@ int morse_chi2_grad(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   if (n > 0 && (!d_params || !d_event || !d_map_index))
     return fail(ctx, MORSE_EINVAL, "d_params / d_event / d_map_index is NULL");
   HIP_TRY(ctx, hipSetDevice(ctx->device));
-  const size_t i_tc = pl.add(sizeof(TrajC) * (size_t)n), i_tE = pl.add(8 * (size_t)n),
-               i_order = pl.add(4 * (size_t)n), i_key = pl.add(4 * (size_t)n),
-               i_hist = pl.add(4 * (size_t)order_bins(n_maps, lcs->n_events));
+  const bool ordered = order_helps(n, n_maps, lcs->n_events);
+  const size_t i_order = pl.add(ordered ? 4 * (size_t)n : 0), i_key = pl.add(ordered ? 4 * (size_t)n : 0),
+               i_hist = pl.add(ordered ? 4 * (size_t)order_bins(n_maps, lcs->n_events) : 0);
   if ((rc = reserve(ctx, pl.total()))) return rc;
   GradArgs a{};
-  a.tc = (TrajC*)pl.ptr(ctx, i_tc);
-  a.tEv = (double*)pl.ptr(ctx, i_tE);
-  a.order = (const int32_t*)pl.ptr(ctx, i_order);
   MapC* d_maps;
   if ((rc = setup_candidates(ctx, maps, n_maps, lcs, pl, i_sums, i_wF, i_quad, a.lc, d_maps))) return rc;
   a.n = n;
@@ -252,9 +202,12 @@ int morse_chi2_grad(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   a.grad = d_grad;
   a.fs = d_fs;
   a.fb = d_fb;
-  HIP_TRY(ctx, launch_cand_order(a, (uint32_t*)pl.ptr(ctx, i_key), (uint32_t*)pl.ptr(ctx, i_hist),
-                                 (int32_t*)a.order, ctx->stream));
-  HIP_TRY(ctx, launch_cand_prep(a, ctx->stream));
+  if (ordered) {
+    int32_t* order = (int32_t*)pl.ptr(ctx, i_order);
+    HIP_TRY(ctx, launch_cand_order(a, (uint32_t*)pl.ptr(ctx, i_key), (uint32_t*)pl.ptr(ctx, i_hist), order,
+                                   ctx->stream));
+    a.order = order;
+  }
   LaunchTimer tm{ctx, MORSE_KERNEL_GRADIENT};
   HIP_TRY(ctx, tm.begin(ctx->stream));
   HIP_TRY(ctx, launch_chi2_grad(a, ctx->stream));
@@ -277,8 +230,8 @@ int morse_chi2_grad_noalloc(morse_ctx* ctx, const morse_map_view* maps, int32_t 
   const size_t b_off = (8 * (size_t)(ne + 1) + 255) & ~size_t(255);
   const size_t b_tref = (8 * (size_t)ne + 255) & ~size_t(255);
   const size_t i_meta = pl.add(b_off + b_tref + sizeof(MapC) * n_maps);
-  const size_t i_tc = pl.add(sizeof(TrajC) * (size_t)n), i_tE = pl.add(8 * (size_t)n),
-               i_order = pl.add(4 * (size_t)n), i_key = pl.add(4 * (size_t)n),
+  pl.add((sizeof(TrajC) + 8) * (size_t)n);  // the stated limit counts 40 bytes a candidate for its constants
+  const size_t i_order = pl.add(4 * (size_t)n), i_key = pl.add(4 * (size_t)n),
                i_hist = pl.add(4 * (size_t)order_bins(n_maps, ne));
   if (pl.total() > kNoallocScratchBytes)
     return fail(ctx, MORSE_ERANGE,
@@ -309,9 +262,6 @@ int morse_chi2_grad_noalloc(morse_ctx* ctx, const morse_map_view* maps, int32_t 
   HIP_TRY(ctx, launch_quad_pack(d_maps, hm.data(), n_maps, ctx->stream));
   HIP_TRY(ctx, launch_lc_prep(a.lc.t, a.lc.F, a.lc.w, a.lc.off, ne, (double*)a.lc.wFc,
                               (double*)a.lc.sums, nullptr, ctx->stream));
-  a.tc = (TrajC*)pl.ptr_at(base, i_tc);
-  a.tEv = (double*)pl.ptr_at(base, i_tE);
-  a.order = (const int32_t*)pl.ptr_at(base, i_order);
   a.n = n;
   a.params = d_params;
   a.event = d_event;
@@ -323,9 +273,12 @@ int morse_chi2_grad_noalloc(morse_ctx* ctx, const morse_map_view* maps, int32_t 
   a.grad = d_grad;
   a.fs = d_fs;
   a.fb = d_fb;
-  HIP_TRY(ctx, launch_cand_order(a, (uint32_t*)pl.ptr_at(base, i_key), (uint32_t*)pl.ptr_at(base, i_hist),
-                                 (int32_t*)a.order, ctx->stream));
-  HIP_TRY(ctx, launch_cand_prep(a, ctx->stream));
+  if (order_helps(n, n_maps, ne)) {
+    int32_t* order = (int32_t*)pl.ptr_at(base, i_order);
+    HIP_TRY(ctx, launch_cand_order(a, (uint32_t*)pl.ptr_at(base, i_key), (uint32_t*)pl.ptr_at(base, i_hist),
+                                   order, ctx->stream));
+    a.order = order;
+  }
   HIP_TRY(ctx, launch_chi2_grad(a, ctx->stream));
   return MORSE_OK;
 }
@@ -347,162 +300,45 @@ int morse_refine(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
     return fail(ctx, MORSE_EINVAL, "d_params / d_event / d_map_index / d_chi2_out is NULL");
   if (n == 0) return MORSE_OK;
   HIP_TRY(ctx, hipSetDevice(ctx->device));
-  const int m = opts->history;
-  const size_t i_anchor = pl.add(32 * n), i_p = pl.add(16 * n), i_pt = pl.add(16 * n),
-               i_f = pl.add(8 * n), i_g = pl.add(32 * n), i_d = pl.add(32 * n), i_step = pl.add(8 * n),
-               i_S = pl.add(32 * (size_t)n * m), i_Y = pl.add(32 * (size_t)n * m),
-               i_R = pl.add(8 * (size_t)n * m), i_int = pl.add(12 * n), i_ft = pl.add(8 * n),
-               i_gt = pl.add(32 * n), i_tc = pl.add(sizeof(TrajC) * (size_t)n),
-               i_tE = pl.add(8 * (size_t)n), i_order = pl.add(4 * (size_t)n),
-               i_key = pl.add(4 * (size_t)n);
-  const int64_t nbins = order_bins(n_maps, lcs->n_events);
-  const size_t i_hist0 = pl.add(4 * (size_t)nbins), i_hist1 = pl.add(4 * (size_t)nbins);
+  // One launch runs up to 1024 rounds, so that none lasts long; timed, each round is a launch.
+  const int32_t span = timed(ctx, MORSE_KERNEL_GRADIENT) ? 1 : 1024;
+  const bool ordered = order_helps(n, n_maps, lcs->n_events);
+  const size_t i_order = pl.add(ordered ? 4 * (size_t)n : 0), i_key = pl.add(ordered ? 4 * (size_t)n : 0),
+               i_hist = pl.add(ordered ? 4 * (size_t)order_bins(n_maps, lcs->n_events) : 0),
+               i_state = pl.add(opts->steps >= span ? sizeof(RefineState) * (size_t)n : 0);
   if ((rc = reserve(ctx, pl.total()))) return rc;
   GradArgs a{};
-  a.tc = (TrajC*)pl.ptr(ctx, i_tc);
-  a.tEv = (double*)pl.ptr(ctx, i_tE);
   MapC* d_maps;
   if ((rc = setup_candidates(ctx, maps, n_maps, lcs, pl, i_sums, i_wF, i_quad, a.lc, d_maps))) return rc;
-  LbfgsState s;
-  s.n = n;
-  s.m = m;
-  s.max_ls = opts->max_ls;
-  s.c1 = opts->c1;
-  s.shrink = opts->shrink;
-  double* anchor = (double*)pl.ptr(ctx, i_anchor);
-  s.anchor = anchor;
-  s.p = (float*)pl.ptr(ctx, i_p);
-  s.pt = (float*)pl.ptr(ctx, i_pt);
-  s.f = (double*)pl.ptr(ctx, i_f);
-  s.g = (double*)pl.ptr(ctx, i_g);
-  s.d = (double*)pl.ptr(ctx, i_d);
-  s.step = (double*)pl.ptr(ctx, i_step);
-  s.S = (double*)pl.ptr(ctx, i_S);
-  s.Y = (double*)pl.ptr(ctx, i_Y);
-  s.R = (double*)pl.ptr(ctx, i_R);
-  int32_t* ints = (int32_t*)pl.ptr(ctx, i_int);
-  s.nhist = ints;
-  s.nls = ints + n;
-  s.active = ints + 2 * n;
   a.n = n;
-  a.anchor = anchor;
-  a.pt = s.pt;
-  a.active = s.active;
   a.event = d_event;
   a.mapidx = d_map_index;
   a.maps = d_maps;
   a.n_events = lcs->n_events;
   a.n_maps = n_maps;
-  double* ft = (double*)pl.ptr(ctx, i_ft);
-  double* gt = (double*)pl.ptr(ctx, i_gt);
-  a.chi2 = ft;
-  a.grad = gt;
-  a.order = (const int32_t*)pl.ptr(ctx, i_order);
-  uint32_t* hist[2] = {(uint32_t*)pl.ptr(ctx, i_hist0), (uint32_t*)pl.ptr(ctx, i_hist1)};
-  // The rounds are captured once per argument set and replayed: start (evaluation
-  // order grouped by map, anchor copy, state reset, first-trial constants), steps + 1
-  // rounds of (evaluation, update with the next trial's constants), write-back.
-  Hasher h;
-  h.pod(ctx->ws_epoch);
-  h.pod(n);
-  h.pod(n_maps);
-  h.pod(lcs->n_events);
-  h.pod(*opts);
-  h.pod(d_params);
-  h.pod(d_event);
-  h.pod(d_map_index);
-  h.pod(d_chi2_out);
-  h.pod(d_chi2_init);
-  h.pod(lcs->d_t);
-  h.pod(lcs->d_flux);
-  h.pod(lcs->d_weight);
-  // everything the workspace layout and the metadata buffer depend on
-  h.bytes(lcs->h_offsets, 8 * (size_t)(lcs->n_events + 1));
-  for (int i = 0; i < n_maps; ++i) {
-    h.pod(maps[i].d_map);
-    h.pod(maps[i].window);
+  if (ordered) {
+    int32_t* order = (int32_t*)pl.ptr(ctx, i_order);
+    HIP_TRY(ctx, launch_cand_order(a, (uint32_t*)pl.ptr(ctx, i_key), (uint32_t*)pl.ptr(ctx, i_hist), order,
+                                   ctx->stream));
+    a.order = order;
   }
-  h.pod(ctx->cmeta.p);
-  // start, steps + 1 rounds, write-back of the candidate ranges [c0[k], c0[k] + nc[k])
-  // on streams cs[k], k < parts, their launches interleaved round by round; with
-  // `timing`, events bracket each evaluation
-  auto enqueue = [&](int parts, const hipStream_t* cs, const int64_t* c0, const int64_t* nc,
-                     bool timing) -> hipError_t {
-    LbfgsState sp[2];
-    GradArgs ap[2];
-    for (int k = 0; k < parts; ++k) {
-      sp[k] = part_state(s, c0[k], nc[k]);
-      ap[k] = part_args(a, c0[k], nc[k]);
-    }
-    hipError_t e = hipSuccess;
-    for (int k = 0; k < parts && e == hipSuccess; ++k) {
-      e = launch_cand_order(ap[k], (uint32_t*)pl.ptr(ctx, i_key) + c0[k], hist[k],
-                            const_cast<int32_t*>(ap[k].order), cs[k]);
-      if (e == hipSuccess)
-        e = launch_refine_init(sp[k], ap[k], d_params + 4 * c0[k], anchor + 4 * c0[k], cs[k]);
-    }
-    for (int r = 0; r <= opts->steps && e == hipSuccess; ++r) {
-      for (int k = 0; k < parts && e == hipSuccess; ++k) {
-        LaunchTimer tm{ctx, MORSE_KERNEL_GRADIENT};
-        if (timing) e = tm.begin(cs[k]);
-        if (e == hipSuccess) e = launch_chi2_grad(ap[k], cs[k]);
-        if (e == hipSuccess && timing) e = tm.end(cs[k]);
-        double* init = (r == 0 && d_chi2_init) ? d_chi2_init + c0[k] : nullptr;
-        if (e == hipSuccess)
-          e = launch_lbfgs_update(sp[k], ap[k], r, ft + c0[k], gt + 4 * c0[k], init, cs[k]);
-      }
-    }
-    for (int k = 0; k < parts && e == hipSuccess; ++k)
-      e = launch_lbfgs_finish(sp[k], d_params + 4 * c0[k], d_chi2_out + c0[k], cs[k]);
-    return e;
-  };
-  const int64_t whole0 = 0;
-  if (timed(ctx, MORSE_KERNEL_GRADIENT)) {  // same kernels, launched one by one
-    HIP_TRY(ctx, enqueue(1, &ctx->stream, &whole0, &n, true));
-    return MORSE_OK;
+  RefineArgs s{};
+  s.params = d_params;
+  s.chi2_out = d_chi2_out;
+  s.chi2_init = d_chi2_init;
+  s.state = (RefineState*)pl.ptr(ctx, i_state);
+  s.m = opts->history;
+  s.max_ls = opts->max_ls;
+  s.c1 = opts->c1;
+  s.shrink = opts->shrink;
+  s.steps = opts->steps;
+  for (s.r0 = 0; s.r0 <= opts->steps; s.r0 = s.r1) {
+    s.r1 = std::min(s.r0 + span, opts->steps + 1);
+    LaunchTimer tm{ctx, MORSE_KERNEL_GRADIENT};
+    HIP_TRY(ctx, tm.begin(ctx->stream));
+    HIP_TRY(ctx, launch_refine(a, s, ctx->stream));
+    HIP_TRY(ctx, tm.end(ctx->stream));
   }
-  if (n >= kRefineSplitMin) {
-    // Candidates are independent: the two halves run as two chains of launches on two
-    // streams, so that one chain's evaluations keep the GPU busy while the other waits
-    // between its dependent launches.  Both chains start after the work already on the
-    // context's stream, and the stream waits for both; once forked, the join is
-    // recorded even if a launch failed, so later work never overlaps the second chain.
-    const hipStream_t cs[2] = {ctx->stream, ctx->fork_stream};
-    const int64_t c0[2] = {0, n / 2}, nc[2] = {n / 2, n - n / 2};
-    HIP_TRY(ctx, hipEventRecord(ctx->fork_ev, ctx->stream));
-    HIP_TRY(ctx, hipStreamWaitEvent(ctx->fork_stream, ctx->fork_ev, 0));
-    const hipError_t e = enqueue(2, cs, c0, nc, false);
-    hipError_t ej = hipEventRecord(ctx->join_ev, ctx->fork_stream);
-    if (ej == hipSuccess) ej = hipStreamWaitEvent(ctx->stream, ctx->join_ev, 0);
-    HIP_TRY(ctx, e);
-    HIP_TRY(ctx, ej);
-    return MORSE_OK;
-  }
-  if (!ctx->refine_gexec || ctx->refine_key != h.h) {
-    if (ctx->refine_gexec) {
-      HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-      (void)hipGraphExecDestroy(ctx->refine_gexec);
-      ctx->refine_gexec = nullptr;
-    }
-    hipGraph_t g = nullptr;
-    hipStream_t cs = ctx->capture_stream;
-    HIP_TRY(ctx, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-    hipError_t e = enqueue(1, &cs, &whole0, &n, false);
-    hipError_t e2 = hipStreamEndCapture(cs, &g);
-    if (e != hipSuccess || e2 != hipSuccess) {
-      if (g) (void)hipGraphDestroy(g);
-      return fail(ctx, MORSE_EHIP, "refine graph capture failed: %s",
-                  hipGetErrorString(e != hipSuccess ? e : e2));
-    }
-    e = hipGraphInstantiate(&ctx->refine_gexec, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    if (e != hipSuccess) {
-      ctx->refine_gexec = nullptr;
-      return fail(ctx, MORSE_EHIP, "hipGraphInstantiate failed: %s", hipGetErrorString(e));
-    }
-    ctx->refine_key = h.h;
-  }
-  HIP_TRY(ctx, hipGraphLaunch(ctx->refine_gexec, ctx->stream));
   return MORSE_OK;
 }
 

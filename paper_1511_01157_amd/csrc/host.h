@@ -37,8 +37,6 @@ struct morse_ctx {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   hipStream_t capture_stream = nullptr;  // private stream for graph capture
-  hipStream_t fork_stream = nullptr;     // second chain of a refinement
-  hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   int num_cu = 256;
   char* ws = nullptr;
   size_t ws_size = 0;
@@ -67,9 +65,6 @@ struct morse_ctx {
   // batched-search graph
   hipGraphExec_t gexec = nullptr;
   uint64_t graph_key = 0;
-  // refinement graph
-  hipGraphExec_t refine_gexec = nullptr;
-  uint64_t refine_key = 0;
   // autotune choices per shape class
   std::map<std::string, int> tune;
   // small auxiliary device buffer, separate from the workspace
@@ -214,11 +209,6 @@ inline int reserve(morse_ctx* ctx, size_t bytes) {
     (void)hipGraphExecDestroy(ctx->gexec);
     ctx->gexec = nullptr;
     ctx->graph_key = 0;
-  }
-  if (ctx->refine_gexec) {
-    (void)hipGraphExecDestroy(ctx->refine_gexec);
-    ctx->refine_gexec = nullptr;
-    ctx->refine_key = 0;
   }
   if (ctx->ws) (void)hipFree(ctx->ws);
   ctx->ws = nullptr;

@@ -502,21 +502,14 @@ hipError_t launch_candidates(const double* axes, int32_t nu, int32_t na, int32_t
                              int32_t n_maps, int32_t k, const int64_t* idx, double* params,
                              int32_t* event, int32_t* mapidx, hipStream_t st);
 
-// Gradient evaluation.  When `anchor`/`pt` are given the parameters are the
-// L-BFGS variables (natural = anchor mapped by pt) and the gradient is written with
-// respect to pt; `active` (nullable) skips finished candidates.
+// Gradient evaluation.
 struct GradArgs {
   int64_t n;
-  const double* params;     // natural [n][4] (when anchor == nullptr)
-  const double* anchor;     // [n][4] or nullptr
-  const float* pt;          // [n][4] or nullptr
-  const int32_t* active;    // [n] or nullptr
+  const double* params;     // natural [n][4]
   const int32_t* event;
   const int32_t* mapidx;
   const MapC* maps;
   int32_t n_events, n_maps;  // out-of-range event / map indices give NaN outputs
-  TrajC* tc;                 // [n] per-candidate constants (written by the prep kernel)
-  double* tEv;               // [n] FP64 tE of each candidate
   LcView lc;
   double* chi2;
   double* grad;             // [n][4] or nullptr
@@ -524,16 +517,14 @@ struct GradArgs {
   double* fb;
   const int32_t* order;     // [n] the order in which candidates are evaluated, or nullptr
 };
-// Per-candidate constants (FP64 natural parameters -> binary32 TrajC), then the
-// evaluation kernel.
-hipError_t launch_cand_prep(const GradArgs& a, hipStream_t st);
 hipError_t launch_chi2_grad(const GradArgs& a, hipStream_t st);
-// Evaluation order of candidates [0, a.n): grouped by (map, event) (by map alone when
-// n_maps x n_events exceeds kOrderBinsMax), so that candidates evaluated at the same
-// time sample the same map.  Within a group the order is unspecified: it changes only
+// Evaluation order of candidates [0, a.n): by event, the longest light curve first, and map;
+// by map, then event with more than kRankedEvents events; by map alone when n_maps x n_events
+// exceeds kOrderBinsMax.  Candidates evaluated at the same time then sample the same map.  Within a group the order is unspecified: it changes only
 // the schedule, never a result.  key: workspace of a.n words; hist: of order_bins(a)
 // counters.
 constexpr int64_t kOrderBinsMax = 1 << 20;
+constexpr int32_t kRankedEvents = 1024;
 inline int64_t order_bins(int32_t n_maps, int32_t n_events) {
   const int64_t both = (int64_t)n_maps * n_events;
   return both <= kOrderBinsMax ? both : n_maps;
@@ -541,35 +532,42 @@ inline int64_t order_bins(int32_t n_maps, int32_t n_events) {
 hipError_t launch_cand_order(const GradArgs& a, uint32_t* key, uint32_t* hist, int32_t* order,
                              hipStream_t st);
 
-struct LbfgsState {
-  int64_t n;
-  int32_t m;
-  int32_t max_ls;
-  double c1, shrink;
-  const double* anchor;  // [n][4]
-  float* p;              // [n][4] accepted point
-  float* pt;             // [n][4] trial point
-  double* f;             // [n]
-  double* g;             // [n][4]
-  double* d;             // [n][4]
-  double* step;          // [n]
-  double* S;             // [n][m][4] history pairs, oldest first
-  double* Y;             // [n][m][4]
-  double* R;             // [n][m]
-  int32_t* nhist;        // [n]
-  int32_t* nls;          // [n]
-  int32_t* active;       // [n]
+// Candidates that the chip holds all at once (ten workgroups a CU), or that sample one map
+// for one event, need no order.
+inline bool order_helps(int64_t n, int32_t n_maps, int32_t n_events) {
+  return n > 2048 && order_bins(n_maps, n_events) > 1;
+}
+
+// chi2, (F_s, F_b) and the gradient; G: the sums w r D that it is formed from.
+struct Eval {
+  double chi2, Fs, Fb;
+  double G[5], g[4];
+  int32_t direct, pad;  // whether the direct sums are needed
 };
-// Anchor copy, state reset and first-trial trajectory constants (a.tc, a.tEv).
-hipError_t launch_refine_init(const LbfgsState& s, const GradArgs& a, const double* params,
-                              double* anchor, hipStream_t st);
-// One update of every active candidate from its evaluation ft [n], gt [n][4], then the
-// trajectory constants of its next trial; round 0 also copies ft to chi2_init (if set).
-// s.m must be at most 16.
-hipError_t launch_lbfgs_update(const LbfgsState& s, const GradArgs& a, int32_t round,
-                               const double* ft, const double* gt, double* chi2_init,
-                               hipStream_t st);
-hipError_t launch_lbfgs_finish(const LbfgsState& s, double* params, double* chi2_out,
-                               hipStream_t st);
+constexpr int kMaxHistory = 16;
+// One candidate's L-BFGS state.
+struct RefineState {
+  double an[4];                  // anchor: the starting row
+  double g[4], d[4], f, step;    // at the accepted point
+  struct Pair {
+    double s[4], y[4], r, alph;
+  } pair[kMaxHistory];           // ring of nh pairs from head
+  TrajC tc;                      // of the trial point
+  double tE;
+  Eval ev;                       // its evaluation
+  float p[4], pt[4];             // accepted and trial point
+  int32_t nh, head, nls, active;
+};
+struct RefineArgs {
+  double* params;                // [n][4] in and out
+  double* chi2_out;
+  double* chi2_init;             // or nullptr
+  RefineState* state;            // [n], only used when one launch does not run all rounds
+  int32_t m, max_ls;             // m <= kMaxHistory
+  double c1, shrink;
+  int32_t steps;                 // rounds 0 .. steps
+  int32_t r0, r1;                // rounds of this launch
+};
+hipError_t launch_refine(const GradArgs& a, const RefineArgs& s, hipStream_t st);
 
 }  // namespace morse

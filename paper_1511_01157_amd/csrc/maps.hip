@@ -542,17 +542,45 @@ __global__ __launch_bounds__(1024) void k_scan_u32(uint32_t* v, int64_t nb) {
   }
 }
 
+// Adds one to h[k] for every active lane and returns the lane's place: h[k] before, plus the
+// lanes below with the same k.  Lanes that share the first active lane's k, then the first of
+// the others', add together: neighbours mostly do, and the atomics of one address go one
+// after another (8192 keys in order over 8 bins: 26 us each alone).
+__device__ __forceinline__ uint32_t bucket_add(uint32_t* h, uint32_t k, bool act) {
+  const int lane = threadIdx.x & (kWave - 1);
+  uint32_t place = 0;
+#pragma unroll
+  for (int round = 0; round < 2; ++round) {
+    const uint64_t m = __builtin_amdgcn_ballot_w64(act);
+    if (m == 0) return place;
+    const int first = __builtin_ctzll(m);
+    const uint32_t k0 = (uint32_t)__builtin_amdgcn_readlane((int)k, first);
+    const bool mine = act && k == k0;
+    const uint64_t same = __builtin_amdgcn_ballot_w64(mine);
+    uint32_t at = 0;
+    if (lane == first) at = atomicAdd(&h[k0], (uint32_t)__popcll(same));
+    at = (uint32_t)__builtin_amdgcn_readlane((int)at, first);
+    if (mine) place = at + (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+    act = act && !mine;
+  }
+  if (act) place = atomicAdd(&h[k], 1u);
+  return place;
+}
+
 __global__ void k_bucket_count(const uint32_t* __restrict__ key, int64_t n, uint32_t* hist) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    atomicAdd(&hist[key[i]], 1u);
+  for (int64_t i0 = blockIdx.x * (int64_t)blockDim.x; i0 < n; i0 += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t i = i0 + threadIdx.x;
+    bucket_add(hist, i < n ? key[i] : 0u, i < n);
+  }
 }
 
 __global__ void k_bucket_scatter(const uint32_t* __restrict__ key, int64_t n, uint32_t* cursor,
                                  int32_t* order) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    order[atomicAdd(&cursor[key[i]], 1u)] = (int32_t)i;
+  for (int64_t i0 = blockIdx.x * (int64_t)blockDim.x; i0 < n; i0 += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t i = i0 + threadIdx.x;
+    const uint32_t at = bucket_add(cursor, i < n ? key[i] : 0u, i < n);
+    if (i < n) order[at] = (int32_t)i;
+  }
 }
 
 }  // namespace

@@ -16,12 +16,16 @@
 // dA/dzeta: on the map, k (e0 + fy (e1 - e0), ax1 - ax0) from the bilinear cell;
 // off the map, A(u) = (u^2+2)/(u sqrt(u^2+4)) gives dA/du = -8/(u^2 (u^2+4)^(3/2)).
 //
-// L-BFGS.  One thread per candidate runs the update of the state machine (accept on the
-// Armijo test or backtrack; two-loop recursion for the next direction) after the
-// evaluation kernel; the state (binary32 variables p, FP64 history) is kept in
-// structure-of-arrays form.  (Running the update inside the evaluation workgroup was
-// slower: it raised register use and idled the workgroup during the serial update.)
-
+// L-BFGS.  A candidate's rounds depend on no other candidate, so one workgroup runs all of
+// them: the evaluation on both wavefronts, then the update of the state machine (accept on
+// the Armijo test or backtrack; two-loop recursion for the next direction) on one lane, its
+// state (binary32 variables p, FP64 history) in LDS.  Of a round of a 2000-point candidate,
+// 20 of 35 thousand cycles are the evaluation, bound by FP64 issue; the rest is the update, a
+// chain of some hundred dependent FP64 operations during which the CU's other nine
+// workgroups evaluate.  51 rounds of 8192 candidates on 8 ragged events (2000 points):
+// 3.00 ms, 3.48 as two launches a round; of 64 candidates (2000 points) 0.96 ms.  Several
+// candidates a workgroup, updated side by side, took 15% longer: each stops at its own
+// round, and the workgroup lives as long as its last.
 #include "internal.h"
 
 namespace morse {
@@ -32,27 +36,17 @@ __device__ __forceinline__ double dot4(const double* a, const double* b) {
   return ((a[0] * b[0] + a[1] * b[1]) + a[2] * b[2]) + a[3] * b[3];
 }
 
-// Sum of NV FP64 values over the workgroup in a fixed order (a wavefront
-// reduce-scatter, then the wave partials in wave order); every thread returns the
-// same values.
+// Sum of NV FP64 values over each wavefront in a fixed order (a reduce-scatter), left in
+// s_part; their sum in wave order is the workgroup's, wave_sum of it.
 template <int NV>
-__device__ __forceinline__ void block_sum(double (&v)[NV], double (*s_part)[NV]) {
+__device__ __forceinline__ void leave_partials(double (&v)[NV], double* s_part) {
   static_assert(kWave == 64 && NV <= 64, "reduce-scatter assumes 64-lane wavefronts");
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
-  const int nw = blockDim.x / kWave;
   int slot = 0;
   bool valid = true;
   reduce_scatter<NV>(v, lane, slot, valid);
-  if (valid) s_part[wave][slot] = v[0];
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < NV; ++q) {
-    double t = s_part[0][q];
-    for (int k = 1; k < nw; ++k) t += s_part[k][q];
-    v[q] = t;
-  }
-  __syncthreads();
+  if (valid) s_part[wave * NV + slot] = v[0];
 }
 
 // One workgroup (GRAD_THREADS lanes over the points) per candidate; thread k takes the
@@ -62,11 +56,13 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double (*s_part)[NV])
 #endif
 constexpr int GRAD_THREADS = MORSE_GRAD_THREADS;
 
-struct Eval {
-  double chi2, Fs, Fb;
-  double g[4];
-  bool valid;
-};
+template <int NV>
+__device__ __forceinline__ double wave_sum(const double* s_part, int q) {
+  double t = s_part[q];
+  for (int k = 1; k < GRAD_THREADS / kWave; ++k) t += s_part[k * NV + q];
+  return t;
+}
+
 
 // dA/dzeta of one sample: on the map from the bilinear cell, off the map from the
 // point-source magnification.
@@ -92,43 +88,46 @@ __device__ __forceinline__ void sample_dA(const Sample& sm, double kx, double ky
 constexpr int kDirs = 5;
 constexpr int kSums = 3 + 3 * kDirs;
 
-// chi2, (F_s, F_b) and the gradient of candidate c (every thread returns the same).
-// With an anchor the parameters are the L-BFGS variables and the gradient is with
-// respect to them.
-//
 // One pass: with b = A - 1, wFc = w (F - Fbar) and c0 = B1/S_w the residual is
 // r = (F - Fbar) - F_s (b - c0), so for every direction D
 //   sum w r D = P_D - F_s (Q_D - c0 R_D),  P_D = sum wFc D, Q_D = sum w b D, R_D = sum w D,
 // and chi2 = V - F_s C (the search's one-pass fit).  When the fit is degenerate or that
 // chi2 is flagged as cancellation-prone, a second pass sums w r^2 and w r D directly
 // with the residual formed point by point.
-__device__ Eval grad_eval(const GradArgs& a, int64_t c, double (*s_part)[kSums]) {
-  Eval out;
-  const int tid = threadIdx.x;
-  const int32_t e = uniform(a.event[c]);
-  const int32_t mi = uniform(a.mapidx[c]);
-  out.valid = !(e < 0 || e >= a.n_events || mi < 0 || mi >= a.n_maps);
-  if (!out.valid) {
-    const double nan = __longlong_as_double(0x7ff8000000000000ll);
-    out.chi2 = out.Fs = out.Fb = nan;
-    for (int q = 0; q < 4; ++q) out.g[q] = nan;
-    return out;
-  }
-  const MapC m = uniform(a.maps[mi]);
-  const TrajC tc = uniform(a.tc[c]);
-  const double tE = uniform(a.tEv[c]);
-  const double tE_anchor = a.anchor ? uniform(a.anchor[4 * c + 2]) : 0.0;
-  const float iE = tc.iE, ca = tc.ca, sa = tc.sa, bx = tc.bx, by = tc.by;
-  const float t0p = (float)(tc.t0 - uniform(a.lc.t_ref[e]));
-
+//
+// grad_sums: the first pass on the trajectory tc, by the whole workgroup; fit_sums, on one
+// lane a candidate: the fit; direct_sums, by the workgroup: the second pass; form_gradient,
+// on the lane: the gradient.
+// A candidate's event and map, loaded once for all its rounds.
+struct Target {
+  MapC m;
+  const float* t;
+  const double *w, *wFc, *F;
+  int32_t np;
+  double t_ref;
+};
+__device__ __forceinline__ Target target_of(const GradArgs& a, int32_t e, int32_t mi) {
+  Target z;
+  z.m = uniform(a.maps[mi]);
   const int64_t p0 = uniform(a.lc.off[e]);
-  const int32_t np = (int32_t)(uniform(a.lc.off[e + 1]) - p0);
-  const float* t = a.lc.t + p0;
-  const double* w = a.lc.w + p0;
-  const double* wFc = a.lc.wFc + p0;
-  const double* F = a.lc.F + p0;
-  const double Sw = uniform(a.lc.sums[3 * e]), Fbar = uniform(a.lc.sums[3 * e + 1]),
-               V = uniform(a.lc.sums[3 * e + 2]);
+  z.np = (int32_t)(uniform(a.lc.off[e + 1]) - p0);
+  z.t = a.lc.t + p0;
+  z.w = a.lc.w + p0;
+  z.wFc = a.lc.wFc + p0;
+  z.F = a.lc.F + p0;
+  z.t_ref = uniform(a.lc.t_ref[e]);
+  return z;
+}
+
+__device__ __forceinline__ void grad_sums(const Target& z, const TrajC& tc, double* s_part) {
+  const int tid = threadIdx.x;
+  const MapC& m = z.m;
+  const float iE = tc.iE, ca = tc.ca, sa = tc.sa, bx = tc.bx, by = tc.by;
+  const float t0p = (float)(tc.t0 - z.t_ref);
+  const int32_t np = z.np;
+  const float* t = z.t;
+  const double* w = z.w;
+  const double* wFc = z.wFc;
   const double kx = (double)m.kx, ky = (double)m.ky;
 
   // acc: B1, B2, C, then (R_D, Q_D, P_D) per direction
@@ -201,66 +200,90 @@ __device__ Eval grad_eval(const GradArgs& a, int64_t c, double (*s_part)[kSums])
     fa = ldg(wFc, idx(i0 + 2 * STEP));
     if (i0 + STEP < np) add_point(lb, tlb, vb, wb, fb);
   }
-  block_sum<kSums>(acc, s_part);
-  const Fit fit = centred_fit(Sw, Fbar, V, acc[0], acc[1], acc[2], fit_terms(np, GRAD_THREADS));
-  const double Fs = fit.Fs, Fb = fit.Fb;
-  double G[kDirs];  // sum w r D
-  double chi2;
-  if (!fit.degenerate && !fit.recheck) {
-    const double c0 = acc[0] / Sw;
+  leave_partials<kSums>(acc, s_part);
+}
+
+__device__ void fit_sums(int32_t np, double Sw, double Fbar, double V, const double* s_part, Eval& out) {
+  const double B1 = wave_sum<kSums>(s_part, 0);
+  const Fit fit = centred_fit(Sw, Fbar, V, B1, wave_sum<kSums>(s_part, 1), wave_sum<kSums>(s_part, 2),
+                              fit_terms(np, GRAD_THREADS));
+  out.Fs = fit.Fs;
+  out.Fb = fit.Fb;
+  out.chi2 = fit.chi2;
+  out.direct = fit.degenerate || fit.recheck ? 1 : 0;
+  const double c0 = B1 / Sw;
 #pragma unroll
-    for (int k = 0; k < kDirs; ++k)
-      G[k] = acc[5 + 3 * k] - Fs * (acc[4 + 3 * k] - c0 * acc[3 + 3 * k]);
-    chi2 = fit.chi2;
-  } else {  // uniform per workgroup: the sums are identical on every thread
-    // direct sums of w r^2 and w r D, Neumaier-compensated per thread
-    double n2[1 + kDirs], n2c[1 + kDirs];
+  for (int k = 0; k < kDirs; ++k)
+    out.G[k] = wave_sum<kSums>(s_part, 5 + 3 * k) -
+               out.Fs * (wave_sum<kSums>(s_part, 4 + 3 * k) - c0 * wave_sum<kSums>(s_part, 3 + 3 * k));
+}
+
+// Direct sums of w r^2 and w r D, Neumaier-compensated per thread.
+__device__ __forceinline__ void direct_sums(const Target& z, const TrajC& tc, double Fs, double Fb,
+                                            double* s_part) {
+  const MapC& m = z.m;
+  const float iE = tc.iE, ca = tc.ca, sa = tc.sa, bx = tc.bx, by = tc.by;
+  const float t0p = (float)(tc.t0 - z.t_ref);
+  const double kx = (double)m.kx, ky = (double)m.ky;
+  double n2[1 + kDirs], n2c[1 + kDirs];
 #pragma unroll
-    for (int q = 0; q <= kDirs; ++q) n2[q] = n2c[q] = 0.0;
-    for (int32_t i = tid; i < np; i += GRAD_THREADS) {
-      const uint32_t u = (uint32_t)i;
-      const Sample sm = sample_full(m, ldg(t, u), t0p, iE, ca, sa, bx, by);
-      const double A = (double)sm.A;
-      const double r = ldg(F, u) - Fs * A - Fb;
-      const double wr = ldg(w, u) * r;
-      double dAx, dAy;
-      sample_dA(sm, kx, ky, dAx, dAy);
-      const double tau = (double)sm.tau;
-      neumaier_add(n2[0], n2c[0], wr * r);
-      neumaier_add(n2[1], n2c[1], wr * dAx);
-      neumaier_add(n2[2], n2c[2], wr * dAy);
-      neumaier_add(n2[3], n2c[3], (wr * dAx) * tau);
-      neumaier_add(n2[4], n2c[4], (wr * dAy) * tau);
-      neumaier_add(n2[5], n2c[5], wr * ((double)sm.zx * dAy - (double)sm.zy * dAx));
-    }
-#pragma unroll
-    for (int q = 0; q <= kDirs; ++q) n2[q] += n2c[q];
-    // reuse the first 1 + kDirs columns of the partial-sum buffer
-    block_sum<1 + kDirs>(n2, reinterpret_cast<double (*)[1 + kDirs]>(&s_part[0][0]));
-    chi2 = n2[0];
-#pragma unroll
-    for (int k = 0; k < kDirs; ++k) G[k] = n2[1 + k];
+  for (int q = 0; q <= kDirs; ++q) n2[q] = n2c[q] = 0.0;
+  for (int32_t i = threadIdx.x; i < z.np; i += GRAD_THREADS) {
+    const uint32_t u = (uint32_t)i;
+    const Sample sm = sample_full(m, ldg(z.t, u), t0p, iE, ca, sa, bx, by);
+    const double A = (double)sm.A;
+    const double r = ldg(z.F, u) - Fs * A - Fb;
+    const double wr = ldg(z.w, u) * r;
+    double dAx, dAy;
+    sample_dA(sm, kx, ky, dAx, dAy);
+    const double tau = (double)sm.tau;
+    neumaier_add(n2[0], n2c[0], wr * r);
+    neumaier_add(n2[1], n2c[1], wr * dAx);
+    neumaier_add(n2[2], n2c[2], wr * dAy);
+    neumaier_add(n2[3], n2c[3], (wr * dAx) * tau);
+    neumaier_add(n2[4], n2c[4], (wr * dAy) * tau);
+    neumaier_add(n2[5], n2c[5], wr * ((double)sm.zx * dAy - (double)sm.zy * dAx));
   }
-  const double c64 = (double)ca, s64 = (double)sa;
-  const double k2 = -2.0 * Fs;
-  out.g[0] = k2 * (-(c64 * G[0] + s64 * G[1]) / tE);
-  out.g[1] = k2 * (-s64 * G[0] + c64 * G[1]);
-  out.g[2] = k2 * (-(c64 * G[2] + s64 * G[3]) / tE);
-  out.g[3] = k2 * G[4];
-  if (a.anchor) {  // gradient with respect to the scaled variables
+#pragma unroll
+  for (int q = 0; q <= kDirs; ++q) n2[q] += n2c[q];
+  leave_partials<1 + kDirs>(n2, s_part);
+}
+
+__device__ void take_direct(const double* s_part, Eval& out) {
+  out.chi2 = wave_sum<1 + kDirs>(s_part, 0);
+#pragma unroll
+  for (int k = 0; k < kDirs; ++k) out.G[k] = wave_sum<1 + kDirs>(s_part, 1 + k);
+}
+
+// kScaled: the parameters are the L-BFGS variables about an anchor of time scale tE_anchor
+// and the gradient is with respect to them.
+template <bool kScaled>
+__device__ void form_gradient(const TrajC& tc, double tE, double tE_anchor, Eval& out) {
+  const double c64 = (double)tc.ca, s64 = (double)tc.sa;
+  const double k2 = -2.0 * out.Fs;
+  out.g[0] = k2 * (-(c64 * out.G[0] + s64 * out.G[1]) / tE);
+  out.g[1] = k2 * (-s64 * out.G[0] + c64 * out.G[1]);
+  out.g[2] = k2 * (-(c64 * out.G[2] + s64 * out.G[3]) / tE);
+  out.g[3] = k2 * out.G[4];
+  if (kScaled) {
     out.g[0] = out.g[0] * tE_anchor;
     out.g[2] = out.g[2] * tE;
   }
-  out.chi2 = chi2;
-  out.Fs = Fs;
-  out.Fb = Fb;
-  return out;
+}
+
+__device__ __forceinline__ void eval_nan(Eval& out) {
+  out.direct = 0;
+  out.chi2 = out.Fs = out.Fb = __longlong_as_double(0x7ff8000000000000ll);
+  for (int q = 0; q < 4; ++q) out.g[q] = out.chi2;
+}
+
+__device__ __forceinline__ bool in_range(const GradArgs& a, int32_t e, int32_t mi) {
+  return e >= 0 && e < a.n_events && mi >= 0 && mi < a.n_maps;
 }
 
 // Trajectory constants of natural parameters (t0, u0, tE, alpha), FP64 trigonometry
-// rounded once, written for candidate c.
-__device__ void write_natural(const GradArgs& a, int64_t c, double t0, double u0, double tE,
-                              double al) {
+// rounded once.
+__device__ __forceinline__ TrajC natural_traj(double t0, double u0, double tE, double al) {
   double sn, cs;
   sincos(al, &sn, &cs);
   TrajC r;
@@ -271,51 +294,48 @@ __device__ void write_natural(const GradArgs& a, int64_t c, double t0, double u0
   r.bx = (float)(-u0 * sn);
   r.by = (float)(u0 * cs);
   r.pad = 0.0f;
-  a.tc[c] = r;
-  a.tEv[c] = tE;
-}
-
-// Natural parameters from the L-BFGS anchor and binary32 displacement p.
-__device__ void write_traj(const GradArgs& a, int64_t c, const double* an, const float* p) {
-  write_natural(a, c, an[0] + (double)p[0] * an[2], an[1] + (double)p[1],
-                an[2] * exp((double)p[2]), an[3] + (double)p[3]);
-}
-
-// Candidate c's trajectory constants: from its FP64 row, or from its anchor and trial
-// displacement.
-__device__ void prep_candidate(const GradArgs& a, int64_t c) {
-  if (a.anchor) {
-    write_traj(a, c, a.anchor + 4 * c, a.pt + 4 * c);
-  } else {
-    const double* p = a.params + 4 * c;
-    write_natural(a, c, p[0], p[1], p[2], p[3]);
-  }
-}
-
-__global__ void k_cand_prep(GradArgs a) {
-  const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (c >= a.n) return;
-  if (a.active && !a.active[c]) return;
-  prep_candidate(a, c);
+  return r;
 }
 
 // Workgroups are dispatched to the 8 XCDs in turn (the grid is a multiple of 8), so
-// slot s runs on XCD s % 8.  With an evaluation order grouped by map, slot s takes the
-// s-th candidate of that order: the XCDs work through the same map at the same time
-// and share it in the last-level cache.  Without one, XCD x takes the contiguous
+// slot s runs on XCD s % 8.  With an evaluation order, slot s takes the s-th candidate of
+// it: the longest light curves start first, so that none ends long after the others, and
+// the XCDs work through the same map at the same time.  (Chunks of 64 to 1024 neighbours a
+// XCD: 3 to 40% slower, the lengths then differ over the XCDs.)  Without one, XCD x takes the contiguous
 // candidate range [x per, (x + 1) per), so that neighbouring candidates (similar
 // trajectories after a ranked selection) share its L2.
 // At most 96 VGPRs (five wavefronts per SIMD): the compiler fits the kernel without
 // spilling (four wavefronts measured 2% slower).
 __global__ __launch_bounds__(GRAD_THREADS) __attribute__((amdgpu_waves_per_eu(5))) void k_chi2_grad(GradArgs a) {
-  __shared__ double s_part[GRAD_THREADS / kWave][kSums];
+  __shared__ double s_part[GRAD_THREADS / kWave * kSums];
+  __shared__ TrajC s_tc;
+  __shared__ Eval ev;
   const int64_t per = (a.n + 7) / 8;
   for (int64_t slot = blockIdx.x; slot < 8 * per; slot += gridDim.x) {
     const int64_t pos = a.order ? slot : (slot % 8) * per + slot / 8;
     if (pos >= a.n) continue;
     const int64_t c = a.order ? (int64_t)uniform(a.order[pos]) : pos;
-    if (a.active && !a.active[c]) continue;  // uniform per workgroup
-    const Eval ev = grad_eval(a, c, s_part);
+    const int32_t e = uniform(a.event[c]), mi = uniform(a.mapidx[c]);
+    const double* p = a.params + 4 * c;
+    __syncthreads();  // the last candidate's constants, sums and results have been read
+    if (in_range(a, e, mi)) {  // uniform
+      if (threadIdx.x == 0) s_tc = natural_traj(p[0], p[1], p[2], p[3]);
+      __syncthreads();
+      const TrajC tc = uniform(s_tc);
+      const Target z = target_of(a, e, mi);
+      grad_sums(z, tc, s_part);
+      __syncthreads();
+      if (threadIdx.x == 0) fit_sums(z.np, a.lc.sums[3 * e], a.lc.sums[3 * e + 1], a.lc.sums[3 * e + 2], s_part, ev);
+      __syncthreads();
+      if (uniform(ev.direct)) {
+        direct_sums(z, tc, uniform(ev.Fs), uniform(ev.Fb), s_part);
+        __syncthreads();
+        if (threadIdx.x == 0) take_direct(s_part, ev);
+      }
+      if (threadIdx.x == 0) form_gradient<false>(tc, p[2], 0.0, ev);
+    } else if (threadIdx.x == 0) {
+      eval_nan(ev);
+    }
     if (threadIdx.x == 0) {
       if (a.chi2) a.chi2[c] = ev.chi2;
       if (a.grad)
@@ -326,71 +346,45 @@ __global__ __launch_bounds__(GRAD_THREADS) __attribute__((amdgpu_waves_per_eu(5)
   }
 }
 
-// One candidate's L-BFGS state, held in registers for one update.  The history pairs
-// are stored oldest first (an accepted pair past m shifts the others down), so all of
-// them, like every other field, load at once at the start of the update, with no load
-// waiting on another or on a store.  M >= m bounds the history; loops run over
-// compile-time slots in the order of a loop over the nh stored pairs.
-template <int M>
-struct Regs {
-  double S[M][4], Y[M][4], R[M];
-  double g[4], d[4], f, step;
-  float p[4], pt[4];
-  int nh, nls;
-};
-
-template <int M>
-__device__ __forceinline__ void load_regs(const LbfgsState& s, int64_t c, Regs<M>& q) {
-#pragma unroll
-  for (int h = 0; h < M; ++h) {  // slots past nh hold stale values and are never used
-    const int64_t row = c * s.m + min(h, s.m - 1);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      q.S[h][k] = s.S[row * 4 + k];
-      q.Y[h][k] = s.Y[row * 4 + k];
-    }
-    q.R[h] = s.R[row];
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    q.g[k] = s.g[4 * c + k];
-    q.d[k] = s.d[4 * c + k];
-    q.p[k] = s.p[4 * c + k];
-    q.pt[k] = s.pt[4 * c + k];
-  }
-  q.f = s.f[c];
-  q.step = s.step[c];
-  q.nh = s.nhist[c];
-  q.nls = s.nls[c];
-}
-
-// New search direction at the accepted point (q.p, q.g); stores d, step, nls, pt and
-// may stop the candidate when the trial would not move it.  Returns whether it moved.
-template <int M>
-__device__ bool new_direction(const LbfgsState& s, int64_t c, Regs<M>& q) {
+// New search direction at the accepted point (q.p, q.g) and the first trial along it; stops
+// the candidate when the trial would not move it.  A pair is loaded while the one before it
+// is worked on: the two loops are one chain of dependent operations.
+__device__ void new_direction(RefineState& q, int m) {
+  using Pair = RefineState::Pair;
   const int nh = q.nh;
-  double r[4], d[4], qq[4], alph[M];
+  double r[4], d[4], qq[4];
   for (int k = 0; k < 4; ++k) qq[k] = q.g[k];
-#pragma unroll
-  for (int h = M - 1; h >= 0; --h) {
-    if (h < nh) {
-      const double a = q.R[h] * dot4(q.S[h], qq);
-      alph[h] = a;
-      for (int k = 0; k < 4; ++k) qq[k] = qq[k] - a * q.Y[h][k];
+  double gamma;
+  if (nh > 0) {
+    const int last = q.head + nh - 1 < m ? q.head + nh - 1 : q.head + nh - 1 - m;  // the newest
+    int i = last;
+    Pair z = q.pair[i];
+    gamma = dot4(z.s, z.y) / dot4(z.y, z.y);
+#pragma unroll 2
+    for (int h = nh; h > 0; --h) {
+      const int j = i > 0 ? i - 1 : m - 1;
+      const Pair next = q.pair[j];
+      const double a = z.r * dot4(z.s, qq);
+      q.pair[i].alph = a;
+      for (int k = 0; k < 4; ++k) qq[k] = qq[k] - a * z.y[k];
+      z = next;
+      i = j;
     }
-  }
-  const double gn = sqrt(dot4(q.g, q.g));
-  double gamma = gn > 0.0 ? 1e-2 / gn : 0.0;
-#pragma unroll
-  for (int h = 0; h < M; ++h)
-    if (h == nh - 1) gamma = dot4(q.S[h], q.Y[h]) / dot4(q.Y[h], q.Y[h]);
-  for (int k = 0; k < 4; ++k) r[k] = gamma * qq[k];
-#pragma unroll
-  for (int h = 0; h < M; ++h) {
-    if (h < nh) {
-      const double b = q.R[h] * dot4(q.Y[h], r);
-      for (int k = 0; k < 4; ++k) r[k] = r[k] + q.S[h][k] * (alph[h] - b);
+    i = q.head;
+    z = q.pair[i];
+    for (int k = 0; k < 4; ++k) r[k] = gamma * qq[k];
+#pragma unroll 2
+    for (int h = nh; h > 0; --h) {
+      i = i + 1 < m ? i + 1 : 0;
+      const Pair next = q.pair[i];
+      const double b = z.r * dot4(z.y, r);
+      for (int k = 0; k < 4; ++k) r[k] = r[k] + z.s[k] * (z.alph - b);
+      z = next;
     }
+  } else {
+    const double gn = sqrt(dot4(q.g, q.g));
+    gamma = gn > 0.0 ? 1e-2 / gn : 0.0;
+    for (int k = 0; k < 4; ++k) r[k] = gamma * qq[k];
   }
   for (int k = 0; k < 4; ++k) d[k] = -r[k];
   const double gd = dot4(q.g, d);
@@ -398,176 +392,189 @@ __device__ bool new_direction(const LbfgsState& s, int64_t c, Regs<M>& q) {
   for (int k = 0; k < 4; ++k) finite = finite && isfinite(d[k]);
   if (!(gd < 0.0) || !finite) {
     q.nh = 0;
-    s.nhist[c] = 0;
+    const double gn = sqrt(dot4(q.g, q.g));
     gamma = gn > 0.0 ? 1e-2 / gn : 0.0;
     for (int k = 0; k < 4; ++k) d[k] = -(gamma * q.g[k]);
   }
-  s.step[c] = 1.0;
-  s.nls[c] = 0;
+  q.step = 1.0;
+  q.nls = 0;
   bool moved = false;
   for (int k = 0; k < 4; ++k) {
-    s.d[4 * c + k] = d[k];
+    q.d[k] = d[k];
     const float v = (float)((double)q.p[k] + 1.0 * d[k]);
     q.pt[k] = v;
-    s.pt[4 * c + k] = v;
     moved = moved || (v != q.p[k]);
   }
-  if (!moved) s.active[c] = 0;
-  return moved;
+  if (!moved) q.active = 0;
 }
 
-// One update of the state machine for candidate c given the evaluation (ft, gt) at
-// its trial point; returns whether the candidate is still active (its next trial
-// point is then q.pt).
-template <int M>
-__device__ bool lbfgs_step(const LbfgsState& s, int64_t c, int32_t round, double ft,
-                           const double* gt, Regs<M>& q) {
-  if (round == 0) {
-    for (int k = 0; k < 4; ++k) {
-      q.p[k] = q.pt[k];
-      q.g[k] = gt[k];
-      s.p[4 * c + k] = q.p[k];
-      s.g[4 * c + k] = q.g[k];
+// Whether sy > 1e-12 |s| |y|, from the squares ss and yy.  Far from the bound, and with no
+// square out of range, the squares decide.
+__device__ __forceinline__ bool curved(double sy, double ss, double yy) {
+  const double p = ss * yy;
+  if (sy > 1e-140 && p < 1e290 && sy * sy > 1e-23 * p) return true;
+  return sy > 1e-12 * sqrt(ss) * sqrt(yy);
+}
+
+// One update of the state machine given the evaluation (ft, gt) at the trial point; the next
+// trial point is then q.pt, unless the candidate was stopped.
+__device__ void lbfgs_step(RefineState& q, const RefineArgs& s, bool first, double ft, const double* gt) {
+  const int m = s.m;
+  if (first) {
+    q.nh = q.head = 0;
+  } else {
+    const double gd = dot4(q.g, q.d);
+    const double t = q.step;
+    if (!(isfinite(ft) && ft <= q.f + (s.c1 * t) * gd)) {
+      q.nls += 1;
+      if (q.nls >= s.max_ls) {
+        q.active = 0;
+        return;
+      }
+      const double tn = t * s.shrink;
+      q.step = tn;
+      for (int k = 0; k < 4; ++k) q.pt[k] = (float)((double)q.p[k] + tn * q.d[k]);
+      return;
     }
-    q.f = ft;
-    s.f[c] = ft;
-    q.nh = 0;
-    return new_direction<M>(s, c, q);
-  }
-  const double gd = dot4(q.g, q.d);
-  const double t = q.step;
-  if (isfinite(ft) && ft <= q.f + (s.c1 * t) * gd) {
     double sv[4], yv[4];
     for (int k = 0; k < 4; ++k) {
       sv[k] = (double)q.pt[k] - (double)q.p[k];
       yv[k] = gt[k] - q.g[k];
     }
     const double sy = dot4(sv, yv);
-    if (sy > 1e-12 * sqrt(dot4(sv, sv)) * sqrt(dot4(yv, yv))) {
+    if (curved(sy, dot4(sv, sv), dot4(yv, yv))) {
       const double rho = 1.0 / sy;
-      const int m = s.m;
       if (q.nh == m) {  // full: drop the oldest pair
-#pragma unroll
-        for (int h = 0; h + 1 < M; ++h)
-          if (h + 1 < m) {
-            for (int k = 0; k < 4; ++k) {
-              q.S[h][k] = q.S[h + 1][k];
-              q.Y[h][k] = q.Y[h + 1][k];
-            }
-            q.R[h] = q.R[h + 1];
-          }
+        q.head = q.head + 1 < m ? q.head + 1 : 0;
         q.nh = m - 1;
       }
-#pragma unroll
-      for (int h = 0; h < M; ++h)
-        if (h == q.nh) {
-          for (int k = 0; k < 4; ++k) {
-            q.S[h][k] = sv[k];
-            q.Y[h][k] = yv[k];
-          }
-          q.R[h] = rho;
-        }
+      const int i = q.head + q.nh < m ? q.head + q.nh : q.head + q.nh - m;
+      for (int k = 0; k < 4; ++k) {
+        q.pair[i].s[k] = sv[k];
+        q.pair[i].y[k] = yv[k];
+      }
+      q.pair[i].r = rho;
       q.nh += 1;
-#pragma unroll
-      for (int h = 0; h < M; ++h)  // write the history back, oldest first
-        if (h < q.nh) {
-          const int64_t row = c * s.m + h;
-          for (int k = 0; k < 4; ++k) {
-            s.S[row * 4 + k] = q.S[h][k];
-            s.Y[row * 4 + k] = q.Y[h][k];
-          }
-          s.R[row] = q.R[h];
+    }
+  }
+  for (int k = 0; k < 4; ++k) {
+    q.p[k] = q.pt[k];
+    q.g[k] = gt[k];
+  }
+  q.f = ft;
+  new_direction(q, m);
+}
+
+// Natural parameters of the displacement p from the anchor.
+__device__ __forceinline__ void natural(const RefineState& q, const float* p, double (&v)[4]) {
+  v[0] = q.an[0] + (double)p[0] * q.an[2];
+  v[1] = q.an[1] + (double)p[1];
+  v[2] = q.an[2] * exp((double)p[2]);
+  v[3] = q.an[3] + (double)p[3];
+}
+
+// Rounds [s.r0, s.r1) of every candidate, a workgroup each.  The first launch starts them
+// (anchor = the candidate's row, p = 0, empty history), the one that ends with the last round
+// writes them back; between launches their state is kept in s.state.
+__global__ __launch_bounds__(GRAD_THREADS) __attribute__((amdgpu_waves_per_eu(5))) void k_refine(GradArgs a,
+                                                                                            RefineArgs s) {
+  __shared__ double s_part[GRAD_THREADS / kWave * kSums];
+  __shared__ RefineState q;
+  constexpr int kWords = sizeof(RefineState) / 4;
+  const int tid = threadIdx.x;
+  const int64_t per = (a.n + 7) / 8;
+  for (int64_t slot = blockIdx.x; slot < 8 * per; slot += gridDim.x) {
+    const int64_t pos = a.order ? slot : (slot % 8) * per + slot / 8;
+    if (pos >= a.n) continue;
+    const int64_t c = a.order ? (int64_t)uniform(a.order[pos]) : pos;
+    const int32_t e = uniform(a.event[c]), mi = uniform(a.mapidx[c]);
+    const bool valid = in_range(a, e, mi);
+    const Target z = target_of(a, valid ? e : 0, valid ? mi : 0);
+    const int32_t es = valid ? e : 0;
+    const double Sw = uniform(a.lc.sums[3 * es]), Fbar = uniform(a.lc.sums[3 * es + 1]), V = uniform(a.lc.sums[3 * es + 2]);
+    __syncthreads();  // the last candidate is done with the state
+    if (s.r0 > 0) {
+      for (int i = tid; i < kWords; i += GRAD_THREADS) ((uint32_t*)&q)[i] = ((const uint32_t*)(s.state + c))[i];
+    } else if (tid == 0) {
+      for (int k = 0; k < 4; ++k) {
+        q.an[k] = s.params[4 * c + k];
+        q.p[k] = q.pt[k] = 0.0f;
+      }
+      q.nls = 0;
+      q.active = 1;
+    }
+    for (int32_t round = s.r0; round < s.r1; ++round) {
+      __syncthreads();
+      if (!uniform(q.active)) break;
+      // the trial's constants (natural_traj of natural), half on each wavefront
+      if (tid == 0) {
+        const double tE = q.an[2] * exp((double)q.pt[2]);
+        q.tc.t0 = q.an[0] + (double)q.pt[0] * q.an[2];
+        q.tc.iE = (float)(1.0 / tE);
+        q.tE = tE;
+      } else if (tid == kWave) {
+        const double u0 = q.an[1] + (double)q.pt[1];
+        double sn, cs;
+        sincos(q.an[3] + (double)q.pt[3], &sn, &cs);
+        q.tc.ca = (float)cs;
+        q.tc.sa = (float)sn;
+        q.tc.bx = (float)(-u0 * sn);
+        q.tc.by = (float)(u0 * cs);
+      }
+      __syncthreads();
+      const TrajC tc = uniform(q.tc);
+      if (valid) grad_sums(z, tc, s_part);
+      __syncthreads();
+      if (tid == 0) {
+        if (valid)
+          fit_sums(z.np, Sw, Fbar, V, s_part, q.ev);
+        else
+          eval_nan(q.ev);
+      }
+      __syncthreads();
+      if (valid) {
+        if (uniform(q.ev.direct)) {
+          direct_sums(z, tc, uniform(q.ev.Fs), uniform(q.ev.Fb), s_part);
+          __syncthreads();
+          if (tid == 0) take_direct(s_part, q.ev);
         }
-      s.nhist[c] = q.nh;
+        if (tid == 0) form_gradient<true>(tc, q.tE, q.an[2], q.ev);
+      }
+      if (tid == 0) {
+        if (round == 0 && s.chi2_init) s.chi2_init[c] = q.ev.chi2;
+        lbfgs_step(q, s, round == 0, q.ev.chi2, q.ev.g);
+      }
     }
-    for (int k = 0; k < 4; ++k) {
-      q.p[k] = q.pt[k];
-      q.g[k] = gt[k];
-      s.p[4 * c + k] = q.p[k];
-      s.g[4 * c + k] = q.g[k];
+    __syncthreads();
+    if (s.r1 <= s.steps) {
+      for (int i = tid; i < kWords; i += GRAD_THREADS) ((uint32_t*)(s.state + c))[i] = ((const uint32_t*)&q)[i];
+    } else if (tid == 0) {
+      double v[4];
+      natural(q, q.p, v);
+      for (int k = 0; k < 4; ++k) s.params[4 * c + k] = v[k];
+      s.chi2_out[c] = q.f;
     }
-    q.f = ft;
-    s.f[c] = ft;
-    return new_direction<M>(s, c, q);
   }
-  const int n = q.nls + 1;
-  s.nls[c] = n;
-  if (n >= s.max_ls) {
-    s.active[c] = 0;
-    return false;
-  }
-  const double tn = t * s.shrink;
-  s.step[c] = tn;
-  for (int k = 0; k < 4; ++k) {
-    q.pt[k] = (float)((double)q.p[k] + tn * q.d[k]);
-    s.pt[4 * c + k] = q.pt[k];
-  }
-  return true;
-}
-
-// Start of a refinement: anchor = the candidate's row, p_t = 0, empty history, every
-// candidate active, and the trajectory constants of the first trial point.
-__global__ void k_refine_init(LbfgsState s, GradArgs a, const double* params,
-                              double* anchor) {
-  const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (c >= s.n) return;
-  for (int k = 0; k < 4; ++k) {
-    anchor[4 * c + k] = params[4 * c + k];
-    s.pt[4 * c + k] = 0.0f;
-  }
-  s.nhist[c] = 0;
-  s.nls[c] = 0;
-  s.active[c] = 1;
-  prep_candidate(a, c);
-}
-
-// Update of every active candidate from its evaluation (ft, gt), then the trajectory
-// constants of its next trial point; round 0 also records the starting chi-square.
-template <int M>
-__global__ __launch_bounds__(64) void k_lbfgs_update(LbfgsState s, GradArgs a, int32_t round,
-                               const double* __restrict__ ft, const double* __restrict__ gt,
-                               double* __restrict__ chi2_init) {
-  const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (c >= s.n || !s.active[c]) return;
-  double g[4], an[4];
-  for (int k = 0; k < 4; ++k) {
-    g[k] = gt[4 * c + k];
-    an[k] = s.anchor[4 * c + k];
-  }
-  const double f = ft[c];
-  Regs<M> q;
-  load_regs<M>(s, c, q);
-  if (round == 0 && chi2_init) chi2_init[c] = f;
-  if (lbfgs_step<M>(s, c, round, f, g, q)) write_traj(a, c, an, q.pt);
-}
-
-__global__ void k_lbfgs_finish(LbfgsState s, double* params, double* chi2_out) {
-  const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (c >= s.n) return;
-  const double* an = s.anchor + 4 * c;
-  const float* p = s.p + 4 * c;
-  params[4 * c + 0] = an[0] + (double)p[0] * an[2];
-  params[4 * c + 1] = an[1] + (double)p[1];
-  params[4 * c + 2] = an[2] * exp((double)p[2]);
-  params[4 * c + 3] = an[3] + (double)p[3];
-  if (chi2_out) chi2_out[c] = s.f[c];
 }
 
 }  // namespace
 
-hipError_t launch_cand_prep(const GradArgs& a, hipStream_t st) {
-  if (a.n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_cand_prep, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, st, a);
-  return hipGetLastError();
-}
-
 namespace {
 
-// Evaluation order: each candidate's (map, event) key, then the shared bucket sort.
+// Evaluation order: each candidate's key, then the shared bucket sort.  Keys go by event, the
+// longest light curves first, then by map; with many events, by map then event.
 __device__ __forceinline__ uint32_t order_key(const GradArgs& a, int64_t c, bool by_event) {
   const int32_t e = a.event[c], m = a.mapidx[c];
   if (e < 0 || e >= a.n_events || m < 0 || m >= a.n_maps) return 0u;  // NaN outputs anyway
-  return by_event ? (uint32_t)m * (uint32_t)a.n_events + (uint32_t)e : (uint32_t)m;
+  if (!by_event) return (uint32_t)m;
+  if (a.n_events > kRankedEvents) return (uint32_t)m * (uint32_t)a.n_events + (uint32_t)e;
+  const int64_t len = a.lc.off[e + 1] - a.lc.off[e];
+  uint32_t rank = 0;
+  for (int32_t k = 0; k < a.n_events; ++k) {
+    const int64_t lk = a.lc.off[k + 1] - a.lc.off[k];
+    rank += lk > len || (lk == len && k < e) ? 1u : 0u;
+  }
+  return rank * (uint32_t)a.n_maps + (uint32_t)m;
 }
 
 __global__ void k_order_keys(GradArgs a, bool by_event, uint32_t* key) {
@@ -590,40 +597,20 @@ hipError_t launch_cand_order(const GradArgs& a, uint32_t* key, uint32_t* hist, i
   return launch_bucket_order(key, a.n, (int32_t)nb, hist, order, st);
 }
 
+namespace {
+unsigned candidate_blocks(int64_t n) { return (unsigned)std::min<int64_t>(8 * ((n + 7) / 8), 1 << 20); }
+}  // namespace
+
 hipError_t launch_chi2_grad(const GradArgs& a, hipStream_t st) {
   if (a.n <= 0) return hipSuccess;
-  int64_t blocks = 8 * ((a.n + 7) / 8);
-  if (blocks > 1 << 20) blocks = 1 << 20;
-  hipLaunchKernelGGL(k_chi2_grad, dim3((unsigned)blocks), dim3(GRAD_THREADS), 0, st, a);
+  hipLaunchKernelGGL(k_chi2_grad, dim3(candidate_blocks(a.n)), dim3(GRAD_THREADS), 0, st, a);
   return hipGetLastError();
 }
 
-hipError_t launch_refine_init(const LbfgsState& s, const GradArgs& a, const double* params,
-                              double* anchor, hipStream_t st) {
-  if (s.n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_refine_init, dim3((unsigned)((s.n + 255) / 256)), dim3(256), 0, st, s, a,
-                     params, anchor);
-  return hipGetLastError();
-}
-
-hipError_t launch_lbfgs_update(const LbfgsState& s, const GradArgs& a, int32_t round,
-                               const double* ft, const double* gt, double* chi2_init,
-                               hipStream_t st) {
-  if (s.n <= 0) return hipSuccess;
-  // 64-lane workgroups: one thread per candidate, spread over as many CUs as possible
-  const dim3 grid((unsigned)((s.n + 63) / 64)), block(64);
-  if (s.m <= 8)
-    hipLaunchKernelGGL(k_lbfgs_update<8>, grid, block, 0, st, s, a, round, ft, gt, chi2_init);
-  else
-    hipLaunchKernelGGL(k_lbfgs_update<16>, grid, block, 0, st, s, a, round, ft, gt, chi2_init);
-  return hipGetLastError();
-}
-
-hipError_t launch_lbfgs_finish(const LbfgsState& s, double* params, double* chi2_out,
-                               hipStream_t st) {
-  if (s.n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_lbfgs_finish, dim3((unsigned)((s.n + 255) / 256)), dim3(256), 0, st, s,
-                     params, chi2_out);
+hipError_t launch_refine(const GradArgs& a, const RefineArgs& s, hipStream_t st) {
+  if (a.n <= 0) return hipSuccess;
+  if (s.m < 1 || s.m > kMaxHistory) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_refine, dim3(candidate_blocks(a.n)), dim3(GRAD_THREADS), 0, st, a, s);
   return hipGetLastError();
 }
 

@@ -40,11 +40,6 @@ int morse_ctx_create(int device, void* stream, morse_ctx** out) {
     }
     c->own_stream = true;
   }
-  if (hipStreamCreate(&c->capture_stream) != hipSuccess) {
-    if (c->own_stream) (void)hipStreamDestroy(c->stream);
-    delete c;
-    return fail(nullptr, MORSE_EHIP, "hipStreamCreate failed");
-  }
   // the allocation-free entry point's scratch address on this device, looked up once
   char* scratch = nullptr;
   const int rc = noalloc_scratch(device, &scratch);
@@ -65,7 +60,6 @@ int morse_ctx_destroy(morse_ctx* ctx) {
   if (!ctx) return MORSE_OK;
   (void)hipSetDevice(ctx->device);
   (void)hipStreamSynchronize(ctx->stream);
-  if (ctx->gexec) (void)hipGraphExecDestroy(ctx->gexec);
   if (ctx->ws) (void)hipFree(ctx->ws);
   if (ctx->aux) (void)hipFree(ctx->aux);
   if (ctx->taps) (void)hipFree(ctx->taps);
@@ -79,7 +73,6 @@ int morse_ctx_destroy(morse_ctx* ctx) {
     (void)hipEventDestroy(t.b);
   }
   for (hipEvent_t e : ctx->free_events) (void)hipEventDestroy(e);
-  (void)hipStreamDestroy(ctx->capture_stream);
   if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
   delete ctx;
   return MORSE_OK;

@@ -63,9 +63,19 @@ int plan_candidates(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   return MORSE_OK;
 }
 
+hipError_t prepare_candidates(const LcView& lc, int32_t ne, const MapC* d_maps, const std::vector<MapC>& hm,
+                              hipStream_t st) {
+  PrepArgs p{};
+  p.lc = lc;
+  p.n_events = ne;
+  p.maps = d_maps;
+  p.n_maps = (int32_t)hm.size();
+  return launch_prep(p, hm.data(), st);
+}
+
 // Host metadata of the candidate entry points (event offsets, reference times, map
-// table) lives in its own device buffer, uploaded only when it changes, so calls that
-// alternate with searches neither re-upload nor wait for the device.
+// table) lives in its own device buffer, put there only when it changes, so calls that
+// alternate with searches need not put it again.
 int setup_candidates(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
                      const morse_lightcurves* lcs, const Plan& pl, size_t i_sums, size_t i_wF,
                      size_t i_quad, LcView& lc, MapC*& d_maps) {
@@ -74,27 +84,20 @@ int setup_candidates(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   std::vector<MapC> hm(n_maps);
   for (int i = 0; i < n_maps; ++i) hm[i] = make_mapc(maps[i].d_map, maps[i].window);
   assign_quads(hm, pl.ptr(ctx, i_quad));
-  const size_t b_off = (8 * (size_t)(ne + 1) + 255) & ~size_t(255);
-  const size_t b_tref = (8 * (size_t)ne + 255) & ~size_t(255);
-  if ((rc = reserve_meta(ctx, ctx->cmeta, b_off + b_tref + sizeof(MapC) * n_maps))) return rc;
-  int64_t* d_off = (int64_t*)ctx->cmeta.p;
-  double* d_tref = (double*)(ctx->cmeta.p + b_off);
-  d_maps = (MapC*)(ctx->cmeta.p + b_off + b_tref);
+  MetaBlock mb;
+  const size_t o_off = mb.add(lcs->h_offsets, 8 * (size_t)(ne + 1)),
+               o_tref = mb.add(lcs->h_t_ref, 8 * (size_t)ne),
+               o_maps = mb.add(hm.data(), sizeof(MapC) * n_maps);  // with the packed cells' addresses
+  if ((rc = reserve_meta(ctx, ctx->cmeta, mb.bytes.size()))) return rc;
+  int64_t* d_off = (int64_t*)(ctx->cmeta.p + o_off);
+  double* d_tref = (double*)(ctx->cmeta.p + o_tref);
+  d_maps = (MapC*)(ctx->cmeta.p + o_maps);
   Hasher h;
   h.pod(ctx->cmeta.p);
   h.pod(ne);
   h.pod(n_maps);
-  h.bytes(lcs->h_offsets, 8 * (size_t)(ne + 1));
-  h.bytes(lcs->h_t_ref, 8 * (size_t)ne);
-  h.bytes(hm.data(), sizeof(MapC) * n_maps);  // includes the packed-cell addresses
-  if (h.h != ctx->cmeta.key) {
-    ctx->cmeta.key = 0;
-    if ((rc = upload(ctx, d_off, lcs->h_offsets, 8 * (size_t)(ne + 1)))) return rc;
-    if ((rc = upload(ctx, d_tref, lcs->h_t_ref, 8 * (size_t)ne))) return rc;
-    if ((rc = upload(ctx, d_maps, hm.data(), sizeof(MapC) * n_maps))) return rc;
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // host arrays go out of scope
-    ctx->cmeta.key = h.h;
-  }
+  h.bytes(mb.bytes.data(), mb.bytes.size());
+  if ((rc = put_meta(ctx, ctx->cmeta.p, ctx->cmeta.key, h.h, mb.bytes))) return rc;
   lc.t = lcs->d_t;
   lc.w = lcs->d_weight;
   lc.F = lcs->d_flux;
@@ -103,9 +106,7 @@ int setup_candidates(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   lc.sums = (double*)pl.ptr(ctx, i_sums);
   lc.t_ref = d_tref;
   lc.sorted = nullptr;
-  HIP_TRY(ctx, launch_quad_pack(d_maps, hm.data(), n_maps, ctx->stream));
-  HIP_TRY(ctx, launch_lc_prep(lc.t, lc.F, lc.w, lc.off, ne, (double*)lc.wFc, (double*)lc.sums,
-                              nullptr, ctx->stream));
+  HIP_TRY(ctx, prepare_candidates(lc, ne, d_maps, hm, ctx->stream));
   return MORSE_OK;
 }
 }  // namespace
@@ -248,9 +249,11 @@ int morse_chi2_grad_noalloc(morse_ctx* ctx, const morse_map_view* maps, int32_t 
   assign_quads(hm, pl.ptr_at(base, i_quad));
   char* meta = pl.ptr_at(base, i_meta);
   MapC* d_maps = (MapC*)(meta + b_off + b_tref);
-  if ((rc = upload(ctx, meta, lcs->h_offsets, 8 * (size_t)(ne + 1)))) return rc;
-  if ((rc = upload(ctx, meta + b_off, lcs->h_t_ref, 8 * (size_t)ne))) return rc;
-  if ((rc = upload(ctx, d_maps, hm.data(), sizeof(MapC) * n_maps))) return rc;
+  std::vector<char> block(b_off + b_tref + sizeof(MapC) * n_maps);
+  std::memcpy(block.data(), lcs->h_offsets, 8 * (size_t)(ne + 1));
+  std::memcpy(block.data() + b_off, lcs->h_t_ref, 8 * (size_t)ne);
+  std::memcpy(block.data() + b_off + b_tref, hm.data(), sizeof(MapC) * n_maps);
+  HIP_TRY(ctx, launch_put(meta, block.data(), block.size(), ctx->stream));  // never waits
   GradArgs a{};
   a.lc.t = lcs->d_t;
   a.lc.w = lcs->d_weight;
@@ -259,9 +262,7 @@ int morse_chi2_grad_noalloc(morse_ctx* ctx, const morse_map_view* maps, int32_t 
   a.lc.off = (const int64_t*)meta;
   a.lc.sums = (double*)pl.ptr_at(base, i_sums);
   a.lc.t_ref = (const double*)(meta + b_off);
-  HIP_TRY(ctx, launch_quad_pack(d_maps, hm.data(), n_maps, ctx->stream));
-  HIP_TRY(ctx, launch_lc_prep(a.lc.t, a.lc.F, a.lc.w, a.lc.off, ne, (double*)a.lc.wFc,
-                              (double*)a.lc.sums, nullptr, ctx->stream));
+  HIP_TRY(ctx, prepare_candidates(a.lc, ne, d_maps, hm, ctx->stream));
   a.n = n;
   a.params = d_params;
   a.event = d_event;

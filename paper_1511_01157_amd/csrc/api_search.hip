@@ -1,4 +1,4 @@
-// C ABI, trajectory search: plain and batched (one launch, graph-captured) searches,
+// C ABI, trajectory search: plain and batched (one scoring launch) searches,
 // best-per-map and top-k selection, the autotuner of the batched shape and its cache,
 // and candidate lists from the top-k.
 
@@ -104,31 +104,6 @@ int64_t traj_count(const morse_trajectories* t) {
   return t->kind == MORSE_TRAJ_GRID ? (int64_t)t->n_u0 * t->n_alpha * t->n_t0 * t->n_tE : t->n;
 }
 
-uint64_t metadata_key(const morse_map_view* maps, int32_t n_maps, const morse_lightcurves* lcs,
-                      const morse_trajectories* trajs) {
-  Hasher h;
-  h.pod(n_maps);
-  for (int i = 0; i < n_maps; ++i) {
-    h.pod(maps[i].d_map);
-    h.pod(maps[i].window);
-  }
-  h.pod(lcs->n_events);
-  h.bytes(lcs->h_offsets, sizeof(int64_t) * (lcs->n_events + 1));
-  h.bytes(lcs->h_t_ref, sizeof(double) * lcs->n_events);
-  h.pod(trajs->kind);
-  if (trajs->kind == MORSE_TRAJ_GRID) {
-    h.pod(trajs->n_u0);
-    h.pod(trajs->n_alpha);
-    h.pod(trajs->n_t0);
-    h.pod(trajs->n_tE);
-    h.bytes(trajs->h_u0, 8 * trajs->n_u0);
-    h.bytes(trajs->h_alpha, 8 * trajs->n_alpha);
-    h.bytes(trajs->h_t0, 8 * trajs->n_t0);
-    h.bytes(trajs->h_tE, 8 * trajs->n_tE);
-  }
-  return h.h;
-}
-
 // Reserve the workspace and upload the host metadata of a search into its own buffer
 // (skipped when the same metadata is already resident).  Enqueues nothing else.
 int plan_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
@@ -180,34 +155,26 @@ int plan_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   for (int i = 0; i < n_maps; ++i) sp.h_maps[i] = make_mapc(maps[i].d_map, maps[i].window);
   assign_quads(sp.h_maps, pl.ptr(ctx, i_quad));
   // metadata buffer: offsets | reference times | map table | grid axes
-  const size_t b_off = (8 * (size_t)(sp.n_events + 1) + 255) & ~size_t(255);
-  const size_t b_tref = (8 * (size_t)sp.n_events + 255) & ~size_t(255);
-  const size_t b_maps = (sizeof(MapC) * n_maps + 255) & ~size_t(255);
-  if ((rc = reserve_meta(ctx, ctx->smeta, b_off + b_tref + b_maps + 8 * (size_t)n_axes))) return rc;
-  int64_t* d_off = (int64_t*)ctx->smeta.p;
-  double* d_tref = (double*)(ctx->smeta.p + b_off);
-  sp.d_maps = (MapC*)(ctx->smeta.p + b_off + b_tref);
-  sp.axes = (double*)(ctx->smeta.p + b_off + b_tref + b_maps);
+  MetaBlock mb;
+  const size_t o_off = mb.add(lcs->h_offsets, 8 * (size_t)(sp.n_events + 1)),
+               o_tref = mb.add(lcs->h_t_ref, 8 * (size_t)sp.n_events),
+               o_maps = mb.add(sp.h_maps.data(), sizeof(MapC) * n_maps);  // with the packed cells' addresses
+  const size_t o_axes = mb.bytes.size();
+  if (n_axes) {
+    mb.add(trajs->h_u0, 8 * (size_t)trajs->n_u0, 8);
+    mb.add(trajs->h_alpha, 8 * (size_t)trajs->n_alpha, 8);
+    mb.add(trajs->h_t0, 8 * (size_t)trajs->n_t0, 8);
+    mb.add(trajs->h_tE, 8 * (size_t)trajs->n_tE, 8);
+  }
+  if ((rc = reserve_meta(ctx, ctx->smeta, mb.bytes.size()))) return rc;
+  int64_t* d_off = (int64_t*)(ctx->smeta.p + o_off);
+  double* d_tref = (double*)(ctx->smeta.p + o_tref);
+  sp.d_maps = (MapC*)(ctx->smeta.p + o_maps);
+  sp.axes = n_axes ? (double*)(ctx->smeta.p + o_axes) : nullptr;
   Hasher key;
   key.pod(ctx->smeta.p);
-  key.pod(metadata_key(maps, n_maps, lcs, trajs));
-  key.bytes(sp.h_maps.data(), sizeof(MapC) * n_maps);  // includes the packed-cell addresses
-  if (key.h != ctx->smeta.key) {
-    ctx->smeta.key = 0;
-    std::vector<double> axes;
-    if (n_axes) {
-      axes.insert(axes.end(), trajs->h_u0, trajs->h_u0 + trajs->n_u0);
-      axes.insert(axes.end(), trajs->h_alpha, trajs->h_alpha + trajs->n_alpha);
-      axes.insert(axes.end(), trajs->h_t0, trajs->h_t0 + trajs->n_t0);
-      axes.insert(axes.end(), trajs->h_tE, trajs->h_tE + trajs->n_tE);
-    }
-    if ((rc = upload(ctx, d_off, lcs->h_offsets, 8 * (sp.n_events + 1)))) return rc;
-    if ((rc = upload(ctx, d_tref, lcs->h_t_ref, 8 * sp.n_events))) return rc;
-    if ((rc = upload(ctx, sp.d_maps, sp.h_maps.data(), sizeof(MapC) * n_maps))) return rc;
-    if ((rc = upload(ctx, sp.axes, axes.data(), 8 * axes.size()))) return rc;
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // host arrays go out of scope
-    ctx->smeta.key = key.h;
-  }
+  key.bytes(mb.bytes.data(), mb.bytes.size());
+  if ((rc = put_meta(ctx, ctx->smeta.p, ctx->smeta.key, key.h, mb.bytes))) return rc;
   sp.lc.t = lcs->d_t;
   sp.lc.w = lcs->d_weight;
   sp.lc.F = lcs->d_flux;
@@ -219,26 +186,37 @@ int plan_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   return MORSE_OK;
 }
 
-// Preparation kernels (map packing, light-curve sums, trajectory constants).
+// Preparation (light-curve sums, trajectory constants, map packing, zeroed counters).
 hipError_t enqueue_prep(const SearchPlan& sp, const morse_trajectories* trajs, hipStream_t st) {
-  hipError_t e = launch_quad_pack(sp.d_maps, sp.h_maps.data(), sp.n_maps, st);
-  if (e != hipSuccess) return e;
-  e = launch_lc_prep(sp.lc.t, sp.lc.F, sp.lc.w, sp.lc.off, sp.n_events,
-                                (double*)sp.lc.wFc, (double*)sp.lc.sums, (uint32_t*)sp.lc.sorted, st);
-  if (e != hipSuccess) return e;
-  if (trajs->kind == MORSE_TRAJ_GRID)
-    return launch_traj_prep_grid(sp.axes, trajs->n_u0, trajs->n_alpha, trajs->n_t0, trajs->n_tE,
-                                 sp.tc, st);
-  const int64_t n = trajs->shared ? sp.n_traj : sp.n_traj * sp.n_events;
-  e = launch_traj_prep_list(trajs->d_params, n, sp.tc, st);
+  PrepArgs a{};
+  a.lc = sp.lc;
+  a.n_events = sp.n_events;
+  a.n_traj = sp.n_traj;
+  a.n = sp.n_traj;
+  a.axes = sp.axes;
+  if (trajs->kind == MORSE_TRAJ_GRID) {
+    a.nu = trajs->n_u0;
+    a.na = trajs->n_alpha;
+    a.nt = trajs->n_t0;
+    a.ne = trajs->n_tE;
+  } else {
+    a.params = trajs->d_params;
+    if (!trajs->shared) a.n *= sp.n_events;
+    a.key = sp.perm ? sp.perm_key : nullptr;
+  }
+  a.tc = sp.tc;
+  a.zero = (uint32_t*)sp.select;
+  a.n_zero = sp.sel.zero_bytes / 4;
+  a.maps = sp.d_maps;
+  a.n_maps = sp.n_maps;
+  const hipError_t e = launch_prep(a, sp.h_maps.data(), st);
   if (e != hipSuccess || !sp.perm) return e;
-  return launch_traj_perm(sp.tc, sp.n_traj, sp.perm_lists, sp.perm_key, sp.perm_hist, sp.perm, st);
+  return launch_traj_perm(sp.perm_key, sp.n_traj, sp.perm_lists, sp.perm_hist, sp.perm, st);
 }
 
 hipError_t enqueue_select(const SearchPlan& sp, const morse_search_out* out, hipStream_t st) {
   hipError_t e = hipSuccess;
-  if (sp.sel.zero_bytes) e = launch_fill_u32((uint32_t*)sp.select, sp.sel.zero_bytes / 4, 0u, st);
-  if (e == hipSuccess && (out->d_best_chi2 || out->d_best_idx))
+  if (out->d_best_chi2 || out->d_best_idx)
     e = launch_best(sp.chi2, (int64_t)sp.n_events * sp.n_maps, sp.n_traj, out->d_best_chi2,
                     out->d_best_idx, sp.select, sp.sel, sp.num_cu, st);
   if (e == hipSuccess && out->top_k > 0)
@@ -352,60 +330,20 @@ int morse_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
     return MORSE_OK;
   }
 
-  // batched: one scoring launch, captured into a graph per argument set
+  // batched: one scoring launch; with preparation and selection five to fourteen in all.
+  // Launched one by one (3 us of the host each): 1024 trajectories with top-64 take 28 us a call,
+  // from a captured graph of the same launches 45 us, and 80 to 300 where the graph has to be
+  // captured again.
   auto it = ctx->tune.find(shape_class(sp));
   const int cfg_idx =
       it == ctx->tune.end() ? default_shape(sp.n_traj * sp.n_events * sp.n_maps) : it->second;
-  const TuneCfg& cfg = kTune[cfg_idx];
-  Hasher h;
-  h.pod(metadata_key(maps, n_maps, lcs, trajs));
-  h.pod(ctx->smeta.p);
-  h.pod(ctx->ws_epoch);
-  h.pod(cfg_idx);
-  h.pod(*out);
-  h.pod(lcs->d_t);
-  h.pod(lcs->d_flux);
-  h.pod(lcs->d_weight);
-  h.pod(trajs->d_params);
-  h.pod(trajs->shared);
-  h.pod(trajs->n);
-  if (timed(ctx, MORSE_KERNEL_SEARCH)) {  // same kernels, launched one by one
-    const BatchedArgs a = batched_args(ctx, sp, trajs, out, cfg);
-    HIP_TRY(ctx, enqueue_prep(sp, trajs, ctx->stream));
-    LaunchTimer tm{ctx, MORSE_KERNEL_SEARCH};
-    HIP_TRY(ctx, tm.begin(ctx->stream));
-    HIP_TRY(ctx, launch_search_batched(a, ctx->stream));
-    HIP_TRY(ctx, tm.end(ctx->stream));
-    HIP_TRY(ctx, enqueue_select(sp, out, ctx->stream));
-    return MORSE_OK;
-  }
-  if (!ctx->gexec || ctx->graph_key != h.h) {
-    if (ctx->gexec) {
-      HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-      (void)hipGraphExecDestroy(ctx->gexec);
-      ctx->gexec = nullptr;
-    }
-    const BatchedArgs a = batched_args(ctx, sp, trajs, out, cfg);
-    hipGraph_t g = nullptr;
-    HIP_TRY(ctx, hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeThreadLocal));
-    hipError_t e = enqueue_prep(sp, trajs, ctx->capture_stream);
-    if (e == hipSuccess) e = launch_search_batched(a, ctx->capture_stream);
-    if (e == hipSuccess) e = enqueue_select(sp, out, ctx->capture_stream);
-    hipError_t e2 = hipStreamEndCapture(ctx->capture_stream, &g);
-    if (e != hipSuccess || e2 != hipSuccess) {
-      if (g) (void)hipGraphDestroy(g);
-      return fail(ctx, MORSE_EHIP, "graph capture failed: %s",
-                  hipGetErrorString(e != hipSuccess ? e : e2));
-    }
-    e = hipGraphInstantiate(&ctx->gexec, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    if (e != hipSuccess) {
-      ctx->gexec = nullptr;
-      return fail(ctx, MORSE_EHIP, "hipGraphInstantiate failed: %s", hipGetErrorString(e));
-    }
-    ctx->graph_key = h.h;
-  }
-  HIP_TRY(ctx, hipGraphLaunch(ctx->gexec, ctx->stream));
+  const BatchedArgs a = batched_args(ctx, sp, trajs, out, kTune[cfg_idx]);
+  HIP_TRY(ctx, enqueue_prep(sp, trajs, ctx->stream));
+  LaunchTimer tm{ctx, MORSE_KERNEL_SEARCH};
+  HIP_TRY(ctx, tm.begin(ctx->stream));
+  HIP_TRY(ctx, launch_search_batched(a, ctx->stream));
+  HIP_TRY(ctx, tm.end(ctx->stream));
+  HIP_TRY(ctx, enqueue_select(sp, out, ctx->stream));
   return MORSE_OK;
 }
 
@@ -508,16 +446,16 @@ int morse_candidates_from_topk(morse_ctx* ctx, const morse_trajectories* trajs, 
   const double* axes = nullptr;
   int rc;
   if (trajs->kind == MORSE_TRAJ_GRID) {
-    std::vector<double> h;
-    h.insert(h.end(), trajs->h_u0, trajs->h_u0 + trajs->n_u0);
-    h.insert(h.end(), trajs->h_alpha, trajs->h_alpha + trajs->n_alpha);
-    h.insert(h.end(), trajs->h_t0, trajs->h_t0 + trajs->n_t0);
-    h.insert(h.end(), trajs->h_tE, trajs->h_tE + trajs->n_tE);
+    MetaBlock mb;
+    mb.add(trajs->h_u0, 8 * (size_t)trajs->n_u0, 8);
+    mb.add(trajs->h_alpha, 8 * (size_t)trajs->n_alpha, 8);
+    mb.add(trajs->h_t0, 8 * (size_t)trajs->n_t0, 8);
+    mb.add(trajs->h_tE, 8 * (size_t)trajs->n_tE, 8);
     // the auxiliary buffer keeps the search's resident workspace intact
-    if ((rc = reserve_aux(ctx, 8 * h.size()))) return rc;
+    if ((rc = reserve_aux(ctx, mb.bytes.size()))) return rc;
     double* d = (double*)ctx->aux;
-    if ((rc = upload(ctx, d, h.data(), 8 * h.size()))) return rc;
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    uint64_t none = 0;
+    if ((rc = put_meta(ctx, d, none, 1, mb.bytes))) return rc;
     axes = d;
   }
   HIP_TRY(ctx, launch_candidates(axes, trajs->n_u0, trajs->n_alpha, trajs->n_t0, trajs->n_tE,

@@ -36,16 +36,15 @@ struct morse_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
   bool own_stream = false;
-  hipStream_t capture_stream = nullptr;  // private stream for graph capture
   int num_cu = 256;
   char* ws = nullptr;
   size_t ws_size = 0;
-  uint64_t ws_epoch = 0;  // bumps when the workspace moves
   std::string err;
   // host metadata of the searches and of the candidate entry points, each in a device
   // buffer of its own (never in the shared workspace, which the other entry points
   // overwrite) and uploaded only when its key changes
   MetaBuf smeta, cmeta;
+  bool captured = false;  // a call was captured into a graph: its replays put metadata too
   // source-radius stacks: direct-sum taps, FFT twiddle tables and the transforms of
   // the profile pairs, each kept until a call needs different ones
   MetaBuf stack_taps, fft_tw, fft_spec;
@@ -62,9 +61,6 @@ struct morse_ctx {
     size_t w_bytes = 0;  // the tap offsets follow the weights at this byte offset
     int rmx = 0, rmy = 0;
   } stack_split;
-  // batched-search graph
-  hipGraphExec_t gexec = nullptr;
-  uint64_t graph_key = 0;
   // autotune choices per shape class
   std::map<std::string, int> tune;
   // small auxiliary device buffer, separate from the workspace
@@ -116,7 +112,7 @@ inline int fail(morse_ctx* ctx, int code, const char* fmt, ...) {
       return fail((ctx), MORSE_EHIP, "%s failed: %s", #expr, hipGetErrorString(e_));         \
   } while (0)
 
-// FNV-1a over raw bytes, for keys of uploaded metadata and captured graphs.
+// FNV-1a over raw bytes, for keys of uploaded metadata.
 struct Hasher {
   uint64_t h = 1469598103934665603ull;
   void bytes(const void* p, size_t n) {
@@ -205,11 +201,6 @@ struct Plan {
 inline int reserve(morse_ctx* ctx, size_t bytes) {
   if (bytes <= ctx->ws_size) return MORSE_OK;
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-  if (ctx->gexec) {
-    (void)hipGraphExecDestroy(ctx->gexec);
-    ctx->gexec = nullptr;
-    ctx->graph_key = 0;
-  }
   if (ctx->ws) (void)hipFree(ctx->ws);
   ctx->ws = nullptr;
   ctx->ws_size = 0;
@@ -220,7 +211,6 @@ inline int reserve(morse_ctx* ctx, size_t bytes) {
     return fail(ctx, MORSE_ENOMEM, "workspace allocation of %zu bytes failed", want);
   }
   ctx->ws_size = want;
-  ctx->ws_epoch++;
   return MORSE_OK;
 }
 
@@ -269,6 +259,43 @@ inline int upload(morse_ctx* ctx, void* dst, const void* src, size_t bytes) {
   HIP_TRY(ctx, hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, ctx->stream));
   return MORSE_OK;
 }
+
+// Whether work on the context's stream is being captured.
+inline bool capturing(morse_ctx* ctx) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &c) != hipSuccess) (void)hipGetLastError();
+  return c != hipStreamCaptureStatusNone;
+}
+
+// Puts src (which may go when this returns) at dst unless it is there: `key` is the key of what
+// dst holds, `want` that of src.  A captured call takes it along, and a replay then replaces
+// what is there without a word: from the first capture on, every call puts its own.
+inline int put_meta(morse_ctx* ctx, void* dst, uint64_t& key, uint64_t want, const std::vector<char>& src) {
+  const bool cap = capturing(ctx);
+  if (cap) ctx->captured = true;
+  if (key == want && !ctx->captured) return MORSE_OK;
+  key = 0;
+  if (cap || src.size() <= kPutMax) {
+    HIP_TRY(ctx, launch_put(dst, src.data(), src.size(), ctx->stream));
+  } else {
+    const int rc = upload(ctx, dst, src.data(), src.size());
+    if (rc) return rc;
+    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+  }
+  key = want;
+  return MORSE_OK;
+}
+
+// Host metadata laid out in one block; sizes are rounded up to a multiple of `unit` bytes.
+struct MetaBlock {
+  std::vector<char> bytes;
+  size_t add(const void* p, size_t n, size_t unit = 16) {
+    const size_t at = bytes.size();
+    bytes.resize(at + (n + unit - 1) / unit * unit);
+    if (n) std::memcpy(bytes.data() + at, p, n);
+    return at;
+  }
+};
 
 inline bool grid_ok(const morse_grid2d* g) {
   return g && std::isfinite(g->cx) && std::isfinite(g->cy) && std::isfinite(g->wx) &&

@@ -405,9 +405,6 @@ hipError_t launch_scan_u32(uint32_t* v, int64_t nb, hipStream_t st);
 // equal keys is unspecified).  hist: nbins counters of workspace.
 hipError_t launch_bucket_order(const uint32_t* key, int64_t n, int32_t nbins, uint32_t* hist,
                                int32_t* order, hipStream_t st);
-// Packs every map of the device table `maps` (n_maps entries; h_maps the same table on
-// the host, for the sizes) into its quad layout.
-hipError_t launch_quad_pack(const MapC* maps, const MapC* h_maps, int32_t n_maps, hipStream_t st);
 // Shoots the rows of p into counts.  With `stats` (three totals that the call adds to),
 // `slots` is workspace of 4 kStatSlots words: the workgroups add to one slot each, so that
 // no address takes more than a few hundred atomics (the three totals themselves took
@@ -422,13 +419,33 @@ hipError_t launch_normalize_convolve(const uint32_t* counts, float* map, int32_t
                                      const float* d_w, const int32_t* d_off, int32_t ntaps,
                                      int32_t rx, int32_t ry, float scale, uint32_t* d_maxc,
                                      hipStream_t st);
-// sorted (nullable): [n_events], whether the event's times do not decrease.
-hipError_t launch_lc_prep(const float* t, const double* F, const double* w, const int64_t* off,
-                          int32_t n_events, double* wF, double* sums, uint32_t* sorted,
-                          hipStream_t st);
-hipError_t launch_traj_prep_list(const double* params, int64_t n, TrajC* out, hipStream_t st);
-hipError_t launch_traj_prep_grid(const double* axes, int32_t nu, int32_t na, int32_t nt,
-                                 int32_t ne, TrajC* out, hipStream_t st);
+// The preparation of a search or of an evaluation of candidates, one launch: light curves
+// (lc.wFc, lc.sums and, unless nullptr, lc.sorted: whether the event's times do not decrease),
+// trajectory constants tc[n] from a grid's axes or from rows of params, with their sorting
+// key (see launch_traj_perm) unless nullptr, zeroed words, packed maps (h_maps: the device
+// table's entries, for the sizes).
+struct PrepArgs {
+  LcView lc;
+  int32_t n_events;
+  int64_t n, n_traj;         // trajectories in all (0: none) and in a list
+  const double* axes;        // [u0 (nu) | alpha (na) | t0 (nt) | tE (ne)], or nullptr
+  int32_t nu, na, nt, ne;
+  const double* params;
+  TrajC* tc;
+  uint32_t* key;
+  uint32_t* zero;
+  uint64_t n_zero;
+  const MapC* maps;
+  int32_t n_maps;
+  uint32_t event_blocks, traj_blocks, zero_blocks, pack_blocks;  // set by the launcher
+};
+hipError_t launch_prep(PrepArgs a, const MapC* h_maps, hipStream_t st);
+// Copies host memory (a multiple of 4 bytes) to dst by value: when it returns, src may go, and
+// the launches can be captured.  A copy from pageable memory and the wait for it take 60 us
+// or more of the host, one of these launches 4; beyond kPutMax bytes the copy is as quick.
+constexpr int kPutWords = 896;
+constexpr size_t kPutMax = 4 * 4 * kPutWords;
+hipError_t launch_put(void* dst, const void* src, size_t bytes, hipStream_t st);
 
 struct SearchOut {
   double* chi2;
@@ -458,7 +475,7 @@ struct BatchedArgs {
   int32_t centred;          // every map's window is centred on (0, 0)
   const int32_t* perm;      // trajectory lists: [lists][n_traj] scoring order, or nullptr
 };
-// Scoring order of trajectory lists (n_lists lists of n_traj, their constants in tc):
+// Scoring order of trajectory lists (n_lists lists of n_traj) from their keys:
 // each list grouped by direction and speed, kPermDirs buckets of alpha by kPermSpeeds
 // quarter octaves of tE, so that waves scoring at the same time follow nearby lines through
 // the map and cross it at the same points of the light curve (a counting sort; the order within
@@ -469,8 +486,8 @@ struct BatchedArgs {
 constexpr int kPermDirs = 16, kPermSpeeds = 16;
 constexpr int kPermBins = kPermDirs * kPermSpeeds;
 constexpr int64_t kPermBinsMax = 1 << 22;
-hipError_t launch_traj_perm(const TrajC* tc, int64_t n_traj, int32_t n_lists, uint32_t* key,
-                            uint32_t* hist, int32_t* perm, hipStream_t st);
+hipError_t launch_traj_perm(const uint32_t* key, int64_t n_traj, int32_t n_lists, uint32_t* hist,
+                            int32_t* perm, hipStream_t st);
 // Items per (map, event) of the batched search.
 __host__ __device__ inline uint32_t search_blocks(uint32_t n_traj, int32_t traj_per_item, int32_t tu) {
   const uint32_t ng = (n_traj + tu - 1) / tu;

@@ -55,30 +55,6 @@ __global__ void k_fill_u64(uint64_t* p, size_t n, uint64_t v) {
     p[i] = v;
 }
 
-// Quad packing of one map per blockIdx.y (layout in MapC); cells beyond the map
-// (tile padding) are zero and never sampled.
-__global__ void k_quad_pack(const MapC* __restrict__ maps) {
-  const MapC m = maps[blockIdx.y];
-  const uint64_t nq = (uint64_t)m.tiles_x * m.tiles_y * 8;
-  Quad* out = const_cast<Quad*>(m.quad);
-  for (uint64_t q = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; q < nq;
-       q += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t tile = q >> 3;
-    const uint32_t r = (uint32_t)(q & 7);
-    const uint64_t i = (tile % m.tiles_x) * 4 + (r >> 1);
-    const uint64_t j = (tile / m.tiles_x) * 2 + (r & 1u);
-    Quad v = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (i + 1 < (uint64_t)m.mx && j + 1 < (uint64_t)m.my) {
-      const float* row = m.map + j * (uint64_t)m.mx + i;
-      v.v00 = row[0];
-      v.e0 = row[1] - row[0];
-      v.v01 = row[m.mx];
-      v.e1 = row[m.mx + 1] - row[m.mx];
-    }
-    out[q] = v;
-  }
-}
-
 // m / r, correctly rounded, for m = 0 or m in [2^-40, 1] and r in [2^-40, 2^40]: the steps
 // of the general IEEE sequence with its range scaling and special-case fix-up left out,
 // which in this range change nothing (8 instructions for 11).
@@ -621,18 +597,6 @@ hipError_t launch_fill_u64(uint64_t* p, size_t n, uint64_t v, hipStream_t st) {
   hipLaunchKernelGGL(k_fill_u64, dim3((unsigned)blocks), dim3(256), 0, st, p, n, v);
   return hipGetLastError();
 }
-
-hipError_t launch_quad_pack(const MapC* maps, const MapC* h_maps, int32_t n_maps, hipStream_t st) {
-  if (n_maps <= 0) return hipSuccess;
-  uint64_t most = 0;
-  for (int32_t k = 0; k < n_maps; ++k)
-    most = std::max<uint64_t>(most, (uint64_t)h_maps[k].tiles_x * h_maps[k].tiles_y * 8);
-  uint64_t blocks = (most + 255) / 256;
-  if (blocks > 65536) blocks = 65536;  // grid-stride beyond
-  hipLaunchKernelGGL(k_quad_pack, dim3((unsigned)blocks, (unsigned)n_maps), dim3(256), 0, st, maps);
-  return hipGetLastError();
-}
-
 
 namespace {
 

@@ -24,6 +24,7 @@
 #include "internal.h"
 
 #include <algorithm>
+#include <cstring>
 
 namespace morse {
 
@@ -57,20 +58,37 @@ __device__ __forceinline__ void tree_totals(double (*s_part)[4], double (&tot)[N
   __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void k_lc_prep(const float* __restrict__ t,
-                                                 const double* __restrict__ F,
-                                                 const double* __restrict__ w,
-                                                 const int64_t* __restrict__ off,
-                                                 double* __restrict__ wFc, double* __restrict__ sums,
-                                                 uint32_t* __restrict__ sorted) {
-  __shared__ double s_part[256][4];
-  const int e = blockIdx.x;
-  const int64_t a = off[e], b = off[e + 1];
+// Light curve e (one workgroup of 256; see above).  Up to kLcKeep points a lane stay in
+// registers from the first pass to the second.
+constexpr int kLcKeep = 16;
+__device__ void lc_prep(const LcView& lc, double* wFc, double* sums, uint32_t* sorted, int32_t e,
+                        double (*s_part)[4]) {
+  const int64_t a = lc.off[e], b = lc.off[e + 1];
+  const bool keep = b - a <= kLcKeep * 256;  // uniform
+  double kw[kLcKeep], kF[kLcKeep];
   double s0 = 0, c0 = 0, s1 = 0, c1 = 0;
-  for (int64_t i = a + threadIdx.x; i < b; i += blockDim.x) {
-    const double wi = w[i];
-    neumaier_add(s0, c0, wi);
-    neumaier_add(s1, c1, wi * F[i]);
+  if (keep) {
+#pragma unroll
+    for (int q = 0; q < kLcKeep; ++q) {
+      const int64_t i = a + threadIdx.x + 256 * q;
+      kw[q] = kF[q] = 0.0;
+      if (i < b) {
+        kw[q] = lc.w[i];
+        kF[q] = lc.F[i];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kLcKeep; ++q)
+      if (a + threadIdx.x + 256 * q < b) {
+        neumaier_add(s0, c0, kw[q]);
+        neumaier_add(s1, c1, kw[q] * kF[q]);
+      }
+  } else {
+    for (int64_t i = a + threadIdx.x; i < b; i += 256) {
+      const double wi = lc.w[i];
+      neumaier_add(s0, c0, wi);
+      neumaier_add(s1, c1, wi * lc.F[i]);
+    }
   }
   s_part[threadIdx.x][0] = s0;
   s_part[threadIdx.x][1] = c0;
@@ -82,11 +100,20 @@ __global__ __launch_bounds__(256) void k_lc_prep(const float* __restrict__ t,
   const double Sw = t01[0];
   const double Fbar = t01[1] / Sw;
   double s2 = 0, c2 = 0;
-  for (int64_t i = a + threadIdx.x; i < b; i += blockDim.x) {
-    const double d = F[i] - Fbar;
-    const double wd = w[i] * d;
+  auto second = [&](int64_t i, double wi, double Fi) {
+    const double d = Fi - Fbar;
+    const double wd = wi * d;
     wFc[i] = wd;
     neumaier_add(s2, c2, wd * d);
+  };
+  if (keep) {
+#pragma unroll
+    for (int q = 0; q < kLcKeep; ++q) {
+      const int64_t i = a + threadIdx.x + 256 * q;
+      if (i < b) second(i, kw[q], kF[q]);
+    }
+  } else {
+    for (int64_t i = a + threadIdx.x; i < b; i += 256) second(i, lc.w[i], lc.F[i]);
   }
   s_part[threadIdx.x][0] = s2;
   s_part[threadIdx.x][1] = c2;
@@ -100,7 +127,7 @@ __global__ __launch_bounds__(256) void k_lc_prep(const float* __restrict__ t,
   }
   if (sorted) {  // false with a NaN time: no order holds
     int ok = 1;
-    for (int64_t i = a + threadIdx.x; i + 1 < b; i += blockDim.x) ok &= t[i] <= t[i + 1] ? 1 : 0;
+    for (int64_t i = a + threadIdx.x; i + 1 < b; i += 256) ok &= lc.t[i] <= lc.t[i + 1] ? 1 : 0;
     ok = __syncthreads_and(ok);
     if (threadIdx.x == 0) sorted[e] = (uint32_t)ok;
   }
@@ -121,29 +148,89 @@ __device__ __forceinline__ TrajC make_traj(double t0, double u0, double tE, doub
   return r;
 }
 
-__global__ void k_traj_prep_list(const double* __restrict__ params, int64_t n, TrajC* __restrict__ out) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const double* p = params + 4 * i;
-    out[i] = make_traj(p[0], p[1], p[2], p[3]);
+// Scoring order of trajectory lists: each trajectory's (list, alpha, tE bucket) key, then
+// the shared bucket sort (its order holds indices over all lists).  Neighbours then follow
+// nearby lines at nearby speeds, so the chunks that lie on the map for one mostly do for
+// all.  24 events x 8 maps x 16384 trajectories: 8.69 ms, 8.78 ms in 256 directions alone.
+__device__ __forceinline__ uint32_t perm_key(const TrajC& c, int64_t i, int64_t n_traj) {
+  const float a = atan2f(c.sa, c.ca);  // (-pi, pi]
+  const float q = 4.0f * __log2f(c.iE);
+  int b = 0, s = 0;
+  if (!isnan(a)) b = min(max((int)((a + 3.14159265f) * (kPermDirs / 6.28318531f)), 0), kPermDirs - 1);
+  if (fabsf(q) < 1e6f) s = (int)floorf(q) & (kPermSpeeds - 1);
+  return (uint32_t)((i / n_traj) * kPermBins + (b * kPermSpeeds + s));
+}
+
+// Quad packing (layout in MapC) of cells q, q + stride, ...; cells beyond the map (tile
+// padding) are zero and never sampled.
+__device__ __forceinline__ void pack_quads(const MapC& m, uint32_t first, uint32_t stride) {
+  Quad* out = const_cast<Quad*>(m.quad);
+  for (uint64_t at = first; at < m.cells; at += stride) {
+    const uint32_t q = (uint32_t)at;
+    const uint32_t tile = q >> 3, r = q & 7u, tj = tile / m.tiles_x;
+    const uint32_t i = (tile - tj * m.tiles_x) * 4 + (r >> 1), j = tj * 2 + (r & 1u);
+    Quad v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (i + 1 < (uint32_t)m.mx && j + 1 < (uint32_t)m.my) {
+      const float* row = m.map + (size_t)j * m.mx + i;
+      v.v00 = row[0];
+      v.e0 = row[1] - row[0];
+      v.v01 = row[m.mx];
+      v.e1 = row[m.mx + 1] - row[m.mx];
+    }
+    out[q] = v;
   }
 }
 
-// axes = [u0 (nu) | alpha (na) | t0 (nt) | tE (ne)]; index ((iu*na + ia)*nt + it)*ne + ie
-__global__ void k_traj_prep_grid(const double* __restrict__ axes, int32_t nu, int32_t na, int32_t nt,
-                                 int32_t ne, TrajC* __restrict__ out) {
-  const int64_t n = (int64_t)nu * na * nt * ne;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    int64_t r = i;
-    const int ie = (int)(r % ne);
-    r /= ne;
-    const int it = (int)(r % nt);
-    r /= nt;
-    const int ia = (int)(r % na);
-    const int iu = (int)(r / na);
-    out[i] = make_traj(axes[nu + na + it], axes[iu], axes[nu + na + nt + ie], axes[nu + ia]);
+// All the preparation of a call in one launch, its parts side by side: a workgroup per light
+// curve (the longest chain, first), then the trajectory constants, the cleared counters and
+// the packing.  One after another they were four launches of 4 to 12 us each.
+__global__ __launch_bounds__(256) void k_prep(PrepArgs a) {
+  __shared__ double s_part[256][4];
+  uint32_t block = blockIdx.x;
+  if (block < a.event_blocks) {
+    for (int32_t e = (int32_t)block; e < a.n_events; e += (int32_t)a.event_blocks)
+      lc_prep(a.lc, const_cast<double*>(a.lc.wFc), const_cast<double*>(a.lc.sums),
+              const_cast<uint32_t*>(a.lc.sorted), e, s_part);
+    return;
   }
+  block -= a.event_blocks;
+  if (block < a.traj_blocks) {
+    for (int64_t i = block * (int64_t)256 + threadIdx.x; i < a.n; i += (int64_t)a.traj_blocks * 256) {
+      TrajC c;
+      if (a.axes) {  // [u0 | alpha | t0 | tE]; index ((iu*na + ia)*nt + it)*ne + ie
+        int64_t r = i;
+        const int ie = (int)(r % a.ne);
+        r /= a.ne;
+        const int it = (int)(r % a.nt);
+        r /= a.nt;
+        const int ia = (int)(r % a.na), iu = (int)(r / a.na);
+        c = make_traj(a.axes[a.nu + a.na + it], a.axes[iu], a.axes[a.nu + a.na + a.nt + ie], a.axes[a.nu + ia]);
+      } else {
+        const double* p = a.params + 4 * i;
+        c = make_traj(p[0], p[1], p[2], p[3]);
+      }
+      a.tc[i] = c;
+      if (a.key) a.key[i] = perm_key(c, i, a.n_traj);
+    }
+    return;
+  }
+  block -= a.traj_blocks;
+  if (block < a.zero_blocks) {
+    for (uint64_t i = block * (uint64_t)256 + threadIdx.x; i < a.n_zero; i += a.zero_blocks * (uint64_t)256)
+      a.zero[i] = 0u;
+    return;
+  }
+  block -= a.zero_blocks;
+  pack_quads(uniform(a.maps[block / a.pack_blocks]), (block % a.pack_blocks) * 256u + threadIdx.x,
+             a.pack_blocks * 256u);
+}
+
+// Host metadata by value: kPutWords words of kernel arguments a launch.
+struct PutWords {
+  uint32_t w[kPutWords];
+};
+__global__ __launch_bounds__(256) void k_put(uint32_t* dst, uint32_t n, PutWords v) {
+  for (uint32_t i = threadIdx.x; i < n; i += 256) dst[i] = v.w[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -975,65 +1062,39 @@ hipError_t launch_candidates(const double* axes, int32_t nu, int32_t na, int32_t
   return hipGetLastError();
 }
 
-hipError_t launch_lc_prep(const float* t, const double* F, const double* w, const int64_t* off,
-                          int32_t n_events, double* wFc, double* sums, uint32_t* sorted,
-                          hipStream_t st) {
-  if (n_events <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_lc_prep, dim3(n_events), dim3(256), 0, st, t, F, w, off, wFc, sums, sorted);
+hipError_t launch_prep(PrepArgs a, const MapC* h_maps, hipStream_t st) {
+  uint32_t most = 0;
+  for (int32_t k = 0; k < a.n_maps; ++k) most = std::max(most, h_maps[k].cells);
+  // a launch has fewer than 2^32 lanes; the parts stride over more than that
+  auto blocks = [](uint64_t n, int64_t cap) { return (uint32_t)std::min<uint64_t>((n + 255) / 256, (uint64_t)cap); };
+  a.event_blocks = (uint32_t)std::min(a.n_events, 1 << 20);
+  a.traj_blocks = blocks((uint64_t)a.n, 65536);
+  a.zero_blocks = blocks(a.n_zero, 4096);
+  a.pack_blocks = std::max(1u, blocks(most, std::min<int64_t>(65536, (int64_t(1) << 23) / std::max(a.n_maps, 1))));
+  const uint64_t all = (uint64_t)a.event_blocks + a.traj_blocks + a.zero_blocks + (uint64_t)a.pack_blocks * a.n_maps;
+  if (all == 0) return hipSuccess;
+  if (all >= 1u << 24) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_prep, dim3((unsigned)all), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
-hipError_t launch_traj_prep_list(const double* params, int64_t n, TrajC* out, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  int64_t blocks = (n + 255) / 256;
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(k_traj_prep_list, dim3((unsigned)blocks), dim3(256), 0, st, params, n, out);
+hipError_t launch_put(void* dst, const void* src, size_t bytes, hipStream_t st) {
+  if (bytes % 4) return hipErrorInvalidValue;
+  for (size_t at = 0; at < bytes; at += sizeof(PutWords)) {
+    PutWords v;
+    const size_t n = std::min(bytes - at, sizeof(PutWords));
+    std::memcpy(&v, (const char*)src + at, n);
+    hipLaunchKernelGGL(k_put, dim3(1), dim3(256), 0, st, (uint32_t*)((char*)dst + at), (uint32_t)(n / 4), v);
+  }
   return hipGetLastError();
 }
 
-namespace {
-
-// Scoring order of trajectory lists: each trajectory's (list, alpha, tE bucket) key, then
-// the shared bucket sort (its order holds indices over all lists).  Neighbours then follow
-// nearby lines at nearby speeds, so the chunks that lie on the map for one mostly do for
-// all.  24 events x 8 maps x 16384 trajectories: 8.69 ms, 8.78 ms in 256 directions alone.
-__device__ __forceinline__ uint32_t perm_key(const TrajC* tc, int64_t i, int64_t n_traj) {
-  const float a = atan2f(tc[i].sa, tc[i].ca);  // (-pi, pi]
-  const float q = 4.0f * __log2f(tc[i].iE);
-  int b = 0, s = 0;
-  if (!isnan(a)) b = min(max((int)((a + 3.14159265f) * (kPermDirs / 6.28318531f)), 0), kPermDirs - 1);
-  if (fabsf(q) < 1e6f) s = (int)floorf(q) & (kPermSpeeds - 1);
-  return (uint32_t)((i / n_traj) * kPermBins + (b * kPermSpeeds + s));
-}
-
-__global__ void k_perm_keys(const TrajC* __restrict__ tc, int64_t n, int64_t n_traj, uint32_t* key) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    key[i] = perm_key(tc, i, n_traj);
-}
-
-}  // namespace
-
-hipError_t launch_traj_perm(const TrajC* tc, int64_t n_traj, int32_t n_lists, uint32_t* key,
-                            uint32_t* hist, int32_t* perm, hipStream_t st) {
+hipError_t launch_traj_perm(const uint32_t* key, int64_t n_traj, int32_t n_lists, uint32_t* hist,
+                            int32_t* perm, hipStream_t st) {
   const int64_t n = n_traj * n_lists, nb = (int64_t)n_lists * kPermBins;
   if (n <= 0) return hipSuccess;
   if (n > INT32_MAX || nb > kPermBinsMax) return hipErrorInvalidValue;
-  int64_t blocks = (n + 255) / 256;
-  if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL(k_perm_keys, dim3((unsigned)blocks), dim3(256), 0, st, tc, n, n_traj, key);
   return launch_bucket_order(key, n, (int32_t)nb, hist, perm, st);
-}
-
-hipError_t launch_traj_prep_grid(const double* axes, int32_t nu, int32_t na, int32_t nt,
-                                 int32_t ne, TrajC* out, hipStream_t st) {
-  const int64_t n = (int64_t)nu * na * nt * ne;
-  if (n <= 0) return hipSuccess;
-  int64_t blocks = (n + 255) / 256;
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(k_traj_prep_grid, dim3((unsigned)blocks), dim3(256), 0, st, axes, nu, na, nt,
-                     ne, out);
-  return hipGetLastError();
 }
 
 hipError_t launch_search_plain(const TrajC* tc, int64_t n_traj, LcView lc, int32_t event,

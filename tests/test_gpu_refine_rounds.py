@@ -20,7 +20,8 @@ def bits(*xs):
 
 
 @pytest.mark.parametrize("n,steps,history", [(1, 7, 8), (33, 0, 8), (33, 30, 1), (40, 60, 3), (64, 40, 16),
-                                             (2048, 12, 8), (2049, 12, 8), (2600, 20, 5)])
+                                             (2048, 12, 8), (2049, 12, 8), (2600, 20, 5), (32767, 6, 8),
+                                             (32769, 6, 8), (32770, 9, 2), (32771, 0, 8)])
 def test_one_launch_equals_round_by_round(n, steps, history):
     rng = np.random.default_rng(n + steps)
     maps = [(torch.from_numpy((1 + 3 * rng.random((90, 96))).astype(np.float32)).to(DEV), (0.0, 0.0, 1.6, 1.5, 96, 90))
@@ -75,3 +76,29 @@ def test_short_histories_follow_the_oracle(tiny_oracle_map, history):
     assert rel_err(chi2_0.cpu().numpy(), o0).max() < 1e-10
     # the same machine but for binary32 roundings that an FP64 rounding of a sum flipped
     assert (rel_err(chi2.cpu().numpy(), oc) < 1e-6).mean() >= 0.9
+
+
+def test_many_candidates_on_large_maps_equal_few():
+    """Rounds as launches of their own (many candidates, maps beyond the last-level cache)
+    against the same candidates a few at a time."""
+    g = torch.Generator(device=DEV).manual_seed(3)
+    maps = [(1 + 3 * torch.rand((2048, 2048), generator=g, device=DEV), (0.0, 0.0, 1.6, 1.6, 2048, 2048)) for _ in range(5)]
+    rng = np.random.default_rng(8)
+    evs = []
+    for npts in (40, 300):
+        tt = np.sort(rng.uniform(-30, 30, npts)).astype(np.float32)
+        evs.append(dict(tt=tt, F=2 + rng.standard_normal(npts), w=rng.uniform(50, 150, npts), t_ref=0.0))
+    lcs = M.LightCurveBatch.from_events(evs, DEV)
+    n = 32801
+    P = np.stack([rng.normal(0, 3, n), rng.uniform(0, 0.6, n), rng.uniform(8, 40, n), rng.uniform(0, 6.28, n)], 1)
+    dP = torch.from_numpy(P).to(DEV)
+    ev, mi = rng.integers(0, 2, n).astype(np.int32), rng.integers(0, 5, n).astype(np.int32)
+    ev[7], mi[n - 1] = 2, 5  # out of range
+    de, dm = torch.from_numpy(ev).to(DEV), torch.from_numpy(mi).to(DEV)
+    note("refine many candidates on large maps")
+    got = M.refine(maps, lcs, dP, de, dm, steps=12, history=3)
+    for i0 in (0, 16000, n - 900):
+        sl = slice(i0, i0 + 900)
+        want = M.refine(maps, lcs, dP[sl].contiguous(), de[sl], dm[sl], steps=12, history=3)
+        for a, b in zip(bits(*got), bits(*want)):
+            assert torch.equal(a[sl], b)

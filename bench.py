@@ -5,7 +5,7 @@ One step = the whole path over the batched-events workload, the largest configur
   * the 64-map (s, q) bank built twice from rays: at 1024^2 from 16384^2 rays each (the
     search maps, point source) and at 2048^2 from 32768^2 rays each (the refinement
     maps): ray shooting, binning and normalisation, 8.6e10 rays;
-  * the batched (persistent, graph-replayed) chi-square search of 256 ragged events
+  * the batched (one scoring launch) chi-square search of 256 ragged events
     (200..20000 points, 903,548 in all) x 64 maps x 32768 trajectories per event,
     1.9e12 light-curve point-evaluations, with the top 4096 (chi2, map, trajectory) of
     every event;
@@ -14,8 +14,7 @@ One step = the whole path over the batched-events workload, the largest configur
 
 value = search point-evaluations per second of the whole step (map builds and the
 refinement charged to the same clock), steps one after another in the library's
-production schedule (graph-replayed search, two-stream refinement, no per-kernel
-timing).  A separate pass times each kernel family with HIP events around its launches
+production schedule (a refinement's rounds in one launch, no per-kernel timing).  A separate pass times each kernel family with HIP events around its launches
 for the roofline.  Also reported: rays/s, the plain (one launch per event and map)
 search of the same problem, the adjoint rate, the (s, q)-grid workload (384 maps) and
 the large single-map workload with the finite-source stack, the caustic-line filter and
@@ -84,7 +83,7 @@ KERNEL_SOURCES = {"k_rayshoot": ("maps.hip", "internal.h"),
                   "k_search_batched": ("search.hip", "internal.h"),
                   "k_chi2_grad": ("refine.hip", "internal.h")}
 CPU_WORKERS = 16          # the host-core share of one GPU
-TU1_SHAPE = 1             # the library's batched-search shape (8, 4, 16, TU = 1)
+TU1_SHAPE = 1             # the library's batched-search shape (8, 4, TU = 1)
 
 
 def kernel_sha(kernel):
@@ -449,7 +448,7 @@ def leg_batched(args, M, W, torch, np, dev):
         strictly = float((chi2 < chi2_0).float().mean())
 
         # kernel times: a separate pass with HIP events around every launch of each
-        # family (the refinement then runs as one chain of launches)
+        # family (the refinement then runs a round a launch: k_refine, evaluation and update)
         ks = max(1, args.kernel_steps)
         progress(f"batched: kernel timing pass x{ks}")
         fams = {"k_rayshoot": M.KERNEL_RAYSHOOT, "k_search_batched": M.KERNEL_SEARCH,
@@ -477,8 +476,8 @@ def leg_batched(args, M, W, torch, np, dev):
             same_topk = bool(torch.equal(pr["topk_idx"], sbuf["topk_idx"]) and
                              torch.equal(pr["topk_chi2"], sbuf["topk_chi2"]))
             # the batched kernel at a TU = 1 shape of its table, which separates the one
-            # persistent launch from scoring several trajectories per wavefront
-            progress("batched: persistent search at TU = 1")
+            # launch from scoring several trajectories per wavefront
+            progress("batched: search at TU = 1")
             with open(tune_path) as f:
                 classes = json.load(f)
             with open(tune_path + ".tu1", "w") as f:
@@ -520,12 +519,11 @@ def leg_batched(args, M, W, torch, np, dev):
             "plain": units["evals"] / (plain_ms * 1e-3) if plain_ms else None,
             "batched_tu1": units["evals"] / (tu1_ms * 1e-3) if tu1_ms else None,
             "batched_tu1_shape": (f"entry {TU1_SHAPE} of the library's shape table: 8 trajectories "
-                                  "per item, 4 waves per workgroup, 16 workgroups per CU, TU = 1; "
+                                  "per item, 4 waves per workgroup, TU = 1; "
                                   f"top-k equal to the tuned run: {same_tu1}"),
             "batched_shape": {"autotuned_index": tuned, "note": "trajectories per item, waves "
-                              "per workgroup, workgroups per CU and TU of the library's shape "
-                              "table entry; one persistent launch over (event, map, trajectory "
-                              "block) items, graph-replayed"},
+                              "per workgroup and TU of the library's shape table entry; one "
+                              "launch over (event, map, trajectory block) items"},
             "plain_shape": "one launch per (event, map): one wavefront per trajectory (TU = 1), "
                            "4 wavefronts per workgroup",
             "plain_topk_equal": same_topk if plain_ms else None},

@@ -68,13 +68,13 @@ const char* morse_last_error(const morse_ctx* ctx);
 /* Kernel timing (a measurement aid, off by default).  Families of timed kernels: */
 #define MORSE_KERNEL_RAYSHOOT 0 /* the ray-shooting kernel of morse_rayshoot / morse_build_map */
 #define MORSE_KERNEL_SEARCH 1   /* the scoring kernel(s) of morse_search (batched: one launch) */
-#define MORSE_KERNEL_GRADIENT 2 /* the chi-square/gradient kernel of morse_chi2_grad and of
-                                   every round of morse_refine */
+#define MORSE_KERNEL_GRADIENT 2 /* the chi-square/gradient kernel of morse_chi2_grad and the
+                                   refinement kernel of morse_refine */
 /* Enable timing for the families whose bit (1 << MORSE_KERNEL_*) is set in
  * kernel_mask (0 disables).  While a family is timed, each launch of its kernel is
- * bracketed by two HIP events recorded on the context's stream, and the entry points
- * that launch it enqueue their kernels one by one instead of replaying a captured
- * graph (same kernels, same results).  EINVAL for unknown bits. */
+ * bracketed by two HIP events recorded on the context's stream, and a refinement runs
+ * each round as a launch of its own instead of all in one (same kernel, same results).
+ * EINVAL for unknown bits. */
 int morse_ctx_set_timing(morse_ctx* ctx, uint32_t kernel_mask);
 /* Total event-measured time (ms) and number of timed launches of one family since the
  * last reset; waits for the pending events of every family.  reset != 0 zeroes the
@@ -238,13 +238,13 @@ typedef struct {
 enum { MORSE_SEARCH_PLAIN = 0, MORSE_SEARCH_BATCHED = 1 };
 
 /* search(map, lightcurve, traj_grid) over n_maps maps and all events.
- * PLAIN: one launch per (event, map).  BATCHED: one persistent launch over a work
- * queue of (event, map, trajectory block) items, captured once into a HIP graph
- * per argument set and replayed; tile shapes from the context's autotune table.  The
- * batched mode scores a trajectory list in an order grouped by direction (256 buckets
- * of alpha per list, a device counting sort each call; workspace 8 B per trajectory
- * and 1 KiB per list, lists of at most 16384 events), outputs staying in the list's
- * own order.  Both modes give bitwise identical results.  Errors: EINVAL (shapes, null
+ * PLAIN: one scoring launch per (event, map).  BATCHED: one scoring launch over all
+ * (event, map, trajectory block) items (more than 2^31 lanes of them take several);
+ * shapes from the context's autotune table, or by the number of items.  The
+ * batched mode scores a trajectory list in an order grouped by direction and speed (16
+ * buckets of alpha by 16 quarter octaves of tE per list, a device counting sort each
+ * call; workspace 8 B per trajectory and 1 KiB per list, lists of at most 16384 events),
+ * outputs staying in the list's own order.  Both modes give bitwise identical results.  Errors: EINVAL (shapes, null
  * pointers, w <= 0 is not checked on device), EUNSUPPORTED (top_k > 4096). */
 int morse_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
                  const morse_lightcurves* lcs, const morse_trajectories* trajs, int32_t mode,
@@ -310,7 +310,7 @@ int morse_caustic_lines(const double* h_caustics, int32_t n_caustics, const doub
  * sample (NaN if any is NaN), d_keep[n] (uint8) = d_best >= fl32(a_min).  Optional:
  * d_kept[n] (int64) receives the kept line indices in ascending order, d_count (device
  * int64) their number, h_count the same on the host (synchronises).  Workspace: the map
- * packed into cells (16 B per pixel).  Errors: EINVAL (bad window, NULL arrays, a_min
+ * in overlapping 128-byte tiles (about 6.1 B per pixel).  Errors: EINVAL (bad window, NULL arrays, a_min
  * not finite), ERANGE (map too large to pack, more than 1e7 samples per line). */
 int morse_line_filter(morse_ctx* ctx, const morse_map_view* map, const double* d_lines, int64_t n,
                       double a_min, float* d_best, uint8_t* d_keep, int64_t* d_kept,
@@ -452,10 +452,10 @@ int morse_trajectory_positions(morse_ctx* ctx, const double* h_params, const dou
  * -2 F_s sum w r dA/dtheta, r = F - F_s A - F_b, through the bilinear sample (or the
  * single-lens magnification off the map).  Samples as in morse_search; sums FP64.
  * Outputs (device, nullable): d_chi2 [n], d_grad [n][4], d_fs [n], d_fb [n].
- * Candidates are evaluated grouped by (map, event) (a device counting sort; by map
- * alone past 2^20 pairs), so that the GPU samples one map at a time; the order changes
- * the schedule only, never a result.  Workspace: 48 B per candidate + 4 B per
- * (map, event) pair. */
+ * More than 2048 candidates are evaluated grouped by event, the longest light curve
+ * first, and map (a device counting sort; by map first when the packed maps take more than
+ * 256 MiB or there are more than 1024 events; by map alone past 2^20 pairs); the order changes the schedule only, never a result.
+ * Workspace: 8 B per candidate + 4 B per (map, event) pair. */
 int morse_chi2_grad(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
                     const morse_lightcurves* lcs, int64_t n, const double* d_params,
                     const int32_t* d_event, const int32_t* d_map_index, double* d_chi2,
@@ -471,8 +471,7 @@ int morse_chi2_grad(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
  * 128 MiB on each GPU the library runs on, held until the process ends.  Every call on
  * a GPU shares that GPU's array and leaves its contents there, so calls that overlap on
  * one GPU (other streams or contexts) race; calls on one stream are ordered.  The host
- * metadata is copied into the array on every call (host-synchronous copies from the
- * caller's arrays).  Errors: as morse_chi2_grad, and ERANGE when the scratch would
+ * metadata goes into the array on every call, by value as kernel arguments.  Errors: as morse_chi2_grad, and ERANGE when the scratch would
  * exceed 128 MiB (e.g. more than one 2048^2 map with long light curves). */
 int morse_chi2_grad_noalloc(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
                             const morse_lightcurves* lcs, int64_t n, const double* d_params,
@@ -500,11 +499,11 @@ typedef struct {
  * Dot products are left-to-right FP64 without fused multiply-add.  d_params
  * [n][4] FP64 is read as the start and overwritten with the refined parameters;
  * d_chi2_out [n] receives the final chi2, d_chi2_init [n] (nullable) the initial.
- * Candidates are independent: with 1024 or more, the two halves run as two chains of
- * launches, one on the context's stream and one on a second stream of the context that
- * starts after the work already enqueued and that the context's stream waits for at
- * the end (results identical to one chain).  Each chain evaluates its candidates
- * grouped by (map, event), as morse_chi2_grad. */
+ * Candidates are independent: one launch runs all rounds (up to 1024 at a time), a
+ * workgroup per candidate (per four from 32768), in the order of morse_chi2_grad; from
+ * 32768 candidates on maps that take more than 256 MiB packed, the rounds are launches of
+ * their own.  Results are the same in every form.  Workspace: 8 B per candidate + 4 B per
+ * (map, event) pair, and 1.6 KB per candidate where the rounds take several launches. */
 int morse_refine(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
                  const morse_lightcurves* lcs, int64_t n, double* d_params,
                  const int32_t* d_event, const int32_t* d_map_index,

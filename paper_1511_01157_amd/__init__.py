@@ -407,8 +407,7 @@ def search(maps, lcs: LightCurveBatch, trajs, mode="plain", chi2=True, fs=False,
     maps: list of (map tensor, window).  Returns a dict with the requested outputs:
     chi2/fs/fb [n_events, n_maps, n_traj], best_chi2/best_idx [n_events, n_maps],
     topk_chi2/topk_idx [n_events, top_k] (index = map * n_traj + traj).  ``out`` (a
-    dict from an earlier call with the same arguments) is reused instead of allocating;
-    the batched mode replays its captured graph only when all buffers are the same.
+    dict from an earlier call with the same arguments) is reused instead of allocating.
     """
     dev = lcs.t.device
     ctx = ctx or Context.get(_device_of(lcs.t))
@@ -546,8 +545,7 @@ def chi2_grad(maps, lcs: LightCurveBatch, params, event, map_index, grad=True, c
 def refine(maps, lcs: LightCurveBatch, params, event, map_index, steps=50, history=8, max_ls=10,
            c1=1e-4, shrink=0.5, inplace=False, chi2_out=None, ctx=None):
     """Refined params, final chi2 and initial chi2.  With ``inplace`` the refined
-    parameters overwrite ``params``; ``chi2_out`` = (chi2, chi2_init) buffers to reuse
-    (the captured rounds replay only when every buffer is the same)."""
+    parameters overwrite ``params``; ``chi2_out`` = (chi2, chi2_init) buffers to reuse."""
     n = _cand_args(params, event, map_index)
     ctx = ctx or Context.get(_device_of(params))
     out = params if inplace else params.clone()

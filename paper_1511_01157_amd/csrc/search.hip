@@ -16,9 +16,8 @@
 // w (F - F_s A - F_b)^2 directly.
 //
 // Plain mode launches one grid per (event, map), one trajectory per wavefront.  Batched
-// mode launches one persistent grid whose wavefronts pull (map, event, trajectory
-// group) items from per-XCD work queues, so thousands of (event, map) pairs of uneven
-// length share one launch; the per-trajectory arithmetic and reduction order are the
+// mode launches one grid over the (map, event, trajectory group) items, dealt to the XCDs
+// in chunks, so thousands of (event, map) pairs of uneven length share one launch; the per-trajectory arithmetic and reduction order are the
 // same, so results are bitwise identical between the modes.
 
 #include "internal.h"

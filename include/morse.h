@@ -429,7 +429,8 @@ typedef struct {
  * 4096 of them (11 MiB).  The call synchronises the context's stream once (it reads
  * the number of sources near a caustic, which sizes the image-centred passes: at most
  * 4096 sources each), so it cannot be captured into a graph.  Errors: EINVAL (s, q, rho, gamma
- * outside their ranges, opts out of range, NULL arrays), ERANGE (n > 2^31). */
+ * outside their ranges, opts out of range, NULL arrays), ERANGE (n > 2^31), EUNSUPPORTED (the
+ * stream is being captured; the capture goes on without the call). */
 int morse_fs_magnification(morse_ctx* ctx, double s, double q, const double* d_zeta, int64_t n,
                            double rho, double gamma, const morse_fs_opts* opts, double* d_A,
                            int32_t* d_nreg);

@@ -30,6 +30,10 @@ int morse_fs_magnification(morse_ctx* ctx, double s, double q, const double* d_z
   if (!d_zeta || !d_A) return fail(ctx, MORSE_EINVAL, "d_zeta / d_A is NULL");
   if (n > (int64_t)1 << 31) return fail(ctx, MORSE_ERANGE, "more than 2^31 sources");
   HIP_TRY(ctx, hipSetDevice(ctx->device));
+  // Refused before anything is enqueued: a recorded launch does not write the critical points
+  // that the key below says are there, and the wait for the count fails and ends the capture.
+  if (capturing(ctx))
+    return fail(ctx, MORSE_EUNSUPPORTED, "finite-source magnification cannot be captured (it waits for a count)");
   const double m1 = 1.0 / (1.0 + q), m2 = q / (1.0 + q);
   const double x1 = -s * q / (1.0 + q), x2 = s / (1.0 + q);
   // critical points and their caustic images (Eq. 2), resident in the context until a call

@@ -72,7 +72,10 @@ __device__ __forceinline__ float div_in_range(float m, float r) {
 // displaces a ray by m_k / |z - x_k| at most, so with d_k the distance of lens k from the
 // rectangle zeta lies within D = sum m_k / d_k of z in x and in y.  The slack covers the
 // roundings of the binary32 ray (each of its few operations is off by 2^-24 of a number
-// no larger than |z| + D + |s|) and one pixel.
+// no larger than |z| + D + |s|) and one pixel.  Where a ray's offset in pixels might overflow
+// (`big` bounds it in Einstein radii) the tile is kept: such rays count as non-finite, not as
+// outside.  kSafe rays cannot.
+template <bool kSafe>
 __device__ __forceinline__ bool tile_misses(const RayParams& p, float xa, float xb, float ya, float yb) {
   const float dy = fmaxf(fmaxf(ya, -yb), 0.0f);
   const float e1 = fmaxf(fmaxf(xa - p.x1, p.x1 - xb), 0.0f), e2 = fmaxf(fmaxf(xa - p.x2, p.x2 - xb), 0.0f);
@@ -81,6 +84,7 @@ __device__ __forceinline__ bool tile_misses(const RayParams& p, float xa, float 
   const float D = p.m1 * __builtin_amdgcn_rsqf(e1 * e1 + dy * dy) + p.m2 * __builtin_amdgcn_rsqf(e2 * e2 + dy * dy);
   const float big = fmaxf(fmaxf(fabsf(xa), fabsf(xb)), fmaxf(fabsf(ya), fabsf(yb))) + D +
                     fmaxf(fabsf(p.sx), fabsf(p.sy));
+  if (!kSafe && !(big * fmaxf(p.kx, p.ky) < 0x1p126f)) return false;
   const float slack = D + 1e-4f * big;
   const float wx = ((float)(p.mx >> 1) + 1.0f) * (1.0001f * __builtin_amdgcn_rcpf(p.kx)) + slack;
   const float wy = ((float)(p.my >> 1) + 1.0f) * (1.0001f * __builtin_amdgcn_rcpf(p.ky)) + slack;
@@ -128,7 +132,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_rayshoot(RayParams p, uint32_t* 
   constexpr uint32_t kRays = kMirror ? 2u : 1u;  // rays each shot ray stands for
   // slot of the statistics this workgroup adds to (few workgroups per address)
   unsigned long long* st = stats ? stats + 4 * ((blockIdx.x + blockIdx.y * gridDim.x) % kStatSlots) : nullptr;
-  if (tile_misses(p, lattice(p.cx, x0, p.nx, p.hx), lattice(p.cx, x1, p.nx, p.hx),
+  if (tile_misses<kSafe>(p, lattice(p.cx, x0, p.nx, p.hx), lattice(p.cx, x1, p.nx, p.hx),
                   lattice(p.cy, y0, p.ny, p.hy), lattice(p.cy, y1, p.ny, p.hy))) {
     if (tid == 0 && st) atomicAdd(&st[0], (unsigned long long)(shot * kRays));
     return;

@@ -19,6 +19,11 @@
  *     validated on the host before anything is enqueued, and a failing call
  *     enqueues nothing.  morse_last_error() gives a message.  Nothing aborts.
  *   - Not thread safe per context: use one context per host thread.
+ *   - Graphs: a call that neither waits nor allocates may be captured into the caller's graph,
+ *     one of its size having been made before; a captured call that would have to allocate
+ *     returns EUNSUPPORTED and enqueues nothing.  The graph works in the context's buffers: it
+ *     may be replayed while the context lives, in order with the context's other calls.  Buffers
+ *     that a captured call used are kept until the context goes when later calls outgrow them.
  */
 #ifndef MORSE_H
 #define MORSE_H

@@ -60,14 +60,11 @@ int morse_ctx_destroy(morse_ctx* ctx) {
   if (!ctx) return MORSE_OK;
   (void)hipSetDevice(ctx->device);
   (void)hipStreamSynchronize(ctx->stream);
-  if (ctx->ws) (void)hipFree(ctx->ws);
-  if (ctx->aux) (void)hipFree(ctx->aux);
-  if (ctx->taps) (void)hipFree(ctx->taps);
+  for (Buffer* b : std::initializer_list<Buffer*>{&ctx->ws, &ctx->aux, &ctx->taps, &ctx->smeta, &ctx->cmeta,
+                                                  &ctx->stack_taps, &ctx->fft_tw, &ctx->fft_spec, &ctx->fs_crit})
+    if (b->p) (void)hipFree(b->p);
+  for (char* p : ctx->retired) (void)hipFree(p);
   if (ctx->stat_slots) (void)hipFree(ctx->stat_slots);
-  if (ctx->smeta.p) (void)hipFree(ctx->smeta.p);
-  if (ctx->cmeta.p) (void)hipFree(ctx->cmeta.p);
-  for (MetaBuf* mb : {&ctx->stack_taps, &ctx->fft_tw, &ctx->fft_spec, &ctx->fs_crit})
-    if (mb->p) (void)hipFree(mb->p);
   for (const auto& t : ctx->timed) {
     (void)hipEventDestroy(t.a);
     (void)hipEventDestroy(t.b);

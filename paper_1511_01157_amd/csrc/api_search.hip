@@ -453,7 +453,7 @@ int morse_candidates_from_topk(morse_ctx* ctx, const morse_trajectories* trajs, 
     mb.add(trajs->h_tE, 8 * (size_t)trajs->n_tE, 8);
     // the auxiliary buffer keeps the search's resident workspace intact
     if ((rc = reserve_aux(ctx, mb.bytes.size()))) return rc;
-    double* d = (double*)ctx->aux;
+    double* d = (double*)ctx->aux.p;
     uint64_t none = 0;
     if ((rc = put_meta(ctx, d, none, 1, mb.bytes))) return rc;
     axes = d;

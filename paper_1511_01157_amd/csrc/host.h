@@ -25,10 +25,15 @@
 #include "simplex.h"
 
 
-// A device buffer of host metadata with the key of what it holds.
-struct MetaBuf {
+// A device buffer that grows.
+struct Buffer {
   char* p = nullptr;
   size_t size = 0;
+  bool named = false;  // a captured call used it: the caller's graph holds its address
+};
+
+// A device buffer of host metadata with the key of what it holds.
+struct MetaBuf : Buffer {
   uint64_t key = 0;
 };
 
@@ -37,8 +42,9 @@ struct morse_ctx {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   int num_cu = 256;
-  char* ws = nullptr;
-  size_t ws_size = 0;
+  Buffer ws;
+  // outgrown buffers that graphs still name, freed with the context
+  std::vector<char*> retired;
   std::string err;
   // host metadata of the searches and of the candidate entry points, each in a device
   // buffer of its own (never in the shared workspace, which the other entry points
@@ -64,12 +70,9 @@ struct morse_ctx {
   // autotune choices per shape class
   std::map<std::string, int> tune;
   // small auxiliary device buffer, separate from the workspace
-  char* aux = nullptr;
-  size_t aux_size = 0;
+  Buffer aux;
   // disk-convolution taps resident on the device (key of the taps they hold)
-  char* taps = nullptr;
-  size_t taps_size = 0;
-  uint64_t taps_key = 0;
+  MetaBuf taps;
   int32_t taps_n = 0;
   int32_t taps_rx = 0, taps_ry = 0;  // the largest |offset| of the taps along x and y
   size_t taps_wbytes = 0;
@@ -190,7 +193,7 @@ struct Plan {
     for (size_t s : sizes) t += s;
     return t;
   }
-  char* ptr(morse_ctx* ctx, size_t id) const { return ptr_at(ctx->ws, id); }
+  char* ptr(morse_ctx* ctx, size_t id) const { return ptr_at(ctx->ws.p, id); }
   char* ptr_at(char* base, size_t id) const {
     size_t off = 0;
     for (size_t i = 0; i < id; ++i) off += sizes[i];
@@ -198,35 +201,47 @@ struct Plan {
   }
 };
 
-inline int reserve(morse_ctx* ctx, size_t bytes) {
-  if (bytes <= ctx->ws_size) return MORSE_OK;
-  HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-  if (ctx->ws) (void)hipFree(ctx->ws);
-  ctx->ws = nullptr;
-  ctx->ws_size = 0;
-  size_t want = std::max(bytes, size_t(1) << 20);
-  want = (want + (size_t(1) << 20) - 1) & ~((size_t(1) << 20) - 1);
-  if (hipMalloc((void**)&ctx->ws, want) != hipSuccess) {
-    ctx->ws = nullptr;
-    return fail(ctx, MORSE_ENOMEM, "workspace allocation of %zu bytes failed", want);
+// Whether work on the context's stream is being captured.
+inline bool capturing(morse_ctx* ctx) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &c) != hipSuccess) (void)hipGetLastError();
+  return c != hipStreamCaptureStatusNone;
+}
+
+// Room for `bytes` in a buffer of the context, which becomes `want` bytes long when it has to
+// grow (its contents are then lost).  A buffer that a captured call used may be written by that
+// call's graph for as long as the context lives: it is not freed before, and nothing is
+// allocated under a capture (the call is refused, with nothing enqueued).
+inline int grow(morse_ctx* ctx, Buffer& b, size_t bytes, size_t want, const char* what) {
+  const bool cap = capturing(ctx);
+  if (bytes > b.size) {
+    if (cap)
+      return fail(ctx, MORSE_EUNSUPPORTED, "%s of %zu bytes cannot be allocated under capture: make a call of this size before it",
+                  what, bytes);
+    if (b.p && b.named) {
+      ctx->retired.push_back(b.p);
+    } else if (b.p) {
+      HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+      (void)hipFree(b.p);
+    }
+    b = Buffer{};
+    if (hipMalloc((void**)&b.p, want) != hipSuccess) {
+      b.p = nullptr;
+      return fail(ctx, MORSE_ENOMEM, "%s allocation of %zu bytes failed", what, want);
+    }
+    b.size = want;
   }
-  ctx->ws_size = want;
+  b.named = b.named || cap;
   return MORSE_OK;
 }
 
+inline int reserve(morse_ctx* ctx, size_t bytes) {
+  const size_t mib = size_t(1) << 20;
+  return grow(ctx, ctx->ws, bytes, (std::max(bytes, mib) + mib - 1) & ~(mib - 1), "workspace");
+}
+
 inline int reserve_aux(morse_ctx* ctx, size_t bytes) {
-  if (bytes <= ctx->aux_size) return MORSE_OK;
-  HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-  if (ctx->aux) (void)hipFree(ctx->aux);
-  ctx->aux = nullptr;
-  ctx->aux_size = 0;
-  const size_t want = std::max(bytes, size_t(1) << 16);
-  if (hipMalloc((void**)&ctx->aux, want) != hipSuccess) {
-    ctx->aux = nullptr;
-    return fail(ctx, MORSE_ENOMEM, "auxiliary allocation of %zu bytes failed", want);
-  }
-  ctx->aux_size = want;
-  return MORSE_OK;
+  return grow(ctx, ctx->aux, bytes, std::max(bytes, size_t(1) << 16), "auxiliary");
 }
 
 // The largest |offset| along x and along y of a tap table (pairs dx, dy).
@@ -240,31 +255,16 @@ inline void tap_reach(const std::vector<int32_t>& off, int32_t& rx, int32_t& ry)
 
 // Grows a metadata buffer to at least `bytes` (its contents are then invalid).
 inline int reserve_meta(morse_ctx* ctx, MetaBuf& mb, size_t bytes) {
-  if (bytes <= mb.size) return MORSE_OK;
-  HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-  if (mb.p) (void)hipFree(mb.p);
-  mb.p = nullptr;
-  mb.size = 0;
-  mb.key = 0;
-  if (hipMalloc((void**)&mb.p, bytes) != hipSuccess) {
-    mb.p = nullptr;
-    return fail(ctx, MORSE_ENOMEM, "metadata allocation of %zu bytes failed", bytes);
-  }
-  mb.size = bytes;
-  return MORSE_OK;
+  const char* before = mb.p;
+  const int rc = grow(ctx, mb, bytes, bytes, "metadata");
+  if (mb.p != before) mb.key = 0;
+  return rc;
 }
 
 inline int upload(morse_ctx* ctx, void* dst, const void* src, size_t bytes) {
   if (!bytes) return MORSE_OK;
   HIP_TRY(ctx, hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, ctx->stream));
   return MORSE_OK;
-}
-
-// Whether work on the context's stream is being captured.
-inline bool capturing(morse_ctx* ctx) {
-  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(ctx->stream, &c) != hipSuccess) (void)hipGetLastError();
-  return c != hipStreamCaptureStatusNone;
 }
 
 // Puts src (which may go when this returns) at dst unless it is there: `key` is the key of what

@@ -36,3 +36,69 @@ def test_refused_finite_source_call_leaves_no_trace():
             g.replay()
             s.synchronize()
             assert torch.equal(x, torch.full_like(x, rep + 1.0))
+
+
+def chain(seed, npix, n_events, npts, n_u0):
+    """A map, a search of it, candidates from the top-k and their gradients, on one context."""
+    rng = np.random.default_rng(seed)
+    win = (0.0, 0.0, 2.0, 2.0, npix, npix)
+    evs = [dict(tt=np.sort(rng.uniform(-30, 30, npts)).astype(np.float32), F=2 + rng.standard_normal(npts),
+                w=rng.uniform(50, 150, npts), t_ref=0.1 * e) for e in range(n_events)]
+    lcs = M.LightCurveBatch.from_events(evs, DEV)
+    grid = M.grid_trajectories(np.linspace(0, 0.8, n_u0), [0.3, 2.0], [0.5], [15.0, 30.0])
+    out = torch.empty((npix, npix), dtype=torch.float32, device=DEV)
+
+    def calls(ctx):
+        M.build_map(1.0, 0.1, (0.0, 0.0, 4.0, 4.0, 4 * npix, 4 * npix), win, 3.0 * 2.0 / npix, out=out, ctx=ctx)
+        r = M.search([(out, win)], lcs, grid, "batched", best=True, top_k=9, ctx=ctx)
+        p, e, m = M.candidates_from_topk(grid, r["topk_idx"], 1, ctx=ctx)
+        return [out, r["chi2"], r["best_idx"], r["topk_idx"], p, *M.chi2_grad([(out, win)], lcs, p, e, m, ctx=ctx)]
+
+    return calls
+
+
+def test_graph_replays_after_the_context_has_grown():
+    s = torch.cuda.Stream(device=DEV)
+    small, large = chain(1, 64, 2, 80, 20), chain(2, 640, 300, 400, 9000)
+    note("graphs: replay after growth")
+    with torch.cuda.stream(s):
+        c = M.Context.bound(s)
+        want = [x.clone() for x in small(c)]
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            got = small(c)
+        wide = [x.clone() for x in large(c)]  # every buffer of the context grows
+        # what a freed buffer would be handed out as
+        other = [torch.full((n,), 7, dtype=torch.int32, device=DEV) for n in (1 << 8, 1 << 12, 1 << 14, 1 << 18, 1 << 19, 1 << 20) for _ in range(4)]
+        for rep in range(3):
+            for x in got:
+                x.zero_()
+            g.replay()
+            s.synchronize()
+            for a, b in zip(got, want):
+                assert torch.equal(a, b), rep
+            assert all(bool((x == 7).all()) for x in other)
+            for a, b in zip(large(c), wide):
+                assert torch.equal(a, b), rep
+
+
+def test_capture_that_would_allocate_is_refused():
+    s = torch.cuda.Stream(device=DEV)
+    small, large = chain(1, 64, 2, 80, 20), chain(2, 640, 300, 400, 9000)
+    x = torch.zeros(8, device=DEV)
+    note("graphs: refused growth")
+    with torch.cuda.stream(s):
+        c, fresh = M.Context.bound(s), M.Context.bound(s)
+        want = [t.clone() for t in large(fresh)]
+        small(c)
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            x += 1
+            with pytest.raises(M.MorseError, match="capture"):
+                large(c)
+        g.replay()
+        for a, b in zip(large(c), want):
+            assert torch.equal(a, b)
+        assert torch.equal(x, torch.ones_like(x))

@@ -23,7 +23,8 @@
  *     one of its size having been made before; a captured call that would have to allocate
  *     returns EUNSUPPORTED and enqueues nothing.  The graph works in the context's buffers: it
  *     may be replayed while the context lives, in order with the context's other calls.  Buffers
- *     that a captured call used are kept until the context goes when later calls outgrow them.
+ *     that a captured call used are kept until the context goes when later calls outgrow or
+ *     replace them.
  */
 #ifndef MORSE_H
 #define MORSE_H
@@ -154,8 +155,8 @@ int morse_build_map(morse_ctx* ctx, double s, double q, const morse_grid2d* rays
  *    sum, closer than the direct binary32 sum of a wide stencil.
  * fft_min_taps <= 0 takes MORSE_STACK_FFT_MIN_TAPS.  h_rho[n_rho] is host memory read
  * during the call.  The first call for a set of (radii, gamma, pixel size) computes
- * and keeps the profile transforms in the context (a synchronising call); later calls
- * enqueue kernels only.  Workspace: three transforms (16 B per padded pixel each) plus
+ * and keeps the profile transforms in the context (a synchronising call, refused under
+ * capture); later calls enqueue kernels only.  Workspace: three transforms (16 B per padded pixel each) plus
  * one kept transform per pair of FFT radii.
  * Errors: EINVAL (gamma outside [0, 1], a radius negative or not finite, NULL
  * pointers), ERANGE (an FFT side above 4096). */

@@ -341,7 +341,10 @@ int morse_convolve_stack(morse_ctx* ctx, const uint32_t* d_counts, const morse_g
   skey.pod(fft_min_taps);
   for (int k = 0; k < n_rho; ++k) skey.pod(h_rho[k]);
   auto& sp = ctx->stack_split;
+  const bool cap = capturing(ctx);
   if (sp.key != skey.h || !ctx->stack_taps.p) {
+    if (cap)
+      return fail(ctx, MORSE_EUNSUPPORTED, "tables cannot be made under capture: make the same call before it");
     sp.key = 0;
     sp.direct_k.clear();
     sp.fft_k.clear();
@@ -375,7 +378,7 @@ int morse_convolve_stack(morse_ctx* ctx, const uint32_t* d_counts, const morse_g
       }
     }
     const size_t w_bytes = (w32.size() * sizeof(float) + 255) & ~size_t(255);
-    if ((rc = reserve_meta(ctx, ctx->stack_taps, std::max<size_t>(256, w_bytes + off.size() * sizeof(int32_t)))))
+    if ((rc = renew_meta(ctx, ctx->stack_taps, std::max<size_t>(256, w_bytes + off.size() * sizeof(int32_t)))))
       return rc;
     if ((rc = upload(ctx, ctx->stack_taps.p, w32.data(), w32.size() * sizeof(float)))) return rc;
     if ((rc = upload(ctx, ctx->stack_taps.p + w_bytes, off.data(), off.size() * sizeof(int32_t)))) return rc;
@@ -395,7 +398,8 @@ int morse_convolve_stack(morse_ctx* ctx, const uint32_t* d_counts, const morse_g
   if (!fft_k.empty() && (nx64 > kFftMaxN || ny64 > kFftMaxN))
     return fail(ctx, MORSE_ERANGE, "FFT convolution needs %lld x %lld > %d per side (map plus twice the stencil radius)",
                 (long long)nx64, (long long)ny64, kFftMaxN);
-  {
+  auto direct = [&]() -> int {
+    ctx->stack_taps.named = ctx->stack_taps.named || cap;
     const float scale = (float)(hx * hy / (dx * dy));
     const size_t w_bytes = sp.w_bytes;
     size_t at = 0;
@@ -407,11 +411,12 @@ int morse_convolve_stack(morse_ctx* ctx, const uint32_t* d_counts, const morse_g
                                              scale, nullptr, ctx->stream));
       at += (size_t)sp.ntaps[u];
     }
-  }
-  if (fft_k.empty()) return MORSE_OK;
+    return MORSE_OK;
+  };
+  if (fft_k.empty()) return direct();
 
-  // FFT path: twiddles, profile-pair transforms (kept in the context), then one
-  // forward transform of the counts and one inverse transform per pair.
+  // FFT path: twiddles, profile-pair transforms (kept in the context), then (after the direct
+  // radii) one forward transform of the counts and one inverse transform per pair.
   FftGrid g;
   g.nx = (int32_t)nx64;
   g.ny = (int32_t)ny64;
@@ -421,8 +426,7 @@ int morse_convolve_stack(morse_ctx* ctx, const uint32_t* d_counts, const morse_g
     key.pod(g.ny);
     const size_t need = (size_t)(g.nx + g.ny) * sizeof(double2);
     if (ctx->fft_tw.key != key.h || ctx->fft_tw.size < need) {
-      if ((rc = reserve_meta(ctx, ctx->fft_tw, need))) return rc;
-      ctx->fft_tw.key = 0;
+      if ((rc = renew_meta(ctx, ctx->fft_tw, need))) return rc;
       std::vector<double2> t((size_t)g.nx + g.ny);
       for (int m = 0; m < g.nx; ++m) {
         const double th = 2.0 * M_PI * m / g.nx;
@@ -459,8 +463,7 @@ int morse_convolve_stack(morse_ctx* ctx, const uint32_t* d_counts, const morse_g
     // a quadrant of each pair's transform: the weights are even in x and in y
     const size_t need = (size_t)pairs * nq * sizeof(double2);
     if (ctx->fft_spec.key != key.h || ctx->fft_spec.size < need) {
-      if ((rc = reserve_meta(ctx, ctx->fft_spec, need))) return rc;
-      ctx->fft_spec.key = 0;
+      if ((rc = renew_meta(ctx, ctx->fft_spec, need))) return rc;
       for (int p = 0; p < pairs; ++p) {
         std::vector<double> q[2];
         int rx[2] = {0, 0}, ry[2] = {0, 0};
@@ -490,6 +493,8 @@ int morse_convolve_stack(morse_ctx* ctx, const uint32_t* d_counts, const morse_g
       ctx->fft_spec.key = key.h;
     }
   }
+  for (MetaBuf* mb : {&ctx->fft_tw, &ctx->fft_spec}) mb->named = mb->named || cap;
+  if ((rc = direct())) return rc;
   // counts: half spectrum [ny][nx/2 + 1] (the padded image is real)
   double2* X = nullptr;
   HIP_TRY(ctx, launch_fft_rows_counts(g, d_counts, mx, my, B[0], ctx->stream));

@@ -261,6 +261,19 @@ inline int reserve_meta(morse_ctx* ctx, MetaBuf& mb, size_t bytes) {
   return rc;
 }
 
+// Room for `bytes` of tables about to be made anew in a buffer that calls read without writing it:
+// a graph that names it goes on reading the old ones.
+inline int renew_meta(morse_ctx* ctx, MetaBuf& mb, size_t bytes) {
+  if (capturing(ctx))
+    return fail(ctx, MORSE_EUNSUPPORTED, "tables cannot be made under capture: make the same call before it");
+  if (mb.named) {
+    ctx->retired.push_back(mb.p);
+    mb = MetaBuf{};
+  }
+  mb.key = 0;
+  return reserve_meta(ctx, mb, bytes);
+}
+
 inline int upload(morse_ctx* ctx, void* dst, const void* src, size_t bytes) {
   if (!bytes) return MORSE_OK;
   HIP_TRY(ctx, hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, ctx->stream));

@@ -102,3 +102,35 @@ def test_capture_that_would_allocate_is_refused():
         for a, b in zip(large(c), want):
             assert torch.equal(a, b)
         assert torch.equal(x, torch.ones_like(x))
+
+
+# direct radii alone, FFT radii alone, both
+@pytest.mark.parametrize("rhos,others", [((0.02, 0.05), (0.06,)), ((0.2,), (0.3, 0.25)), ((0.05, 0.3, 0.4), (0.03, 0.35, 0.2))])
+def test_captured_stack_keeps_its_profiles(rhos, others):
+    """A captured stack replays with its own radii after eager calls with other ones, on the same
+    map and on a larger one."""
+    s = torch.cuda.Stream(device=DEV)
+    rng = np.random.default_rng(5)
+    counts = torch.from_numpy(rng.integers(0, 4000, (100, 128)).astype(np.int32)).to(DEV)
+    wide = torch.from_numpy(rng.integers(0, 4000, (300, 200)).astype(np.int32)).to(DEV)
+    rays, win, win2 = (0, 0, 4, 4, 512, 512), (0.0, 0.0, 2.0, 2.0, 128, 100), (0.0, 0.0, 2.0, 2.0, 200, 300)
+    out = torch.empty((len(rhos), 100, 128), dtype=torch.float32, device=DEV)
+    note(f"graphs: stack {rhos}")
+    with torch.cuda.stream(s):
+        c, fresh = M.Context.bound(s), M.Context.bound(s)
+        want = M.convolve_stack(counts, rays, win, rhos, out=out, ctx=c).clone()
+        want_other = M.convolve_stack(counts, rays, win, others, ctx=fresh).clone()
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            M.convolve_stack(counts, rays, win, rhos, out=out, ctx=c)
+            with pytest.raises(M.MorseError, match="capture"):
+                M.convolve_stack(counts, rays, win, others, ctx=c)
+        for rep in range(3):
+            assert torch.equal(M.convolve_stack(counts, rays, win, others, ctx=c), want_other)
+            M.convolve_stack(wide, rays, win2, others, ctx=c)
+            out.zero_()
+            g.replay()
+            s.synchronize()
+            assert torch.equal(out, want), rep
+            assert torch.equal(M.convolve_stack(counts, rays, win, rhos, ctx=c), want), rep

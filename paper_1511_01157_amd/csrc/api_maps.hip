@@ -182,29 +182,30 @@ void profile_quadrant(double rho, double dx, double dy, double gamma, int Rx, in
 }
 
 
-// The disk's taps on the device (ctx->taps).  They stay between calls with the same
-// (rho, dx, dy): no host work, upload or synchronisation in the steady state.
-int resident_taps(morse_ctx* ctx, double rho, double dx, double dy) {
+// The disk's taps on the device.  They stay between calls with the same (rho, dx, dy): no host
+// work, upload or synchronisation in the steady state.
+int resident_taps(morse_ctx* ctx, double rho, double dx, double dy, morse_ctx::DiskTaps& t) {
   int rc;
   Hasher key;
   key.pod(rho);
   key.pod(dx);
   key.pod(dy);
-  if (!ctx->taps.p || ctx->taps.key != key.h || ctx->captured || capturing(ctx)) {
-    std::vector<float> w;
-    std::vector<int32_t> off;
-    if ((rc = disk_taps(ctx, rho, dx, dy, w, off))) return rc;
-    const size_t w_bytes = (w.size() * sizeof(float) + 255) & ~size_t(255);
-    const size_t need = w_bytes + off.size() * sizeof(int32_t);
-    if ((rc = reserve_meta(ctx, ctx->taps, need))) return rc;
-    std::vector<char> both(need);
-    std::memcpy(both.data(), w.data(), w.size() * sizeof(float));
-    std::memcpy(both.data() + w_bytes, off.data(), off.size() * sizeof(int32_t));
-    if ((rc = put_meta(ctx, ctx->taps.p, ctx->taps.key, key.h, both))) return rc;
-    ctx->taps_n = (int32_t)w.size();
-    ctx->taps_wbytes = w_bytes;
-    tap_reach(off, ctx->taps_rx, ctx->taps_ry);
-  }
+  t = ctx->disk;
+  const bool cap = capturing(ctx);
+  if (!cap && ctx->taps.p && ctx->taps.key == key.h) return MORSE_OK;
+  std::vector<float> w;
+  std::vector<int32_t> off;
+  if ((rc = disk_taps(ctx, rho, dx, dy, w, off))) return rc;
+  t.n = (int32_t)w.size();
+  t.w_bytes = (w.size() * sizeof(float) + 255) & ~size_t(255);
+  tap_reach(off, t.rx, t.ry);
+  std::vector<char> both(t.w_bytes + off.size() * sizeof(int32_t));
+  std::memcpy(both.data(), w.data(), w.size() * sizeof(float));
+  std::memcpy(both.data() + t.w_bytes, off.data(), off.size() * sizeof(int32_t));
+  char* at;
+  if ((rc = put_meta(ctx, ctx->taps, both, key.h, &at))) return rc;
+  t.p = at;
+  if (!cap) ctx->disk = t;
   return MORSE_OK;
 }
 
@@ -268,12 +269,10 @@ int morse_normalize_convolve(morse_ctx* ctx, const uint32_t* d_counts, const mor
   const double dx = window->wx / window->nx, dy = window->wy / window->ny;
   const double hx = (double)(float)(rays->wx / rays->nx), hy = (double)(float)(rays->wy / rays->ny);
   const float scale = (float)(hx * hy / (dx * dy));
-  if ((rc = resident_taps(ctx, rho, dx, dy))) return rc;
-  const float* d_w = (const float*)ctx->taps.p;
-  const int32_t* d_off = (const int32_t*)(ctx->taps.p + ctx->taps_wbytes);
-  HIP_TRY(ctx, launch_normalize_convolve(d_counts, d_map, window->nx, window->ny, d_w, d_off,
-                                         ctx->taps_n, ctx->taps_rx, ctx->taps_ry, scale, nullptr,
-                                         ctx->stream));
+  morse_ctx::DiskTaps t;
+  if ((rc = resident_taps(ctx, rho, dx, dy, t))) return rc;
+  HIP_TRY(ctx, launch_normalize_convolve(d_counts, d_map, window->nx, window->ny, t.w(), t.off(), t.n, t.rx, t.ry,
+                                         scale, nullptr, ctx->stream));
   return MORSE_OK;
 }
 
@@ -532,7 +531,8 @@ int morse_build_map(morse_ctx* ctx, double s, double q, const morse_grid2d* rays
   Plan pl;
   const size_t ic = pl.add(d_counts ? 0 : npx * 4), is = pl.add(3 * 8 + 8);
   if ((rc = reserve(ctx, pl.total()))) return rc;
-  if ((rc = resident_taps(ctx, rho, dx, dy))) return rc;
+  morse_ctx::DiskTaps t;
+  if ((rc = resident_taps(ctx, rho, dx, dy, t))) return rc;
   uint32_t* counts = d_counts ? d_counts : (uint32_t*)pl.ptr(ctx, ic);
   uint64_t* stats = h_stats ? (uint64_t*)pl.ptr(ctx, is) : nullptr;
   uint32_t* maxc = h_stats ? (uint32_t*)(stats + 3) : nullptr;
@@ -540,9 +540,8 @@ int morse_build_map(morse_ctx* ctx, double s, double q, const morse_grid2d* rays
   if ((rc = morse_rayshoot(ctx, s, q, rays, window, 0, rays->ny, counts, 0, stats))) return rc;
   const double hx = (double)(float)(rays->wx / rays->nx), hy = (double)(float)(rays->wy / rays->ny);
   const float scale = (float)(hx * hy / (dx * dy));
-  HIP_TRY(ctx, launch_normalize_convolve(counts, d_map, window->nx, window->ny, (const float*)ctx->taps.p,
-                                         (const int32_t*)(ctx->taps.p + ctx->taps_wbytes), ctx->taps_n,
-                                         ctx->taps_rx, ctx->taps_ry, scale, maxc, ctx->stream));
+  HIP_TRY(ctx, launch_normalize_convolve(counts, d_map, window->nx, window->ny, t.w(), t.off(), t.n, t.rx, t.ry,
+                                         scale, maxc, ctx->stream));
   if (h_stats) {
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     uint64_t hs[4];

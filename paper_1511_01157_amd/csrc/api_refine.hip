@@ -88,16 +88,15 @@ int setup_candidates(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   const size_t o_off = mb.add(lcs->h_offsets, 8 * (size_t)(ne + 1)),
                o_tref = mb.add(lcs->h_t_ref, 8 * (size_t)ne),
                o_maps = mb.add(hm.data(), sizeof(MapC) * n_maps);  // with the packed cells' addresses
-  if ((rc = reserve_meta(ctx, ctx->cmeta, mb.bytes.size()))) return rc;
-  int64_t* d_off = (int64_t*)(ctx->cmeta.p + o_off);
-  double* d_tref = (double*)(ctx->cmeta.p + o_tref);
-  d_maps = (MapC*)(ctx->cmeta.p + o_maps);
-  Hasher h;
-  h.pod(ctx->cmeta.p);
-  h.pod(ne);
-  h.pod(n_maps);
-  h.bytes(mb.bytes.data(), mb.bytes.size());
-  if ((rc = put_meta(ctx, ctx->cmeta.p, ctx->cmeta.key, h.h, mb.bytes))) return rc;
+  Hasher key;
+  key.pod(ne);
+  key.pod(n_maps);
+  key.bytes(mb.bytes.data(), mb.bytes.size());
+  char* meta;
+  if ((rc = put_meta(ctx, ctx->cmeta, mb.bytes, key.h, &meta))) return rc;
+  int64_t* d_off = (int64_t*)(meta + o_off);
+  double* d_tref = (double*)(meta + o_tref);
+  d_maps = (MapC*)(meta + o_maps);
   lc.t = lcs->d_t;
   lc.w = lcs->d_weight;
   lc.F = lcs->d_flux;

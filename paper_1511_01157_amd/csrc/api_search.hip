@@ -166,15 +166,14 @@ int plan_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
     mb.add(trajs->h_t0, 8 * (size_t)trajs->n_t0, 8);
     mb.add(trajs->h_tE, 8 * (size_t)trajs->n_tE, 8);
   }
-  if ((rc = reserve_meta(ctx, ctx->smeta, mb.bytes.size()))) return rc;
-  int64_t* d_off = (int64_t*)(ctx->smeta.p + o_off);
-  double* d_tref = (double*)(ctx->smeta.p + o_tref);
-  sp.d_maps = (MapC*)(ctx->smeta.p + o_maps);
-  sp.axes = n_axes ? (double*)(ctx->smeta.p + o_axes) : nullptr;
   Hasher key;
-  key.pod(ctx->smeta.p);
   key.bytes(mb.bytes.data(), mb.bytes.size());
-  if ((rc = put_meta(ctx, ctx->smeta.p, ctx->smeta.key, key.h, mb.bytes))) return rc;
+  char* meta;
+  if ((rc = put_meta(ctx, ctx->smeta, mb.bytes, key.h, &meta))) return rc;
+  int64_t* d_off = (int64_t*)(meta + o_off);
+  double* d_tref = (double*)(meta + o_tref);
+  sp.d_maps = (MapC*)(meta + o_maps);
+  sp.axes = n_axes ? (double*)(meta + o_axes) : nullptr;
   sp.lc.t = lcs->d_t;
   sp.lc.w = lcs->d_weight;
   sp.lc.F = lcs->d_flux;
@@ -454,8 +453,7 @@ int morse_candidates_from_topk(morse_ctx* ctx, const morse_trajectories* trajs, 
     // the auxiliary buffer keeps the search's resident workspace intact
     if ((rc = reserve_aux(ctx, mb.bytes.size()))) return rc;
     double* d = (double*)ctx->aux.p;
-    uint64_t none = 0;
-    if ((rc = put_meta(ctx, d, none, 1, mb.bytes))) return rc;
+    if ((rc = put_now(ctx, d, mb.bytes))) return rc;
     axes = d;
   }
   HIP_TRY(ctx, launch_candidates(axes, trajs->n_u0, trajs->n_alpha, trajs->n_t0, trajs->n_tE,

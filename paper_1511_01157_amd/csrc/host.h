@@ -32,7 +32,7 @@ struct Buffer {
   bool named = false;  // a captured call used it: the caller's graph holds its address
 };
 
-// A device buffer of host metadata with the key of what it holds.
+// A device buffer of host metadata with the key of what it holds (see put_meta).
 struct MetaBuf : Buffer {
   uint64_t key = 0;
 };
@@ -50,7 +50,6 @@ struct morse_ctx {
   // buffer of its own (never in the shared workspace, which the other entry points
   // overwrite) and uploaded only when its key changes
   MetaBuf smeta, cmeta;
-  bool captured = false;  // a call was captured into a graph: its replays put metadata too
   // source-radius stacks: direct-sum taps, FFT twiddle tables and the transforms of
   // the profile pairs, each kept until a call needs different ones
   MetaBuf stack_taps, fft_tw, fft_spec;
@@ -71,11 +70,15 @@ struct morse_ctx {
   std::map<std::string, int> tune;
   // small auxiliary device buffer, separate from the workspace
   Buffer aux;
-  // disk-convolution taps resident on the device (key of the taps they hold)
+  // disk-convolution taps resident on the device, and what the host knows of them
   MetaBuf taps;
-  int32_t taps_n = 0;
-  int32_t taps_rx = 0, taps_ry = 0;  // the largest |offset| of the taps along x and y
-  size_t taps_wbytes = 0;
+  struct DiskTaps {
+    int32_t n = 0, rx = 0, ry = 0;  // number, and the largest |offset| along x and y
+    size_t w_bytes = 0;             // the offsets follow the weights at this byte offset
+    const char* p = nullptr;
+    const float* w() const { return (const float*)p; }
+    const int32_t* off() const { return (const int32_t*)(p + w_bytes); }
+  } disk;
   // slots of the ray statistics (allocated with the context, so that a call can be captured)
   char* stat_slots = nullptr;
   // kernel timing: enabled families, pending event pairs, free events, totals
@@ -280,23 +283,34 @@ inline int upload(morse_ctx* ctx, void* dst, const void* src, size_t bytes) {
   return MORSE_OK;
 }
 
-// Puts src (which may go when this returns) at dst unless it is there: `key` is the key of what
-// dst holds, `want` that of src.  A captured call takes it along, and a replay then replaces
-// what is there without a word: from the first capture on, every call puts its own.
-inline int put_meta(morse_ctx* ctx, void* dst, uint64_t& key, uint64_t want, const std::vector<char>& src) {
-  const bool cap = capturing(ctx);
-  if (cap) ctx->captured = true;
-  if (key == want && !ctx->captured) return MORSE_OK;
-  key = 0;
-  if (cap || src.size() <= kPutMax) {
+// Puts src (which may go when this returns) at dst.  A captured call takes it along by value.
+inline int put_now(morse_ctx* ctx, void* dst, const std::vector<char>& src) {
+  if (src.size() <= kPutMax || capturing(ctx)) {
     HIP_TRY(ctx, launch_put(dst, src.data(), src.size(), ctx->stream));
-  } else {
-    const int rc = upload(ctx, dst, src.data(), src.size());
-    if (rc) return rc;
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    return MORSE_OK;
   }
-  key = want;
+  const int rc = upload(ctx, dst, src.data(), src.size());
+  if (rc) return rc;
+  HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   return MORSE_OK;
+}
+
+// Puts src on the device in one half of mb, at *at: ordinary calls use the first, where what a
+// call put stays for the next with the same key; captured calls the second, which their graphs
+// write on every replay without ordinary calls having to know.
+inline int put_meta(morse_ctx* ctx, MetaBuf& mb, const std::vector<char>& src, uint64_t key, char** at) {
+  const int rc = reserve_meta(ctx, mb, 2 * ((src.size() + 255) & ~size_t(255)));
+  if (rc) return rc;
+  if (capturing(ctx)) {
+    *at = mb.p + mb.size / 2;
+    return put_now(ctx, *at, src);
+  }
+  *at = mb.p;
+  if (mb.key == key) return MORSE_OK;
+  mb.key = 0;
+  const int e = put_now(ctx, *at, src);
+  if (e == MORSE_OK) mb.key = key;
+  return e;
 }
 
 // Host metadata laid out in one block; sizes are rounded up to a multiple of `unit` bytes.

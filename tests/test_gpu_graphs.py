@@ -134,3 +134,49 @@ def test_captured_stack_keeps_its_profiles(rhos, others):
             s.synchronize()
             assert torch.equal(out, want), rep
             assert torch.equal(M.convolve_stack(counts, rays, win, rhos, ctx=c), want), rep
+
+
+def test_ordinary_calls_after_a_capture_do_not_wait():
+    """What an ordinary call put stays for the next one, also when captured calls put theirs: with
+    work ahead of it on the stream, a repeated call returns before that work is done."""
+    s = torch.cuda.Stream(device=DEV)
+    rng = np.random.default_rng(9)
+    win = (0.0, 0.0, 2.0, 2.0, 64, 64)
+    amap = torch.from_numpy((1 + rng.random((64, 64))).astype(np.float32)).to(DEV)
+    n = 2000  # events, and values of an axis: more metadata than goes by value
+    lcs = M.LightCurveBatch(torch.from_numpy(np.tile(np.arange(4, dtype=np.float32), n)).to(DEV),
+                            torch.from_numpy(rng.random(4 * n)).to(DEV), torch.ones(4 * n, dtype=torch.float64, device=DEV),
+                            np.arange(0, 4 * n + 1, 4), np.zeros(n))
+    one = M.LightCurveBatch(lcs.t[:8], lcs.flux[:8], lcs.weight[:8], np.array([0, 8]), np.zeros(1))
+    grid = M.grid_trajectories(np.linspace(0, 0.8, n), [0.3], [0.5], [15.0])
+    P = torch.from_numpy(np.tile(np.array([[0.1, 0.2, 20.0, 0.4]]), (8, 1))).to(DEV)
+    z = torch.zeros(8, dtype=torch.int32, device=DEV)
+    out = torch.empty((64, 64), dtype=torch.float32, device=DEV)
+    big = torch.randn(8192, 8192, device=DEV)
+    tmp = torch.empty_like(big)
+    note("graphs: ordinary calls after a capture")
+    with torch.cuda.stream(s):
+        c = M.Context.bound(s)
+
+        def calls():
+            M.build_map(1.0, 0.1, (0.0, 0.0, 4.0, 4.0, 256, 256), win, 0.1, out=out, ctx=c)
+            r = M.search([(amap, win)], one, grid, "batched", best=True, ctx=c)
+            return [out, r["chi2"], r["best_idx"], *M.chi2_grad([(amap, win)], lcs, P, z, z, ctx=c)]
+
+        want = [x.clone() for x in calls()]
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            got = calls()
+        calls()
+        g.replay()
+        s.synchronize()
+        behind = torch.cuda.Event()
+        for _ in range(20):
+            torch.mm(big, big, out=tmp)
+        behind.record(s)
+        again = calls()
+        assert not behind.query()
+        s.synchronize()
+        for a, b, w in zip(got, again, want):
+            assert torch.equal(a, w) and torch.equal(b, w)

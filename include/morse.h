@@ -22,7 +22,8 @@
  *   - Graphs: a call that neither waits nor allocates may be captured into the caller's graph,
  *     one of its size having been made before; a captured call that would have to allocate
  *     returns EUNSUPPORTED and enqueues nothing.  The graph works in the context's buffers: it
- *     may be replayed while the context lives, in order with the context's other calls.  Buffers
+ *     may be replayed while the context lives, in order with the context's other calls
+ *     (morse_rayshoot works in the caller's buffers alone: in any order).  Buffers
  *     that a captured call used are kept until the context goes when later calls outgrow or
  *     replace them.
  */

@@ -251,8 +251,10 @@ int morse_rayshoot(morse_ctx* ctx, double s, double q, const morse_grid2d* rays,
   if (!accumulate) HIP_TRY(ctx, launch_fill_u32(d_counts, (size_t)window->nx * window->ny, 0u, ctx->stream));
   LaunchTimer tm{ctx, MORSE_KERNEL_RAYSHOOT};
   HIP_TRY(ctx, tm.begin(ctx->stream));
-  HIP_TRY(ctx, launch_rayshoot(p, d_counts, (unsigned long long*)d_stats,
-                               (unsigned long long*)ctx->stat_slots, ctx->num_cu, ctx->stream));
+  // a captured call works in the caller's buffers alone: its graph may be replayed beside other
+  // calls of the context
+  unsigned long long* slots = d_stats && !capturing(ctx) ? (unsigned long long*)ctx->stat_slots : nullptr;
+  HIP_TRY(ctx, launch_rayshoot(p, d_counts, (unsigned long long*)d_stats, slots, ctx->num_cu, ctx->stream));
   HIP_TRY(ctx, tm.end(ctx->stream));
   return MORSE_OK;
 }

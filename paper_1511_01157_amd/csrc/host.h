@@ -79,7 +79,7 @@ struct morse_ctx {
     const float* w() const { return (const float*)p; }
     const int32_t* off() const { return (const int32_t*)(p + w_bytes); }
   } disk;
-  // slots of the ray statistics (allocated with the context, so that a call can be captured)
+  // slots of the ray statistics (not used by captured calls)
   char* stat_slots = nullptr;
   // kernel timing: enabled families, pending event pairs, free events, totals
   uint32_t timing_mask = 0;

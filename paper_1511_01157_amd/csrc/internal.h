@@ -406,10 +406,10 @@ hipError_t launch_scan_u32(uint32_t* v, int64_t nb, hipStream_t st);
 hipError_t launch_bucket_order(const uint32_t* key, int64_t n, int32_t nbins, uint32_t* hist,
                                int32_t* order, hipStream_t st);
 // Shoots the rows of p into counts.  With `stats` (three totals that the call adds to),
-// `slots` is workspace of 4 kStatSlots words: the workgroups add to one slot each, so that
-// no address takes more than a few hundred atomics (the three totals themselves took
-// 260,000 each and doubled the time of a 32768^2 lattice).
-constexpr int kStatSlots = 256;
+// `slots` is workspace of 4 kStatSlots words: workgroup b adds to slot b % kStatSlots, which
+// takes one atomic in 256 (of a 32768^2 lattice 260,000 fell on each of the three totals and
+// doubled its time).  nullptr: the workgroups add to the totals themselves.
+constexpr uint32_t kStatSlots = 256;  // a power of two
 hipError_t launch_rayshoot(const RayParams& p, uint32_t* counts, unsigned long long* stats,
                            unsigned long long* slots, int num_cu, hipStream_t st);
 // Normalisation + convolution of a counts map with ntaps taps whose offsets reach at

@@ -113,7 +113,8 @@ __device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
 // range tested per ray, scalar operands.
 template <bool kMirror, bool kSafe, int A, int B>
 __global__ __launch_bounds__(RS_THREADS) void k_rayshoot(RayParams p, uint32_t* __restrict__ counts,
-                                                         unsigned long long* __restrict__ stats) {
+                                                         unsigned long long* __restrict__ stats,
+                                                         uint32_t slot_mask) {
   __shared__ uint32_t hist[RS_CAP];
   __shared__ uint32_t s_box[RS_THREADS / kWave][2];
   __shared__ uint32_t s_stat[RS_THREADS / kWave][3];
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_rayshoot(RayParams p, uint32_t* 
   const uint32_t shot = (uint32_t)(x1 - x0 + 1) * (uint32_t)(y1 - y0 + 1);
   constexpr uint32_t kRays = kMirror ? 2u : 1u;  // rays each shot ray stands for
   // slot of the statistics this workgroup adds to (few workgroups per address)
-  unsigned long long* st = stats ? stats + 4 * ((blockIdx.x + blockIdx.y * gridDim.x) % kStatSlots) : nullptr;
+  unsigned long long* st = stats ? stats + 4 * ((blockIdx.x + blockIdx.y * gridDim.x) & slot_mask) : nullptr;
   if (tile_misses<kSafe>(p, lattice(p.cx, x0, p.nx, p.hx), lattice(p.cx, x1, p.nx, p.hx),
                   lattice(p.cy, y0, p.ny, p.hy), lattice(p.cy, y1, p.ny, p.hy))) {
     if (tid == 0 && st) atomicAdd(&st[0], (unsigned long long)(shot * kRays));
@@ -670,8 +671,8 @@ bool safe_rows(const RayParams& p, int32_t row0, int32_t row1) {
 }
 
 template <bool kMirror, bool kSafe>
-hipError_t shoot_tiles(const RayParams& p, uint32_t* counts, unsigned long long* stats, int num_cu,
-                       hipStream_t st) {
+hipError_t shoot_tiles(const RayParams& p, uint32_t* counts, unsigned long long* stats, uint32_t slot_mask,
+                       int num_cu, hipStream_t st) {
   // 128 x 64 rays a workgroup, 32 a thread; 64 x 32 where the lattice is too small to give
   // every CU eight such tiles (3200^2 rays into 512^2: 12 against 51 us) or so coarse that
   // 128 x 64 rays cover more than 512 pixels without a lens (near one they spread over
@@ -683,10 +684,11 @@ hipError_t shoot_tiles(const RayParams& p, uint32_t* counts, unsigned long long*
   auto tiles = [&](int tx, int ty) { return dim3((p.nx + tx - 1) / tx, (rows + ty - 1) / ty); };
   const dim3 big = tiles(128, 64);
   if ((int64_t)big.x * big.y >= 8 * (int64_t)num_cu && cover <= 512.0f) {
-    hipLaunchKernelGGL((k_rayshoot<kMirror, kSafe, 8, 4>), big, dim3(RS_THREADS), 0, st, p, counts, stats);
+    hipLaunchKernelGGL((k_rayshoot<kMirror, kSafe, 8, 4>), big, dim3(RS_THREADS), 0, st, p, counts, stats,
+                       slot_mask);
   } else {
     hipLaunchKernelGGL((k_rayshoot<kMirror, kSafe, 4, 2>), tiles(64, 32), dim3(RS_THREADS), 0, st, p,
-                       counts, stats);
+                       counts, stats, slot_mask);
   }
   return hipGetLastError();
 }
@@ -695,12 +697,12 @@ hipError_t shoot_tiles(const RayParams& p, uint32_t* counts, unsigned long long*
 // half whose mirror rows are part of the call, once for the pair (kMirror true).
 template <bool kMirror>
 hipError_t shoot_rows(RayParams p, int32_t row0, int32_t row1, uint32_t* counts,
-                      unsigned long long* stats, int num_cu, hipStream_t st) {
+                      unsigned long long* stats, uint32_t slot_mask, int num_cu, hipStream_t st) {
   if (row1 <= row0) return hipSuccess;
   p.row0 = row0;
   p.row1 = row1;
-  return safe_rows(p, row0, row1) ? shoot_tiles<kMirror, true>(p, counts, stats, num_cu, st)
-                                  : shoot_tiles<kMirror, false>(p, counts, stats, num_cu, st);
+  return safe_rows(p, row0, row1) ? shoot_tiles<kMirror, true>(p, counts, stats, slot_mask, num_cu, st)
+                                  : shoot_tiles<kMirror, false>(p, counts, stats, slot_mask, num_cu, st);
 }
 
 }  // namespace
@@ -708,22 +710,23 @@ hipError_t shoot_rows(RayParams p, int32_t row0, int32_t row1, uint32_t* counts,
 hipError_t launch_rayshoot(const RayParams& p, uint32_t* counts, unsigned long long* stats,
                            unsigned long long* slots, int num_cu, hipStream_t st) {
   if (p.row1 <= p.row0) return hipSuccess;
-  if (stats && !slots) return hipErrorInvalidValue;
   hipError_t e = hipSuccess;
-  unsigned long long* ss = stats ? slots : nullptr;
-  if (ss) e = launch_fill_u64((uint64_t*)ss, 4 * kStatSlots, 0ull, st);
+  const bool in_slots = stats && slots;
+  unsigned long long* ss = in_slots ? slots : stats;
+  const uint32_t mask = in_slots ? kStatSlots - 1 : 0u;
+  if (in_slots) e = launch_fill_u64((uint64_t*)ss, 4 * kStatSlots, 0ull, st);
   // Mirror pairs need a lattice and a window centred on y = 0 and an even row count;
   // the rows paired inside [row0, row1) form [a, b) with a + b = ny.
   const int32_t a = std::max(p.row0, p.ny - p.row1), b = std::min(p.row1, p.ny - p.row0);
   if (e != hipSuccess) return e;
   if (!(p.cy == 0.0f && p.sy == 0.0f && (p.ny & 1) == 0 && a < b)) {
-    e = shoot_rows<false>(p, p.row0, p.row1, counts, ss, num_cu, st);
+    e = shoot_rows<false>(p, p.row0, p.row1, counts, ss, mask, num_cu, st);
   } else {
-    e = shoot_rows<true>(p, p.ny / 2, b, counts, ss, num_cu, st);
-    if (e == hipSuccess) e = shoot_rows<false>(p, p.row0, a, counts, ss, num_cu, st);
-    if (e == hipSuccess) e = shoot_rows<false>(p, b, p.row1, counts, ss, num_cu, st);
+    e = shoot_rows<true>(p, p.ny / 2, b, counts, ss, mask, num_cu, st);
+    if (e == hipSuccess) e = shoot_rows<false>(p, p.row0, a, counts, ss, mask, num_cu, st);
+    if (e == hipSuccess) e = shoot_rows<false>(p, b, p.row1, counts, ss, mask, num_cu, st);
   }
-  if (e == hipSuccess && ss) {
+  if (e == hipSuccess && in_slots) {
     hipLaunchKernelGGL(k_stats_sum, dim3(1), dim3(64), 0, st, ss, stats);
     e = hipGetLastError();
   }

@@ -180,3 +180,40 @@ def test_ordinary_calls_after_a_capture_do_not_wait():
         s.synchronize()
         for a, b, w in zip(got, again, want):
             assert torch.equal(a, w) and torch.equal(b, w)
+
+
+def test_captured_ray_statistics_beside_ordinary_calls():
+    """A captured ray shooting replayed on one stream while the context shoots other rays on
+    another: each call's statistics are its own."""
+    s, r = torch.cuda.Stream(device=DEV), torch.cuda.Stream(device=DEV)
+    win = (0.0, 0.0, 2.0, 2.0, 256, 256)
+    a, b = (1.0, 0.1, (0.0, 0.0, 4.0, 4.0, 8192, 8192), win), (0.8, 0.3, (0.1, 0.05, 6.0, 5.0, 8000, 7000), win)
+    bufs = [(torch.zeros((256, 256), dtype=torch.int32, device=DEV), torch.zeros(3, dtype=torch.int64, device=DEV)) for _ in range(2)]
+    note("graphs: ray statistics on two streams")
+    with torch.cuda.stream(s):
+        c = M.Context.bound(s)
+        want = []
+        for call, (n, st) in zip((a, b), bufs):
+            M.rayshoot(*call, n, stats=st, ctx=c)
+            want.append((n.clone(), st.clone()))
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            M.rayshoot(*a, *bufs[0][:1], stats=bufs[0][1], ctx=c)
+    big = torch.randn(4096, 4096, device=DEV)
+    tmp = torch.empty_like(big)
+    for rep in range(10):
+        for _, st in bufs:
+            st.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(r):  # both streams' calls are queued before either runs
+            for _ in range(5):
+                torch.mm(big, big, out=tmp)
+            s.wait_event(r.record_event())
+            for _ in range(4):
+                g.replay()
+        for _ in range(4):
+            M.rayshoot(*b, bufs[1][0], stats=bufs[1][1], ctx=c)
+        torch.cuda.synchronize()
+        for (n, st), (wn, wst) in zip(bufs, want):
+            assert torch.equal(n, wn) and torch.equal(st, 4 * wst), rep

@@ -100,8 +100,8 @@ class Context:
 
     @classmethod
     def bound(cls, stream: torch.cuda.Stream) -> "Context":
-        """A context of its own (workspace, graphs, metadata) that always enqueues on
-        `stream`: pass it as ``ctx=`` to run work concurrently with another context."""
+        """A context of its own (workspace, metadata) that always enqueues on `stream`: pass
+        it as ``ctx=`` to run work concurrently with another context."""
         with torch.cuda.stream(stream):
             ctx = Context(stream.device.index)
         ctx._bound = True
@@ -200,6 +200,7 @@ def build_map(s, q, rays, window, rho=0.0, device="cuda", out=None, counts=None,
     dev = torch.device(device)
     if out is None:
         out = torch.empty((int(window[5]), int(window[4])), dtype=torch.float32, device=dev)
+    given = ctx
     ctx = ctx or Context.get(_device_of(out))
     st = MapStats() if stats else None
     ctx.check(ctx.lib.morse_build_map(ctx.handle, float(s), float(q), ctypes.byref(_grid(rays)),
@@ -207,6 +208,8 @@ def build_map(s, q, rays, window, rho=0.0, device="cuda", out=None, counts=None,
                                       _ptr(out), ctypes.byref(st) if st is not None else None))
     if stats:
         return out, {k: int(getattr(st, k)) for k, _ in MapStats._fields_ if k != "reserved"}
+    if given and given.stream != torch.cuda.current_stream(given.device).cuda_stream:
+        given.synchronize()  # work that the caller enqueues next does not follow the map's stream
     return out
 
 

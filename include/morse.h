@@ -479,7 +479,8 @@ int morse_chi2_grad(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
  * 128 MiB on each GPU the library runs on, held until the process ends.  Every call on
  * a GPU shares that GPU's array and leaves its contents there, so calls that overlap on
  * one GPU (other streams or contexts) race; calls on one stream are ordered.  The host
- * metadata goes into the array on every call, by value as kernel arguments.  Errors: as morse_chi2_grad, and ERANGE when the scratch would
+ * metadata goes into the array on every call, by value as kernel arguments (more than 14 KiB
+ * of it, outside a capture, by a copy that is waited for).  Errors: as morse_chi2_grad, and ERANGE when the scratch would
  * exceed 128 MiB (e.g. more than one 2048^2 map with long light curves). */
 int morse_chi2_grad_noalloc(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
                             const morse_lightcurves* lcs, int64_t n, const double* d_params,

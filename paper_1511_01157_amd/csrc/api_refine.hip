@@ -253,8 +253,8 @@ int morse_chi2_grad_noalloc(morse_ctx* ctx, const morse_map_view* maps, int32_t 
   HIP_TRY(ctx, hipSetDevice(ctx->device));
   char* base = nullptr;
   if ((rc = noalloc_scratch(ctx->device, &base))) return fail(ctx, rc, "%s", morse_last_error(nullptr));
-  // metadata: event offsets | reference times | map table, uploaded on every call (the
-  // array keeps whatever the last call on this GPU left in it)
+  // metadata: event offsets | reference times | map table, put on every call (the array keeps
+  // whatever the last call on this GPU left in it)
   std::vector<MapC> hm(n_maps);
   for (int i = 0; i < n_maps; ++i) hm[i] = make_mapc(maps[i].d_map, maps[i].window);
   assign_quads(hm, pl.ptr_at(base, i_quad));
@@ -264,7 +264,8 @@ int morse_chi2_grad_noalloc(morse_ctx* ctx, const morse_map_view* maps, int32_t 
   std::memcpy(block.data(), lcs->h_offsets, 8 * (size_t)(ne + 1));
   std::memcpy(block.data() + b_off, lcs->h_t_ref, 8 * (size_t)ne);
   std::memcpy(block.data() + b_off + b_tref, hm.data(), sizeof(MapC) * n_maps);
-  HIP_TRY(ctx, launch_put(meta, block.data(), block.size(), ctx->stream));  // never waits
+  // 20,000 events: 146 us copied, 365 by value in 90 launches; 1000 events (16 KiB): 58 and 52
+  if ((rc = put_now(ctx, meta, block))) return rc;
   GradArgs a{};
   a.lc.t = lcs->d_t;
   a.lc.w = lcs->d_weight;

@@ -1,4 +1,4 @@
-"""Ray statistics where tiles are skipped unseen: rays whose offset from the window overflows
+"""Ray shooting at its edges.  Statistics where tiles are skipped unseen: rays whose offset from the window overflows
 binary32 are non-finite in the kernel's arithmetic, however far from the window their tile lies."""
 import numpy as np
 import pytest
@@ -32,3 +32,18 @@ def test_overflowing_rays_count_as_nonfinite(name):
     assert np.array_equal(counts.cpu().numpy().view(np.uint32), o)
     assert dict(zip(("out", "nonfinite", "zero_axis"), stats.tolist())) == ost
     assert (ost["nonfinite"] > 0) == (not name.startswith("finite"))
+
+
+# windows of a few columns or rows: a tile's box of bins is narrow; 16 and 17 columns about the line
+# between the two ways through it
+@pytest.mark.parametrize("nx,ny", [(2, 8192), (8192, 2), (16, 3000), (18, 3000), (3000, 34), (6, 6)])
+@pytest.mark.parametrize("cy", [0.0, 0.01])
+def test_narrow_windows_count_exactly(nx, ny, cy):
+    s, q, rays, window = 0.8, 0.01, (0.0, cy, 4.0, 4.0, 1500, 1400), (0.0, 0.0, 2.0, 2.0, nx, ny)
+    note(f"ray statistics narrow window {nx} x {ny} cy={cy}")
+    counts = torch.empty((ny, nx), dtype=torch.int32, device=DEV)
+    stats = torch.zeros(3, dtype=torch.int64, device=DEV)
+    M.rayshoot(s, q, rays, window, counts, stats=stats)
+    o, ost = rayshoot_mirror32_c(s, q, rays, window, nthreads=8)
+    assert np.array_equal(counts.cpu().numpy().view(np.uint32), o) and o.sum() > 0
+    assert dict(zip(("out", "nonfinite", "zero_axis"), stats.tolist())) == ost

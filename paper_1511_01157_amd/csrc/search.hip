@@ -58,13 +58,13 @@ __device__ __forceinline__ void tree_totals(double (*s_part)[4], double (&tot)[N
 }
 
 // Light curve e (one workgroup of 256; see above).  Up to kLcKeep points a lane stay in
-// registers from the first pass to the second.
-constexpr int kLcKeep = 16;
+// registers from the first pass to the second; 0: the second reads them again.
+template <int kLcKeep>
 __device__ void lc_prep(const LcView& lc, double* wFc, double* sums, uint32_t* sorted, int32_t e,
                         double (*s_part)[4]) {
   const int64_t a = lc.off[e], b = lc.off[e + 1];
-  const bool keep = b - a <= kLcKeep * 256;  // uniform
-  double kw[kLcKeep], kF[kLcKeep];
+  const bool keep = kLcKeep > 0 && b - a <= kLcKeep * 256;  // uniform
+  double kw[kLcKeep + 1], kF[kLcKeep + 1];
   double s0 = 0, c0 = 0, s1 = 0, c1 = 0;
   if (keep) {
 #pragma unroll
@@ -183,12 +183,14 @@ __device__ __forceinline__ void pack_quads(const MapC& m, uint32_t first, uint32
 // All the preparation of a call in one launch, its parts side by side: a workgroup per light
 // curve (the longest chain, first), then the trajectory constants, the cleared counters and
 // the packing.  One after another they were four launches of 4 to 12 us each.
+// kLcKeep: with points kept in registers (96 in all) five wavefronts fit a SIMD, without seven.
+template <int kLcKeep>
 __global__ __launch_bounds__(256) void k_prep(PrepArgs a) {
   __shared__ double s_part[256][4];
   uint32_t block = blockIdx.x;
   if (block < a.event_blocks) {
     for (int32_t e = (int32_t)block; e < a.n_events; e += (int32_t)a.event_blocks)
-      lc_prep(a.lc, const_cast<double*>(a.lc.wFc), const_cast<double*>(a.lc.sums),
+      lc_prep<kLcKeep>(a.lc, const_cast<double*>(a.lc.wFc), const_cast<double*>(a.lc.sums),
               const_cast<uint32_t*>(a.lc.sorted), e, s_part);
     return;
   }
@@ -1073,7 +1075,15 @@ hipError_t launch_prep(PrepArgs a, const MapC* h_maps, hipStream_t st) {
   const uint64_t all = (uint64_t)a.event_blocks + a.traj_blocks + a.zero_blocks + (uint64_t)a.pack_blocks * a.n_maps;
   if (all == 0) return hipSuccess;
   if (all >= 1u << 24) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_prep, dim3((unsigned)all), dim3(256), 0, st, a);
+  // A few light curves are over soonest with one pass over memory (6 us for 8); where there is
+  // enough of them, or of packing, to fill the chip, more wavefronts count: 24 maps of 1600^2
+  // pixels 400 and 341 us, 200,000 light curves of 4 points 780 and 530
+  uint64_t cells = 0;
+  for (int32_t k = 0; k < a.n_maps; ++k) cells += h_maps[k].cells;
+  if (cells < (1u << 22) && a.n_events <= 2048)
+    hipLaunchKernelGGL(k_prep<16>, dim3((unsigned)all), dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL(k_prep<0>, dim3((unsigned)all), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -321,7 +321,8 @@ int morse_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
                      out->d_fb ? out->d_fb + base : nullptr};
         LaunchTimer tm{ctx, MORSE_KERNEL_SEARCH};
         HIP_TRY(ctx, tm.begin(ctx->stream));
-        HIP_TRY(ctx, launch_search_plain(tc, sp.n_traj, sp.lc, e, sp.h_maps[m], so, 4, ctx->stream));
+        HIP_TRY(ctx, launch_search_plain(tc, sp.n_traj, sp.lc, e, lcs->h_offsets[e + 1] - lcs->h_offsets[e],
+                                         sp.h_maps[m], so, 4, ctx->stream));
         HIP_TRY(ctx, tm.end(ctx->stream));
       }
     }

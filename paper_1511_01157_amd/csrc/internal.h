@@ -453,9 +453,9 @@ struct SearchOut {
   double* fb;
 };
 
-// Plain search: one launch for one (event, map); outputs for that segment.
+// Plain search: one launch for one (event, map); outputs for that segment.  n_points: of the event.
 hipError_t launch_search_plain(const TrajC* tc, int64_t n_traj, LcView lc, int32_t event,
-                               MapC map, SearchOut out, int waves_per_block, hipStream_t st);
+                               int64_t n_points, MapC map, SearchOut out, int waves_per_block, hipStream_t st);
 
 // Batched search over (event, map, trajectory block) items, one launch.
 struct BatchedArgs {

@@ -129,10 +129,14 @@ __device__ __forceinline__ T ldg(const T* __restrict__ base, uint32_t i) {
 }
 
 // Index of packed cell (i, j); below 2^28 since the packed map is below 4 GiB, and both
-// factors of the product fit 24 bits.
+// factors of the product fit 24 bits.  kFewest: the sum is kept as one shift-add, else the
+// compiler takes a shift, a product and a three-way sum, which it can schedule more freely: the
+// line simplex, bound by latency, takes 3% less with those (4000 lines x 300 points 4.54 and
+// 4.43 ms), the others half a percent more.
+template <bool kFewest = true>
 __device__ __forceinline__ uint32_t cell_index(const MapC& m, uint32_t i, uint32_t j) {
   uint32_t s = (i << 1) + j;
-  asm("" : "+v"(s));  // kept as one shift-add: else a shift, a product and a three-way sum
+  if (kFewest) asm("" : "+v"(s));
   return __umul24(j >> 1, m.row) + s;
 }
 
@@ -152,6 +156,7 @@ struct Loc {
   bool on;
 };
 
+template <bool kFewest = true>
 __device__ __forceinline__ Loc locate(const MapC& m, float tt, float t0p, float iE, float ca,
                                       float sa, float bx, float by) {
   Loc l;
@@ -169,7 +174,7 @@ __device__ __forceinline__ Loc locate(const MapC& m, float tt, float t0p, float 
   // on the map g >= 0, so truncation is the floor and fract(g) = g - floor(g) exactly
   l.fx = __builtin_amdgcn_fractf(gx);
   l.fy = __builtin_amdgcn_fractf(gy);
-  l.q = l.on ? cell_index(m, (uint32_t)gx, (uint32_t)gy) : 0u;
+  l.q = l.on ? cell_index<kFewest>(m, (uint32_t)gx, (uint32_t)gy) : 0u;
   return l;
 }
 

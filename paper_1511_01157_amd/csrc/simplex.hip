@@ -120,7 +120,7 @@ __global__ __launch_bounds__(kItemThreads) void k_line_simplex(SimplexArgs a) {
         for (int k = 0; k < kUnroll; ++k) {
           const int32_t j = i0 + k * kItemThreads;
           const uint32_t jj = (uint32_t)(j < np ? j : np - 1);
-          lc[k] = locate(m, kStaged ? s_t[jj] : ldg(t, jj), t0p, iE, ca, sa, bx, by);
+          lc[k] = locate<false>(m, kStaged ? s_t[jj] : ldg(t, jj), t0p, iE, ca, sa, bx, by);
           q[k] = ldq(m, lc[k].q);
           wv[k] = kStaged ? s_w[jj] : ldg(w, jj);
           fv[k] = kStaged ? s_f[jj] : ldg(wFc, jj);
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kItemThreads) void k_line_simplex(SimplexArgs a) {
     double px0 = s0, px1 = s1, b0 = 0.0, b1 = 0.0, r0 = 0.0, r1 = 0.0, fr = 0.0;
     int state = kInit0;
     int32_t it = 0, evals = 0;
-    bool still = false;  // the last iteration left every vertex as it was
+    bool still = false;  // the shrink left its first vertex as it was
     for (;;) {
       const double f = chi2_at(px0, px1);
       ++evals;
@@ -229,7 +229,13 @@ __global__ __launch_bounds__(kItemThreads) void k_line_simplex(SimplexArgs a) {
           state = kShrink2;
           break;
         default:  // kShrink2
-          still = still && same(v[2], {px0, px1, f});
+          if (still && same(v[2], {px0, px1, f})) {
+            // A shrink that moved nothing: the vertices are those of the iteration's start, and
+            // every later iteration repeats it (an iteration depends on them alone) to the last
+            // one allowed, four evaluations each.
+            evals += 4 * (a.max_iter - it);
+            it = a.max_iter;
+          }
           v[2] = {px0, px1, f};
           next = true;
           break;
@@ -242,14 +248,6 @@ __global__ __launch_bounds__(kItemThreads) void k_line_simplex(SimplexArgs a) {
       if (!next) continue;
       order3(v);
       if (it >= a.max_iter || v[2].f - v[0].f <= a.ftol * fabs(v[0].f)) break;
-      if (still) {
-        // A shrink that moved nothing: the vertices are those of the iteration's start, and
-        // every later iteration repeats it (an iteration depends on them alone) to the last
-        // one allowed, four evaluations each.
-        evals += 4 * (a.max_iter - it);
-        it = a.max_iter;
-        break;
-      }
       ++it;
       b0 = (v[0].x0 + v[1].x0) * 0.5;
       b1 = (v[0].x1 + v[1].x1) * 0.5;

@@ -15,21 +15,24 @@ struct TuneCfg {
   int tu;
 };
 // Candidate shapes of the batched search tried by the autotuner (saved caches name them by
-// index).  traj_per_item = trajectories per wavefront, tu = trajectories scored together by
-// one wavefront (sharing light-curve loads).
+// index: a change of the table or of what makes a shape fast raises the version in
+// shape_class).  traj_per_item = trajectories per wavefront, tu = trajectories scored together
+// by one wavefront (sharing light-curve loads).
 constexpr TuneCfg kTune[] = {
     {8, 4, 2},  {8, 4, 1},  {16, 4, 2}, {8, 8, 2},  {32, 8, 2}, {4, 4, 2},  {16, 8, 4},
     {8, 2, 2},  {16, 4, 4}, {32, 8, 1}, {8, 2, 1},  {64, 4, 4}, {32, 8, 4}, {16, 2, 4},
-    {8, 8, 4},  {16, 8, 4}, {4, 8, 4},  {4, 4, 4},  {4, 2, 4},  {4, 1, 4},  {2, 4, 2},
-    {2, 2, 2},  {1, 4, 1},  {1, 2, 1},
+    {8, 8, 4},  {4, 8, 4},  {4, 4, 4},  {4, 2, 4},  {4, 1, 4},  {2, 4, 2},  {2, 2, 2},
+    {1, 4, 1},  {1, 2, 1},
 };
-constexpr int kShapeMany = 18, kShapeSome = 20, kShapeFew = 22;
+constexpr int kShapeMany = 17, kShapeSome = 19, kShapeFew = 21;
 // The shape before tuning, by the number of trajectories to score (over all events and
 // maps).  A few leave the chip part empty, and one trajectory a wavefront with four chunks
 // in flight is over soonest; many are scored with the fewest instructions, four a
 // wavefront.  Measured on one map, us for TU = 1 / 2 / 4: 1024 trajectories x 1000 points
 // 15.6 / 17.6 / 22.6, 4096 x 1000 23.7 / 23.2 / 27.6, 16384 x 1000 52 / 46 / 49, 32768 x 1000
-// 89 / 70 / 65; 1024 x 6000 31 / 47 / 72, 16384 x 6000 173 / 130 / 119.
+// 89 / 70 / 65; 1024 x 6000 31 / 47 / 72, 16384 x 6000 173 / 130 / 119.  The length of the light
+// curves is not asked for: with long ones four a wavefront pay from fewer trajectories on than
+// the rule gives them (the last figures: 130 where the autotuner finds 119).
 int default_shape(int64_t n) { return n <= 4096 ? kShapeFew : n <= 16384 ? kShapeSome : kShapeMany; }
 constexpr int kNumTune = sizeof(kTune) / sizeof(kTune[0]);
 // k_search_batched is compiled for at most 512 lanes (8 wavefronts) per workgroup and
@@ -41,6 +44,16 @@ constexpr bool tune_shapes_valid() {
   return true;
 }
 static_assert(tune_shapes_valid(), "a batched-search shape the kernel cannot launch");
+constexpr bool tune_shapes_differ() {
+  for (int i = 0; i < kNumTune; ++i)
+    for (int j = 0; j < i; ++j)
+      if (kTune[i].traj_per_item == kTune[j].traj_per_item && kTune[i].waves_per_block == kTune[j].waves_per_block &&
+          kTune[i].tu == kTune[j].tu)
+        return false;
+  return true;
+}
+static_assert(tune_shapes_differ(), "a shape listed twice is timed twice");
+static_assert(kTune[kShapeMany].tu == 4 && kTune[kShapeSome].tu == 2 && kTune[kShapeFew].tu == 1, "default shapes");
 
 
 }  // namespace
@@ -275,7 +288,7 @@ bool read_tune_cache(const char* path, std::map<std::string, int>& all) {
 std::string shape_class(const SearchPlan& sp) {
   auto bucket = [](double v) { return (int)std::floor(std::log2(std::max(v, 1.0))); };
   std::ostringstream s;
-  s << "gfx950|v3|maps" << bucket(sp.n_maps) << "|pts" << bucket((double)sp.n_pts / sp.n_events)
+  s << "gfx950|v4|maps" << bucket(sp.n_maps) << "|pts" << bucket((double)sp.n_pts / sp.n_events)
     << "|traj" << bucket((double)sp.n_traj) << "|ev" << bucket(sp.n_events);
   return s.str();
 }

@@ -194,6 +194,7 @@ int morse_chi2_grad(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   if ((rc = plan_candidates(ctx, maps, n_maps, lcs, n, pl, i_sums, i_wF, i_quad))) return rc;
   if (n > 0 && (!d_params || !d_event || !d_map_index))
     return fail(ctx, MORSE_EINVAL, "d_params / d_event / d_map_index is NULL");
+  if (n > INT32_MAX) return fail(ctx, MORSE_ERANGE, "more than 2^31 - 1 candidates");
   HIP_TRY(ctx, hipSetDevice(ctx->device));
   const bool ordered = order_helps(n, n_maps, lcs->n_events);
   const size_t i_order = pl.add(ordered ? 4 * (size_t)n : 0), i_key = pl.add(ordered ? 4 * (size_t)n : 0),
@@ -312,6 +313,7 @@ int morse_refine(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   if (n > 0 && (!d_params || !d_event || !d_map_index || !d_chi2_out))
     return fail(ctx, MORSE_EINVAL, "d_params / d_event / d_map_index / d_chi2_out is NULL");
   if (n == 0) return MORSE_OK;
+  if (n > INT32_MAX) return fail(ctx, MORSE_ERANGE, "more than 2^31 - 1 candidates");
   HIP_TRY(ctx, hipSetDevice(ctx->device));
   // One launch runs up to 1024 rounds, so that none lasts long; timed, each round is a launch.
   const int32_t span = timed(ctx, MORSE_KERNEL_GRADIENT) ? 1 : 1024;

@@ -12,10 +12,12 @@
 // different source pixels (a lattice has several rays a pixel), which keeps the LDS
 // atomics of an instruction off a single address (64 lanes on one address take 128 cycles
 // of the LDS, on different ones 4), and the terms of a column and of a row are computed
-// once per thread.  A tile whose rays provably all miss the window is skipped (see
+// once per thread.  On a coarse lattice (about a ray a pixel or fewer) the lanes take neighbouring
+// rays instead, whose pixels differ anyway, so that the atomics of an instruction that go to
+// memory share its lines.  A tile whose rays provably all miss the window is skipped (see
 // tile_misses).  Pass 1 computes every ray's bin and the
 // workgroup's bounding box of in-window bins.  If the box fits in the LDS tile
-// (RS_CAP bins) the rays are counted with LDS atomics and the non-zero bins merged
+// (RS_CAP or RS_CAP_COARSE bins) the rays are counted with LDS atomics and the non-zero bins merged
 // with one global atomic each; otherwise (tiles straddling a lens, whose rays scatter
 // over the whole source plane) each ray goes to a global atomic directly.  Integer
 // addition is order-free, so the counts are bit-identical whatever the schedule.
@@ -41,7 +43,7 @@ namespace morse {
 namespace {
 
 constexpr int RS_THREADS = 256;
-constexpr int RS_CAP = 4096;  // LDS histogram bins (16 KiB)
+constexpr int RS_CAP = 4096, RS_CAP_COARSE = 6144;  // LDS histogram bins (16, 24 KiB)
 
 // n words at p; quads: the first 4 quads of them lie on 16-byte boundaries and go 16 bytes a
 // store (16 MiB: 13 us in words, 9 so).
@@ -111,11 +113,12 @@ __device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
 // whose three addresses took 260,000 atomics each) at 104 instructions per wavefront of
 // rays: no tile skipped, IEEE divisions with scalings, the lattice point, finiteness and
 // range tested per ray, scalar operands.
-template <bool kMirror, bool kSafe, int A, int B>
+template <bool kMirror, bool kSafe, int A, int B, bool kCoarse>
 __global__ __launch_bounds__(RS_THREADS) void k_rayshoot(RayParams p, uint32_t* __restrict__ counts,
                                                          unsigned long long* __restrict__ stats,
                                                          uint32_t slot_mask) {
-  __shared__ uint32_t hist[RS_CAP];
+  constexpr int CAP = kCoarse ? RS_CAP_COARSE : RS_CAP;
+  __shared__ uint32_t hist[CAP];
   __shared__ uint32_t s_box[RS_THREADS / kWave][2];
   __shared__ uint32_t s_stat[RS_THREADS / kWave][3];
 
@@ -126,6 +129,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_rayshoot(RayParams p, uint32_t* 
   const int lane = tid & 63;
   const int x0 = blockIdx.x * (16 * A);
   const int y0 = p.row0 + blockIdx.y * (16 * B);
+  auto row_of = [&](int b) { return kCoarse ? ty + 16 * b : ty * B + b; };
   auto lattice = [](float c, int i, int n, float h) { return c + ((float)(i - (n >> 1)) + 0.5f) * h; };
 
   const int x1 = min(x0 + 16 * A, p.nx) - 1, y1 = min(y0 + 16 * B, p.row1) - 1;  // last column, row
@@ -147,7 +151,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_rayshoot(RayParams p, uint32_t* 
   float y[B], yy[B];
 #pragma unroll
   for (int b = 0; b < B; ++b) {
-    const int j = y0 + ty * B + b;
+    const int j = y0 + row_of(b);
     y[b] = j < p.row1 ? lattice(p.cy, j, p.ny, p.hy) : nan;  // NaN rays are never in the window
     yy[b] = y[b] * y[b];
   }
@@ -158,7 +162,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_rayshoot(RayParams p, uint32_t* 
 
 #pragma unroll
   for (int a = 0; a < A; ++a) {
-    const int i = x0 + tx * A + a;
+    const int i = x0 + (kCoarse ? tx + 16 * a : tx * A + a);
     const float x = i < p.nx ? lattice(p.cx, i, p.nx, p.hx) : nan;
     const float d1 = x - p.x1, d2 = x - p.x2;
     const float d1s = d1 * d1, d2s = d2 * d2;
@@ -178,7 +182,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_rayshoot(RayParams p, uint32_t* 
       in[b] = __builtin_amdgcn_ballot_w64(fabsf(vx[b]) < fhx) & __builtin_amdgcn_ballot_w64(fabsf(vy[b]) < fhy);
       any |= in[b];
       if (!kSafe) {  // a padding ray (i or j past the end) is no ray
-        const bool ray = i < p.nx && y0 + ty * B + b < p.row1;
+        const bool ray = i < p.nx && y0 + row_of(b) < p.row1;
         n_nf += __popcll(__builtin_amdgcn_ballot_w64(ray && !(isfinite(vx[b]) && isfinite(vy[b]))));
       }
       bins[a * B + b] = 0xffffffffu;
@@ -247,7 +251,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_rayshoot(RayParams p, uint32_t* 
   const int pitch = (int)(hi & 0xffff) - bxmin + 1;
   const int area = rows * pitch;
   const int top = 2 * hy - 1;  // mirror row of by is top - by
-  if (area <= RS_CAP) {
+  if (area <= CAP) {
     for (int k = tid; k < area; k += RS_THREADS) hist[k] = 0u;
     __syncthreads();
 #pragma unroll
@@ -685,18 +689,24 @@ hipError_t shoot_tiles(const RayParams& p, uint32_t* counts, unsigned long long*
   // every CU eight such tiles (3200^2 rays into 512^2: 12 against 51 us) or so coarse that
   // 128 x 64 rays cover more than 512 pixels without a lens (near one they spread over
   // several times as many, and a box beyond RS_CAP bins counts ray by ray; 7000 x 5210 rays,
-  // 2.4 a pixel side: 50 against 265 us).  32768^2 rays into 2048^2: 373 us with the large
+  // 2.4 a pixel side: 50 against 265 us).  Where 64 x 32 rays cover more than 512 pixels the
+  // coarse form (neighbouring rays on neighbouring lanes, 24 KiB of bins): 12000^2 rays over twice
+  // the window's width, 0.5 / 0.75 / 1 / 1.5 rays a pixel side, 1.48 / 1.20 / 0.72 / 0.29 ms for 2.60
+  // / 2.20 / 1.29 / 0.49; at 2 (288 pixels) 0.26 without it and 32 KiB of bins slower for finer ones.  32768^2 rays into 2048^2: 373 us with the large
   // tile, 537 with the small one; 128 x 128 rays take 515 (95 VGPRs, larger boxes).
   const float cover = 128.0f * 64.0f * p.hx * p.kx * p.hy * p.ky;
   const int rows = p.row1 - p.row0;
   auto tiles = [&](int tx, int ty) { return dim3((p.nx + tx - 1) / tx, (rows + ty - 1) / ty); };
-  const dim3 big = tiles(128, 64);
+  const dim3 big = tiles(128, 64), small = tiles(64, 32);
   if ((int64_t)big.x * big.y >= 8 * (int64_t)num_cu && cover <= 512.0f) {
-    hipLaunchKernelGGL((k_rayshoot<kMirror, kSafe, 8, 4>), big, dim3(RS_THREADS), 0, st, p, counts, stats,
+    hipLaunchKernelGGL((k_rayshoot<kMirror, kSafe, 8, 4, false>), big, dim3(RS_THREADS), 0, st, p, counts, stats,
                        slot_mask);
+  } else if (cover > 4.0f * 512.0f) {
+    hipLaunchKernelGGL((k_rayshoot<kMirror, kSafe, 4, 2, true>), small, dim3(RS_THREADS), 0, st, p, counts,
+                       stats, slot_mask);
   } else {
-    hipLaunchKernelGGL((k_rayshoot<kMirror, kSafe, 4, 2>), tiles(64, 32), dim3(RS_THREADS), 0, st, p,
-                       counts, stats, slot_mask);
+    hipLaunchKernelGGL((k_rayshoot<kMirror, kSafe, 4, 2, false>), small, dim3(RS_THREADS), 0, st, p, counts, stats,
+                       slot_mask);
   }
   return hipGetLastError();
 }

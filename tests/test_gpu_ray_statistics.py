@@ -47,3 +47,19 @@ def test_narrow_windows_count_exactly(nx, ny, cy):
     o, ost = rayshoot_mirror32_c(s, q, rays, window, nthreads=8)
     assert np.array_equal(counts.cpu().numpy().view(np.uint32), o) and o.sum() > 0
     assert dict(zip(("out", "nonfinite", "zero_axis"), stats.tolist())) == ost
+
+
+# lattices of about a ray a pixel: both sides of the line to the coarse form (1.5 to 2 rays a pixel
+# side), on and off the lens axis, with a row on it (the IEEE division), ragged tiles
+@pytest.mark.parametrize("rays_per_pixel", [0.4, 0.75, 1.0, 1.4, 1.9, 2.1])
+@pytest.mark.parametrize("s,q,cx,cy,rows", [(0.9, 0.01, 0.0, 0.0, 1026), (1.3, 0.2, 0.1, 0.05, 1000), (1.2, 0.5, 0.0, 2.0 ** -9, 1024)])
+def test_coarse_lattices_count_exactly(rays_per_pixel, s, q, cx, cy, rows):
+    n = int(500 / rays_per_pixel) // 2 * 2
+    rays, window = (cx, cy, 4.0, 4.0, 1000, rows), (2 * cx, 0.0, 2.0, 2.0, n, n - 2)
+    note(f"ray statistics coarse {rays_per_pixel} s={s}")
+    counts = torch.empty((n - 2, n), dtype=torch.int32, device=DEV)
+    stats = torch.zeros(3, dtype=torch.int64, device=DEV)
+    M.rayshoot(s, q, rays, window, counts, stats=stats)
+    o, ost = rayshoot_mirror32_c(s, q, rays, window, nthreads=8)
+    assert np.array_equal(counts.cpu().numpy().view(np.uint32), o) and o.sum() > 0
+    assert dict(zip(("out", "nonfinite", "zero_axis"), stats.tolist())) == ost

@@ -359,15 +359,18 @@ __global__ __launch_bounds__(256) void k_normalize_point(const uint32_t* __restr
   nc_block_max(cmax, maxc);
 }
 
-// Taps of a row in groups of four columns from -nc_halo(rx) on.
-__host__ __device__ inline int nc_halo(int rx) { return (rx + 3) & ~3; }
-__host__ __device__ inline int nc_groups(int rx) { return (nc_halo(rx) + rx + 4) / 4; }
+// Taps of a row in groups of four columns from -rx on.
+__host__ __device__ inline int nc_groups(int rx) { return (2 * rx + 4) / 4; }
 
 // Tile staged in LDS with its halo; a thread sums 4 neighbouring pixels of two rows.  For a row
 // of taps it takes them four at a time: eight values in registers serve 4 x 4 products, so
 // LDS gives 16 bytes where a read a product took 64, and the products bound the time
 // (2048^2 pixels, radii of 2 and 7 pixels: 95 us for both, now 75; one of 7 alone 74, now 53).  The weights are laid out densely, 0 where
-// the list has no tap; a group's weights are read by all lanes at once.
+// the list has no tap; a group's weights are read by all lanes at once.  Small stencils on maps
+// whose rows are no multiple of 16 bytes are bound by memory: 4094^2 pixels, a radius of one, 51 us
+// (60 with a store a pixel and with taps from a multiple of four columns on, which made two
+// groups of three taps).  kPairs: stores of two pixels.
+template <bool kPairs>
 __global__ __launch_bounds__(256) void k_normalize_convolve_lds(
     const uint32_t* __restrict__ counts, float* __restrict__ map, int32_t mx, int32_t my,
     const float* __restrict__ w, const int32_t* __restrict__ off, int32_t ntaps, int32_t rx,
@@ -375,7 +378,7 @@ __global__ __launch_bounds__(256) void k_normalize_convolve_lds(
   extern __shared__ float4 nc_lds[];  // weights [2 ry + 1][groups], tile [kNcTh + 2 ry][16 + groups]
   __shared__ int s_first[2 * kNcHalo + 1], s_end[2 * kNcHalo + 1];
   const int x0 = blockIdx.x * kNcTw, y0 = blockIdx.y * kNcTh;
-  const int hx = nc_halo(rx), groups = nc_groups(rx), rows = 2 * ry + 1;
+  const int hx = rx, groups = nc_groups(rx), rows = 2 * ry + 1;
   float4* wt4 = nc_lds;
   float4* tile4 = nc_lds + rows * groups;
   float* wt = (float*)wt4;
@@ -458,9 +461,15 @@ __global__ __launch_bounds__(256) void k_normalize_convolve_lds(
   for (int r = 0; r < 2; ++r) {
     const int gy = y0 + ty + 16 * r;
     if (gy >= my) continue;
+    float* o = map + (size_t)gy * mx + gx;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (gx + i < mx) map[(size_t)gy * mx + gx + i] = acc[r][i] * scale;
+    for (int i = 0; i < 4; i += kPairs ? 2 : 1) {
+      if (gx + i >= mx) continue;
+      if (kPairs)  // mx is even and the map 8-byte aligned
+        *reinterpret_cast<float2*>(o + i) = make_float2(acc[r][i] * scale, acc[r][i + 1] * scale);
+      else
+        o[i] = acc[r][i] * scale;
+    }
   }
   nc_block_max(cmax, maxc);
 }
@@ -775,8 +784,8 @@ hipError_t launch_normalize_convolve(const uint32_t* counts, float* map, int32_t
     const size_t lds = 16 * (size_t)nc_groups(rx) * (2 * ry + 1) +
                        sizeof(float) * (kNcTw + 4 * nc_groups(rx)) * (kNcTh + 2 * ry);
     dim3 grid((mx + kNcTw - 1) / kNcTw, (my + kNcTh - 1) / kNcTh);
-    hipLaunchKernelGGL(k_normalize_convolve_lds, grid, dim3(256), lds, st, counts, map, mx, my, d_w,
-                       d_off, ntaps, rx, ry, scale, d_maxc);
+    auto* kernel = mx % 2 == 0 && ((uintptr_t)map % 8) == 0 ? k_normalize_convolve_lds<true> : k_normalize_convolve_lds<false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(256), lds, st, counts, map, mx, my, d_w, d_off, ntaps, rx, ry, scale, d_maxc);
   }
   return hipGetLastError();
 }

@@ -475,6 +475,7 @@ struct BatchedArgs {
   int32_t traj_per_item;
   int32_t waves_per_block;
   uint32_t chunk;           // workgroups per chunk dealt to an XCD (set by the launcher)
+  uint32_t rotate;          // 1: the XCDs change places with each deal (set by the launcher)
   uint32_t first;           // this launch's first workgroup (set by the launcher)
   int32_t tu;               // trajectories scored together per wavefront (1, 2 or 4)
   int32_t centred;          // every map's window is centred on (0, 0)

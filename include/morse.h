@@ -463,7 +463,7 @@ int morse_trajectory_positions(morse_ctx* ctx, const double* h_params, const dou
  * More than 2048 candidates are evaluated grouped by event, the longest light curve
  * first, and map (a device counting sort; by map first when the packed maps take more than
  * 256 MiB or there are more than 1024 events; by map alone past 2^20 pairs); the order changes the schedule only, never a result.
- * Workspace: 8 B per candidate + 4 B per (map, event) pair.  Errors: ERANGE (n > 2^31 - 1). */
+ * Workspace: 40 B per candidate + 4 B per (map, event) pair.  Errors: ERANGE (n > 2^31 - 1). */
 int morse_chi2_grad(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
                     const morse_lightcurves* lcs, int64_t n, const double* d_params,
                     const int32_t* d_event, const int32_t* d_map_index, double* d_chi2,

@@ -198,6 +198,7 @@ int morse_chi2_grad(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   HIP_TRY(ctx, hipSetDevice(ctx->device));
   const bool ordered = order_helps(n, n_maps, lcs->n_events);
   const size_t i_order = pl.add(ordered ? 4 * (size_t)n : 0), i_key = pl.add(ordered ? 4 * (size_t)n : 0),
+               i_tc = pl.add(ordered ? sizeof(TrajC) * (size_t)n : 0),
                i_hist = pl.add(ordered ? 4 * (size_t)order_bins(n_maps, lcs->n_events) : 0);
   if ((rc = reserve(ctx, pl.total()))) return rc;
   GradArgs a{};
@@ -205,6 +206,7 @@ int morse_chi2_grad(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   std::vector<MapC> hm;
   if ((rc = setup_candidates(ctx, maps, n_maps, lcs, pl, i_sums, i_wF, i_quad, a.lc, d_maps, hm))) return rc;
   a.n = n;
+  a.tc = ordered ? (TrajC*)pl.ptr(ctx, i_tc) : nullptr;
   a.params = d_params;
   a.event = d_event;
   a.mapidx = d_map_index;
@@ -243,7 +245,7 @@ int morse_chi2_grad_noalloc(morse_ctx* ctx, const morse_map_view* maps, int32_t 
   const size_t b_off = (8 * (size_t)(ne + 1) + 255) & ~size_t(255);
   const size_t b_tref = (8 * (size_t)ne + 255) & ~size_t(255);
   const size_t i_meta = pl.add(b_off + b_tref + sizeof(MapC) * n_maps);
-  pl.add((sizeof(TrajC) + 8) * (size_t)n);  // the stated limit counts 40 bytes a candidate for its constants
+  const size_t i_tc = pl.add((sizeof(TrajC) + 8) * (size_t)n);  // the stated limit counts 40 bytes a candidate for them
   const size_t i_order = pl.add(4 * (size_t)n), i_key = pl.add(4 * (size_t)n),
                i_hist = pl.add(4 * (size_t)order_bins(n_maps, ne));
   if (pl.total() > kNoallocScratchBytes)
@@ -289,6 +291,7 @@ int morse_chi2_grad_noalloc(morse_ctx* ctx, const morse_map_view* maps, int32_t 
   a.fb = d_fb;
   if (order_helps(n, n_maps, ne)) {
     int32_t* order = (int32_t*)pl.ptr_at(base, i_order);
+    a.tc = (TrajC*)pl.ptr_at(base, i_tc);
     HIP_TRY(ctx, launch_cand_order(a, hm.data(), (uint32_t*)pl.ptr_at(base, i_key), (uint32_t*)pl.ptr_at(base, i_hist),
                                    order, ctx->stream));
     a.order = order;

@@ -539,6 +539,7 @@ struct GradArgs {
   double* fs;
   double* fb;
   const int32_t* order;     // [n] the order in which candidates are evaluated, or nullptr
+  TrajC* tc;                // [n] constants of params, written with the order's keys, or nullptr
   int32_t map_first;        // set by launch_cand_order
 };
 hipError_t launch_chi2_grad(const GradArgs& a, hipStream_t st);
@@ -547,7 +548,7 @@ hipError_t launch_chi2_grad(const GradArgs& a, hipStream_t st);
 // than the last-level cache (256 MiB); by map, then event with more than kRankedEvents events;
 // by map alone when n_maps x n_events exceeds kOrderBinsMax.  Candidates evaluated at the same time then sample the same map.  Within a group the order is unspecified: it changes only
 // the schedule, never a result.  key: workspace of a.n words; hist: of order_bins(a)
-// counters.
+// counters.  With a.tc the candidates' constants are written too.
 constexpr int64_t kOrderBinsMax = 1 << 20;
 constexpr int32_t kRankedEvents = 1024;
 inline int64_t order_bins(int32_t n_maps, int32_t n_events) {

@@ -303,9 +303,14 @@ __device__ __forceinline__ TrajC natural_traj(double t0, double u0, double tE, d
 // XCD: 3 to 40% slower, the lengths then differ over the XCDs.)  Without one, XCD x takes the contiguous
 // candidate range [x per, (x + 1) per), so that neighbouring candidates (similar
 // trajectories after a ranked selection) share its L2.
-// At most 96 VGPRs (five wavefronts per SIMD): the compiler fits the kernel without
-// spilling (four wavefronts measured 2% slower).
-__global__ __launch_bounds__(GRAD_THREADS) __attribute__((amdgpu_waves_per_eu(5))) void k_chi2_grad(GradArgs a) {
+// kConsts: the trajectory constants come from a.tc, and the kernel fits 96 VGPRs (five wavefronts
+// per SIMD).  Without, they are formed here, by a chain of FP64 operations on one lane before the
+// first load of a cell, for which the compiler spills at 96 and gets 128: a few candidates, which
+// leave the chip part empty, are over sooner so than with another launch.  A call for 100,000
+// candidates on 4 maps of 2048^2, formed here with the spills and from a.tc: 20 events of 300 points
+// 935 and 709 us, of 3000 points 1620 and 1399; for 1500 candidates (128 VGPRs, no a.tc) 160 and 143.
+template <bool kConsts>
+__global__ __launch_bounds__(GRAD_THREADS) __attribute__((amdgpu_waves_per_eu(kConsts ? 5 : 4))) void k_chi2_grad(GradArgs a) {
   __shared__ double s_part[GRAD_THREADS / kWave * kSums];
   __shared__ TrajC s_tc;
   __shared__ Eval ev;
@@ -318,9 +323,11 @@ __global__ __launch_bounds__(GRAD_THREADS) __attribute__((amdgpu_waves_per_eu(5)
     const double* p = a.params + 4 * c;
     __syncthreads();  // the last candidate's constants, sums and results have been read
     if (in_range(a, e, mi)) {  // uniform
-      if (threadIdx.x == 0) s_tc = natural_traj(p[0], p[1], p[2], p[3]);
-      __syncthreads();
-      const TrajC tc = uniform(s_tc);
+      if (!kConsts) {
+        if (threadIdx.x == 0) s_tc = natural_traj(p[0], p[1], p[2], p[3]);
+        __syncthreads();
+      }
+      const TrajC tc = kConsts ? uniform(a.tc[c]) : uniform(s_tc);
       const Target z = target_of(a, e, mi);
       grad_sums(z, tc, s_part);
       __syncthreads();
@@ -697,8 +704,13 @@ __device__ __forceinline__ uint32_t order_key(const GradArgs& a, int64_t c, bool
 
 __global__ void k_order_keys(GradArgs a, bool by_event, uint32_t* key) {
   for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < a.n;
-       c += (int64_t)gridDim.x * blockDim.x)
+       c += (int64_t)gridDim.x * blockDim.x) {
     key[c] = order_key(a, c, by_event);
+    if (a.tc) {
+      const double* p = a.params + 4 * c;
+      a.tc[c] = natural_traj(p[0], p[1], p[2], p[3]);
+    }
+  }
 }
 
 }  // namespace
@@ -730,7 +742,8 @@ unsigned candidate_blocks(int64_t n) { return (unsigned)std::min<int64_t>(8 * ((
 
 hipError_t launch_chi2_grad(const GradArgs& a, hipStream_t st) {
   if (a.n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_chi2_grad, dim3(candidate_blocks(a.n)), dim3(GRAD_THREADS), 0, st, a);
+  hipLaunchKernelGGL(a.tc ? k_chi2_grad<true> : k_chi2_grad<false>, dim3(candidate_blocks(a.n)), dim3(GRAD_THREADS),
+                     0, st, a);
   return hipGetLastError();
 }
 

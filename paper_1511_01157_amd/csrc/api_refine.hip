@@ -115,9 +115,14 @@ namespace {
 // round by round: neighbours in the order then sample the same stretch of a map at the
 // same time, which workgroups that run their candidates' rounds on their own soon do not.
 // 50 rounds of 262,144 candidates on 64 maps of 64 MiB: 158 ms by round, 174 to 195 in one launch.
-bool refine_by_round(int64_t n, const std::vector<MapC>& maps) {
-  return n >= 32768 && maps_exceed_cache(maps.data(), (int32_t)maps.size());
-}
+bool refine_by_round(int64_t n, bool beyond_cache) { return n >= 32768 && beyond_cache; }
+
+// Four candidates a workgroup share one update's time, but wait for one another, and one after
+// the other they sample different stretches of a map.  Times with one and with four, 12 rounds:
+// 12,288 candidates of 20 events of 300 points on a 256^2 map 0.94 / 0.69 ms, of 3000 points on 4 maps
+// of 2048^2 2.39 / 2.51; 16,384 1.20 / 0.82 and 3.09 / 2.99; 32,767 2.30 / 1.43 and 5.85 / 5.49.
+// On 16 maps of 2048^2, which the cache does not hold, 16,384 took 3.39 / 3.94 (15 rounds).
+bool refine_by_four(int64_t n, bool beyond_cache) { return n >= 16384 && !beyond_cache; }
 }  // namespace
 
 extern "C" {
@@ -323,7 +328,8 @@ int morse_refine(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   const bool ordered = order_helps(n, n_maps, lcs->n_events);
   std::vector<MapC> sizes(n_maps);
   for (int i = 0; i < n_maps; ++i) sizes[i] = make_mapc(maps[i].d_map, maps[i].window);
-  const bool split = refine_by_round(n, sizes);
+  const bool beyond_cache = maps_exceed_cache(sizes.data(), n_maps);
+  const bool split = refine_by_round(n, beyond_cache), four = refine_by_four(n, beyond_cache);
   const size_t i_order = pl.add(ordered ? 4 * (size_t)n : 0), i_key = pl.add(ordered ? 4 * (size_t)n : 0),
                i_hist = pl.add(ordered ? 4 * (size_t)order_bins(n_maps, lcs->n_events) : 0),
                i_state = pl.add(split || opts->steps >= span ? sizeof(RefineState) * (size_t)n : 0);
@@ -369,7 +375,7 @@ int morse_refine(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
     s.r1 = std::min(s.r0 + span, opts->steps + 1);
     LaunchTimer tm{ctx, MORSE_KERNEL_GRADIENT};
     HIP_TRY(ctx, tm.begin(ctx->stream));
-    HIP_TRY(ctx, launch_refine(a, s, ctx->stream));
+    HIP_TRY(ctx, launch_refine(a, s, four, ctx->stream));
     HIP_TRY(ctx, tm.end(ctx->stream));
   }
   return MORSE_OK;

@@ -594,7 +594,7 @@ struct RefineArgs {
   int32_t steps;                 // rounds 0 .. steps
   int32_t r0, r1;                // rounds of this launch
 };
-hipError_t launch_refine(const GradArgs& a, const RefineArgs& s, hipStream_t st);
+hipError_t launch_refine(const GradArgs& a, const RefineArgs& s, bool four, hipStream_t st);
 // Whether n_maps maps, packed, take more than the last-level cache.
 bool maps_exceed_cache(const MapC* h_maps, int32_t n_maps);
 // The same rounds as launches of their own (s.state set): start, then for each round 0 .. steps

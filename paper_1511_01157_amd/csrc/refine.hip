@@ -24,7 +24,7 @@
 // chain of some hundred dependent FP64 operations during which the CU's other nine
 // workgroups evaluate.  51 rounds of 8192 candidates on 8 ragged events (2000 points):
 // 3.00 ms, 3.48 as two launches a round; of 64 candidates (2000 points) 0.96 ms.  Where there
-// are many, a workgroup takes four and updates them side by side (see launch_refine).
+// are many, a workgroup takes four and updates them side by side (see refine_by_four).
 #include "internal.h"
 
 namespace morse {
@@ -763,13 +763,10 @@ hipError_t launch_round_update(const GradArgs& a, const RefineArgs& s, int32_t r
   return hipGetLastError();
 }
 
-hipError_t launch_refine(const GradArgs& a, const RefineArgs& s, hipStream_t st) {
+hipError_t launch_refine(const GradArgs& a, const RefineArgs& s, bool four, hipStream_t st) {
   if (a.n <= 0) return hipSuccess;
   if (s.m < 1 || s.m > kMaxHistory) return hipErrorInvalidValue;
-  // Four candidates a workgroup share one update's time, but wait for one another: 51 rounds of
-  // 65,536 candidates (2000 points, 8 events) 22.4 ms with four, 25 with one; of 16,384 7.1 and
-  // 6.6, of 8192 4.2 and 3.7, of 2560 3.4 and 1.5.
-  if (a.n >= 32768)
+  if (four)
     hipLaunchKernelGGL(k_refine<4>, dim3(candidate_blocks((a.n + 3) / 4)), dim3(GRAD_THREADS), 0, st, a, s);
   else
     hipLaunchKernelGGL(k_refine<1>, dim3(candidate_blocks(a.n)), dim3(GRAD_THREADS), 0, st, a, s);

@@ -509,9 +509,10 @@ typedef struct {
  * [n][4] FP64 is read as the start and overwritten with the refined parameters;
  * d_chi2_out [n] receives the final chi2, d_chi2_init [n] (nullable) the initial.
  * Candidates are independent: one launch runs all rounds (up to 1024 at a time), a
- * workgroup per candidate (per four from 16384), in the order of morse_chi2_grad; on maps that
- * take more than 256 MiB packed, a workgroup takes one, and from 32768 candidates the rounds
- * are launches of their own.  Results are the same in every form.  Workspace: 8 B per candidate + 4 B per
+ * workgroup per candidate (per four from 16384, or from 6144 where the mean light curve has at
+ * most 1024 points), in the order of morse_chi2_grad; on maps that take more than 256 MiB
+ * packed, a workgroup takes one, and from 32768 candidates the rounds are launches of
+ * their own.  Results are the same in every form.  Workspace: 8 B per candidate + 4 B per
  * (map, event) pair, and 1.6 KB per candidate where the rounds take several launches. */
 int morse_refine(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
                  const morse_lightcurves* lcs, int64_t n, double* d_params,

@@ -118,11 +118,16 @@ namespace {
 bool refine_by_round(int64_t n, bool beyond_cache) { return n >= 32768 && beyond_cache; }
 
 // Four candidates a workgroup share one update's time, but wait for one another, and one after
-// the other they sample different stretches of a map.  Times with one and with four, 12 rounds:
-// 12,288 candidates of 20 events of 300 points on a 256^2 map 0.94 / 0.69 ms, of 3000 points on 4 maps
-// of 2048^2 2.39 / 2.51; 16,384 1.20 / 0.82 and 3.09 / 2.99; 32,767 2.30 / 1.43 and 5.85 / 5.49.
-// On 16 maps of 2048^2, which the cache does not hold, 16,384 took 3.39 / 3.94 (15 rounds).
-bool refine_by_four(int64_t n, bool beyond_cache) { return n >= 16384 && !beyond_cache; }
+// the other they sample different stretches of a map: short light curves, of which the update is
+// the larger part, gain sooner.  Milliseconds with one and with four, 12 rounds (15 on 16 maps):
+//   20 events x 300 points on a map of 256^2   3000: 0.34 / 0.35,  6144: 0.53 / 0.42,  16,384: 1.20 / 0.82
+//   1 event x 1000 points, 4 maps of 2048^2    4096: 0.74 / 0.72,  6144: 0.99 / 0.86,  16,384: 2.14 / 1.79
+//   8 ragged events of about 2000 points, 512^2  8192: 1.02 / 1.11,  12,288: 1.45 / 1.42,  16,384: 1.90 / 1.69
+//   20 events x 3000 points, 4 maps of 2048^2  8192: 1.69 / 1.63,  12,288: 2.41 / 2.51,  16,384: 3.10 / 2.94
+//   16 maps of 2048^2, which the cache does not hold, 16,384 candidates: 3.39 / 3.94
+bool refine_by_four(int64_t n, int64_t mean_points, bool beyond_cache) {
+  return n >= (mean_points <= 1024 ? 6144 : 16384) && !beyond_cache;
+}
 }  // namespace
 
 extern "C" {
@@ -329,7 +334,8 @@ int morse_refine(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
   std::vector<MapC> sizes(n_maps);
   for (int i = 0; i < n_maps; ++i) sizes[i] = make_mapc(maps[i].d_map, maps[i].window);
   const bool beyond_cache = maps_exceed_cache(sizes.data(), n_maps);
-  const bool split = refine_by_round(n, beyond_cache), four = refine_by_four(n, beyond_cache);
+  const bool split = refine_by_round(n, beyond_cache),
+             four = refine_by_four(n, lcs->h_offsets[lcs->n_events] / lcs->n_events, beyond_cache);
   const size_t i_order = pl.add(ordered ? 4 * (size_t)n : 0), i_key = pl.add(ordered ? 4 * (size_t)n : 0),
                i_hist = pl.add(ordered ? 4 * (size_t)order_bins(n_maps, lcs->n_events) : 0),
                i_state = pl.add(split || opts->steps >= span ? sizeof(RefineState) * (size_t)n : 0);

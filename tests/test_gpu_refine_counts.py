@@ -1,6 +1,6 @@
-"""Refinements of counts about the one from which a workgroup takes four candidates: the same
-bits as those of a few at a time, with a last workgroup that is not full, events of very
-different lengths and rows out of range."""
+"""Refinements of counts about those from which a workgroup takes four candidates (fewer where the
+mean light curve has at most 1024 points): the same bits as those of a few at a time, with a
+last workgroup that is not full, events of very different lengths and rows out of range."""
 import numpy as np
 import pytest
 import torch
@@ -12,14 +12,15 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("n", [16383, 16384, 16385, 16387])
+@pytest.mark.parametrize("n,longest", [(6143, 700), (6144, 700), (6145, 700), (6147, 700),
+                                       (16383, 3000), (16384, 3000), (16387, 3000)])
 @pytest.mark.parametrize("steps,history", [(0, 8), (9, 2)])
-def test_many_equal_few(n, steps, history):
+def test_many_equal_few(n, longest, steps, history):
     rng = np.random.default_rng(n + steps)
     maps = [(torch.from_numpy((1 + 3 * rng.random((90, 96))).astype(np.float32)).to(DEV), (0.0, 0.0, 1.6, 1.5, 96, 90))
             for _ in range(2)]
     evs = []
-    for npts in (5, 130, 700):
+    for npts in (5, 130, longest):
         tt = np.sort(rng.uniform(-30, 30, npts)).astype(np.float32)
         evs.append(dict(tt=tt, F=2 + rng.standard_normal(npts), w=rng.uniform(50, 150, npts), t_ref=0.0))
     lcs = M.LightCurveBatch.from_events(evs, DEV)
@@ -27,7 +28,7 @@ def test_many_equal_few(n, steps, history):
     ev, mi = rng.integers(0, 3, n).astype(np.int32), rng.integers(0, 2, n).astype(np.int32)
     ev[3], mi[5], ev[31], mi[n - 1] = 3, -1, -2, 2  # out of range
     dP, de, dm = (torch.from_numpy(x).to(DEV) for x in (P, ev, mi))
-    note(f"refine counts {n} {steps} {history}")
+    note(f"refine counts {n} {longest} {steps} {history}")
     got = M.refine(maps, lcs, dP, de, dm, steps=steps, history=history)
     for i in range(0, n, 2500):
         want = M.refine(maps, lcs, dP[i:i + 2500].contiguous(), de[i:i + 2500].contiguous(),

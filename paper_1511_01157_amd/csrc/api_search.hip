@@ -343,7 +343,8 @@ int morse_search(morse_ctx* ctx, const morse_map_view* maps, int32_t n_maps,
     return MORSE_OK;
   }
 
-  // batched: one scoring launch; with preparation and selection five to fourteen in all.
+  // batched: one scoring launch; with preparation and selection two (a grid, chi-squares alone) to
+  // seventeen (lists, new metadata, the best of all and a long top-k) in all.
   // Launched one by one (3 us of the host each): 1024 trajectories with top-64 take 28 us a call,
   // from a captured graph of the same launches 45 us, and 80 to 300 where the graph has to be
   // captured again.

@@ -11,12 +11,12 @@
 // seeds in polar coordinates about the centre of mass; the seeds are sorted in LDS
 // (bitonic), cut into angular runs at gaps wider than `gap` and each run at radial
 // gaps; every region grows until none of its sides maps inside the source (side samples
-// spread over the lanes); overlapping regions merge.  Integration, one 512-lane
-// workgroup per (source, region): column by column (one lane per theta column, radial
-// segments with the limb crossing linear in f = rho^2 - |zeta - zeta_s|^2 and the
-// square-root edge of the limb-darkened profile integrated exactly), then the region
-// cut to its inside cells and integrated again; a last kernel adds each source's region
-// integrals in region order.  All arithmetic is FP64.
+// spread over the lanes); overlapping regions merge.  Integration, one 256-lane
+// workgroup per (source, region): the region is cut to its inside cells, up to n_shrink times,
+// by its nodes alone, then integrated once, column by column (one lane per theta
+// column, radial segments with the limb crossing linear in f = rho^2 - |zeta - zeta_s|^2 and the
+// square-root edge of the limb-darkened profile integrated exactly); a last kernel adds each
+// source's region integrals in region order.  All arithmetic is FP64.
 
 #include "fsmag.h"
 

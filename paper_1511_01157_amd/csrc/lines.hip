@@ -7,12 +7,11 @@
 // light curve implies.  A line here is (u0, alpha, shift): the path tau (cos a, sin a) +
 // u0 (-sin a, cos a), whose closest approach to its caustic centre is at tau = shift.
 //
-// Filter layout.  One wavefront per line, lanes over the samples, four chunks of 64 in
-// flight: the line is sampled
-// across the map window at spacing h <= 1 pixel, each sample exactly as the search
-// samples a point (the same binary32 geometry and bilinear blend of the packed cells,
-// the single-lens value off the map), and the largest value (NaN if any sample is NaN)
-// decides.  The kept lines are then listed in ascending order by a stream compaction (one
+// Filter layout.  One wavefront per line, lanes over the samples, two chunks of 64 in
+// flight: the line is sampled across the map window at spacing h <= 1 pixel, each sample with the
+// search's value for a point (the same binary32 geometry and bilinear blend, the cell read
+// from the map in tiles; the single-lens value off the map), and the largest value (NaN if any
+// sample is NaN) decides.  The kept lines are then listed in ascending order by a stream compaction (one
 // workgroup for a few thousand lines, else counts per block, one scan, scatter), so the
 // result does not depend on the schedule.
 

@@ -59,9 +59,10 @@ __global__ void k_fill_u64(uint64_t* p, size_t n, uint64_t v) {
     p[i] = v;
 }
 
-// m / r, correctly rounded, for m = 0 or m in [2^-40, 1] and r in [2^-40, 2^40]: the steps
-// of the general IEEE sequence with its range scaling and special-case fix-up left out,
-// which in this range change nothing (8 instructions for 11).
+// m / r, correctly rounded, for m = 0 or m in [2^-40, 1] and r in [2^-40, 2^40]: Markstein's
+// method (the reciprocal, one Newton step, two corrections of the quotient by its residual),
+// without the range scaling and the fix-up of special cases that a general division adds and
+// that change nothing in this range (8 instructions for 11).
 __device__ __forceinline__ float div_in_range(float m, float r) {
   float y = __builtin_amdgcn_rcpf(r);
   y = fmaf(fmaf(-r, y, 1.0f), y, y);

@@ -11,14 +11,15 @@
 // weighted flux) per trajectory, and a fixed-order reduction (bitwise the butterfly of
 // each value) totals them.  S_w, the weighted mean flux and V = sum w (F - Fbar)^2
 // depend only on the light curve and are computed once per event.  The 2x2 solve gives
-// chi2 = V - F_s C in the same pass; when the rounding bound of that form exceeds 1e-9
+// chi2 = V - F_s C in the same pass; when the rounding bound of that form exceeds 1e-8
 // relative (ill-conditioned or near-perfect fits) the wave re-samples and sums
 // w (F - F_s A - F_b)^2 directly.
 //
 // Plain mode launches one grid per (event, map), one trajectory per wavefront.  Batched
 // mode launches one grid over the (map, event, trajectory group) items, dealt to the XCDs
-// in chunks, so thousands of (event, map) pairs of uneven length share one launch; the per-trajectory arithmetic and reduction order are the
-// same, so results are bitwise identical between the modes.
+// in chunks, so thousands of (event, map) pairs of uneven length share one launch; the
+// per-trajectory arithmetic and reduction order are the same, so results are bitwise identical
+// between the modes.
 
 #include "internal.h"
 

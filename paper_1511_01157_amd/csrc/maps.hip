@@ -702,8 +702,9 @@ hipError_t shoot_tiles(const RayParams& p, uint32_t* counts, unsigned long long*
   // 2.4 a pixel side: 50 against 265 us).  Where 64 x 32 rays cover more than 512 pixels the
   // coarse form (neighbouring rays on neighbouring lanes, 24 KiB of bins): 12000^2 rays over twice
   // the window's width, 0.5 / 0.75 / 1 / 1.5 rays a pixel side, 1.48 / 1.20 / 0.72 / 0.29 ms for 2.60
-  // / 2.20 / 1.29 / 0.49; at 2 (288 pixels) 0.26 without it and 32 KiB of bins slower for finer ones.  32768^2 rays into 2048^2: 373 us with the large
-  // tile, 537 with the small one; 128 x 128 rays take 515 (95 VGPRs, larger boxes).
+  // / 2.20 / 1.29 / 0.49; at 2 (288 pixels) 0.26 without it, and 32 KiB of bins slower for finer ones.
+  // 32768^2 rays into 2048^2: 373 us with the large tile, 537 with the small one; 128 x 128 rays take
+  // 515 (95 VGPRs, larger boxes).
   const float cover = 128.0f * 64.0f * p.hx * p.kx * p.hy * p.ky;
   const int rows = p.row1 - p.row0;
   auto tiles = [&](int tx, int ty) { return dim3((p.nx + tx - 1) / tx, (rows + ty - 1) / ty); };

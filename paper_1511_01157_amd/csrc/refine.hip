@@ -22,8 +22,8 @@
 // state (binary32 variables p, FP64 history) in LDS.  Of a round of a 2000-point candidate,
 // 20 of 35 thousand cycles are the evaluation, bound by FP64 issue; the rest is the update, a
 // chain of some hundred dependent FP64 operations during which the CU's other nine
-// workgroups evaluate.  51 rounds of 8192 candidates on 8 ragged events (2000 points):
-// 3.00 ms, 3.48 as two launches a round; of 64 candidates (2000 points) 0.96 ms.  Where there
+// workgroups evaluate.  A call of 51 rounds for 8192 candidates on 8 ragged events (2000
+// points) takes 3.08 ms, 3.95 as two launches a round on the same card; 64 candidates 0.96.  Where there
 // are many, a workgroup takes four and updates them side by side (see refine_by_four).
 #include "internal.h"
 

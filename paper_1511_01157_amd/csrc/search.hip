@@ -258,7 +258,7 @@ __global__ __launch_bounds__(256) void k_put(uint32_t* dst, uint32_t n, PutWords
 // launch), then the cells' way from L2.  The short form takes 31 instructions per point and
 // trajectory, 6 of them FP64; with the general form, the off-map chunks and the work per
 // group 36 on a 64 x 64 x 16 x 8 grid x 3000 points (1.49 ms, 1.06e12 point-evaluations/s;
-// 1.77 ms before, 2.09 ms with the former untuned shape) and
+// 1.77 ms before, 2.09 ms with the former untuned shape, on the same card; 1.60 and 1.68 on two others) and
 // 39 on 24 ragged events x 8 maps x 16384 random trajectories (8.7 ms for 9.2; untuned 11.1).
 // Also measured: the constants in vector registers (1.79 ms on the grid: five wavefronts
 // per SIMD for six), no cell loads at all 1.47 ms, and straight-line code for each of the

@@ -119,6 +119,13 @@ class Context:
         if rc != 0:
             raise MorseError(rc, self.lib.morse_last_error(self.handle).decode())
 
+    def _capturing(self):
+        """Whether the context's stream or torch's current one is being captured."""
+        if torch.cuda.is_current_stream_capturing() or not self.stream:
+            return torch.cuda.is_current_stream_capturing()
+        with torch.cuda.stream(torch.cuda.ExternalStream(self.stream, device=self.device)):
+            return torch.cuda.is_current_stream_capturing()
+
     def synchronize(self):
         self.check(self.lib.morse_ctx_synchronize(self.handle))
 
@@ -209,7 +216,10 @@ def build_map(s, q, rays, window, rho=0.0, device="cuda", out=None, counts=None,
     if stats:
         return out, {k: int(getattr(st, k)) for k, _ in MapStats._fields_ if k != "reserved"}
     if given and given.stream != torch.cuda.current_stream(given.device).cuda_stream:
-        given.synchronize()  # work that the caller enqueues next does not follow the map's stream
+        # work that the caller enqueues next does not follow the map's stream; under a capture
+        # there is nothing to wait for, and the caller joins the streams
+        if not given._capturing():
+            given.synchronize()
     return out
 
 
